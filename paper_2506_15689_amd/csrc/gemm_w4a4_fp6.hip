@@ -36,6 +36,18 @@ __device__ __forceinline__ void wait_loads_and_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// The same where the last n of this wave's stages may still be in flight, n known at run time (the last steps of a tile,
+// when no further stage is requested) and uniform over the wave; PER: this wave's loads per stage.
+template <int PER, int MAXN>
+__device__ __forceinline__ void wait_stages_and_barrier(int n) {
+    if constexpr (MAXN > 0) {
+        if (n >= MAXN) { wait_loads_and_barrier<PER * MAXN>(); return; }
+        wait_stages_and_barrier<PER, MAXN - 1>(n);
+    } else {
+        wait_loads_and_barrier<0>();
+    }
+}
+
 #ifndef G6_GROUP_M
 #define G6_GROUP_M 4
 #endif
@@ -56,7 +68,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
     static_assert(STAGE_BYTES % 1024 == 0, "a stage is a whole number of 1 KB pieces");
     static_assert(BM % 32 == 0 && BN % 32 == 0, "tiles are made of 32-row blocks");
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
-    static_assert(STAGES == 2 || STAGES == 3, "the wait counts below assume at most one stage in flight beyond the next");
+    static_assert(STAGES >= 2 && LOADS * (STAGES - 2) < 64, "the wait counter counts to 63");
     static_assert((BM + BN) * 16 <= STAGE_BYTES, "the epilogue constants live in the last stage");
 
     __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGES * STAGE_BYTES];
@@ -109,25 +121,32 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
             soff[i] = blk * BLOCK + part * 1024;
         }
     };
-    auto issue_loads = [&](int ks) {
-        uint8_t* stage = lds + (ks % STAGES) * STAGE_BYTES + swave * 1024;
-        const unsigned koff_a = (unsigned)ks * a_step, koff_w = (unsigned)ks * w_step;   // unsigned 32-bit byte offsets
-#pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            // whether piece i * WAVES + wave exists is known at compile time for all but a last partial round, and
-            // which operand it belongs to whenever the activation pieces fill whole rounds: no branch per load then
-            // (the wave-dependent tests are uniform over the wave)
-            if ((i + 1) * WAVES > PIECES && i * WAVES + swave >= PIECES) continue;
-            if (A_PIECES % WAVES == 0 ? i < A_PIECES / WAVES : i * WAVES + swave < A_PIECES)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, LDS_PTR(stage + i * WAVES * 1024), 16, lane_off, (int)(koff_a + (unsigned)soff[i]), 0, 0);
-            else
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, LDS_PTR(stage + i * WAVES * 1024), 16, lane_off, (int)(koff_w + (unsigned)soff[i]), 0, 0);
-        }
+    // load number i of a K-step: into the stage at byte stage_off of the ring, from chunk offsets koff_a / koff_w (unsigned
+    // 32-bit byte offsets)
+    auto issue_one = [&](int stage_off, unsigned koff_a, unsigned koff_w, int i) {
+        // whether piece i * WAVES + wave exists is known at compile time for all but a last partial round, and
+        // which operand it belongs to whenever the activation pieces fill whole rounds: no branch per load then
+        // (the wave-dependent tests are uniform over the wave)
+        if ((i + 1) * WAVES > PIECES && i * WAVES + swave >= PIECES) return;
+        uint8_t* dst = lds + stage_off + swave * 1024 + i * WAVES * 1024;
+        if (A_PIECES % WAVES == 0 ? i < A_PIECES / WAVES : i * WAVES + swave < A_PIECES)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, LDS_PTR(dst), 16, lane_off, (int)(koff_a + (unsigned)soff[i]), 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, LDS_PTR(dst), 16, lane_off, (int)(koff_w + (unsigned)soff[i]), 0, 0);
+    };
+    constexpr int SPLIT = (LOADS + 1) / 2;                     // the first half of a stage's loads (see `half` below)
+    // Wait until the oldest stage in flight has landed, `ahead` stages having been requested behind it at most
+    auto wait_stages = [&](int ahead) {
+        if (PIECES % WAVES != 0 && swave < PIECES % WAVES) wait_stages_and_barrier<LOADS, STAGES - 2>(ahead);
+        else wait_stages_and_barrier<MIN_LOADS, STAGES - 2>(ahead);
     };
     auto issue_prologue = [&]() {
 #pragma unroll
         for (int s = 0; s < STAGES - 1; ++s)
-            if (s < ksteps) issue_loads(s);
+            if (s < ksteps) {
+#pragma unroll
+                for (int i = 0; i < LOADS; ++i) issue_one(s * STAGE_BYTES, s * a_step, s * w_step, i);
+            }
     };
 
     // ---- fragment addressing: lane (frow, fhalf) feeds k = 64*kb + 32*fhalf .. +31 of its row, i.e.
@@ -211,7 +230,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         // tiles both stages were waited for before the previous epilogue's stores went out.  The barrier
         // also ends every wave's use of the epilogue constants before step 0 refills the last stage.
         if (first) {
-            if (STAGES >= 3 && ksteps > 1) wait_loads_and_barrier<MIN_LOADS*(STAGES - 2)>(); else wait_loads_and_barrier<0>();
+            wait_stages(ksteps - 1);
         } else if (STAGES >= 3) {
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         } else {
@@ -220,39 +239,71 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         first = false;
         read_frags(lds, 0, 0);
 
-        // Half a K-step: the TM*TN MFMAs of one k-block, with the fragment reads of the NEXT k-block issued between
-        // them, one fragment (two LDS reads) in front of each of the first TM+TN MFMAs, in the order in which the
-        // next half will need them (B0, A0, B1 .. , A1 ..).  Issuing all reads first and all MFMAs after made every
-        // wave of the compute unit queue at the LDS at the same time while the matrix cores idled, and then run
-        // its MFMAs while the LDS idled; interleaved, the two pipes work at the same time.
-        auto half = [&](int use_set, const uint8_t* rd_stage, int rd_kb, int rd_set, bool do_reads) {
+        // Half a K-step: the TM*TN MFMAs of one k-block.  Between them go the fragment reads of the NEXT k-block, one
+        // fragment (two LDS reads) in front of each MFMA in the order in which the next half will need them (B0, A0,
+        // B1 .. , A1 ..), and half of a stage's direct loads, one behind each MFMA.  Issuing all reads first and all
+        // MFMAs after made every wave of the compute unit queue at the LDS at the same time while the matrix cores
+        // idled, and then run its MFMAs while the LDS idled; and a compute unit accepts one direct load (1 KB) per 16
+        // cycles, so a burst of them blocks its waves while the matrix cores idle (a step of the 128 x 128 tile
+        // alone on its compute unit: 256 cycles of MFMAs, 384 of load issue, 850 in all with the loads in a burst).
+        auto half = [&](int use_set, const uint8_t* rd_stage, int rd_kb, int rd_set, auto do_reads, int fill, unsigned koff_a, unsigned koff_w, int from, auto do_loads) {
+            constexpr int MFMAS = TM * TN;
+            constexpr int READS = (TM + TN + MFMAS - 1) / MFMAS;                      // fragments read per MFMA
+            constexpr int PER = (SPLIT + MFMAS - 1) / MFMAS;                            // loads issued per MFMA
     #pragma unroll
-            for (int t = 0; t < TM * TN; ++t) {
-                if (do_reads && t < TM + TN) read_nth(t, rd_stage, rd_kb, rd_set);
+            for (int t = 0; t < MFMAS; ++t) {
+                if (decltype(do_reads)::value) {
+    #pragma unroll
+                    for (int u = 0; u < READS; ++u)
+                        if (t * READS + u < TM + TN) read_nth(t * READS + u, rd_stage, rd_kb, rd_set);
+                }
                 const int i = t / TN, j = t % TN;
                 acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(pa[use_set][i], pb[use_set][j], acc[i][j], 2, 2, 0, 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
+                if (decltype(do_loads)::value) {
+    #pragma unroll
+                    for (int u = 0; u < PER; ++u)
+                        if (t * PER + u < SPLIT && from + t * PER + u < LOADS) issue_one(fill, koff_a, koff_w, from + t * PER + u);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         };
-        // One K-step.  The last one is peeled off the loop: with the "is there a next stage to read" test inside the
-        // loop, two paths meet in front of the second block of MFMAs, one of them without the reads of the next
-        // stage in flight, and the compiler then waits for every outstanding LDS read there -- including the ones
-        // just issued -- instead of only for the operands the MFMAs use (a bubble of an LDS latency per step).
-        auto k_step = [&](int ks, auto has_next) {
-            const uint8_t* st = lds + (ks % STAGES) * STAGE_BYTES;
-            // the stage refilled now was read during step ks-1; every wave has passed that step's barrier
-            if (ks + STAGES - 1 < ksteps) issue_loads(ks + STAGES - 1);
-            __builtin_amdgcn_sched_barrier(0);
+        // One K-step.  A stage is refilled from the moment every wave has passed the barrier behind its last reads: the
+        // first half of the loads of stage ks + STAGES goes out with the second block of MFMAs of step ks, the other
+        // half with the first block of step ks + 1.  The last steps, which request nothing, and the very last, which
+        // reads no next stage, are peeled off the loop: with these tests inside it, two paths met in front of a block
+        // of MFMAs, and the compiler then waited for every outstanding LDS read there -- including the ones just
+        // issued -- instead of only for the operands the MFMAs use (a bubble of an LDS latency per step).
+        //
+        // Ring positions and chunk offsets are carried along: a remainder by the number of stages in front of each block
+        // of reads (a multiply chain unless it is a power of two) costs a tenth of a step.
+        int prev = (STAGES - 1) * STAGE_BYTES, cur = 0, next = STAGE_BYTES;      // stages of steps ks - 1, ks, ks + 1
+        unsigned koff_a = (STAGES - 1) * a_step, koff_w = (STAGES - 1) * w_step;   // chunk ks + STAGES - 1
+        auto k_step = [&](int ks, auto loads0, auto loads1, auto has_next) {
             // kb = 0, reading kb = 1 of this stage ahead
-            half(0, st, 1, 1, true);
+            half(0, lds + cur, 1, 1, std::true_type{}, prev, koff_a, koff_w, SPLIT, loads0);
+            koff_a += a_step;
+            koff_w += w_step;
             // every read of this stage has been issued; pass the barrier (next stage complete and visible: all but
             // the newest STAGES-2 loads have landed), then kb = 1, reading the next stage's kb = 0 ahead
-            if (STAGES >= 3 && ks + STAGES - 1 < ksteps) wait_loads_and_barrier<MIN_LOADS*(STAGES - 2)>(); else wait_loads_and_barrier<0>();
-            half(1, lds + ((ks + 1) % STAGES) * STAGE_BYTES, 0, 0, decltype(has_next)::value);
+            wait_stages(decltype(loads0)::value ? STAGES - 2 : ksteps - 2 - ks);
+            half(1, lds + next, 0, 0, has_next, cur, koff_a, koff_w, 0, loads1);
+            prev = cur;
+            cur = next;
+            next = next == (STAGES - 1) * STAGE_BYTES ? 0 : next + STAGE_BYTES;
         };
+        constexpr std::true_type yes{};
+        constexpr std::false_type no{};
+        if (STAGES - 1 < ksteps) {
+#pragma unroll
+            for (int i = 0; i < SPLIT; ++i) issue_one(prev, koff_a, koff_w, i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
         int ks = 0;
-        for (; ks + 1 < ksteps; ++ks) k_step(ks, std::true_type{});
-        k_step(ks, std::false_type{});
+        for (; ks + STAGES < ksteps; ++ks) k_step(ks, yes, yes, yes);
+        if (ks + STAGES - 1 < ksteps) { k_step(ks, yes, no, yes); ++ks; }
+        for (; ks + 1 < ksteps; ++ks) k_step(ks, no, no, yes);
+        k_step(ks, no, no, no);
         // every wave has passed the last step's barrier, after which nothing reads the ring: request the
         // next tile's first stages now, so that their latency hides behind this tile's epilogue
         const int next_pid = pid + gridDim.x;

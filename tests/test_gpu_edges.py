@@ -464,3 +464,33 @@ def test_packed_operands_of_two_to_four_gib_and_beyond(M):
     worst = float((np.abs(y - y_ref) - 2.0 ** -8 * np.abs(y_ref)).max() / top)
     assert worst <= 1e-5, f"worst excess over one bf16 step: {worst} of max|ref| on identical codes"
     announce(f"ok worst excess {worst:.2e}")
+
+
+@pytest.mark.parametrize("K", [128, 256, 384, 512, 640, 896])
+@pytest.mark.parametrize("M,N,pad", [(129, 64, 0), (300, 1000, 0), (257, 514, 2), (131, 333, 1), (700, 20480, 8)])
+def test_fp6_product_over_few_k_steps(K, M, N, pad):
+    """Every length of the K loop around the depth of its ring of LDS stages (no steady step at all, one, several), each
+    with ragged tiles, more tiles than compute units (the last shape) and each alignment of the output rows: the bits of
+    the int8 path (exact integer products, the same epilogue arithmetic, so no tolerance)."""
+    announce(f"fp6 product M={M} N={N} K={K} pad={pad}")
+    gen = torch.Generator(device=DEV).manual_seed(K + M)
+    A = torch.randint(0, 256, (M, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
+    W = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
+    A6, W6 = B.alloc_fp6_buffer(M, K), B.alloc_fp6_buffer(N, K)
+    B.basq_pack_fp6(A, A6)
+    B.basq_pack_fp6(W, W6)
+    codes = A.to(torch.int32)
+    meta = torch.zeros((M, 4), dtype=torch.int32, device=DEV)
+    meta.view(torch.float32)[:, 0] = torch.rand(M, device=DEV, generator=gen) + 0.1
+    meta.view(torch.float32)[:, 1] = -torch.rand(M, device=DEV, generator=gen)
+    meta[:, 2] = ((codes & 15) + (codes >> 4)).sum(dim=1)
+    sw = (torch.rand(N, device=DEV, generator=gen) + 0.1).to(torch.bfloat16)
+    zp = torch.randint(0, 16, (N,), device=DEV, generator=gen).to(torch.bfloat16)
+    ws, c = torch.randn(N, device=DEV, generator=gen), torch.randn(N, device=DEV, generator=gen)
+    out = []
+    for a6, w6 in ((A6, W6), (None, None)):
+        Y = torch.full((M + 1, N + pad), -7.0, dtype=torch.bfloat16, device=DEV)
+        B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, Y[:M, :N], Aq6=a6, Wq6=w6)
+        assert bool((Y[M] == -7.0).all()) and bool((Y[:, N:] == -7.0).all()), "wrote outside the output"
+        out.append(Y[:M, :N].contiguous())
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
