@@ -68,8 +68,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
     static_assert(STAGE_BYTES % 1024 == 0, "a stage is a whole number of 1 KB pieces");
     static_assert(BM % 32 == 0 && BN % 32 == 0, "tiles are made of 32-row blocks");
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
-    static_assert(STAGES >= 2 && LOADS * (STAGES - 2) < 64, "the wait counter counts to 63");
-    static_assert((BM + BN) * 16 <= STAGE_BYTES, "the epilogue constants live in the last stage");
+    static_assert(STAGES >= 3 && LOADS * (STAGES - 2) < 64, "the wait counter counts to 63");
+    static_assert(ROWS * 16 <= STAGE_BYTES, "the epilogue constants live in the last stage");
 
     __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGES * STAGE_BYTES];
 
@@ -95,8 +95,10 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         const int first_m = band * GROUP_M;
         const int rows = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
         const int in_band = t - band * GROUP_M * tiles_n;
-        tile_m = first_m + in_band % rows;
-        tile_n = in_band / rows;
+        // (divisions are vector instructions: without this, in some tilings everything derived from the tile stays in vector
+        // registers, and every load, whose block offset must be scalar, is wrapped in a loop over the lanes' values)
+        tile_m = __builtin_amdgcn_readfirstlane(first_m + in_band % rows);
+        tile_n = __builtin_amdgcn_readfirstlane(in_band / rows);
     };
 
     // ---- direct loads: load i of wave w copies the 1 KB piece number i*WAVES + w of the stage; three
@@ -152,35 +154,56 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
     // ---- fragment addressing: lane (frow, fhalf) feeds k = 64*kb + 32*fhalf .. +31 of its row, i.e.
     // group f = 2*kb + fhalf of the row's block: 16 bytes among the pieces, 8 bytes among the tails
     const int frow = lane & 31, fhalf = lane >> 5;
-    int moff[2], toff[2];
+    int moff[2];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        moff[kb] = 64 * frow + 16 * ((2 * kb + fhalf) ^ ((frow >> 2) & 3));
-        toff[kb] = 2048 + 256 * (2 * kb + fhalf) + 8 * frow;
-    }
+    for (int kb = 0; kb < 2; ++kb) moff[kb] = 64 * frow + 16 * ((2 * kb + fhalf) ^ ((frow >> 2) & 3));
+    const int toff = 2048 + 256 * fhalf + 8 * frow;            // k-block 1: 512 bytes further
     const int a_row = (wm * WM / 32) * BLOCK;
-    const int b_row = (BM / 32 + wn * WN / 32) * BLOCK;
+    // A wave's TN column blocks: pairs of adjacent ones (64 columns, a 128-byte line of outputs), and the odd one left over
+    // from behind all pairs of the tile.
+    constexpr int PAIRED = TN / 2 * 2;
+    auto col_block = [&](int j) { return j < PAIRED ? wn * PAIRED + j : WAVES_N * PAIRED + wn; };
+    auto b_row = [&](int j) { return (BM / 32 + col_block(j)) * BLOCK; };
     // Byte offsets of the 8-byte tail reads, one opaque register each: reads whose addresses share a
     // visible base get merged into paired reads, whose result could not land in two operand tuples
     // without register copies.
-    int ta[2][TM], tb[2][TN];
+    int ta[TM], tb[TN];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int i = 0; i < TM; ++i) { ta[i] = a_row + i * BLOCK + toff; asm volatile("" : "+v"(ta[i])); }
 #pragma unroll
-        for (int i = 0; i < TM; ++i) { ta[kb][i] = a_row + i * BLOCK + toff[kb]; asm volatile("" : "+v"(ta[kb][i])); }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) { tb[kb][j] = b_row + j * BLOCK + toff[kb]; asm volatile("" : "+v"(tb[kb][j])); }
-    }
+    for (int j = 0; j < TN; ++j) { tb[j] = b_row(j) + toff; asm volatile("" : "+v"(tb[j])); }
 
-    // epilogue constants: in the last stage of the ring, which the next tile's first loads do not touch
-    float4* lrow_par = reinterpret_cast<float4*>(lds + (STAGES - 1) * STAGE_BYTES);
-    float4* lcol_par = lrow_par + BM;
+    // Epilogue constants, one 16-byte record per row and column of the tile: in the last stage of the ring, which the next
+    // tile's first loads do not touch.  Kept and read as integers: the compiler puts a wait for every direct-to-LDS load
+    // in flight in front of a float-typed LDS read.
+    v4i* lrow_par = reinterpret_cast<v4i*>(lds + (STAGES - 1) * STAGE_BYTES);
+    v4i* lcol_par = lrow_par + BM;
+    // The raw values of one record per thread (rows first), requested a tile ahead of their use and converted only there:
+    // a conversion behind the loads would wait for them.
+    auto load_par = [&](int tile_m, int tile_n) -> v4i {
+        v4i raw = {0, 0, 0, 0};
+        if (tid < BM) {
+            int64_t m = (int64_t)tile_m * BM + tid;
+            m = m < a.M ? m : a.M - 1;
+            raw = *reinterpret_cast<const v4i*>(a.meta + m);
+        } else if (tid < ROWS) {
+            int n = tile_n * BN + tid - BM;
+            n = n < a.N ? n : a.N - 1;
+            raw[0] = a.w_scale[n];
+            raw[1] = a.w_zero[n];
+            raw[2] = __float_as_int(a.w_sum[n]);
+            if (a.out_bias) raw[3] = __float_as_int(a.out_bias[n]);
+        }
+        return raw;
+    };
+    static_assert(ROWS <= THREADS, "one record per thread");
 
     // ---- persistent loop over this workgroup's tiles
     int pid = blockIdx.x;
     int tile_m, tile_n;
     tile_of(pid, tile_m, tile_n);
     set_tile(tile_m, tile_n);
+    v4i par = load_par(tile_m, tile_n);
     issue_prologue();
     bool first = true;
     while (true) {
@@ -205,10 +228,10 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         // fragment number t of the read order B0, A0, B1, .., B(TN-1), A1, .., A(TM-1): the order in which the MFMAs
         // (row block outer, column block inner) first need them
         auto read_nth = [&](int t, const uint8_t* st, int kb, int set) {
-            if (t == 0) read_one(pb[set][0], st + b_row + moff[kb], st + tb[kb][0]);
-            else if (t == 1) read_one(pa[set][0], st + a_row + moff[kb], st + ta[kb][0]);
-            else if (t < TN + 1) read_one(pb[set][t - 1], st + b_row + (t - 1) * BLOCK + moff[kb], st + tb[kb][t - 1]);
-            else read_one(pa[set][t - TN], st + a_row + (t - TN) * BLOCK + moff[kb], st + ta[kb][t - TN]);
+            if (t == 0) read_one(pb[set][0], st + b_row(0) + moff[kb], st + 512 * kb + tb[0]);
+            else if (t == 1) read_one(pa[set][0], st + a_row + moff[kb], st + 512 * kb + ta[0]);
+            else if (t < TN + 1) read_one(pb[set][t - 1], st + b_row(t - 1) + moff[kb], st + 512 * kb + tb[t - 1]);
+            else read_one(pa[set][t - TN], st + a_row + (t - TN) * BLOCK + moff[kb], st + 512 * kb + ta[t - TN]);
         };
         auto read_frags = [&](const uint8_t* st, int kb, int set) {
     #pragma unroll
@@ -231,11 +254,11 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         // also ends every wave's use of the epilogue constants before step 0 refills the last stage.
         if (first) {
             wait_stages(ksteps - 1);
-        } else if (STAGES >= 3) {
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         } else {
-            wait_loads_and_barrier<0>();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         }
+        // stages this tile starts with that have landed already (beyond stage 0)
+        const int landed = first ? 0 : STAGES - 2;
         first = false;
         read_frags(lds, 0, 0);
 
@@ -258,7 +281,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
                         if (t * READS + u < TM + TN) read_nth(t * READS + u, rd_stage, rd_kb, rd_set);
                 }
                 const int i = t / TN, j = t % TN;
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(pa[use_set][i], pb[use_set][j], acc[i][j], 2, 2, 0, 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(pb[use_set][j], pa[use_set][i], acc[i][j], 2, 2, 0, 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (decltype(do_loads)::value) {
     #pragma unroll
@@ -278,15 +301,17 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         // Ring positions and chunk offsets are carried along: a remainder by the number of stages in front of each block
         // of reads (a multiply chain unless it is a power of two) costs a tenth of a step.
         int prev = (STAGES - 1) * STAGE_BYTES, cur = 0, next = STAGE_BYTES;      // stages of steps ks - 1, ks, ks + 1
+        asm volatile("" : "+s"(prev), "+s"(cur), "+s"(next));    // opaque: no addresses of their own for a tile's first steps
         unsigned koff_a = (STAGES - 1) * a_step, koff_w = (STAGES - 1) * w_step;   // chunk ks + STAGES - 1
-        auto k_step = [&](int ks, auto loads0, auto loads1, auto has_next) {
+        auto k_step = [&](int ks, auto loads0, auto loads1, auto has_next, auto next_landed) {
             // kb = 0, reading kb = 1 of this stage ahead
             half(0, lds + cur, 1, 1, std::true_type{}, prev, koff_a, koff_w, SPLIT, loads0);
             koff_a += a_step;
             koff_w += w_step;
             // every read of this stage has been issued; pass the barrier (next stage complete and visible: all but
             // the newest STAGES-2 loads have landed), then kb = 1, reading the next stage's kb = 0 ahead
-            wait_stages(decltype(loads0)::value ? STAGES - 2 : ksteps - 2 - ks);
+            if (decltype(next_landed)::value) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            else wait_stages(decltype(loads0)::value ? STAGES - 2 : ksteps - 2 - ks);
             half(1, lds + next, 0, 0, has_next, cur, koff_a, koff_w, 0, loads1);
             prev = cur;
             cur = next;
@@ -300,122 +325,156 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         }
         __builtin_amdgcn_sched_barrier(0);
         int ks = 0;
-        for (; ks + STAGES < ksteps; ++ks) k_step(ks, yes, yes, yes);
-        if (ks + STAGES - 1 < ksteps) { k_step(ks, yes, no, yes); ++ks; }
-        for (; ks + 1 < ksteps; ++ks) k_step(ks, no, no, yes);
-        k_step(ks, no, no, no);
-        // every wave has passed the last step's barrier, after which nothing reads the ring: request the
-        // next tile's first stages now, so that their latency hides behind this tile's epilogue
+        // the stages that were waited for before the previous tile's stores went out: no wait here, which would be one for
+        // those stores as well
+        for (; ks < landed && ks + STAGES < ksteps; ++ks) k_step(ks, yes, yes, yes, yes);
+        for (; ks + STAGES < ksteps; ++ks) k_step(ks, yes, yes, yes, no);
+        if (ks + STAGES - 1 < ksteps) { k_step(ks, yes, no, yes, no); ++ks; }
+        for (; ks + 1 < ksteps; ++ks) k_step(ks, no, no, yes, no);
+        k_step(ks, no, no, no, no);
+        // every wave has passed the last step's barrier, after which nothing reads the ring: put this tile's constants there
+        // and request the next tile's first stages, so that their latency hides behind this tile's epilogue
+        if (tid < BM) par[2] = __float_as_int((float)par[2]);
+        else { par[0] <<= 16; par[1] <<= 16; }                    // bf16 -> fp32
+        if (tid < ROWS) lrow_par[tid] = par;
         const int next_pid = pid + gridDim.x;
         const bool more = next_pid < total;
         int next_m = 0, next_n = 0;
         if (more) {
             tile_of(next_pid, next_m, next_n);
             set_tile(next_m, next_n);
-            if (STAGES >= 3) issue_prologue();            // with two stages the constants would be overwritten
+            par = load_par(next_m, next_n);
+            issue_prologue();
         }
 
-        // ---- epilogue: row and column constants through LDS
-        for (int i = tid; i < BM; i += THREADS) {
-            int64_t m = m0 + i;
-            m = m < a.M ? m : a.M - 1;
-            const basq_tokmeta mt = a.meta[m];
-            lrow_par[i] = make_float4(mt.scale, mt.lo, (float)mt.rowsum, 0.0f);
-        }
-        for (int i = tid; i < BN; i += THREADS) {
-            int n = n0 + i;
-            n = n < a.N ? n : a.N - 1;
-            lcol_par[i] = make_float4(bf16_to_f32(a.w_scale[n]), bf16_to_f32(a.w_zero[n]), a.w_sum[n],
-                                      a.out_bias ? a.out_bias[n] : 0.0f);
-        }
-        __syncthreads();
-
+        // ---- epilogue.  The weights are the first MFMA operand: accumulator register r of lane l belongs to token l % 32 of
+        // the row block and to output channel 8*(r/4) + 4*(l/32) + r%4 of the column block, so a lane turns four adjacent
+        // channels into two dwords of packed bf16.
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // LDS only: the next tile's loads stay in flight
         // (re)derived per tile from an opaque copy of the lane index: everything computed from it below
         // would otherwise be hoisted out of the tile loop and held in registers across the main loop
         int elane = lane;
         asm volatile("" : "+v"(elane));
-        const int col_in_tile = elane & 31, rgrp = elane >> 5;
-        float4 cp[TN];
+        const int tok = elane & 31, ehalf = elane >> 5;
+        v4i rp[TM];                                               // scale, lower bound, row sum of this lane's tokens
 #pragma unroll
-        for (int j = 0; j < TN; ++j) cp[j] = lcol_par[wn * WN + j * 32 + col_in_tile];
-
-        // Pair path: two adjacent rows per step.  A lane turns its two values (same column, rows A and A+1)
-        // into one packed bf16 pair, trades it with the neighbouring column's lane (DPP), and a byte permute
-        // leaves even lanes with (row A; columns c, c+1) and odd lanes with (row A+1; columns c-1, c): every
-        // lane stores one dword, every half-wave 64-byte runs of two rows.
-        const bool pair_ok = a.acc_out == nullptr && (a.ldy & 1) == 0 && (a.N & 1) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 3) == 0;
-        if (pair_ok) {
+        for (int i = 0; i < TM; ++i) rp[i] = lrow_par[wm * WM + i * 32 + tok];
+        auto dequant = [&](float s64, v4i row, v4i col) {
+            // 64 * S is the integer accumulator, exactly
+            const float t = fmaf(64.0f, s64, -(__int_as_float(col[1]) * __int_as_float(row[2])));
+            return fmaf(__int_as_float(row[0]) * __int_as_float(col[0]), t,
+                        fmaf(__int_as_float(row[1]), __int_as_float(col[2]), __int_as_float(col[3])));
+        };
+        if (a.acc_out == nullptr && (a.ldy & 1) == 0 && (a.N & 1) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 3) == 0) {
             typedef float f2 __attribute__((ext_vector_type(2)));
             typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-            const int odd = elane & 1;
-            const unsigned sel = odd ? 0x03020706u : 0x05040100u;
-            // first every output dword into registers (they take the accumulators' place) ...
-            unsigned outv[TM][8][TN];
+            // first every output into registers (they take the accumulators' place) ...
+            unsigned outv[TM][TN][4][2];                          // [..][q][p]: channels 8q + 4*ehalf + 2p, +1
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
+            for (int j = 0; j < TN; ++j) {
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int rowA = 8 * (q >> 1) + 4 * rgrp + 2 * (q & 1);        // register 2q; register 2q+1 is the next row
-                    const float4 rpA = lrow_par[wm * WM + i * 32 + rowA];
-                    const float4 rpB = lrow_par[wm * WM + i * 32 + rowA + 1];
+                for (int q = 0; q < 4; ++q) {
+                    v4i cp[4];
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const float tA = fmaf(64.0f, acc[i][j][2 * q], -(cp[j].y * rpA.z));      // 64*S is the integer accumulator, exactly
-                        const float tB = fmaf(64.0f, acc[i][j][2 * q + 1], -(cp[j].y * rpB.z));
-                        const float yA = fmaf(rpA.x * cp[j].x, tA, fmaf(rpA.y, cp[j].z, cp[j].w));
-                        const float yB = fmaf(rpB.x * cp[j].x, tB, fmaf(rpB.y, cp[j].z, cp[j].w));
-                        const unsigned mine = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){yA, yB}, b2));   // hardware round-to-nearest-even
-                        const unsigned other = (unsigned)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xF, 0xF, false);   // lane ^ 1
-                        outv[i][q][j] = __builtin_amdgcn_perm(other, mine, sel);
+                    for (int e = 0; e < 4; ++e) cp[e] = lcol_par[col_block(j) * 32 + 8 * q + 4 * ehalf + e];
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) {
+                            const float y0 = dequant(acc[i][j][4 * q + 2 * p], rp[i], cp[2 * p]);
+                            const float y1 = dequant(acc[i][j][4 * q + 2 * p + 1], rp[i], cp[2 * p + 1]);
+                            outv[i][j][q][p] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){y0, y1}, b2));   // hardware round-to-nearest-even
+                            asm volatile("" : "+v"(outv[i][j][q][p]));   // computed here: one set of column constants at a time
+                        }
                     }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
             // ... then wait for the next tile's first stages (requested before this epilogue, so mostly
             // landed), and only then send the stores: a wait placed after them would have to wait for
             // the stores too, the counter being one and the same
-            if (more && STAGES >= 3) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            // Lane bit 5 (which four of eight channels) trades places with the low bit of q, lane bit 4 (token) with its high
+            // bit, and in a pair of column blocks lane bit 3 (token) with the block: a lane then owns 16 bytes of one token's
+            // row, and a store covers whole 128-byte lines of eight rows.
+            const bool wide = (a.ldy & 7) == 0 && (a.N & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0;
+            const int piece = 2 * ((elane >> 4) & 1) + ehalf;
+            const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;   // of the matrix, from the tile's start
+            auto store16 = [&](int row, int col, unsigned o0, unsigned o1, unsigned o2, unsigned o3) {      // within the tile
+                if (row >= row_end) return;
+                uint16_t* dst = a.Y + (m0 + row) * a.ldy + n0 + col;
+                if (wide) {
+                    if (col < col_end) nt_store16(dst, make_uint4(o0, o1, o2, o3));
+                } else {
+                    const unsigned o[4] = {o0, o1, o2, o3};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + 2 * e < col_end) *reinterpret_cast<uint32_t*>(dst + 2 * e) = o[e];
+                }
+            };
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
+                const int row0 = wm * WM + i * 32;
+                unsigned z[TN][2][4];                             // [block][token / 16][dword] of 16 bytes: piece `piece` of token l % 16
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int rowA = 8 * (q >> 1) + 4 * rgrp + 2 * (q & 1);
-                    const int64_t m = m0 + wm * WM + i * 32 + rowA + odd;
-                    uint16_t* yrow = a.Y + m * a.ldy + n0 + wn * WN + (col_in_tile & ~1);
+                for (int j = 0; j < TN; ++j) {
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int n = n0 + wn * WN + j * 32 + (col_in_tile & ~1);
-                        if (m < a.M && n < a.N) *reinterpret_cast<uint32_t*>(yrow + j * 32) = outv[i][q][j];
+                    for (int p = 0; p < 2; ++p) {
+                        const auto u = __builtin_amdgcn_permlane32_swap(outv[i][j][0][p], outv[i][j][1][p], false, false);
+                        const auto v = __builtin_amdgcn_permlane32_swap(outv[i][j][2][p], outv[i][j][3][p], false, false);
+                        z[j][0][p] = u[0]; z[j][0][2 + p] = u[1];
+                        z[j][1][p] = v[0]; z[j][1][2 + p] = v[1];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const auto u = __builtin_amdgcn_permlane16_swap(z[j][0][e], z[j][1][e], false, false);
+                        z[j][0][e] = u[0]; z[j][1][e] = u[1];
                     }
                 }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int j = 0; j < TN; j += 2) {
+                        if (j + 1 < TN) {
+                            unsigned lo[4], hi[4];                // tokens 0..7 and 8..15 of the sixteen (row rotation by 8 lanes)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                lo[e] = (unsigned)__builtin_amdgcn_update_dpp((int)z[j][h][e], (int)z[j + 1][h][e], 0x128, 0xF, 0xC, false);
+                                hi[e] = (unsigned)__builtin_amdgcn_update_dpp((int)z[j + 1][h][e], (int)z[j][h][e], 0x128, 0xF, 0x3, false);
+                            }
+                            const int row = row0 + 16 * h + (elane & 7), col = (col_block(j) + ((elane >> 3) & 1)) * 32 + 8 * piece;
+                            store16(row, col, lo[0], lo[1], lo[2], lo[3]);
+                            store16(row + 8, col, hi[0], hi[1], hi[2], hi[3]);
+                        } else {
+                            store16(row0 + 16 * h + (elane & 15), col_block(j) * 32 + 8 * piece, z[j][h][0], z[j][h][1], z[j][h][2], z[j][h][3]);
+                        }
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
+            for (int j = 0; j < TN; ++j) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int row = wm * WM + i * 32 + 8 * (r >> 2) + 4 * rgrp + (r & 3);
-                    const int64_t m = m0 + row;
-                    if (m >= a.M) continue;
-                    const float4 rp = lrow_par[row];
-                    uint16_t* yrow = a.Y + m * a.ldy;
+                    const int col = col_block(j) * 32 + 8 * (r >> 2) + 4 * ehalf + (r & 3);
+                    const v4i cp = lcol_par[col];
+                    if (n0 + col < a.N) {
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int n = n0 + wn * WN + j * 32 + col_in_tile;
-                        if (n < a.N) {
-                            const int av = __float2int_rn(64.0f * acc[i][j][r]);
-                            const float t = (float)av - cp[j].y * rp.z;
-                            const float y = fmaf(rp.x * cp[j].x, t, fmaf(rp.y, cp[j].z, cp[j].w));
-                            yrow[n] = f32_to_bf16(y);
-                            if (a.acc_out) a.acc_out[m * (int64_t)a.N + n] = av;
+                        for (int i = 0; i < TM; ++i) {
+                            const int64_t m = m0 + wm * WM + i * 32 + tok;
+                            if (m < a.M) {
+                                a.Y[m * a.ldy + n0 + col] = f32_to_bf16(dequant(acc[i][j][r], rp[i], cp));
+                                if (a.acc_out) a.acc_out[m * (int64_t)a.N + n0 + col] = __float2int_rn(64.0f * acc[i][j][r]);
+                            }
                         }
                     }
                 }
             }
+            if (more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // loads and stores alike
         }
         if (!more) break;
-        if (!pair_ok && STAGES >= 3) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // slow path: loads and stores alike
         pid = next_pid; tile_m = next_m; tile_n = next_n;
-        if (STAGES < 3) issue_prologue();                 // two stages: only now is the ring free of the constants
     }
 #endif  // __HIP_DEVICE_COMPILE__
 }
