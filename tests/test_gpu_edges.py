@@ -467,10 +467,10 @@ def test_packed_operands_of_two_to_four_gib_and_beyond(M):
 
 
 @pytest.mark.parametrize("K", [128, 256, 384, 512, 640, 896])
-@pytest.mark.parametrize("M,N,pad", [(129, 64, 0), (300, 1000, 0), (257, 514, 2), (131, 333, 1), (700, 20480, 8)])
+@pytest.mark.parametrize("M,N,pad", [(129, 64, 0), (300, 1000, 0), (257, 514, 2), (131, 333, 1), (700, 20480, 8), (1030, 4100, 4), (2000, 12300, 4)])
 def test_fp6_product_over_few_k_steps(K, M, N, pad):
     """Every length of the K loop around the depth of its ring of LDS stages (no steady step at all, one, several), each
-    with ragged tiles, more tiles than compute units (the last shape) and each alignment of the output rows: the bits of
+    with ragged tiles, every tiling, more tiles than compute units hold at once and each alignment of the output rows: the bits of
     the int8 path (exact integer products, the same epilogue arithmetic, so no tolerance)."""
     announce(f"fp6 product M={M} N={N} K={K} pad={pad}")
     gen = torch.Generator(device=DEV).manual_seed(K + M)
