@@ -102,11 +102,18 @@ int validate_fp6(const uint8_t* Aq6, const uint8_t* Wq6, bool need_a, int32_t K)
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// The kernels that write the fp6 form of the codes themselves can leave the 4-bit form out.
+// The kernels that write the fp6 form of the codes themselves can leave the 4-bit form out; basq_rotate_quant offers that
+// to its callers for the first two, the one-call layer uses all four.
 bool fp6_only_applicable(const RotateQuantArgs& a) {
     RotateQuantArgs b = a;
     b.Aq = nullptr;
     return b.Aq6 != nullptr && b.group == b.K && (rotate_quant_pow2_applicable(b) || rotate_quant_k28_applicable(b));
+}
+bool layer_fp6_only_applicable(const RotateQuantArgs& a) {
+    RotateQuantArgs b = a;
+    b.Aq = nullptr;
+    return fp6_only_applicable(a) ||
+           (b.Aq6 != nullptr && b.group == b.K && (rotate_quant_small_applicable(b) || rotate_quant_block_applicable(b)));
 }
 
 // the one-call layer on a workspace of the caller's or of the library's own (both entry points end here)
@@ -150,7 +157,7 @@ int linear_fused_impl(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t 
                w_sum, out_bias, static_cast<uint16_t*>(Y), ldy, nullptr, Aq6, Aq6 ? Wq6 : nullptr, w_layout};
     // when the product runs on the fp6 matrix path nothing reads the 4-bit codes: where the quantiser writes the
     // fp6 form itself it leaves them out
-    if (Aq6 && gemm_fp6_applicable(g) && fp6_only_applicable(a)) a.Aq = nullptr;
+    if (Aq6 && gemm_fp6_applicable(g) && layer_fp6_only_applicable(a)) a.Aq = nullptr;
     if (w_layout != BASQ_W_CANONICAL && M > GEMV_MAX_TOKENS && !gemm_fp6_applicable(g))      // before anything is launched
         return fail(BASQ_EUNSUPPORTED, "more than 128 tokens with the streaming weight layout need the fp6 operands "
                                         "(the int8 kernels read canonical weights)");

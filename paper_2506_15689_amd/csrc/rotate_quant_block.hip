@@ -1,4 +1,4 @@
-// Fast rotate + bias + quantise kernel for BLOCKWISE rotations: rot_size n in {128, 256, 512} applied to every
+// Fast rotate + bias + quantise kernels for BLOCKWISE rotations: rot_size n in {128, 256, 512} applied to every
 // block of n channels of a longer token (K a multiple of n and of 256, K <= 16384), per-token ranges.  This is the
 // shape of a layer whose width has no Hadamard matrix of its own size in this library -- e.g. the 11008 = 43 * 256
 // wide MLP of the 7B LLaMA-2 that the paper's Sec. 5.2 times -- rotated in blocks instead (paper Sec. 3.1 rotation,
@@ -20,6 +20,14 @@
 //   codes     a lane's four bytes (two codes each) are 4 bytes apart and the four lanes of a quad fill the gaps:
 //             a 4 x 4 byte transpose inside the quad (DPP + v_perm) gives every lane one aligned dword of the
 //             16-byte segment, and a store instruction writes 256 contiguous bytes of the row.
+//   fp6 form  made from those dwords inside the quad, about 30 vector instructions a piece on top of 100.  A repacking
+//             launch behind the kernel cost 4-6 us up to 2048 tokens and a pass over the codes beyond (the layer with 64
+//             output channels, K = 11008 in blocks of 256: 1021 tokens 87 -> 33 us with the product's share, 16384 tokens
+//             249 -> 187 us).
+//
+// Whole tokens of 512, 1024 or 2048 channels (rotate_quant_small_kernel) are one to four such pieces of ONE wave.  They
+// took the generic kernel of one workgroup per token in LDS: K = 1024, 64 tokens 5.3 -> 3.1 us, 4096 tokens 23.0 -> 5.3 us,
+// 65536 tokens 311 -> 42.8 us (3.9 TB/s; the rest is vector instructions, 16 values a lane).
 #include "rotate_pow2_token.h"
 
 namespace basq {
@@ -49,11 +57,12 @@ __device__ __forceinline__ void rb_cross_lane_bfly(float& x, float& y) {
 
 // B operand of the MFMA: k = 8*(lane/16) + t carries input bits (e0,e1,e2,e7,e8), column lane%16 of half h carries
 // output bits (h; e1,e2,e7,e8).  H over the low LOG2N-4 of those five bits, identity over the rest.
-template <int LOG2N>
+// Entries +-2^-SHIFT.
+template <int LOG2N, int SHIFT>
 __device__ __forceinline__ void rb_make_bop(int lane, v8bf (&bop)[2]) {
     constexpr int MASK = (1 << (LOG2N - 4)) - 1;       // 7 -> 0b00111, 8 -> 0b01111, 9 -> 0b11111
     const int jp = lane & 15, g = lane >> 4;
-    const uint16_t mag = LOG2N == 8 ? (uint16_t)((127 - 4) << 7) : (uint16_t)0x3F80;
+    const uint16_t mag = (uint16_t)((127 - SHIFT) << 7);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         v8s tmp;
@@ -73,22 +82,126 @@ __device__ __forceinline__ uint32_t rb_dpp_u(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
 }
 
+// The stages of one piece: MFMA, then e5, e6 in registers, then e3, e4 across lane bits 4 and 5.
+__device__ __forceinline__ void rb_rotate_piece(const uint4& raw, const v8bf (&bop)[2], float (&d)[2][4]) {
+    const v8bf aop = __builtin_bit_cast(v8bf, raw);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, bop[h], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d[h][r] = acc[r];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        BFLY(d[h][0], d[h][1]);                // e5
+        BFLY(d[h][2], d[h][3]);
+        BFLY(d[h][0], d[h][2]);                // e6
+        BFLY(d[h][1], d[h][3]);
+        rb_cross_lane_bfly<false>(d[h][0], d[h][1]);   // e3 <-> lane bit 4; register bit r0 now means e3
+        rb_cross_lane_bfly<false>(d[h][2], d[h][3]);
+        rb_cross_lane_bfly<true>(d[h][0], d[h][2]);    // e4 <-> lane bit 5; register bit r1 now means e4
+        rb_cross_lane_bfly<true>(d[h][1], d[h][3]);
+    }
+}
+
+// where a lane's values of a piece end up: e = rb_eout + h + 8*r0 + 16*r1
+__device__ __forceinline__ int rb_eout(int lane) {
+    return 2 * (lane & 1) + 4 * ((lane >> 1) & 1) + 128 * ((lane >> 2) & 1) + 256 * ((lane >> 3) & 1) +
+           32 * ((lane >> 4) & 1) + 64 * ((lane >> 5) & 1);
+}
+// the 32-channel segment of the piece whose codes the lane's quad holds
+__device__ __forceinline__ int rb_segment(int lane) {
+    return ((lane >> 4) & 1) + 2 * ((lane >> 5) & 1) + 4 * ((lane >> 2) & 1) + 8 * ((lane >> 3) & 1);
+}
+
+// Codes of a lane's eight values; returns the aligned dword of eight consecutive channels' codes, channels
+// 32*segment + 8*(lane%4) .. +7 of the piece, and adds the lane's own codes to `sum` if `count`.
+__device__ __forceinline__ uint32_t rb_codes(const float (&v)[2][4], float inv, float nlo, int lane, bool count, int& sum) {
+    uint32_t ev = 0, od = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float t0 = __builtin_amdgcn_fmed3f(fmaf(v[0][r], inv, nlo), 0.0f, 15.0f);
+        const float t1 = __builtin_amdgcn_fmed3f(fmaf(v[1][r], inv, nlo), 0.0f, 15.0f);
+        ev = __builtin_amdgcn_cvt_pk_u8_f32(t0, r, ev);          // round-half-to-even, NaN -> 0
+        od = __builtin_amdgcn_cvt_pk_u8_f32(t1, r, od);
+    }
+    if (count) {
+        sum = __builtin_amdgcn_udot4(ev, 0x01010101u, sum, false);
+        sum = __builtin_amdgcn_udot4(od, 0x01010101u, sum, false);
+    }
+    // byte r of `w`: the row's byte at 256*c + 16*seg + q4 + 4*r.  Quad transpose: lane q4 ends with the bytes
+    // q4 of its quad's four words, i.e. the aligned dword at ... + 4*q4.
+    const int q4 = lane & 3;                                             // position in the quad
+    const uint32_t sel = (uint32_t)q4 | ((uint32_t)(4 + q4) << 8);       // v_perm: byte q4 of each of two dwords
+    const uint32_t w = ev | (od << 4);
+    const uint32_t w0 = rb_dpp_u<0x00>(w), w1 = rb_dpp_u<0x55>(w), w2 = rb_dpp_u<0xAA>(w), w3 = rb_dpp_u<0xFF>(w);
+    const uint32_t lo2 = __builtin_amdgcn_perm(w1, w0, sel);             // bytes (w0[q4], w1[q4], -, -)
+    const uint32_t hi2 = __builtin_amdgcn_perm(w3, w2, sel);
+    return __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
+}
+
+// The same codes in the fp6 operand form (fp6_pack.hip): the four lanes of a quad hold a group of 32 codes, whose
+// 24-byte string of 6-bit fields is 48 bits from each lane.  Lane q4 of the quad stores dword q4 of the first 16 bytes,
+// lanes 0 and 1 one dword of the last 8 each.  `group16` and `group8`: where the group's two parts go.
+__device__ __forceinline__ void rb_store_fp6(uint32_t word, int q4, uint8_t* group16, uint8_t* group8) {
+    uint32_t f[4];                                                       // two 6-bit fields each
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = ((word >> (8 * i)) & 15u) | (((word >> (8 * i + 4)) & 15u) << 6);
+    const uint32_t lo = f[0] | (f[1] << 12) | (f[2] << 24);             // bits 0..31 of the lane's 48
+    const uint32_t hi = (f[2] >> 8) | (f[3] << 4);                      // bits 32..47
+    // dwords 0..3: L0.lo; L0.hi, L1.lo (low half); L1.lo (high half), L1.hi; L2.lo
+    const uint32_t plo = rb_dpp_u<0x90>(lo), phi = rb_dpp_u<0x90>(hi);   // from lanes 0, 0, 1, 2 of the quad
+    const uint32_t sel = q4 == 1 ? 0x05040100u : q4 == 2 ? 0x05040302u : 0x03020100u;
+    *reinterpret_cast<uint32_t*>(group16 + 4 * q4) = __builtin_amdgcn_perm(q4 == 1 ? lo : phi, q4 == 1 ? phi : plo, sel);
+    // dwords 4, 5: L2.hi, L3.lo (low half); L3.lo (high half), L3.hi
+    const uint32_t lo3 = rb_dpp_u<0xFF>(lo), hi3 = rb_dpp_u<0xFF>(hi), hi2 = rb_dpp_u<0xAA>(hi);
+    const uint32_t tail = q4 == 0 ? __builtin_amdgcn_perm(lo3, hi2, 0x05040100u) : __builtin_amdgcn_perm(hi3, lo3, 0x05040302u);
+    if (q4 < 2) *reinterpret_cast<uint32_t*>(group8 + 4 * q4) = tail;
+}
+
+// Workgroup number of this block, renumbered so that runs of RUN consecutive workgroups of `total` go to one XCD (blocks
+// congruent mod 8 do): the 8-byte tails that 32 neighbouring tokens write next to each other then meet in one L2.
+template <int RUN>
+__device__ __forceinline__ unsigned rb_renumber(unsigned bid, unsigned total) {
+    const unsigned full = total / (8 * RUN) * (8 * RUN);
+    const unsigned base = bid < full ? 0 : full, run = bid < full ? RUN : (total - full) / 8;
+    const unsigned b = bid - base, xcd = b % 8, i = b / 8;
+    if (bid >= full && i >= run) return bid;                            // the last total % 8
+    return base + (i / (run ? run : 1) * 8 + xcd) * run + i % (run ? run : 1);
+}
+
+// Where the groups of one token that this lane's quad holds go in the fp6 form.
+struct RbFp6 {
+    uint8_t *group16, *group8;      // of piece 0
+    int64_t piece_bytes;            // four chunks of 128 codes
+    __device__ __forceinline__ RbFp6(const RotateQuantArgs& a, int64_t m, int seg) {
+        const int64_t rb6 = (a.M + 31) >> 5;
+        const int r = (int)(m & 31), f = seg & 3;
+        uint8_t* block = a.Aq6 + ((int64_t)(seg >> 2) * rb6 + (m >> 5)) * 3072;
+        group16 = block + 64 * r + 16 * (f ^ ((r >> 2) & 3));
+        group8 = block + 2048 + 256 * f + 8 * r;
+        piece_bytes = 4 * rb6 * 3072;
+    }
+    __device__ __forceinline__ void store(uint32_t word, int q4, int piece) const {
+        rb_store_fp6(word, q4, group16 + piece * piece_bytes, group8 + piece * piece_bytes);
+    }
+};
+
 template <int LOG2N, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
 __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQuantArgs a, float norm) {
     constexpr bool FOLD_NORM = LOG2N == 8;           // 1/sqrt(256) = 2^-4 sits in the MFMA operand
     __shared__ float red_mn[RB_WAVES], red_mx[RB_WAVES];
     __shared__ int red_sum[RB_WAVES];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t m = blockIdx.x;
+    const int64_t m = rb_renumber<32>(blockIdx.x, gridDim.x);
     const int K = a.K;
     const int np = (K + 511) >> 9;                    // pieces of the token (the last one may be half: K % 512 = 256)
     const P2Lane pl = p2_lane(lane);
     v8bf bop[2];
-    rb_make_bop<LOG2N>(lane, bop);
+    rb_make_bop<LOG2N, FOLD_NORM ? 4 : 0>(lane, bop);
 
-    // where this lane's values of a piece end up: e = eout + h + 8*r0 + 16*r1
-    const int eout = 2 * (lane & 1) + 4 * ((lane >> 1) & 1) + 128 * ((lane >> 2) & 1) + 256 * ((lane >> 3) & 1) +
-                     32 * ((lane >> 4) & 1) + 64 * ((lane >> 5) & 1);
+    const int eout = rb_eout(lane);
 
     // ---- all of this wave's pieces are requested at once ------------------------------------------------------
     const uint16_t* x = a.X + m * a.ldx;
@@ -107,25 +220,7 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
         const int c = wave + RB_WAVES * p;
         if (c < np) {                                  // uniform over the wave
             float d[2][4];
-            const v8bf aop = __builtin_bit_cast(v8bf, raw[p]);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                v4f acc = {0.f, 0.f, 0.f, 0.f};
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, bop[h], acc, 0, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) d[h][r] = acc[r];
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                BFLY(d[h][0], d[h][1]);                // e5
-                BFLY(d[h][2], d[h][3]);
-                BFLY(d[h][0], d[h][2]);                // e6
-                BFLY(d[h][1], d[h][3]);
-                rb_cross_lane_bfly<false>(d[h][0], d[h][1]);   // e3 <-> lane bit 4; register bit r0 now means e3
-                rb_cross_lane_bfly<false>(d[h][2], d[h][3]);
-                rb_cross_lane_bfly<true>(d[h][0], d[h][2]);    // e4 <-> lane bit 5; register bit r1 now means e4
-                rb_cross_lane_bfly<true>(d[h][1], d[h][3]);
-            }
+            rb_rotate_piece(raw[p], bop, d);
             const int e0 = 512 * c + eout;
             const bool ok = e0 < K;                    // a half piece: the lanes of its missing 256 channels
 #pragma unroll
@@ -164,35 +259,19 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
 
     // ---- pass 2: quantise, pack, store -------------------------------------------------------------------------
     int sum = 0;
-    const int q4 = lane & 3;                                             // position in the quad
-    const uint32_t sel = (uint32_t)q4 | ((uint32_t)(4 + q4) << 8);       // v_perm: byte q4 of each of two dwords
-    const int seg = ((lane >> 4) & 1) + 2 * ((lane >> 5) & 1) + 4 * ((lane >> 2) & 1) + 8 * ((lane >> 3) & 1);
-    uint8_t* orow = a.Aq + m * (int64_t)(K / 2) + 16 * seg + 4 * q4;
+    const int q4 = lane & 3, seg = rb_segment(lane);
+    uint8_t* orow = a.Aq ? a.Aq + m * (int64_t)(K / 2) + 16 * seg + 4 * q4 : nullptr;
+    const RbFp6 f6(a, m, seg);
 #pragma unroll
     for (int p = 0; p < RB_PMAX; ++p) {
         const int c = wave + RB_WAVES * p;
         if (c < np) {
             const bool ok = 512 * c + eout < K;
-            uint32_t ev = 0, od = 0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float t0 = __builtin_amdgcn_fmed3f(fmaf(v[p][0][r], inv, nlo), 0.0f, 15.0f);
-                const float t1 = __builtin_amdgcn_fmed3f(fmaf(v[p][1][r], inv, nlo), 0.0f, 15.0f);
-                ev = __builtin_amdgcn_cvt_pk_u8_f32(t0, r, ev);          // round-half-to-even, NaN -> 0
-                od = __builtin_amdgcn_cvt_pk_u8_f32(t1, r, od);
-            }
+            const uint32_t word = rb_codes(v[p], inv, nlo, lane, ok, sum);
             if (ok) {
-                sum = __builtin_amdgcn_udot4(ev, 0x01010101u, sum, false);
-                sum = __builtin_amdgcn_udot4(od, 0x01010101u, sum, false);
+                if (a.Aq) *reinterpret_cast<uint32_t*>(orow + 256 * c) = word;
+                if (a.Aq6) f6.store(word, q4, c);
             }
-            // byte r of `w`: the row's byte at 256*c + 16*seg + q4 + 4*r.  Quad transpose: lane q4 ends with the bytes
-            // q4 of its quad's four words, i.e. the aligned dword at ... + 4*q4.
-            const uint32_t w = ev | (od << 4);
-            const uint32_t w0 = rb_dpp_u<0x00>(w), w1 = rb_dpp_u<0x55>(w), w2 = rb_dpp_u<0xAA>(w), w3 = rb_dpp_u<0xFF>(w);
-            const uint32_t lo2 = __builtin_amdgcn_perm(w1, w0, sel);     // bytes (w0[q4], w1[q4], -, -)
-            const uint32_t hi2 = __builtin_amdgcn_perm(w3, w2, sel);
-            const uint32_t word = __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
-            if (ok) *reinterpret_cast<uint32_t*>(orow + 256 * c) = word;
         }
     }
     sum = wave_sum_i(sum);
@@ -202,6 +281,95 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
         basq_tokmeta mt;
         mt.scale = s; mt.lo = lo; mt.rowsum = red_sum[0] + red_sum[1] + red_sum[2] + red_sum[3]; mt.reserved = 0;
         a.meta[m] = mt;
+    }
+}
+
+// rot_size == K = 512 * NP, NP in {1, 2, 4}: the token is one rotation block of up to four pieces, which one wavefront
+// holds (8 values per lane per piece).  The stages over e9 (, e10) pair its pieces register by register; nothing crosses
+// waves, so there is no LDS and no barrier, and the four waves of a workgroup take four tokens.  b^c and s^a stay in
+// registers over a wave's tokens, the next token is requested before the current one is worked on.
+template <int NP, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
+__global__ __launch_bounds__(RB_THREADS) void rotate_quant_small_kernel(RotateQuantArgs a, float norm) {
+    constexpr bool FOLD_NORM = NP == 2;                // 1/sqrt(1024) = 2^-5 sits in the MFMA operand
+    constexpr int K = 512 * NP;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const P2Lane pl = p2_lane(lane);
+    v8bf bop[2];
+    rb_make_bop<9, FOLD_NORM ? 5 : 0>(lane, bop);
+    const int eout = rb_eout(lane), q4 = lane & 3, seg = rb_segment(lane);
+    const int64_t step = (int64_t)gridDim.x * RB_WAVES;
+    int64_t m = (int64_t)rb_renumber<8>(blockIdx.x, gridDim.x) * RB_WAVES + wave;
+    if (m >= a.M) return;
+    uint4 raw[NP];
+#pragma unroll
+    for (int c = 0; c < NP; ++c) raw[c] = nt_load16(a.X + m * a.ldx + 512 * c + 8 * pl.chunk);
+    float2 bb[NP][4], ss[NP][4];
+#pragma unroll
+    for (int c = 0; c < NP; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (HAS_BIAS) bb[c][r] = *reinterpret_cast<const float2*>(a.bias + 512 * c + eout + 8 * r);
+            if (HAS_SCALE) ss[c][r] = *reinterpret_cast<const float2*>(a.act_scale + 512 * c + eout + 8 * r);
+        }
+    while (true) {
+        float v[NP][2][4];
+#pragma unroll
+        for (int c = 0; c < NP; ++c) rb_rotate_piece(raw[c], bop, v[c]);
+        const int64_t next = m + step;
+        if (next < a.M) {
+#pragma unroll
+            for (int c = 0; c < NP; ++c) raw[c] = nt_load16(a.X + next * a.ldx + 512 * c + 8 * pl.chunk);
+        }
+#pragma unroll
+        for (int st = 1; st < NP; st <<= 1)            // e9, e10
+#pragma unroll
+            for (int c = 0; c < NP; ++c)
+                if ((c & st) == 0)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) BFLY(v[c][h][r], v[c + st][h][r]);
+        float mn = INFINITY, mx = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < NP; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float r0 = v[c][0][r], r1 = v[c][1][r];
+                if (!FOLD_NORM) { r0 = r0 * norm; r1 = r1 * norm; }
+                if (ROT_OUT) *reinterpret_cast<float2*>(a.rot_out + m * (int64_t)K + 512 * c + eout + 8 * r) = make_float2(r0, r1);
+                const float b0 = HAS_BIAS ? bb[c][r].x : 0.0f, b1 = HAS_BIAS ? bb[c][r].y : 0.0f;
+                const float v0 = HAS_SCALE ? fmaf(r0, ss[c][r].x, -b0) : r0 - b0;
+                const float v1 = HAS_SCALE ? fmaf(r1, ss[c][r].y, -b1) : r1 - b1;
+                v[c][0][r] = v0;
+                v[c][1][r] = v1;
+                mn = fminf(mn, fminf(v0, v1));
+                mx = fmaxf(mx, fmaxf(v0, v1));
+            }
+        mn = wave_min_f(mn);
+        mx = wave_max_f(mx);
+        const float lo = a.clip_lo * mn;
+        const float hi = a.clip_hi * mx;
+        float s = __fdiv_rn(hi - lo, 15.0f);
+        if (!(s > 0.0f && s < INFINITY)) s = 1.0f;
+        const float inv = __fdiv_rn(1.0f, s);
+        const float nlo = -(lo * inv);
+        int sum = 0;
+        uint8_t* orow = a.Aq ? a.Aq + m * (int64_t)(K / 2) + 16 * seg + 4 * q4 : nullptr;
+        const RbFp6 f6(a, m, seg);
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {
+            const uint32_t word = rb_codes(v[c], inv, nlo, lane, true, sum);
+            if (a.Aq) *reinterpret_cast<uint32_t*>(orow + 256 * c) = word;
+            if (a.Aq6) f6.store(word, q4, c);
+        }
+        sum = wave_sum_i(sum);
+        if (lane == 0) {
+            basq_tokmeta mt;
+            mt.scale = s; mt.lo = lo; mt.rowsum = sum; mt.reserved = 0;
+            a.meta[m] = mt;
+        }
+        if (next >= a.M) return;
+        m = next;
     }
 }
 
@@ -218,13 +386,40 @@ int launch_rb(const RotateQuantArgs& a, hipStream_t s, float norm) {
     return check_hip(hipGetLastError(), "rotate_quant (blockwise) launch");
 }
 
+template <int NP>
+int launch_rs(const RotateQuantArgs& a, hipStream_t s, float norm) {
+    const bool hb = a.bias != nullptr, hs = a.act_scale != nullptr, ro = a.rot_out != nullptr;
+    // one token per wave up to 8192 tokens, then every wave walks on (eight waves per SIMD at most)
+    const int64_t want = (a.M + RB_WAVES - 1) / RB_WAVES;
+    const dim3 grid((unsigned)(want < 2048 ? want : 2048)), block(RB_THREADS);
+#define RS_LAUNCH(HB, HS, RO) hipLaunchKernelGGL((rotate_quant_small_kernel<NP, HB, HS, RO>), grid, block, 0, s, a, norm)
+    if (hb && hs) { if (ro) RS_LAUNCH(true, true, true); else RS_LAUNCH(true, true, false); }
+    else if (hb) { if (ro) RS_LAUNCH(true, false, true); else RS_LAUNCH(true, false, false); }
+    else if (hs) { if (ro) RS_LAUNCH(false, true, true); else RS_LAUNCH(false, true, false); }
+    else { if (ro) RS_LAUNCH(false, false, true); else RS_LAUNCH(false, false, false); }
+#undef RS_LAUNCH
+    return check_hip(hipGetLastError(), "rotate_quant (small token) launch");
+}
+
 }  // namespace
 
 bool rotate_quant_block_applicable(const RotateQuantArgs& a) {
     // per-token ranges; n = 512 needs whole 512-channel pieces, 128 and 256 also take a last piece of 256 channels
     return a.group == a.K && !a.has28 && (a.rot_size == 128 || a.rot_size == 256 || a.rot_size == 512) &&
-           a.K % 256 == 0 && a.K % a.rot_size == 0 && a.K <= RB_WAVES * RB_PMAX * 512 && a.Aq != nullptr &&
-           a.meta != nullptr && a.M <= 0x7FFFFFFFll;
+           a.K % 256 == 0 && a.K % a.rot_size == 0 && a.K <= RB_WAVES * RB_PMAX * 512 &&
+           (a.Aq != nullptr || a.Aq6 != nullptr) && a.meta != nullptr && a.M <= 0x7FFFFFFFll;
+}
+
+bool rotate_quant_small_applicable(const RotateQuantArgs& a) {
+    return a.group == a.K && !a.has28 && a.rot_size == a.K && (a.K == 512 || a.K == 1024 || a.K == 2048) &&
+           (a.Aq != nullptr || a.Aq6 != nullptr) && a.meta != nullptr;
+}
+
+int launch_rotate_quant_small(const RotateQuantArgs& a, hipStream_t s) {
+    const float norm = (float)(1.0 / sqrt((double)a.rot_size));
+    if (a.K == 512) return launch_rs<1>(a, s, norm);
+    if (a.K == 1024) return launch_rs<2>(a, s, norm);
+    return launch_rs<4>(a, s, norm);
 }
 
 int launch_rotate_quant_block(const RotateQuantArgs& a, hipStream_t s) {

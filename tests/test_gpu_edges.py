@@ -494,3 +494,57 @@ def test_fp6_product_over_few_k_steps(K, M, N, pad):
         assert bool((Y[M] == -7.0).all()) and bool((Y[:, N:] == -7.0).all()), "wrote outside the output"
         out.append(Y[:M, :N].contiguous())
     assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+
+
+@pytest.mark.parametrize("K", [512, 1024, 2048])
+@pytest.mark.parametrize("M", [21, 63, 257, 300, 8192 + 37])
+@pytest.mark.parametrize("with_bias,with_scale", [(False, False), (True, True)])
+def test_small_token_rotations(K, M, with_bias, with_scale):
+    """rot_size == K in {512, 1024, 2048}, one wave per token: the token counts around a workgroup, a run of workgroups of
+    one XCD and the persistent loop, with the degenerate tokens at both ends; and the rotation against the dense one in
+    fp64 (fp32 sums of at most 2048 terms of a token's size: 2e-5 of its largest value is 100 roundings)."""
+    announce(f"small tokens K={K} M={M} bias={with_bias} scale={with_scale}")
+    X, bias, sa = gpu_inputs(M, K, seed=K + M, with_bias=with_bias, with_scale=with_scale)
+    specials = [0, M - N_SPECIAL]
+    for f in reversed(specials):
+        plant_degenerate_rows(X, f)
+    rows = rows_to_check(M, specials, np.random.default_rng(M), n_random=48)
+    Aq, meta = B.alloc_activation_buffers(M, K, DEV)
+    Aq.fill_(0xEE); meta.fill_(-7)
+    A6 = B.alloc_fp6_buffer(M, K, DEV)
+    B.basq_rotate_quant(X, K, bias, sa, 0.9, 0.95, Aq, meta, Aq6=A6)
+    torch.cuda.synchronize()
+    pu.check_rows_against_oracle(X, rows, K, bias, sa, 0.9, 0.95, Aq, meta, what="small token")
+    check_fp6_copy(Aq, A6, K, row_blocks=[0, (M // 32) - 1])
+    Xf = X[N_SPECIAL:N_SPECIAL + 1].contiguous()
+    r = torch.empty((1, K), device=DEV)
+    B.basq_rotate_quant(Xf, K, None, None, 1.0, 1.0, torch.empty((1, K // 2), dtype=torch.uint8, device=DEV),
+                        torch.empty((1, 4), dtype=torch.int32, device=DEV), r)
+    H = torch.ones((1, 1), dtype=torch.float64)
+    while H.shape[0] < K:
+        H = torch.cat([torch.cat([H, H], 1), torch.cat([H, -H], 1)], 0)
+    want = Xf.double().cpu() @ H / K ** 0.5
+    assert float((r.double().cpu() - want).abs().max()) <= 2e-5 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("K,rot,N", [(1024, 1024, 72), (11008, 256, 40), (1536, 512, 136)])
+@pytest.mark.parametrize("M", [129, 300, 1021])
+def test_layer_on_the_fp6_form_alone(K, rot, N, M):
+    """Where the one-call layer lets the quantiser leave the 4-bit codes out (M > 128 with fp6 weights): the bits of the
+    two calls that write and read both forms."""
+    announce(f"fp6 form alone K={K} rot={rot} M={M}")
+    X, bias, sa = gpu_inputs(M, K, seed=K + M, with_bias=True, with_scale=True)
+    gen = torch.Generator(device=DEV).manual_seed(M)
+    W = (torch.randn((N, K), generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
+    Wq, sw, zp, ws = B.alloc_weight_buffers(N, K)
+    B.basq_quantize_weights(W, Wq, sw, zp, ws)
+    c, W6 = torch.empty(N, device=DEV), B.alloc_fp6_buffer(N, K)
+    B.basq_prepare_weights(Wq, sw, zp, bias, None, ws, c, W6)
+    Aq, meta = B.alloc_activation_buffers(M, K, DEV)
+    A6 = B.alloc_fp6_buffer(M, K, DEV)
+    B.basq_rotate_quant(X, rot, bias, sa, 0.9, 0.9, Aq, meta, Aq6=A6)
+    two, one = (torch.empty((M, N), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    B.basq_w4a4_gemm(Aq, meta, Wq, sw, zp, ws, c, two, Aq6=A6, Wq6=W6)
+    work = torch.empty(B.basq_workspace_bytes(M, K, N), dtype=torch.uint8, device=DEV)
+    B.basq_linear_fused(X, rot, bias, sa, 0.9, 0.9, Wq, sw, zp, ws, c, one, work, Wq6=W6)
+    assert torch.equal(one.view(torch.int16), two.view(torch.int16))
