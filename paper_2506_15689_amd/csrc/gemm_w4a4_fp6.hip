@@ -10,7 +10,7 @@
 // The operands are stored as 3 KB blocks of 32 rows x 128 codes that already are the LDS image (see
 // fp6_pack.hip): a stage is filled by contiguous 1 KB copies of whole cache lines, and both the 16-byte
 // and the 8-byte fragment reads are free of bank conflicts.  No unpacking: LDS -> registers -> MFMA.
-#include "basq_internal.h"
+#include "gemm_fp6_store.h"
 #include <type_traits>
 
 namespace basq {
@@ -347,9 +347,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
             issue_prologue();
         }
 
-        // ---- epilogue.  The weights are the first MFMA operand: accumulator register r of lane l belongs to token l % 32 of
-        // the row block and to output channel 8*(r/4) + 4*(l/32) + r%4 of the column block, so a lane turns four adjacent
-        // channels into two dwords of packed bf16.
+        // ---- epilogue (which output an accumulator register holds: gemm_fp6_store.h)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // LDS only: the next tile's loads stay in flight
         // (re)derived per tile from an opaque copy of the lane index: everything computed from it below
         // would otherwise be hoisted out of the tile loop and held in registers across the main loop
@@ -394,64 +392,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
             // landed), and only then send the stores: a wait placed after them would have to wait for
             // the stores too, the counter being one and the same
             if (more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            // Lane bit 5 (which four of eight channels) trades places with the low bit of q, lane bit 4 (token) with its high
-            // bit, and in a pair of column blocks lane bit 3 (token) with the block: a lane then owns 16 bytes of one token's
-            // row, and a store covers whole 128-byte lines of eight rows.
-            const bool wide = (a.ldy & 7) == 0 && (a.N & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0;
-            const int piece = 2 * ((elane >> 4) & 1) + ehalf;
-            const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;   // of the matrix, from the tile's start
-            auto store16 = [&](int row, int col, unsigned o0, unsigned o1, unsigned o2, unsigned o3) {      // within the tile
-                if (row >= row_end) return;
-                uint16_t* dst = a.Y + (m0 + row) * a.ldy + n0 + col;
-                if (wide) {
-                    if (col < col_end) nt_store16(dst, make_uint4(o0, o1, o2, o3));
-                } else {
-                    const unsigned o[4] = {o0, o1, o2, o3};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (col + 2 * e < col_end) *reinterpret_cast<uint32_t*>(dst + 2 * e) = o[e];
-                }
-            };
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int row0 = wm * WM + i * 32;
-                unsigned z[TN][2][4];                             // [block][token / 16][dword] of 16 bytes: piece `piece` of token l % 16
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        const auto u = __builtin_amdgcn_permlane32_swap(outv[i][j][0][p], outv[i][j][1][p], false, false);
-                        const auto v = __builtin_amdgcn_permlane32_swap(outv[i][j][2][p], outv[i][j][3][p], false, false);
-                        z[j][0][p] = u[0]; z[j][0][2 + p] = u[1];
-                        z[j][1][p] = v[0]; z[j][1][2 + p] = v[1];
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const auto u = __builtin_amdgcn_permlane16_swap(z[j][0][e], z[j][1][e], false, false);
-                        z[j][0][e] = u[0]; z[j][1][e] = u[1];
-                    }
-                }
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                    for (int j = 0; j < TN; j += 2) {
-                        if (j + 1 < TN) {
-                            unsigned lo[4], hi[4];                // tokens 0..7 and 8..15 of the sixteen (row rotation by 8 lanes)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                lo[e] = (unsigned)__builtin_amdgcn_update_dpp((int)z[j][h][e], (int)z[j + 1][h][e], 0x128, 0xF, 0xC, false);
-                                hi[e] = (unsigned)__builtin_amdgcn_update_dpp((int)z[j + 1][h][e], (int)z[j][h][e], 0x128, 0xF, 0x3, false);
-                            }
-                            const int row = row0 + 16 * h + (elane & 7), col = (col_block(j) + ((elane >> 3) & 1)) * 32 + 8 * piece;
-                            store16(row, col, lo[0], lo[1], lo[2], lo[3]);
-                            store16(row + 8, col, hi[0], hi[1], hi[2], hi[3]);
-                        } else {
-                            store16(row0 + 16 * h + (elane & 15), col_block(j) * 32 + 8 * piece, z[j][h][0], z[j][h][1], z[j][h][2], z[j][h][3]);
-                        }
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            store_outputs<TM, TN, BM>(a, m0, n0, wm * WM, elane, outv, col_block);
         } else {
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
