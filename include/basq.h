@@ -117,10 +117,11 @@ int basq_rotate_quant(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t 
  *   Y          out, bf16 [M, ldy], ldy >= N
  *   acc_out    out, optional debug dump of ACC, int32 [M, N]; NULL to skip
  *   Aq6, Wq6   optional, both or neither: the two code matrices in the fp6 operand form
- *              (basq_pack_fp6; Aq6 also straight from basq_rotate_quant).  With them, and M > 128, the
+ *              (basq_pack_fp6; Aq6 also straight from basq_rotate_quant).  With them, and M > 64 (from 33 on where
+ *              the shape favours it), the
  *              product runs on the f8f6f4 matrix-core path at twice the int8 rate; ACC and Y are
  *              bit-identical to the int8 path.  Needs K % 128 == 0.
- * Any M >= 0, N >= 1; M <= 128 (decode, batched decode) takes a weight-streaming path, same results.
+ * Any M >= 0, N >= 1; otherwise M <= 128 (decode, batched decode) takes a weight-streaming path, same results.
  */
 int basq_w4a4_gemm(const uint8_t* Aq, const basq_tokmeta* meta, int64_t M, int32_t K,
                    const uint8_t* Wq, int32_t N, int32_t w_layout,
@@ -199,7 +200,8 @@ size_t basq_workspace_bytes(int64_t M, int32_t K, int32_t N);
 /*
  * The whole layer in one call: basq_rotate_quant then basq_w4a4_gemm on `stream`, the codes and
  * token records living in `workspace` (256-byte aligned, >= basq_workspace_bytes(M, K, N), else
- * BASQ_EWORKSPACE).  Arguments as in the two calls above; with Wq6, M > 128 takes the fp6 matrix-core path.
+ * BASQ_EWORKSPACE).  Arguments as in the two calls above; with Wq6, M > 64 (from 33 on where the shape
+ * favours it) takes the fp6 matrix-core path.
  * group_size must be 0 or K here (BASQ_EUNSUPPORTED otherwise: groups go through basq_rotate_quant and
  * basq_w4a4_gemm_grouped).  With at most 4 tokens, rot_size == K in {4096, 8192}, N <= 4096 and
  * w_layout = BASQ_W_DECODE16 the whole layer is one kernel launch (same results bit for bit).  Nothing in this

@@ -81,7 +81,8 @@ int validate_gemm(const uint8_t* Aq, const basq_tokmeta* meta, int64_t M, int32_
 }
 
 int run_gemm(const GemmArgs& g, hipStream_t s) {
-    if (g.M <= GEMV_MAX_TOKENS && g.K % 128 == 0) return launch_gemv_decode(g, s);
+    const bool streaming = g.M <= GEMV_MAX_TOKENS && g.K % 128 == 0;
+    if (streaming && !(gemm_fp6_applicable(g) && gemm_fp6_beats_streaming(g.M, g.N, g.K))) return launch_gemv_decode(g, s);
     if (gemm_fp6_applicable(g)) return launch_gemm_fp6(g, s);
     if (g.w_layout != BASQ_W_CANONICAL)
         return fail(BASQ_EUNSUPPORTED, "more than 128 tokens with the streaming weight layout need the fp6 operands "
@@ -146,12 +147,14 @@ int linear_fused_impl(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t 
     a.X = static_cast<const uint16_t*>(X);
     a.M = M; a.K = K; a.ldx = ldx; a.rot_size = rot_size;
     a.bias = bias; a.act_scale = act_scale; a.clip_lo = clip_lo; a.clip_hi = clip_hi;
-    // the fp6 copy of the codes is only worth making when the matrix-core path will take it
-    uint8_t* Aq6 = nullptr;
-    if (Wq6 && M > GEMV_MAX_TOKENS)
-        Aq6 = reinterpret_cast<uint8_t*>(meta) + align_up((size_t)M * sizeof(basq_tokmeta), 256);
+    // the fp6 copy of the codes is only worth making when the matrix-core path will take it; where the weight-streaming
+    // kernel could take the call, also only if it costs no launch of its own
     a.group = K;
-    a.Aq = Aq; a.meta = meta; a.rot_out = nullptr; a.Aq6 = Aq6;
+    a.Aq = Aq; a.meta = meta; a.rot_out = nullptr;
+    a.Aq6 = reinterpret_cast<uint8_t*>(meta) + align_up((size_t)M * sizeof(basq_tokmeta), 256);
+    uint8_t* Aq6 = nullptr;
+    if (Wq6 && (M > GEMV_MAX_TOKENS || (gemm_fp6_beats_streaming(M, N, K) && layer_fp6_only_applicable(a)))) Aq6 = a.Aq6;
+    a.Aq6 = Aq6;
     hipStream_t s = static_cast<hipStream_t>(stream);
     GemmArgs g{Aq, meta, M, K, Wq, N, static_cast<const uint16_t*>(w_scale), static_cast<const uint16_t*>(w_zero),
                w_sum, out_bias, static_cast<uint16_t*>(Y), ldy, nullptr, Aq6, Aq6 ? Wq6 : nullptr, w_layout};

@@ -86,6 +86,7 @@ int launch_linear_decode(const RotateQuantArgs& q, const GemmArgs& g, hipStream_
 int launch_pack_decode16(const uint8_t* Wq, int32_t N, int32_t K, uint8_t* out, hipStream_t s);
 // f8f6f4 MFMA kernel on the fp6 operand form, K % 128 == 0 (gemm_w4a4_fp6.hip)
 bool gemm_fp6_applicable(const GemmArgs& a);
+bool gemm_fp6_beats_streaming(int64_t M, int32_t N, int32_t K);   // ... the weight-streaming kernel, for M <= GEMV_MAX_TOKENS
 int launch_gemm_fp6(const GemmArgs& a, hipStream_t s);
 // INT4 codes [rows, K/2] -> fp6 operand form (fp6_pack.hip)
 int launch_pack_fp6(const uint8_t* codes, int64_t rows, int32_t K, uint8_t* out6, hipStream_t s);

@@ -453,7 +453,45 @@ double tiling_cost(const Tiling& t, int64_t M, int64_t N, int K) {
     return us;
 }
 
+// Six tilings; the cheapest by the table is within 1.1 % of the fastest in the mean over those shapes (14 % at worst).
+// Choosing among the first, second and fourth by how evenly their tiles fill the chip, as before, was 13 % off in the
+// mean and up to 2.6 times: it gave 129 .. 500 tokens tiles too large to occupy the chip (333 x 4096 x 4096: 96 tiles
+// of 128 x 128 take 14.1 us, 384 of 64 x 64 11.9 us), and where a round of 256 x 128 tiles fits exactly it takes
+// 58.9 us against 62.2 us for 256 x 192 and 66.4 us for 128 x 128 (2048 x 4096, K = 14336).  128 x 64 is for 65 .. 128
+// tokens (128 x 12288, K = 4096: 13.9 us against 17.1 us for 64 x 64).
+constexpr int NUM_TILINGS = 6;
+const Tiling tilings[NUM_TILINGS] = {
+    {256, 256, 1, 2.1, {10.8, 0.80}, {{6.9, 0.55}}},
+    {256, 192, 1, 2.8, {9.1, 0.65}, {{4.9, 0.44}}},
+    {256, 128, 1, 2.0, {5.1, 0.52}, {{4.4, 0.36}}},
+    {128, 128, 2, 3.9, {3.4, 0.585}, {{1.1, 0.27}, {1.1, 0.59}}},
+    {128, 64, 2, 2.4, {2.2, 0.41}, {{2.0, 0.228}, {2.5, 0.365}}},
+    {64, 64, 3, 2.9, {1.3, 0.40}, {{0.7, 0.157}, {1.3, 0.243}, {1.7, 0.375}}},
+};
+int cheapest_tiling(int64_t M, int64_t N, int K) {
+    int best = 0;
+    for (int i = 1; i < NUM_TILINGS; ++i)
+        if (tiling_cost(tilings[i], M, N, K) < tiling_cost(tilings[best], M, N, K)) best = i;
+    return best;
+}
+
 }  // namespace
+
+// Against the weight-streaming kernel (gemv_w4a4.hip), weights of both forms cold in memory, 17 .. 128 tokens, N 1024 .. 28672,
+// K 1024 .. 14336.  Above 64 tokens this kernel is the faster one everywhere (128 tokens x 28672, K = 8192: 36 against
+// 64 us; x 1024, K = 4096: 8.5 against 13.8 us): the streaming kernel reads every token's codes again per 32 to 64
+// channels.  Up to 32 it never is: its weights are half as large again.  Between, it is where many channels meet a
+// moderate weight matrix (64 x 12288, K = 8192: 19.5 against 24.5 us; x 28672, where both stream: 36 against 34 us).  The
+// streaming kernel's time is a fit (5 %); the margin covers this kernel's on so few tiles.
+bool gemm_fp6_beats_streaming(int64_t M, int32_t N, int32_t K) {
+    if (M <= 32) return false;
+    if (M > 64) return true;
+    const double k = K / 1024.0, n = N / 4096.0, m = M / 64.0;
+    const double streaming = 3.3 + 1.13 * k + (0.374 * k + 0.417) * n * m;
+    const double memory = 3.0 + 0.75 * (double)N * (double)K / 5.4e6;             // one pass over the weights
+    const double tiles = tiling_cost(tilings[cheapest_tiling(M, N, K)], M, N, K);
+    return 1.2 * (tiles > memory ? tiles : memory) < streaming;
+}
 
 bool gemm_fp6_applicable(const GemmArgs& a) {
     // buffer addressing: both operands must be smaller than 4 GiB.  K <= 32768: the fp32 accumulator holds the sum of
@@ -467,26 +505,12 @@ int launch_gemm_fp6(const GemmArgs& a, hipStream_t s) {
 #ifdef GEMM_FP6_CFG
     return launch_fp6<GEMM_FP6_CFG>(a, s);
 #else
-    // Five tilings; the cheapest by the table is within 1.1 % of the fastest in the mean over those shapes (14 % at worst).
-    // Choosing among the first, second and fourth by how evenly their tiles fill the chip, as before, was 13 % off in the
-    // mean and up to 2.6 times: it gave 129 .. 500 tokens tiles too large to occupy the chip (333 x 4096 x 4096: 96 tiles
-    // of 128 x 128 take 14.1 us, 384 of 64 x 64 11.9 us), and where a round of 256 x 128 tiles fits exactly it takes
-    // 58.9 us against 62.2 us for 256 x 192 and 66.4 us for 128 x 128 (2048 x 4096, K = 14336).
-    static const Tiling tilings[5] = {
-        {256, 256, 1, 2.1, {10.8, 0.80}, {{6.9, 0.55}}},
-        {256, 192, 1, 2.8, {9.1, 0.65}, {{4.9, 0.44}}},
-        {256, 128, 1, 2.0, {5.1, 0.52}, {{4.4, 0.36}}},
-        {128, 128, 2, 3.9, {3.4, 0.585}, {{1.1, 0.27}, {1.1, 0.59}}},
-        {64, 64, 3, 2.9, {1.3, 0.40}, {{0.7, 0.157}, {1.3, 0.243}, {1.7, 0.375}}},
-    };
-    int best = 0;
-    for (int i = 1; i < 5; ++i)
-        if (tiling_cost(tilings[i], a.M, a.N, a.K) < tiling_cost(tilings[best], a.M, a.N, a.K)) best = i;
-    switch (best) {
+    switch (cheapest_tiling(a.M, a.N, a.K)) {
         case 0: return launch_fp6<256, 256, 2, 4, 3, 2>(a, s);
         case 1: return launch_fp6<256, 192, 4, 2, 3, 2>(a, s);
         case 2: return launch_fp6<256, 128, 4, 2, 4, 2>(a, s);
         case 3: return launch_fp6<128, 128, 2, 2, 3, 2>(a, s);
+        case 4: return launch_fp6<128, 64, 4, 1, 4, 2>(a, s);
         default: return launch_fp6<64, 64, 2, 2, 4, 3>(a, s);
     }
 #endif

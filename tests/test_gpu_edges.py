@@ -467,11 +467,13 @@ def test_packed_operands_of_two_to_four_gib_and_beyond(M):
 
 
 @pytest.mark.parametrize("K", [128, 256, 384, 512, 640, 896])
-@pytest.mark.parametrize("M,N,pad", [(129, 64, 0), (300, 1000, 0), (257, 514, 2), (131, 333, 1), (700, 20480, 8), (1030, 4100, 4), (2000, 12300, 4)])
+@pytest.mark.parametrize("M,N,pad", [(129, 64, 0), (300, 1000, 0), (257, 514, 2), (131, 333, 1), (700, 20480, 8), (1030, 4100, 4), (2000, 12300, 4),
+                                     (40, 12288, 0), (64, 6000, 0), (65, 72, 0), (128, 2050, 2)])
 def test_fp6_product_over_few_k_steps(K, M, N, pad):
     """Every length of the K loop around the depth of its ring of LDS stages (no steady step at all, one, several), each
     with ragged tiles, every tiling, more tiles than compute units hold at once and each alignment of the output rows: the bits of
-    the int8 path (exact integer products, the same epilogue arithmetic, so no tolerance)."""
+    the int8 path (exact integer products, the same epilogue arithmetic, so no tolerance).  The last four are token
+    counts that the weight-streaming kernel also takes (it is what they are compared with)."""
     announce(f"fp6 product M={M} N={N} K={K} pad={pad}")
     gen = torch.Generator(device=DEV).manual_seed(K + M)
     A = torch.randint(0, 256, (M, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
