@@ -550,3 +550,26 @@ def test_layer_on_the_fp6_form_alone(K, rot, N, M):
     work = torch.empty(B.basq_workspace_bytes(M, K, N), dtype=torch.uint8, device=DEV)
     B.basq_linear_fused(X, rot, bias, sa, 0.9, 0.9, Wq, sw, zp, ws, c, one, work, Wq6=W6)
     assert torch.equal(one.view(torch.int16), two.view(torch.int16))
+
+
+@pytest.mark.parametrize("K,M", [(4096, 1023), (4096, 1024), (4096, 3077), (8192, 513), (2048, 4099), (1024, 2049), (3072, 701),
+                                 (1536, 1500)])
+@pytest.mark.parametrize("with_bias,with_scale", [(True, False), (True, True)])
+def test_per_head_steps_of_several_items(K, M, with_bias, with_scale):
+    """The per-head kernel with one, two and four 512-channel items a step (by width and token count), on both sides of the
+    token count where it changes and with a last step that only some waves have, dead heads next to ordinary ones."""
+    announce(f"per-head steps K={K} M={M} scale={with_scale}")
+    X, bias, sa = gpu_inputs(M, K, seed=K + M, with_bias=with_bias, with_scale=with_scale)
+    specials = [0, M - N_SPECIAL]
+    for f in reversed(specials):
+        plant_degenerate_rows(X, f)
+    X[12, 256:384] = 0.0
+    X[13, 128 + 5] = float("nan")
+    X[14, 384 + 9] = float("inf")
+    rows = np.union1d(rows_to_check(M, specials, np.random.default_rng(M), n_random=48), [12, 13, 14])
+    Aq = torch.full((M, K // 2), 0xEE, dtype=torch.uint8, device=DEV)
+    meta = torch.full((M * (K // 128), 4), -7, dtype=torch.int32, device=DEV)
+    B.basq_rotate_quant(X, 128, bias, sa, 0.9, 0.95, Aq, meta, group_size=128)
+    torch.cuda.synchronize()
+    pu.check_rows_against_oracle(X, rows, 128, bias, sa, 0.9, 0.95, Aq, meta, group=128, what="per head")
+    assert not bool((meta[:, 3] == -7).any()), "a record was not written"
