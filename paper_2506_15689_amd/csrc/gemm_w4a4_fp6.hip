@@ -480,12 +480,12 @@ int cheapest_tiling(int64_t M, int64_t N, int K) {
 // Against the weight-streaming kernel (gemv_w4a4.hip), weights of both forms cold in memory, 17 .. 128 tokens, N 1024 .. 28672,
 // K 1024 .. 14336.  Above 64 tokens this kernel is the faster one everywhere (128 tokens x 28672, K = 8192: 36 against
 // 64 us; x 1024, K = 4096: 8.5 against 13.8 us): the streaming kernel reads every token's codes again per 32 to 64
-// channels.  Up to 32 it never is: its weights are half as large again.  Between, it is where many channels meet a
-// moderate weight matrix (64 x 12288, K = 8192: 19.5 against 24.5 us; x 28672, where both stream: 36 against 34 us).  The
+// channels.  Up to 32 it never is: its weights are half as large again.  Between, it is where many channels (more than
+// the streaming kernel gives eight waves a workgroup) meet a moderate weight matrix (64 x 12288, K = 8192: 19.5 against 24.5 us; x 28672, where both stream: 36 against 34 us).  The
 // streaming kernel's time is a fit (5 %); the margin covers this kernel's on so few tiles.
 bool gemm_fp6_beats_streaming(int64_t M, int32_t N, int32_t K) {
-    if (M <= 32) return false;
     if (M > 64) return true;
+    if (M <= 32 || N <= 8192) return false;
     const double k = K / 1024.0, n = N / 4096.0, m = M / 64.0;
     const double streaming = 3.3 + 1.13 * k + (0.374 * k + 0.417) * n * m;
     const double memory = 3.0 + 0.75 * (double)N * (double)K / 5.4e6;             // one pass over the weights

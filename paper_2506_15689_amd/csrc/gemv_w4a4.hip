@@ -20,16 +20,17 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-constexpr int GV_WAVES = 4;
-constexpr int GV_THREADS = GV_WAVES * 64;           // the epilogue maps one thread to each of a tile's 16 x 16 outputs
 constexpr int GV_ROWS = 16;                         // output channels per tile
+constexpr int GV_OUT = 256;                         // the epilogue maps one thread to each of a tile's 16 x 16 outputs
 
 // STEPS: 64-byte k-chunks per lane held in registers at once (all of their loads are in flight together).
 // TILES: 16-row weight tiles per workgroup; they share the activation operand, which at 16 tokens is as many
 //        L2 bytes per workgroup as one tile's weights.
 // TT:    16-token tiles (M <= 16 * TT); they share the weight registers.
-template <bool STREAM_LAYOUT, int STEPS, int TILES, int TT>
-__global__ __launch_bounds__(GV_THREADS) void gemv_w4a4_kernel(GemmArgs a) {
+// WAVES: wavefronts per workgroup, which split K.
+template <bool STREAM_LAYOUT, int WAVES, int STEPS, int TILES, int TT>
+__global__ __launch_bounds__(WAVES * 64) void gemv_w4a4_kernel(GemmArgs a) {
+    static_assert(WAVES * 64 >= GV_OUT, "a thread per output of a tile");
     constexpr int NT = TILES * TT;                  // accumulator tiles per wave
     constexpr bool TWO_CHAINS = NT <= 2;            // few tiles: low and high nibbles on separate MFMA chains
     __shared__ int part[NT * 256];                  // cross-wave sums (integer adds: any order gives the same bits)
@@ -42,7 +43,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_w4a4_kernel(GemmArgs a) {
     const int M = (int)a.M;
 
 #pragma unroll
-    for (int i = 0; i < NT; ++i) part[i * 256 + tid] = 0;
+    for (int i = 0; i < NT; ++i) if (tid < GV_OUT) part[i * 256 + tid] = 0;
 
     // chunk c of this lane: canonical = 16 bytes of row n at 64c + 16sub; streaming = piece `lane` of the
     // 16-row block's c-th KB (rows past N are stored as zeros there; a whole block past N does not exist)
@@ -94,11 +95,11 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_w4a4_kernel(GemmArgs a) {
     for (int i = 0; i < NT; ++i) acc[i] = v4i{0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < (TWO_CHAINS ? NT : 1); ++i) acc2[i] = v4i{0, 0, 0, 0};
-    for (int c0 = wave; c0 < nchunks; c0 += GV_WAVES * STEPS) {
+    for (int c0 = wave; c0 < nchunks; c0 += WAVES * STEPS) {
         v4i w[TILES][STEPS], x[TT][STEPS];
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) {
-            const int c = c0 + i * GV_WAVES;
+            const int c = c0 + i * WAVES;
             const bool ok = c < nchunks;
             // the weights are read once per call: streaming (non-temporal) loads
 #pragma unroll
@@ -136,6 +137,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_w4a4_kernel(GemmArgs a) {
         for (int r = 0; r < 4; ++r) atomicAdd(&part[at * 256 + (4 * sub + r) * 16 + row], acc[at][r]);
     }
     __syncthreads();
+    if (tid >= GV_OUT) return;
 
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
@@ -182,19 +184,24 @@ int launch_pack_decode16(const uint8_t* Wq, int32_t N, int32_t K, uint8_t* out, 
     return check_hip(hipGetLastError(), "pack_decode launch");
 }
 
-template <bool SL, int STEPS, int TILES, int TT>
+template <bool SL, int WAVES, int STEPS, int TILES, int TT>
 static void launch_gemv_cfg(const GemmArgs& a, hipStream_t s, int blocks16) {
-    hipLaunchKernelGGL((gemv_w4a4_kernel<SL, STEPS, TILES, TT>), dim3((unsigned)((blocks16 + TILES - 1) / TILES)),
-                       dim3(GV_THREADS), 0, s, a);
+    hipLaunchKernelGGL((gemv_w4a4_kernel<SL, WAVES, STEPS, TILES, TT>), dim3((unsigned)((blocks16 + TILES - 1) / TILES)),
+                       dim3(WAVES * 64), 0, s, a);
 }
 
 template <bool SL, int STEPS, int TT>
 static void launch_gemv_tiles(const GemmArgs& a, hipStream_t s, int blocks16) {
     // More weight tiles per workgroup = fewer passes over the activations, which is what bounds the kernel from
-    // 32 tokens on -- as long as the workgroups still fill the chip (measured on N = 4096, 12288, 28672)
-    if (blocks16 >= 1536) launch_gemv_cfg<SL, STEPS, 4, TT>(a, s, blocks16);
-    else if (blocks16 >= 256) launch_gemv_cfg<SL, STEPS, 2, TT>(a, s, blocks16);
-    else launch_gemv_cfg<SL, STEPS, 1, TT>(a, s, blocks16);
+    // 32 tokens on -- as long as the workgroups still fill the chip (measured on N = 4096, 12288, 28672).  Up to 512 tiles
+    // there is one workgroup per compute unit or less, and its time is the chain of a wave's batches of loads: eight
+    // waves, and a tile each as long as every compute unit gets one at most (17 tokens, K = 14336, N = 4096: 18.9 us with four
+    // waves on two tiles, 16.8 with four on one, 10.6 with eight on one; N = 8192, K = 4096: 7.7 -> 6.7; eight on one for
+    // N = 6144: 12.5 against 10.8 at 64 tokens; eight on two for N = 12288: 9.0 against 8.3).
+    if (blocks16 >= 1536) launch_gemv_cfg<SL, 4, STEPS, 4, TT>(a, s, blocks16);
+    else if (blocks16 > 512) launch_gemv_cfg<SL, 4, STEPS, 2, TT>(a, s, blocks16);
+    else if (blocks16 > 256) launch_gemv_cfg<SL, 8, STEPS, 2, TT>(a, s, blocks16);
+    else launch_gemv_cfg<SL, 8, STEPS, 1, TT>(a, s, blocks16);
 }
 
 template <bool SL>
@@ -204,12 +211,12 @@ static void launch_gemv_layout(const GemmArgs& a, hipStream_t s) {
         // long rows: twice the loads in flight per lane (measured: K = 8192 gains 6 %, K = 4096 loses 5 %)
         const bool deep = a.K / 128 > 32;
         // two tiles per workgroup once the activations weigh in (more than 8 tokens) and the chip stays filled
-        if (a.M > 8 && blocks16 >= 4 * 256) launch_gemv_cfg<SL, 8, 2, 1>(a, s, blocks16);
+        if (a.M > 8 && blocks16 >= 4 * 256) launch_gemv_cfg<SL, 4, 8, 2, 1>(a, s, blocks16);
         // 65 .. 112 chunks per row (K = 14336): all of a lane's loads in one batch instead of one and a ragged one
         // (measured 8.0 us against 8.8 us on N = 4096)
-        else if (a.K / 128 > 64 && a.K / 128 <= 112) launch_gemv_cfg<SL, 28, 1, 1>(a, s, blocks16);
-        else if (deep) launch_gemv_cfg<SL, 16, 1, 1>(a, s, blocks16);
-        else launch_gemv_cfg<SL, 8, 1, 1>(a, s, blocks16);
+        else if (a.K / 128 > 64 && a.K / 128 <= 112) launch_gemv_cfg<SL, 4, 28, 1, 1>(a, s, blocks16);
+        else if (deep) launch_gemv_cfg<SL, 4, 16, 1, 1>(a, s, blocks16);
+        else launch_gemv_cfg<SL, 4, 8, 1, 1>(a, s, blocks16);
     } else if (a.M <= 32) {
         launch_gemv_tiles<SL, 2, 2>(a, s, blocks16);
     } else if (a.M <= 64) {

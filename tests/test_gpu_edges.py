@@ -573,3 +573,28 @@ def test_per_head_steps_of_several_items(K, M, with_bias, with_scale):
     torch.cuda.synchronize()
     pu.check_rows_against_oracle(X, rows, 128, bias, sa, 0.9, 0.95, Aq, meta, group=128, what="per head")
     assert not bool((meta[:, 3] == -7).any()), "a record was not written"
+
+
+@pytest.mark.parametrize("N", [40, 4096, 4112, 8192, 8208])
+@pytest.mark.parametrize("M", [17, 33, 65])
+@pytest.mark.parametrize("K", [128, 640])
+def test_streaming_product_where_its_workgroups_change(K, M, N):
+    """The weight-streaming kernel on both sides of the output widths at which it takes more waves or tiles a workgroup
+    (256 and 512 tiles of 16 channels), fewer chunks of K than waves: its INT32 accumulators against the exact product of
+    the codes (fp64 matmul of integers below 2^53)."""
+    announce(f"streaming product M={M} N={N} K={K}")
+    gen = torch.Generator(device=DEV).manual_seed(N + M)
+    A = torch.randint(0, 256, (M, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
+    W = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
+    Wd = torch.empty(B.basq_decode_bytes(N, K), dtype=torch.uint8, device=DEV)
+    B.basq_pack_decode(W, Wd)
+    meta = torch.ones((M, 4), dtype=torch.int32, device=DEV)
+    one = torch.ones(N, dtype=torch.bfloat16, device=DEV)
+    ws = torch.zeros(N, device=DEV)
+    codes = [torch.stack([t & 15, t >> 4], dim=2).view(t.shape[0], K).double().cpu() for t in (A, W)]
+    want = (codes[0] @ codes[1].T).to(torch.int32)
+    for w, layout in ((Wd, B.BASQ_W_DECODE16), (W, B.BASQ_W_CANONICAL)):
+        acc = torch.full((M, N), -1, dtype=torch.int32, device=DEV)
+        Y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+        B.basq_w4a4_gemm(A, meta, w, one, one, ws, None, Y, acc, w_layout=layout, N=N)
+        assert torch.equal(acc.cpu(), want)
