@@ -43,7 +43,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_w4a4_kernel(GemmArgs a) {
     const int M = (int)a.M;
 
 #pragma unroll
-    for (int i = 0; i < NT; ++i) if (tid < GV_OUT) part[i * 256 + tid] = 0;
+    for (int i = 0; i < NT; ++i) if (WAVES * 64 == GV_OUT || tid < GV_OUT) part[i * 256 + tid] = 0;
 
     // chunk c of this lane: canonical = 16 bytes of row n at 64c + 16sub; streaming = piece `lane` of the
     // 16-row block's c-th KB (rows past N are stored as zeros there; a whole block past N does not exist)
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_w4a4_kernel(GemmArgs a) {
         for (int r = 0; r < 4; ++r) atomicAdd(&part[at * 256 + (4 * sub + r) * 16 + row], acc[at][r]);
     }
     __syncthreads();
-    if (tid >= GV_OUT) return;
+    if (WAVES * 64 > GV_OUT && tid >= GV_OUT) return;
 
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
