@@ -228,10 +228,15 @@ namespace {
 int launch_rotate_quant_generic(const RotateQuantArgs& a, hipStream_t s);
 }
 
+constexpr int64_t GROUPED_FP6_MAX_TOKENS = 32768;
+
 int launch_rotate_quant(const RotateQuantArgs& a, hipStream_t s) {
     if (a.M == 0) return BASQ_OK;
-    if (a.Aq6 && a.group != a.K) {
-        // group-wise ranges: the codes are the same kind of data, the fp6 copy is made from them afterwards
+    // Groups of 128 with a full rotation: the one-wave kernel writes the fp6 form as for per-token ranges (K = 4096: 16 tokens 7.9 ->
+    // 5.5 us against codes and a repacking launch, 2048 tokens 13.8 -> 11.4, 32000 tokens 93.5 -> 87.7; K = 8192: 11.1 -> 8.8,
+    // 21.3 -> 19.1, 214.7 -> 202.1).  Measured up to here, which is also where the per-token form needs staged tails.
+    if (a.Aq6 && a.group != a.K && !(a.M < GROUPED_FP6_MAX_TOKENS && rotate_quant_pow2_applicable(a))) {
+        // other group-wise ranges: the codes are the same kind of data, the fp6 copy is made from them afterwards
         RotateQuantArgs b = a;
         b.Aq6 = nullptr;
         const int rc = launch_rotate_quant(b, s);

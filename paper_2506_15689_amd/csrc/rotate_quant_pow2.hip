@@ -251,9 +251,9 @@ int launch_nc(const RotateQuantArgs& a, hipStream_t s, float norm) {
 }  // namespace
 
 bool rotate_quant_pow2_applicable(const RotateQuantArgs& a) {
-    // per-token ranges, or groups of 128 channels (four neighbouring lanes; no fp6 copy: the GEMM that takes it is per token)
+    // per-token ranges, or groups of 128 channels (four neighbouring lanes)
     // (the 4-bit codes may be left out when the fp6 form is written)
-    return (a.group == a.K || (a.group == 128 && a.Aq6 == nullptr)) && !a.has28 && a.rot_size == a.K &&
+    return (a.group == a.K || a.group == 128) && !a.has28 && a.rot_size == a.K &&
            (a.K == 4096 || a.K == 8192) && (a.Aq != nullptr || a.Aq6 != nullptr) && a.meta != nullptr;
 }
 

@@ -598,3 +598,20 @@ def test_streaming_product_where_its_workgroups_change(K, M, N):
         Y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
         B.basq_w4a4_gemm(A, meta, w, one, one, ws, None, Y, acc, w_layout=layout, N=N)
         assert torch.equal(acc.cpu(), want)
+
+
+@pytest.mark.parametrize("K,M", [(4096, 33), (4096, 2051), (8192, 70), (8192, 1030)])
+@pytest.mark.parametrize("with_bias,with_scale", [(False, False), (True, True)])
+def test_fp6_form_of_groupwise_codes(K, M, with_bias, with_scale):
+    """Full rotation with groups of 128: the fp6 form that the quantiser writes beside the codes is the repacked codes, and
+    codes and records are those of the call without it."""
+    announce(f"fp6 form of groups K={K} M={M} bias={with_bias} scale={with_scale}")
+    X, bias, sa = gpu_inputs(M, K, seed=K + M, with_bias=with_bias, with_scale=with_scale)
+    for f in reversed([0, M - N_SPECIAL]):
+        plant_degenerate_rows(X, f)
+    Aq, meta, Aq2, meta2 = (torch.full(s, 0x5E, dtype=t, device=DEV) for s, t in 2 * [((M, K // 2), torch.uint8), ((M * (K // 128), 4), torch.int32)])
+    A6 = B.alloc_fp6_buffer(M, K, DEV)
+    B.basq_rotate_quant(X, K, bias, sa, 0.9, 0.95, Aq, meta, Aq6=A6, group_size=128)
+    B.basq_rotate_quant(X, K, bias, sa, 0.9, 0.95, Aq2, meta2, group_size=128)
+    assert torch.equal(Aq, Aq2) and torch.equal(meta, meta2)
+    check_fp6_copy(Aq, A6, K, row_blocks=[0, (M // 32) - 1])
