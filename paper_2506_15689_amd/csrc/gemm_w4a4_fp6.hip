@@ -437,36 +437,37 @@ int launch_fp6(const GemmArgs& a, hipStream_t s) {
 
 // What a tiling costs, in microseconds: `base` once; for every round in which all 256 compute units hold `per_cu` tiles
 // round[0] + round[1] * (K / 128); for the tiles left over, the same with the pair of their number per compute unit (a
-// compute unit that holds fewer tiles than it can runs each of them faster).  Least squares over 370 shapes (129 .. 4096
-// tokens, N 1024 .. 28672, K 1024 .. 14336); the standard deviation of the fit is 6-9 % per tiling.
+// compute unit that holds fewer tiles than it can runs each of them faster) and `fill` * (K / 128) more in proportion to
+// the share of the chip they fill (the more matrix cores work, the lower the clock).  Least squares over 370 shapes (129 ..
+// 4096 tokens, N 1024 .. 28672, K 1024 .. 14336); the standard deviation of the fit is 5-7 % per tiling.
 struct Tiling {
     int bm, bn, per_cu;
-    double base, round[2], rest[3][2];
+    double base, round[2], rest[3][2], fill;
 };
 
 double tiling_cost(const Tiling& t, int64_t M, int64_t N, int K) {
-    const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), slots = 256 * t.per_cu;
-    const int64_t left = (tiles % slots + 255) / 256;             // tiles per compute unit in the last round, 0 if it is full
+    const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), slots = 256 * t.per_cu, over = tiles % slots;
+    const int64_t left = (over + 255) / 256;                      // tiles per compute unit in the last round, 0 if it is full
     const double ksteps = K / 128;
     double us = t.base + (double)(tiles / slots) * (t.round[0] + t.round[1] * ksteps);
-    if (left > 0) us += t.rest[left - 1][0] + t.rest[left - 1][1] * ksteps;
+    if (left > 0) us += t.rest[left - 1][0] + (t.rest[left - 1][1] + t.fill * (double)over / (double)slots) * ksteps;
     return us;
 }
 
-// Six tilings; the cheapest by the table is within 1.1 % of the fastest in the mean over those shapes (14 % at worst).
+// Six tilings; the cheapest by the table is within 0.3 % of the fastest in the mean over those shapes (13 % at worst).
 // Choosing among the first, second and fourth by how evenly their tiles fill the chip, as before, was 13 % off in the
 // mean and up to 2.6 times: it gave 129 .. 500 tokens tiles too large to occupy the chip (333 x 4096 x 4096: 96 tiles
 // of 128 x 128 take 14.1 us, 384 of 64 x 64 11.9 us), and where a round of 256 x 128 tiles fits exactly it takes
-// 58.9 us against 62.2 us for 256 x 192 and 66.4 us for 128 x 128 (2048 x 4096, K = 14336).  128 x 64 is for 65 .. 128
-// tokens (128 x 12288, K = 4096: 13.9 us against 17.1 us for 64 x 64).
+// 58.9 us against 62.2 us for 256 x 192 and 66.4 us for 128 x 128 (2048 x 4096, K = 14336; without `fill` the table took
+// 256 x 192 there).  128 x 64 is for 65 .. 128 tokens (128 x 12288, K = 4096: 13.9 us against 17.1 us for 64 x 64).
 constexpr int NUM_TILINGS = 6;
 const Tiling tilings[NUM_TILINGS] = {
-    {256, 256, 1, 2.1, {10.8, 0.80}, {{6.9, 0.55}}},
-    {256, 192, 1, 2.8, {9.1, 0.65}, {{4.9, 0.44}}},
-    {256, 128, 1, 2.0, {5.1, 0.52}, {{4.4, 0.36}}},
-    {128, 128, 2, 3.9, {3.4, 0.585}, {{1.1, 0.27}, {1.1, 0.59}}},
-    {128, 64, 2, 2.4, {2.2, 0.41}, {{2.0, 0.228}, {2.5, 0.365}}},
-    {64, 64, 3, 2.9, {1.3, 0.40}, {{0.7, 0.157}, {1.3, 0.243}, {1.7, 0.375}}},
+    {256, 256, 1, 2.9, {10.7, 0.774}, {{6.1, 0.477}}, 0.31},
+    {256, 192, 1, 3.0, {9.0, 0.639}, {{4.6, 0.379}}, 0.242},
+    {256, 128, 1, 2.3, {5.1, 0.512}, {{4.1, 0.302}}, 0.181},
+    {128, 128, 2, 4.1, {3.4, 0.58}, {{0.9, 0.235}, {0.9, 0.487}}, 0.144},
+    {128, 64, 2, 2.5, {2.2, 0.406}, {{2.0, 0.209}, {2.4, 0.316}}, 0.068},
+    {64, 64, 3, 2.9, {1.3, 0.40}, {{0.7, 0.148}, {1.3, 0.221}, {1.7, 0.339}}, 0.043},
 };
 int cheapest_tiling(int64_t M, int64_t N, int K) {
     int best = 0;
