@@ -7,6 +7,8 @@ namespace basq {
 
 namespace {
 
+typedef float fp6_acc_t __attribute__((ext_vector_type(16)));
+
 // A wave's outputs to memory.  With the weights as the first operand of the 32 x 32 MFMA, accumulator register r of lane l
 // belongs to token l % 32 of a row block and to output channel 8*(r/4) + 4*(l/32) + r%4 of a column block, so four adjacent
 // channels are two dwords of packed bf16: outv[i][j][q][p] = channels 8q + 4*(l/32) + 2p, +1 of row block i, column block j.
@@ -20,22 +22,31 @@ namespace {
 //
 //   row0            first row of the wave inside the tile; m0, n0: the tile's first row and column
 //   col_block(j)    column block of the tile (32 columns each) of the wave's block j; blocks 2k and 2k + 1 are adjacent
-// Needs even ldy and N and 4-byte aligned Y; where ldy, N and Y allow 16-byte pieces they are stored whole.
+// Any ldy >= N, N and Y a bf16 tensor can have.  Where rows start on 16-byte boundaries the pieces leave with the
+// non-temporal hint; elsewhere they are 16-byte stores at the alignment there is, without it (a line is then completed by
+// another instruction's stores).  Only the last piece of a row of N % 8 != 0 channels is stored channel by channel.
+// (1021 tokens, K = 4096: N = 32000 70 us, 32001 91 us in rows of 32001 and 78 us in rows of 32008; with 2-byte stores for
+// odd N or ldy, which from this register layout go to 32 rows an instruction, 211 and 225 us, and dword stores for even N
+// were 7-14 % slower: 2048 x 12290 75.6 us, as built 65.2.)
 template <int TM, int TN, int BM, class ColBlock>
 __device__ __forceinline__ void store_outputs(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const unsigned (&outv)[TM][TN][4][2], ColBlock&& col_block) {
-    const bool wide = (a.ldy & 7) == 0 && (a.N & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0;
+    const bool aligned = (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0;
+    const bool whole = aligned && (a.N & 7) == 0;
     const int piece = 2 * ((lane >> 4) & 1) + (lane >> 5);
     const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;       // of the matrix, from the tile's start
     auto store16 = [&](int row, int col, unsigned o0, unsigned o1, unsigned o2, unsigned o3) {      // within the tile
         if (row >= row_end) return;
         uint16_t* dst = a.Y + (m0 + row) * a.ldy + n0 + col;
-        if (wide) {
+        if (whole) {
             if (col < col_end) nt_store16(dst, make_uint4(o0, o1, o2, o3));
+        } else if (col + 8 <= col_end) {
+            if (aligned) nt_store16(dst, make_uint4(o0, o1, o2, o3));
+            else { const basq_v4u v = {o0, o1, o2, o3}; __builtin_memcpy(dst, &v, 16); }
         } else {
             const unsigned o[4] = {o0, o1, o2, o3};
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (col + 2 * e < col_end) *reinterpret_cast<uint32_t*>(dst + 2 * e) = o[e];
+            for (int e = 0; e < 7; ++e)
+                if (col + e < col_end) dst[e] = (uint16_t)(o[e >> 1] >> (16 * (e & 1)));
         }
     };
 #pragma unroll
@@ -77,6 +88,53 @@ __device__ __forceinline__ void store_outputs(const GemmArgs& a, int64_t m0, int
         }
         __builtin_amdgcn_sched_barrier(0);
     }
+}
+
+// The optional dump of the integer accumulators (64 * acc) into a.acc_out, rows of N int32.  As above, with one channel a
+// dword: lane bits 4 and 3 trade places with the bits of q, so that a store covers 32 channels of eight rows (2048 x 4096,
+// K = 4096: 29 us with the dump, 23.7 without; dword stores into 32 rows an instruction: 128 us).
+template <int TM, int TN, int BM, class ColBlock>
+__device__ __forceinline__ void store_accumulators(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const fp6_acc_t (&acc)[TM][TN], ColBlock&& col_block) {
+    const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;
+    const int piece = 8 * (2 * ((lane >> 4) & 1) + ((lane >> 3) & 1)) + 4 * (lane >> 5);
+    auto store16 = [&](int row, int col, const int (&v)[4]) {
+        if (row >= row_end) return;
+        int32_t* dst = a.acc_out + (m0 + row) * a.N + n0 + col;
+        if (col + 4 <= col_end) {
+            __builtin_memcpy(dst, v, 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (col + e < col_end) dst[e] = v[e];
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            int z[2][2][4];                                   // [token / 16][low bit of q][channel]
+#pragma unroll
+            for (int ql = 0; ql < 2; ++ql)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const auto u = __builtin_amdgcn_permlane16_swap((unsigned)__float2int_rn(64.0f * acc[i][j][4 * ql + e]),
+                                                                    (unsigned)__float2int_rn(64.0f * acc[i][j][4 * (2 + ql) + e]), false, false);
+                    z[0][ql][e] = (int)u[0]; z[1][ql][e] = (int)u[1];
+                }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                int lo[4], hi[4];                             // tokens 0..7 and 8..15 of the sixteen (row rotation by 8 lanes)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    lo[e] = __builtin_amdgcn_update_dpp(z[h][0][e], z[h][1][e], 0x128, 0xF, 0xC, false);
+                    hi[e] = __builtin_amdgcn_update_dpp(z[h][1][e], z[h][0][e], 0x128, 0xF, 0x3, false);
+                }
+                const int row = row0 + i * 32 + 16 * h + (lane & 7), col = col_block(j) * 32 + piece;
+                store16(row, col, lo);
+                store16(row + 8, col, hi);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
 }
 
 }  // namespace

@@ -363,57 +363,36 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
             return fmaf(__int_as_float(row[0]) * __int_as_float(col[0]), t,
                         fmaf(__int_as_float(row[1]), __int_as_float(col[2]), __int_as_float(col[3])));
         };
-        if (a.acc_out == nullptr && (a.ldy & 1) == 0 && (a.N & 1) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 3) == 0) {
-            typedef float f2 __attribute__((ext_vector_type(2)));
-            typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-            // first every output into registers (they take the accumulators' place) ...
-            unsigned outv[TM][TN][4][2];                          // [..][q][p]: channels 8q + 4*ehalf + 2p, +1
+        if (a.acc_out) store_accumulators<TM, TN, BM>(a, m0, n0, wm * WM, elane, acc, col_block);
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+        // first every output into registers (they take the accumulators' place) ...
+        unsigned outv[TM][TN][4][2];                          // [..][q][p]: channels 8q + 4*ehalf + 2p, +1
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
+        for (int j = 0; j < TN; ++j) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    v4i cp[4];
+            for (int q = 0; q < 4; ++q) {
+                v4i cp[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) cp[e] = lcol_par[col_block(j) * 32 + 8 * q + 4 * ehalf + e];
+                for (int e = 0; e < 4; ++e) cp[e] = lcol_par[col_block(j) * 32 + 8 * q + 4 * ehalf + e];
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) {
+                for (int i = 0; i < TM; ++i) {
 #pragma unroll
-                        for (int p = 0; p < 2; ++p) {
-                            const float y0 = dequant(acc[i][j][4 * q + 2 * p], rp[i], cp[2 * p]);
-                            const float y1 = dequant(acc[i][j][4 * q + 2 * p + 1], rp[i], cp[2 * p + 1]);
-                            outv[i][j][q][p] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){y0, y1}, b2));   // hardware round-to-nearest-even
-                            asm volatile("" : "+v"(outv[i][j][q][p]));   // computed here: one set of column constants at a time
-                        }
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            // ... then wait for the next tile's first stages (requested before this epilogue, so mostly
-            // landed), and only then send the stores: a wait placed after them would have to wait for
-            // the stores too, the counter being one and the same
-            if (more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            store_outputs<TM, TN, BM>(a, m0, n0, wm * WM, elane, outv, col_block);
-        } else {
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int col = col_block(j) * 32 + 8 * (r >> 2) + 4 * ehalf + (r & 3);
-                    const v4i cp = lcol_par[col];
-                    if (n0 + col < a.N) {
-#pragma unroll
-                        for (int i = 0; i < TM; ++i) {
-                            const int64_t m = m0 + wm * WM + i * 32 + tok;
-                            if (m < a.M) {
-                                a.Y[m * a.ldy + n0 + col] = f32_to_bf16(dequant(acc[i][j][r], rp[i], cp));
-                                if (a.acc_out) a.acc_out[m * (int64_t)a.N + n0 + col] = __float2int_rn(64.0f * acc[i][j][r]);
-                            }
-                        }
+                    for (int p = 0; p < 2; ++p) {
+                        const float y0 = dequant(acc[i][j][4 * q + 2 * p], rp[i], cp[2 * p]);
+                        const float y1 = dequant(acc[i][j][4 * q + 2 * p + 1], rp[i], cp[2 * p + 1]);
+                        outv[i][j][q][p] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){y0, y1}, b2));   // hardware round-to-nearest-even
+                        asm volatile("" : "+v"(outv[i][j][q][p]));   // computed here: one set of column constants at a time
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // loads and stores alike
         }
+        // ... then wait for the next tile's first stages (requested before this epilogue, so mostly
+        // landed), and only then send the stores: a wait placed after them would have to wait for
+        // the stores too, the counter being one and the same
+        if (more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        store_outputs<TM, TN, BM>(a, m0, n0, wm * WM, elane, outv, col_block);
         if (!more) break;
         pid = next_pid; tile_m = next_m; tile_n = next_n;
     }

@@ -306,43 +306,28 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
         return fmaf(__int_as_float(col[0]), 64.0f * facc[j][16 * i + r], fmaf(-__int_as_float(col[1]), rsum[i], __int_as_float(col[2])));
     };
     auto col_block = [&](int j) { return wn * G6G_TN + j; };
-    if ((a.ldy & 1) == 0 && (a.N & 1) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 3) == 0) {
-        typedef float f2 __attribute__((ext_vector_type(2)));
-        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-        unsigned outv[G6G_TM][G6G_TN][4][2];
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    unsigned outv[G6G_TM][G6G_TN][4][2];
 #pragma unroll
-        for (int j = 0; j < G6G_TN; ++j) {
+    for (int j = 0; j < G6G_TN; ++j) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                v4i cp[4];
+        for (int q = 0; q < 4; ++q) {
+            v4i cp[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) cp[e] = lcol[col_block(j) * 32 + 8 * q + 4 * fhalf + e];
+            for (int e = 0; e < 4; ++e) cp[e] = lcol[col_block(j) * 32 + 8 * q + 4 * fhalf + e];
 #pragma unroll
-                for (int i = 0; i < G6G_TM; ++i)
+            for (int i = 0; i < G6G_TM; ++i)
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        const float y0 = result(i, j, 4 * q + 2 * p, cp[2 * p]), y1 = result(i, j, 4 * q + 2 * p + 1, cp[2 * p + 1]);
-                        outv[i][j][q][p] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){y0, y1}, b2));   // hardware round-to-nearest-even
-                        asm volatile("" : "+v"(outv[i][j][q][p]));         // computed here: one set of column constants at a time
-                    }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        store_outputs<G6G_TM, G6G_TN, G6G_BM>(a, m0, n0, wm * G6G_WM, lane, outv, col_block);
-    } else {
-#pragma unroll
-        for (int j = 0; j < G6G_TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int col = col_block(j) * 32 + 8 * (r >> 2) + 4 * fhalf + (r & 3);
-                const v4i cp = lcol[col];
-#pragma unroll
-                for (int i = 0; i < G6G_TM; ++i) {
-                    const int64_t m = m0 + wm * G6G_WM + i * 32 + frow;
-                    if (m < a.M && n0 + col < a.N) a.Y[m * a.ldy + n0 + col] = f32_to_bf16(result(i, j, r, cp));
+                for (int p = 0; p < 2; ++p) {
+                    const float y0 = result(i, j, 4 * q + 2 * p, cp[2 * p]), y1 = result(i, j, 4 * q + 2 * p + 1, cp[2 * p + 1]);
+                    outv[i][j][q][p] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){y0, y1}, b2));   // hardware round-to-nearest-even
+                    asm volatile("" : "+v"(outv[i][j][q][p]));         // computed here: one set of column constants at a time
                 }
-            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
+    store_outputs<G6G_TM, G6G_TN, G6G_BM>(a, m0, n0, wm * G6G_WM, lane, outv, col_block);
 #endif  // __HIP_DEVICE_COMPILE__
 }
 

@@ -615,3 +615,91 @@ def test_fp6_form_of_groupwise_codes(K, M, with_bias, with_scale):
     B.basq_rotate_quant(X, K, bias, sa, 0.9, 0.95, Aq2, meta2, group_size=128)
     assert torch.equal(Aq, Aq2) and torch.equal(meta, meta2)
     check_fp6_copy(Aq, A6, K, row_blocks=[0, (M // 32) - 1])
+
+
+def random_product(M, N, K, seed, groups=1):
+    """Random codes in every form the products take, records and weight constants of ordinary size."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    rand = lambda *shape: torch.rand(*shape, device=DEV, generator=gen)
+    A = torch.randint(0, 256, (M, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
+    W = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
+    A6, W6 = B.alloc_fp6_buffer(M, K), B.alloc_fp6_buffer(N, K)
+    B.basq_pack_fp6(A, A6)
+    B.basq_pack_fp6(W, W6)
+    meta = torch.zeros((M * groups, 4), dtype=torch.int32, device=DEV)
+    meta.view(torch.float32)[:, 0] = rand(M * groups) + 0.1
+    meta.view(torch.float32)[:, 1] = -rand(M * groups)
+    codes = A.to(torch.int32).view(M * groups, K // 2 // groups)
+    meta[:, 2] = ((codes & 15) + (codes >> 4)).sum(dim=1)
+    sw = (rand(N) + 0.1).to(torch.bfloat16)
+    zp = torch.randint(0, 16, (N,), device=DEV, generator=gen).to(torch.bfloat16)
+    return A, A6, meta, W, W6, sw, zp, rand(N), rand(N)
+
+
+def output_view(M, N, ldy, offset):
+    """A bf16 [M, N] view with rows of ldy elements that starts `offset` elements into its (poisoned) buffer."""
+    buf = torch.full((M * ldy + offset + 8,), -7.0, dtype=torch.bfloat16, device=DEV)
+    return buf, torch.as_strided(buf, (M, N), (ldy, 1), offset)
+
+
+OUTPUT_FORMS = [(300, 333, 333, 0), (300, 334, 336, 0), (129, 1000, 1001, 1), (1021, 4094, 4094, 2), (260, 775, 776, 8),
+                (700, 12289, 12289, 3), (515, 773, 776, 0), (1500, 20482, 20488, 0)]
+
+
+@pytest.mark.parametrize("M,N,ldy,offset", OUTPUT_FORMS)
+@pytest.mark.parametrize("grouped", [False, True])
+def test_fp6_products_into_rows_of_any_alignment(M, N, ldy, offset, grouped):
+    """Output rows that end inside a 16-byte piece and start on any 2-byte boundary: the int8 kernels' bits, nothing beside
+    them."""
+    K = 384
+    announce(f"output rows M={M} N={N} ldy={ldy} offset={offset} grouped={grouped}")
+    A, A6, meta, W, W6, sw, zp, ws, c = random_product(M, N, K, seed=M + N, groups=K // 128 if grouped else 1)
+    gsum = torch.empty((K // 128, N), dtype=torch.int32, device=DEV)
+    B.basq_group_colsums(W, 128, gsum)
+    got = []
+    for a6, w6 in ((A6, W6), (None, None)):
+        buf, Y = output_view(M, N, ldy, offset)
+        dump = torch.full((M * N + 8,), -9, dtype=torch.int32, device=DEV)
+        if grouped:
+            B.basq_w4a4_gemm_grouped(A, meta, 128, W, sw, zp, gsum, c, Y, Aq6=a6, Wq6=w6)
+        else:
+            B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, Y, dump[:M * N].view(M, N), Aq6=a6, Wq6=w6)
+            plain_buf, plain = output_view(M, N, ldy, offset)
+            B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, plain, Aq6=a6, Wq6=w6)
+            assert torch.equal(plain_buf.view(torch.int16), buf.view(torch.int16)), "outputs with and without the accumulators"
+        assert bool((dump[M * N:] == -9).all())
+        got.append((Y.clone(), dump))
+        Y.fill_(-7.0)
+        assert bool((buf == -7.0).all()), "wrote outside the output"
+    assert torch.equal(got[0][1], got[1][1])
+    assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16))
+
+
+@pytest.mark.parametrize("M,N,with_acc,at_most", [(1021, 32001, False, 2.0), (2048, 4096, True, 2.5)])
+def test_fp6_product_is_not_slow_on_odd_rows_or_with_the_accumulators(M, N, with_acc, at_most):
+    """Against the same product into whole 16-byte pieces without the dump.  Stores of two bytes into 32 different rows made
+    it 3.0 and 5.4 times as long; as built 1.3 times each.  The bound is halfway and the quickest of several runs is taken."""
+    K, reps = 4096, 8
+    announce(f"time of odd rows M={M} N={N} acc={with_acc}")
+
+    def quickest(n, acc):
+        A, A6, meta, W, W6, sw, zp, ws, c = random_product(M, n, K, seed=n)
+        Y = torch.empty((M, n), dtype=torch.bfloat16, device=DEV)
+        dump = torch.empty((M, n), dtype=torch.int32, device=DEV) if acc else None
+        best = float("inf")
+        for _ in range(5):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, Y, dump, Aq6=A6, Wq6=W6)
+            torch.cuda._sleep(400000)                       # the launches below queue up behind it
+            begin.record()
+            for _ in range(reps):
+                B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, Y, dump, Aq6=A6, Wq6=W6)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, begin.elapsed_time(end) / reps)
+        return best
+
+    even = quickest(N // 8 * 8, False)
+    odd = quickest(N, with_acc)
+    announce(f"  {1000 * odd:.1f} us against {1000 * even:.1f} us")
+    assert odd <= at_most * even
