@@ -228,14 +228,31 @@ namespace {
 int launch_rotate_quant_generic(const RotateQuantArgs& a, hipStream_t s);
 }
 
+// Groups of 128 with a full rotation: the one-wave kernel writes the fp6 form as for per-token ranges (K = 4096: 16 tokens 7.9 ->
+// 5.5 us against codes and a repacking launch, 2048 tokens 13.8 -> 11.4, 32000 tokens 93.5 -> 87.7; K = 8192: 11.1 -> 8.8,
+// 21.3 -> 19.1, 214.7 -> 202.1).  Measured up to here, which is also where the per-token form needs staged tails.
 constexpr int64_t GROUPED_FP6_MAX_TOKENS = 32768;
+static bool groupwise_fp6_in_one_launch(const RotateQuantArgs& a) {
+    return a.M < GROUPED_FP6_MAX_TOKENS && rotate_quant_pow2_applicable(a);
+}
+
+// Blockwise rotations with both forms of the codes wanted: the blockwise kernel's own fp6 stores (8- and 16-byte pieces of 32
+// tokens' blocks) save the repacking launch but cost more write requests, which shows from some size on.  Codes and a
+// repacking launch against one launch, us: K = 512, 2048 / 8192 / 40000 tokens 8.2 / 19.6 / 83.8 against 6.6 / 20.0 /
+// 93.8; K = 1536, 8192 / 40000 tokens 26.2 / 104 against 25.2 / 112; K = 4096, 40000 tokens 172 against 176; K = 11008, 14000
+// tokens 155 against 151.  It shows on long tokens too with s^a, with the rotation written out (but not in rows of 11008) and
+// beyond 11008 channels (why is not shown): K = 16384, 3500 / 10000 tokens 60 / 153 against 57 / 158, with s^a 71 / 197 against
+// 72 / 210, with the rotation 92 / 284 against 93 / 303; K = 8192, 14000 tokens with s^a 130 against 139.
+static bool blockwise_fp6_in_one_launch(const RotateQuantArgs& a) {
+    if (a.Aq == nullptr) return true;                         // the fp6 form alone: nothing to repack
+    if (a.K <= 2048) return a.M <= 8192;
+    const bool heavy = a.act_scale || a.K > 11008 || (a.rot_out && a.K <= 8192);
+    return !heavy || a.M * a.K <= (1 << 26);
+}
 
 int launch_rotate_quant(const RotateQuantArgs& a, hipStream_t s) {
     if (a.M == 0) return BASQ_OK;
-    // Groups of 128 with a full rotation: the one-wave kernel writes the fp6 form as for per-token ranges (K = 4096: 16 tokens 7.9 ->
-    // 5.5 us against codes and a repacking launch, 2048 tokens 13.8 -> 11.4, 32000 tokens 93.5 -> 87.7; K = 8192: 11.1 -> 8.8,
-    // 21.3 -> 19.1, 214.7 -> 202.1).  Measured up to here, which is also where the per-token form needs staged tails.
-    if (a.Aq6 && a.group != a.K && !(a.M < GROUPED_FP6_MAX_TOKENS && rotate_quant_pow2_applicable(a))) {
+    if (a.Aq6 && a.group != a.K && !groupwise_fp6_in_one_launch(a)) {
         // other group-wise ranges: the codes are the same kind of data, the fp6 copy is made from them afterwards
         RotateQuantArgs b = a;
         b.Aq6 = nullptr;
@@ -248,9 +265,12 @@ int launch_rotate_quant(const RotateQuantArgs& a, hipStream_t s) {
     if (rotate_quant_k28_applicable(a)) return launch_rotate_quant_k28(a, s);
     if (rotate_quant_head_applicable(a)) return launch_rotate_quant_head(a, s);
     if (rotate_quant_small_applicable(a)) return launch_rotate_quant_small(a, s);
-    if (rotate_quant_block_applicable(a)) return launch_rotate_quant_block(a, s);
-    // the generic kernel writes the 4-bit codes only; the fp6 copy is made from them
-    const int rc = launch_rotate_quant_generic(a, s);
+    if (rotate_quant_block_applicable(a) && (a.Aq6 == nullptr || blockwise_fp6_in_one_launch(a))) return launch_rotate_quant_block(a, s);
+    // the generic kernel writes the 4-bit codes only, and the blockwise one does better to for many tokens: the fp6 copy is
+    // made from them
+    RotateQuantArgs b = a;
+    b.Aq6 = nullptr;
+    const int rc = rotate_quant_block_applicable(b) ? launch_rotate_quant_block(b, s) : launch_rotate_quant_generic(b, s);
     if (rc != BASQ_OK || !a.Aq6 || !a.Aq) return rc;
     return launch_pack_fp6(a.Aq, a.M, a.K, a.Aq6, s);
 }

@@ -23,7 +23,7 @@
 //   fp6 form  made from those dwords inside the quad, about 30 vector instructions a piece on top of 100.  A repacking
 //             launch behind the kernel cost 4-6 us up to 2048 tokens and a pass over the codes beyond (the layer with 64
 //             output channels, K = 11008 in blocks of 256: 1021 tokens 87 -> 33 us with the product's share, 16384 tokens
-//             249 -> 187 us).
+//             249 -> 187 us).  Calls that want both forms of many tokens still repack (rotate_quant.hip).
 //
 // Whole tokens of 512, 1024 or 2048 channels (rotate_quant_small_kernel) are one to four such pieces of ONE wave.  They
 // took the generic kernel of one workgroup per token in LDS: K = 1024, 64 tokens 5.3 -> 3.1 us, 4096 tokens 23.0 -> 5.3 us,

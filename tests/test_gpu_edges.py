@@ -703,3 +703,20 @@ def test_fp6_product_is_not_slow_on_odd_rows_or_with_the_accumulators(M, N, with
     odd = quickest(N, with_acc)
     announce(f"  {1000 * odd:.1f} us against {1000 * even:.1f} us")
     assert odd <= at_most * even
+
+
+@pytest.mark.parametrize("K,rot,M,with_scale", [(512, 128, 8192, False), (512, 128, 8197, False), (2048, 512, 8229, True),
+                                                (11008, 256, 6096, True), (11008, 256, 6097, True)])
+def test_fp6_form_of_blockwise_codes_where_its_writer_changes(K, rot, M, with_scale):
+    """Blockwise rotations with both forms of the codes on both sides of the size from which a second launch repacks them:
+    the fp6 form is that of the codes, and codes and records are those of the call without it."""
+    announce(f"fp6 form of blockwise codes K={K} rot={rot} M={M} scale={with_scale}")
+    X, bias, sa = gpu_inputs(M, K, seed=K + M, with_bias=True, with_scale=with_scale)
+    for f in reversed([0, M - N_SPECIAL]):
+        plant_degenerate_rows(X, f)
+    Aq, meta, Aq2, meta2 = (torch.full(s, 0x5E, dtype=t, device=DEV) for s, t in 2 * [((M, K // 2), torch.uint8), ((M, 4), torch.int32)])
+    A6 = B.alloc_fp6_buffer(M, K, DEV)
+    B.basq_rotate_quant(X, rot, bias, sa, 0.9, 0.95, Aq, meta, Aq6=A6)
+    B.basq_rotate_quant(X, rot, bias, sa, 0.9, 0.95, Aq2, meta2)
+    assert torch.equal(Aq, Aq2) and torch.equal(meta, meta2)
+    check_fp6_copy(Aq, A6, K, row_blocks=[0, (M // 32) - 1, M // 32])
