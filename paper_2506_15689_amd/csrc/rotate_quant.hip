@@ -230,10 +230,12 @@ int launch_rotate_quant_generic(const RotateQuantArgs& a, hipStream_t s);
 
 // Groups of 128 with a full rotation: the one-wave kernel writes the fp6 form as for per-token ranges (K = 4096: 16 tokens 7.9 ->
 // 5.5 us against codes and a repacking launch, 2048 tokens 13.8 -> 11.4, 32000 tokens 93.5 -> 87.7; K = 8192: 11.1 -> 8.8,
-// 21.3 -> 19.1, 214.7 -> 202.1).  Measured up to here, which is also where the per-token form needs staged tails.
-constexpr int64_t GROUPED_FP6_MAX_TOKENS = 32768;
+// 21.3 -> 19.1, 214.7 -> 202.1).  Measured up to here, which is also where the per-token form needs staged tails.  With the
+// rotation written out as well it is even from 4096 tokens and the slower from 20000 on (31000 tokens: K = 4096 250 -> 271 us,
+// K = 8192 602 -> 636).
+constexpr int64_t GROUPED_FP6_MAX_TOKENS = 32768, GROUPED_FP6_MAX_TOKENS_ROT_OUT = 16384;
 static bool groupwise_fp6_in_one_launch(const RotateQuantArgs& a) {
-    return a.M < GROUPED_FP6_MAX_TOKENS && rotate_quant_pow2_applicable(a);
+    return a.M < (a.rot_out ? GROUPED_FP6_MAX_TOKENS_ROT_OUT : GROUPED_FP6_MAX_TOKENS) && rotate_quant_pow2_applicable(a);
 }
 
 // Blockwise rotations with both forms of the codes wanted: the blockwise kernel's own fp6 stores (8- and 16-byte pieces of 32

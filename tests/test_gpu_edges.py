@@ -720,3 +720,22 @@ def test_fp6_form_of_blockwise_codes_where_its_writer_changes(K, rot, M, with_sc
     B.basq_rotate_quant(X, rot, bias, sa, 0.9, 0.95, Aq2, meta2)
     assert torch.equal(Aq, Aq2) and torch.equal(meta, meta2)
     check_fp6_copy(Aq, A6, K, row_blocks=[0, (M // 32) - 1, M // 32])
+
+
+@pytest.mark.parametrize("M,with_rot", [(16383, True), (16384, True), (32767, False), (32768, False)])
+def test_fp6_form_of_groupwise_codes_where_its_writer_changes(M, with_rot):
+    """Full rotation with groups of 128 on both sides of the token counts from which a second launch repacks the codes: the
+    fp6 form is that of the codes, and codes, records and rotation are those of the call without it."""
+    K = 4096
+    announce(f"fp6 form of groups M={M} rotation out={with_rot}")
+    X, bias, _ = gpu_inputs(M, K, seed=M, with_bias=True, with_scale=False)
+    got = []
+    for a6 in (B.alloc_fp6_buffer(M, K, DEV), None):
+        Aq = torch.full((M, K // 2), 0x5E, dtype=torch.uint8, device=DEV)
+        meta = torch.full((M * (K // 128), 4), 0x5E, dtype=torch.int32, device=DEV)
+        r = torch.empty((M, K), device=DEV) if with_rot else None
+        B.basq_rotate_quant(X, K, bias, None, 0.9, 0.95, Aq, meta, r, Aq6=a6, group_size=128)
+        got.append((Aq, meta, r, a6))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert not with_rot or torch.equal(got[0][2], got[1][2])
+    check_fp6_copy(got[0][0], got[0][3], K, row_blocks=[0, (M // 32) - 1])
