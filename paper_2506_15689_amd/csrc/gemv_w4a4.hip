@@ -197,9 +197,13 @@ static void launch_gemv_tiles(const GemmArgs& a, hipStream_t s, int blocks16) {
     // there is one workgroup per compute unit or less, and its time is the chain of a wave's batches of loads: eight
     // waves, and a tile each as long as every compute unit gets one at most (17 tokens, K = 14336, N = 4096: 18.9 us with four
     // waves on two tiles, 16.8 with four on one, 10.6 with eight on one; N = 8192, K = 4096: 7.7 -> 6.7; eight on one for
-    // N = 6144: 12.5 against 10.8 at 64 tokens; eight on two for N = 12288: 9.0 against 8.3).
+    // N = 6144: 12.5 against 10.8 at 64 tokens; eight on two for N = 12288: 9.0 against 8.3).  Rows that four waves hold in
+    // one batch have no chain to shorten (17 tokens, K = 1024, N = 8192: 4.4 us with eight waves, 4.0 with four; N = 1024 3.5
+    // with either; 65 tokens, K = 512, N = 8192: 6.1 against 5.6).
+    const bool one_batch = a.K / 128 <= 4 * STEPS;
     if (blocks16 >= 1536) launch_gemv_cfg<SL, 4, STEPS, 4, TT>(a, s, blocks16);
-    else if (blocks16 > 512) launch_gemv_cfg<SL, 4, STEPS, 2, TT>(a, s, blocks16);
+    else if (blocks16 > 512 || (one_batch && blocks16 > 256)) launch_gemv_cfg<SL, 4, STEPS, 2, TT>(a, s, blocks16);
+    else if (one_batch) launch_gemv_cfg<SL, 4, STEPS, 1, TT>(a, s, blocks16);
     else if (blocks16 > 256) launch_gemv_cfg<SL, 8, STEPS, 2, TT>(a, s, blocks16);
     else launch_gemv_cfg<SL, 8, STEPS, 1, TT>(a, s, blocks16);
 }

@@ -577,11 +577,11 @@ def test_per_head_steps_of_several_items(K, M, with_bias, with_scale):
 
 @pytest.mark.parametrize("N", [40, 4096, 4112, 8192, 8208])
 @pytest.mark.parametrize("M", [17, 33, 65])
-@pytest.mark.parametrize("K", [128, 640])
+@pytest.mark.parametrize("K", [128, 512, 640, 1024, 1152])
 def test_streaming_product_where_its_workgroups_change(K, M, N):
     """The weight-streaming kernel on both sides of the output widths at which it takes more waves or tiles a workgroup
-    (256 and 512 tiles of 16 channels), fewer chunks of K than waves: its INT32 accumulators against the exact product of
-    the codes (fp64 matmul of integers below 2^53)."""
+    (256 and 512 tiles of 16 channels) and of the row lengths from which it takes more waves, fewer chunks of K than waves:
+    its INT32 accumulators against the exact product of the codes (fp64 matmul of integers below 2^53)."""
     announce(f"streaming product M={M} N={N} K={K}")
     gen = torch.Generator(device=DEV).manual_seed(N + M)
     A = torch.randint(0, 256, (M, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
