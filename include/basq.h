@@ -301,7 +301,7 @@ int basq_calibrate_bias(const void* X, int64_t M, int32_t K, int64_t ldx, int32_
  * int8 (Paley type-I construction over GF(27) = GF(3)[t]/(t^3 + 2t + 1)). */
 int basq_hadamard28(int8_t* out_host);
 
-/* ---- diagnostics: what this machine sustains (used by the benchmark's measured ceilings) ---------- */
+/* ---- diagnostics: what this machine sustains (used by the benchmark's measured ceilings), single tilings ---- */
 
 /*
  * Pure streaming kernel with the access pattern of basq_rotate_quant (the paper's fused quant kernel,
@@ -331,6 +331,19 @@ int basq_diag_mfma_i8(int32_t* out, int32_t blocks, int32_t iters, void* stream)
  * out receives blocks*256 fp32 checksums.  Executes blocks*4*8*iters*131072 operations.
  */
 int basq_diag_mfma_f6(float* out, int32_t blocks, int32_t iters, void* stream);
+
+/*
+ * The fp6 product of basq_w4a4_gemm has several tilings, of which it takes the one a cost table names for the shape.  For
+ * checking and timing them one by one: the index of that tiling (0 .. BASQ_FP6_TILINGS - 1; -1 where basq_w4a4_gemm takes
+ * another kernel though both fp6 operands are given), and the product on a given one, whatever M is (the bits do not
+ * depend on it).  Arguments as in basq_w4a4_gemm; both fp6 operands are needed.
+ */
+#define BASQ_FP6_TILINGS 6
+int basq_diag_fp6_tiling(int64_t M, int32_t K, int32_t N);
+int basq_diag_w4a4_gemm_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
+                            const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
+                            void* Y, int64_t ldy, int32_t* acc_out,
+                            const uint8_t* Aq6, const uint8_t* Wq6, void* stream);
 
 #ifdef __cplusplus
 }

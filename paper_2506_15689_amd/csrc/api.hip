@@ -80,10 +80,13 @@ int validate_gemm(const uint8_t* Aq, const basq_tokmeta* meta, int64_t M, int32_
     return BASQ_OK;
 }
 
+bool takes_fp6(const GemmArgs& g) {
+    return gemm_fp6_applicable(g) && (g.M > GEMV_MAX_TOKENS || gemm_fp6_beats_streaming(g.M, g.N, g.K));
+}
+
 int run_gemm(const GemmArgs& g, hipStream_t s) {
-    const bool streaming = g.M <= GEMV_MAX_TOKENS && g.K % 128 == 0;
-    if (streaming && !(gemm_fp6_applicable(g) && gemm_fp6_beats_streaming(g.M, g.N, g.K))) return launch_gemv_decode(g, s);
-    if (gemm_fp6_applicable(g)) return launch_gemm_fp6(g, s);
+    if (takes_fp6(g)) return launch_gemm_fp6(g, s);
+    if (g.M <= GEMV_MAX_TOKENS && g.K % 128 == 0) return launch_gemv_decode(g, s);
     if (g.w_layout != BASQ_W_CANONICAL)
         return fail(BASQ_EUNSUPPORTED, "more than 128 tokens with the streaming weight layout need the fp6 operands "
                                         "(the int8 kernels read canonical weights)");
@@ -160,7 +163,7 @@ int linear_fused_impl(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t 
                w_sum, out_bias, static_cast<uint16_t*>(Y), ldy, nullptr, Aq6, Aq6 ? Wq6 : nullptr, w_layout};
     // when the product runs on the fp6 matrix path nothing reads the 4-bit codes: where the quantiser writes the
     // fp6 form itself it leaves them out
-    if (Aq6 && gemm_fp6_applicable(g) && layer_fp6_only_applicable(a)) a.Aq = nullptr;
+    if (Aq6 && takes_fp6(g) && layer_fp6_only_applicable(a)) a.Aq = nullptr;
     if (w_layout != BASQ_W_CANONICAL && M > GEMV_MAX_TOKENS && !gemm_fp6_applicable(g))      // before anything is launched
         return fail(BASQ_EUNSUPPORTED, "more than 128 tokens with the streaming weight layout need the fp6 operands "
                                         "(the int8 kernels read canonical weights)");
@@ -262,6 +265,32 @@ int basq_w4a4_gemm_grouped(const uint8_t* Aq, const basq_tokmeta* meta, int64_t 
     if (M > 0 && gemm_grouped_fp6_applicable(g)) return launch_gemm_grouped_fp6(g, w_gsum, static_cast<hipStream_t>(stream));
     if (M > 0 && !gemm_grouped_applicable(g)) return fail(BASQ_EUNSUPPORTED, "group-wise GEMM: an operand exceeds 4 GiB");
     return launch_gemm_grouped(g, w_gsum, static_cast<hipStream_t>(stream));
+}
+
+int basq_diag_fp6_tiling(int64_t M, int32_t K, int32_t N) {
+    alignas(16) static const uint8_t given[16] = {};           // stands for both operands: only whether they are given counts
+    GemmArgs g{};
+    g.M = M; g.K = K; g.N = N; g.Aq6 = g.Wq6 = given;
+    if (K < 1 || N < 1 || !takes_fp6(g)) return -1;
+    return gemm_fp6_tiling(M, N, K);
+}
+
+int basq_diag_w4a4_gemm_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
+                            const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
+                            void* Y, int64_t ldy, int32_t* acc_out,
+                            const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {
+    if (tiling < 0 || tiling >= BASQ_FP6_TILINGS) return fail(BASQ_EINVAL, "tiling must be 0 .. %d (got %d)", BASQ_FP6_TILINGS - 1, tiling);
+    if (!Aq6 || !Wq6) return fail(BASQ_EINVAL, "an fp6 operand is null");
+    // (the 4-bit codes are not read: the fp6 operands stand in for them in the checks)
+    int rc = validate_gemm(Aq6, meta, M, K, Wq6, N, BASQ_W_CANONICAL, w_scale, w_zero, w_sum, Y, ldy);
+    if (rc != BASQ_OK) return rc;
+    rc = validate_fp6(Aq6, Wq6, true, K);
+    if (rc != BASQ_OK) return rc;
+    GemmArgs g{nullptr, meta, M, K, nullptr, N, static_cast<const uint16_t*>(w_scale), static_cast<const uint16_t*>(w_zero),
+               w_sum, out_bias, static_cast<uint16_t*>(Y), ldy, acc_out, Aq6, Wq6, BASQ_W_CANONICAL};
+    if (M == 0) return BASQ_OK;
+    if (!gemm_fp6_applicable(g)) return fail(BASQ_EUNSUPPORTED, "no fp6 product of this shape");
+    return launch_gemm_fp6_tiling(tiling, g, static_cast<hipStream_t>(stream));
 }
 
 int basq_group_colsums(const uint8_t* Wq, int32_t N, int32_t K, int32_t group_size, int32_t* w_gsum, void* stream) {

@@ -439,7 +439,7 @@ double tiling_cost(const Tiling& t, int64_t M, int64_t N, int K) {
 // of 128 x 128 take 14.1 us, 384 of 64 x 64 11.9 us), and where a round of 256 x 128 tiles fits exactly it takes
 // 58.9 us against 62.2 us for 256 x 192 and 66.4 us for 128 x 128 (2048 x 4096, K = 14336; without `fill` the table took
 // 256 x 192 there).  128 x 64 is for 65 .. 128 tokens (128 x 12288, K = 4096: 13.9 us against 17.1 us for 64 x 64).
-constexpr int NUM_TILINGS = 6;
+constexpr int NUM_TILINGS = BASQ_FP6_TILINGS;
 const Tiling tilings[NUM_TILINGS] = {
     {256, 256, 1, 2.9, {10.7, 0.774}, {{6.1, 0.477}}, 0.31},
     {256, 192, 1, 3.0, {9.0, 0.639}, {{4.6, 0.379}}, 0.242},
@@ -481,11 +481,10 @@ bool gemm_fp6_applicable(const GemmArgs& a) {
            (int64_t)basq_fp6_bytes(a.M, a.K) < 0xFFFFFFFFll && (int64_t)basq_fp6_bytes(a.N, a.K) < 0xFFFFFFFFll;
 }
 
-int launch_gemm_fp6(const GemmArgs& a, hipStream_t s) {
-#ifdef GEMM_FP6_CFG
-    return launch_fp6<GEMM_FP6_CFG>(a, s);
-#else
-    switch (cheapest_tiling(a.M, a.N, a.K)) {
+int gemm_fp6_tiling(int64_t M, int32_t N, int32_t K) { return cheapest_tiling(M, N, K); }
+
+int launch_gemm_fp6_tiling(int tiling, const GemmArgs& a, hipStream_t s) {
+    switch (tiling) {
         case 0: return launch_fp6<256, 256, 2, 4, 3, 2>(a, s);
         case 1: return launch_fp6<256, 192, 4, 2, 3, 2>(a, s);
         case 2: return launch_fp6<256, 128, 4, 2, 4, 2>(a, s);
@@ -493,7 +492,10 @@ int launch_gemm_fp6(const GemmArgs& a, hipStream_t s) {
         case 4: return launch_fp6<128, 64, 4, 1, 4, 2>(a, s);
         default: return launch_fp6<64, 64, 2, 2, 4, 3>(a, s);
     }
-#endif
+}
+
+int launch_gemm_fp6(const GemmArgs& a, hipStream_t s) {
+    return launch_gemm_fp6_tiling(cheapest_tiling(a.M, a.N, a.K), a, s);
 }
 
 }  // namespace basq

@@ -155,6 +155,12 @@ def run_gpu(case: Case, d: DeviceCase) -> GpuResult:
         B.basq_linear_fused(d.X, case.rot_size, d.bias, d.act_scale, case.clip_lo, case.clip_hi, Wd, d.w_scale,
                             d.w_zero, d.w_sum, d.out_bias, Ydf, ws, w_layout=B.BASQ_W_DECODE16, N=N,
                             Wq6=W6 if M > B.STREAM_MAX_TOKENS else None)
+        if M <= B.STREAM_MAX_TOKENS:                     # and with the fp6 weights beside them, on whichever product that takes
+            Ydf6 = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=dev)
+            ws.fill_(0xFF)
+            B.basq_linear_fused(d.X, case.rot_size, d.bias, d.act_scale, case.clip_lo, case.clip_hi, Wd, d.w_scale,
+                                d.w_zero, d.w_sum, d.out_bias, Ydf6, ws, w_layout=B.BASQ_W_DECODE16, N=N, Wq6=W6)
+            assert torch.equal(Ydf6.view(torch.int16), Ydf.view(torch.int16)), "layer with both weight forms"
         torch.cuda.synchronize()
         res.wd, res.accd = Wd.cpu().numpy(), accd.cpu().numpy()
         res.yd_bits, res.yd_fused_bits = si.bf16_bits(Yd.cpu()), si.bf16_bits(Ydf.cpu())

@@ -37,6 +37,22 @@ def test_version_and_error_text(lib):
     assert rc == B.BASQ_EINVAL and "multiple of 32" in B.basq_last_error()
 
 
+def test_fp6_tilings_by_name(lib):
+    """Which tiling a shape takes is known without a GPU; a product by name is refused where it could not run."""
+    T = B.basq_diag_fp6_tiling
+    assert T(4096, 8192, 28672) == 0 and T(2048, 4096, 12288) == 1 and T(2048, 14336, 4096) == 2
+    assert T(1021, 11008, 4096) == 3 and T(260, 11008, 4096) == 4 and T(333, 4096, 4096) == 5
+    # shapes whose product runs elsewhere
+    assert T(32, 4096, 28672) == T(61, 4096, 8192) == T(200, 4096 + 64, 512) == T(200, 32768 + 128, 512) == T(0, 4096, 4096) == -1
+    assert T(61, 4096, 12288) >= 0 and T(65, 128, 1) >= 0
+    call = lambda t, K=256, a=FAKE, w=FAKE, y=FAKE: lib.basq_diag_w4a4_gemm_fp6(
+        t, FAKE, 64, K, 64, FAKE, FAKE, FAKE, None, y, 64, None, a, w, None)
+    assert call(-1) == call(B.FP6_TILINGS) == B.BASQ_EINVAL
+    assert call(0, a=None) == call(0, w=None) == call(0, y=None) == call(0, K=192) == B.BASQ_EINVAL
+    assert call(0, a=ctypes.c_void_p(0x1008)) == B.BASQ_EINVAL
+    assert call(0, K=32768 + 128) == B.BASQ_EUNSUPPORTED
+
+
 FAKE = ctypes.c_void_p(0x1000)      # aligned, never dereferenced: validation fails first
 
 

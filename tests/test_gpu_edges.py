@@ -468,13 +468,14 @@ def test_packed_operands_of_two_to_four_gib_and_beyond(M):
 
 @pytest.mark.parametrize("K", [128, 256, 384, 512, 640, 896])
 @pytest.mark.parametrize("M,N,pad", [(129, 64, 0), (300, 1000, 0), (257, 514, 2), (131, 333, 1), (700, 20480, 8), (1030, 4100, 4), (2000, 12300, 4),
-                                     (40, 12288, 0), (64, 6000, 0), (65, 72, 0), (128, 2050, 2)])
+                                     (61, 24584, 2), (64, 28672, 0), (65, 72, 0), (128, 2050, 2)])
 def test_fp6_product_over_few_k_steps(K, M, N, pad):
     """Every length of the K loop around the depth of its ring of LDS stages (no steady step at all, one, several), each
-    with ragged tiles, every tiling, more tiles than compute units hold at once and each alignment of the output rows: the bits of
+    with ragged tiles and each alignment of the output rows, on the tiling that the shape takes: the bits of
     the int8 path (exact integer products, the same epilogue arithmetic, so no tolerance).  The last four are token
     counts that the weight-streaming kernel also takes (it is what they are compared with)."""
     announce(f"fp6 product M={M} N={N} K={K} pad={pad}")
+    assert B.basq_diag_fp6_tiling(M, K, N) >= 0, "not a case of the fp6 product"
     gen = torch.Generator(device=DEV).manual_seed(K + M)
     A = torch.randint(0, 256, (M, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
     W = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device=DEV, generator=gen)
@@ -673,6 +674,74 @@ def test_fp6_products_into_rows_of_any_alignment(M, N, ldy, offset, grouped):
         assert bool((buf == -7.0).all()), "wrote outside the output"
     assert torch.equal(got[0][1], got[1][1])
     assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16))
+
+
+# tile of each tiling (tokens, channels) and how many workgroups of it are resident at once
+FP6_TILES = [(256, 256, 256), (256, 192, 256), (256, 128, 256), (128, 128, 512), (128, 64, 512), (64, 64, 768)]
+
+
+@pytest.mark.parametrize("K", [128, 256, 384, 512, 640, 896])
+@pytest.mark.parametrize("tiling", range(B.FP6_TILINGS))
+def test_every_tiling_of_the_fp6_product(tiling, K):
+    """Each tiling by name: lengths of the K loop around the depth of its ring of stages, tiles ragged in both directions,
+    fewer tokens and channels than a tile, every kind of output row, and more tiles than are resident at once (so that a
+    workgroup goes on to another tile): the bits of the kernels without the fp6 operands, nothing beside the output."""
+    bm, bn, resident = FP6_TILES[tiling]
+    rows = 9                                                # of tiles, of the case that overflows the chip
+    shapes = [(1, 1, 1, 0), (33, 72, 72, 0), (bm, bn, bn, 0), (bm + 1, bn - 1, bn, 8), (2 * bm - 31, 3 * bn + 32, 3 * bn + 40, 0),
+              (300, 1000, 1000, 0), (131, 333, 333, 1), (257, 514, 516, 2),
+              (rows * bm - 45, (resident // rows + 2) * bn + 8, (resident // rows + 2) * bn + 8, 0)]
+    for M, N, ldy, offset in shapes:
+        announce(f"tiling {tiling} M={M} N={N} K={K} ldy={ldy} offset={offset}")
+        A, A6, meta, W, W6, sw, zp, ws, c = random_product(M, N, K, seed=M + N)
+        buf, Y = output_view(M, N, ldy, offset)
+        with_acc = N < 2000
+        acc = torch.full((M, N), -1, dtype=torch.int32, device=DEV) if with_acc else None
+        B.basq_diag_w4a4_gemm_fp6(tiling, meta, K, sw, zp, ws, c, Y, acc, A6, W6)
+        want = torch.full((M, N), -7.0, dtype=torch.bfloat16, device=DEV)
+        want_acc = torch.full((M, N), -2, dtype=torch.int32, device=DEV) if with_acc else None
+        B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, want, want_acc)
+        assert torch.equal(Y.contiguous().view(torch.int16), want.view(torch.int16))
+        assert not with_acc or torch.equal(acc, want_acc)
+        Y.fill_(-7.0)
+        assert bool((buf == -7.0).all()), "wrote outside the output"
+
+
+@pytest.mark.parametrize("M,K,rot,N,product", [
+    (61, 4096, 4096, 12288, "fp6"), (46, 4096, 4096, 12288, "stream"), (47, 4096, 4096, 12288, "fp6"),    # the rule's edge
+    (61, 4096, 4096, 8192, "stream"), (42, 4096, 4096, 8208, "fp6"), (39, 1024, 1024, 12288, "fp6"),
+    (60, 1024, 256, 12296, "fp6"), (64, 896, 128, 28672, "layer streams"),
+    (65, 4096, 4096, 200, "fp6"), (128, 8192, 8192, 72, "fp6"), (100, 2048, 2048, 333, "fp6"), (96, 1536, 512, 136, "fp6"),
+    (65, 640, 128, 200, "layer streams"), (128, 896, 128, 333, "layer streams"), (128, 14336, 14336, 40, "fp6"),
+    (129, 640, 128, 200, "fp6"), (129, 4096, 4096, 72, "fp6")])
+def test_layer_with_both_weight_forms(M, K, rot, N, product):
+    """The one-call layer with streaming-layout and fp6 weights, the way a serving program keeps them, over the token counts
+    at which either product may take it and with quantisers that write the fp6 form themselves and one that does not ("layer
+    streams": the fp6 product would take the codes, but only from a launch of its own): the bits of the layer without the
+    fp6 weights.  The workspace is poisoned, so a product that reads codes which were left out shows."""
+    announce(f"both weight forms M={M} K={K} rot={rot} N={N}: {product}")
+    assert (B.basq_diag_fp6_tiling(M, K, N) >= 0) == (product != "stream")
+    X, bias, sa = gpu_inputs(M, K, seed=K + M, with_bias=True, with_scale=True)
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    W = (torch.randn((N, K), generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
+    Wq, sw, zp, ws = B.alloc_weight_buffers(N, K)
+    B.basq_quantize_weights(W, Wq, sw, zp, ws)
+    c, W6 = torch.empty(N, device=DEV), B.alloc_fp6_buffer(N, K)
+    B.basq_prepare_weights(Wq, sw, zp, bias, None, ws, c, W6)
+    Wd = torch.empty(B.basq_decode_bytes(N, K), dtype=torch.uint8, device=DEV)
+    B.basq_pack_decode(Wq, Wd)
+    work = torch.empty(B.basq_workspace_bytes(M, K, N), dtype=torch.uint8, device=DEV)
+
+    def layer(poison, w6, w=Wd, layout=B.BASQ_W_DECODE16):
+        work.fill_(poison)
+        Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        B.basq_linear_fused(X, rot, bias, sa, 0.9, 0.9, w, sw, zp, ws, c, Y, work, Wq6=w6, w_layout=layout, N=N)
+        return Y.view(torch.int16)
+
+    want = layer(0, None, Wq, B.BASQ_W_CANONICAL)
+    assert torch.equal(layer(0x5A, W6), want) and torch.equal(layer(0xFF, W6), want)
+    if M <= B.STREAM_MAX_TOKENS:
+        assert torch.equal(layer(0xFF, None), want)
 
 
 @pytest.mark.parametrize("M,N,with_acc,at_most", [(1021, 32001, False, 2.0), (2048, 4096, True, 2.5)])
