@@ -48,6 +48,9 @@ int launch_rotate_quant_small(const RotateQuantArgs& a, hipStream_t s);
 bool rotate_quant_k28_applicable(const RotateQuantArgs& a);
 int launch_rotate_quant_k28(const RotateQuantArgs& a, hipStream_t s);
 
+// How the fp6 kernels store outputs: aligned 16-byte pieces with the non-temporal hint or without it, or at any alignment.
+enum class StoreForm : int32_t { any, whole, whole_nt };
+
 struct GemmArgs {
     const uint8_t* Aq;
     const basq_tokmeta* meta;
@@ -66,6 +69,7 @@ struct GemmArgs {
     const uint8_t* Aq6;
     const uint8_t* Wq6;
     int32_t w_layout;         // layout of Wq: BASQ_W_CANONICAL, or BASQ_W_DECODE16 (read by the weight-streaming kernel only)
+    StoreForm store_form = StoreForm::any;      // set by the launchers of the fp6 kernels (gemm_fp6_store.h)
 };
 int launch_gemm_prefill(const GemmArgs& a, hipStream_t s);
 // direct-to-LDS kernel for K % 256 == 0 (gemm_w4a4_direct.hip)

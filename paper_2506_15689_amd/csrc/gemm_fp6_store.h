@@ -22,31 +22,27 @@ typedef float fp6_acc_t __attribute__((ext_vector_type(16)));
 //
 //   row0            first row of the wave inside the tile; m0, n0: the tile's first row and column
 //   col_block(j)    column block of the tile (32 columns each) of the wave's block j; blocks 2k and 2k + 1 are adjacent
-// Any ldy >= N, N and Y a bf16 tensor can have.  Where rows start on 16-byte boundaries the pieces leave with the
-// non-temporal hint; elsewhere they are 16-byte stores at the alignment there is, without it (a line is then completed by
-// another instruction's stores).  Only the last piece of a row of N % 8 != 0 channels is stored channel by channel.
-// (1021 tokens, K = 4096: N = 32000 70 us, 32001 91 us in rows of 32001 and 78 us in rows of 32008; with 2-byte stores for
-// odd N or ldy, which from this register layout go to 32 rows an instruction, 211 and 225 us, and dword stores for even N
-// were 7-14 % slower: 2048 x 12290 75.6 us, as built 65.2.)
-template <int TM, int TN, int BM, class ColBlock>
-__device__ __forceinline__ void store_outputs(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const unsigned (&outv)[TM][TN][4][2], ColBlock&& col_block) {
-    const bool aligned = (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0;
-    const bool whole = aligned && (a.N & 7) == 0;
+// Any ldy >= N, N and Y a bf16 tensor can have; FORM says what they allow (see store_outputs).
+template <StoreForm FORM, int TM, int TN, int BM, class ColBlock>
+__device__ __forceinline__ void store_outputs_as(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const unsigned (&outv)[TM][TN][4][2], ColBlock&& col_block) {
     const int piece = 2 * ((lane >> 4) & 1) + (lane >> 5);
     const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;       // of the matrix, from the tile's start
     auto store16 = [&](int row, int col, unsigned o0, unsigned o1, unsigned o2, unsigned o3) {      // within the tile
-        if (row >= row_end) return;
+        if (row >= row_end || col >= col_end) return;
         uint16_t* dst = a.Y + (m0 + row) * a.ldy + n0 + col;
-        if (whole) {
-            if (col < col_end) nt_store16(dst, make_uint4(o0, o1, o2, o3));
+        const basq_v4u v = {o0, o1, o2, o3};
+        if (FORM == StoreForm::whole_nt) {
+            nt_store16(dst, make_uint4(o0, o1, o2, o3));
+        } else if (FORM == StoreForm::whole) {
+            *reinterpret_cast<basq_v4u*>(dst) = v;
         } else if (col + 8 <= col_end) {
-            if (aligned) nt_store16(dst, make_uint4(o0, o1, o2, o3));
-            else { const basq_v4u v = {o0, o1, o2, o3}; __builtin_memcpy(dst, &v, 16); }
+            __builtin_memcpy(dst, &v, 16);
         } else {
-            const unsigned o[4] = {o0, o1, o2, o3};
 #pragma unroll
-            for (int e = 0; e < 7; ++e)
-                if (col + e < col_end) dst[e] = (uint16_t)(o[e >> 1] >> (16 * (e & 1)));
+            for (int e = 0; e < 4; ++e) {
+                if (col + 2 * e + 1 < col_end) { const unsigned d = v[e]; __builtin_memcpy(dst + 2 * e, &d, 4); }
+                else if (col + 2 * e < col_end) dst[2 * e] = (uint16_t)v[e];
+            }
         }
     };
 #pragma unroll
@@ -88,6 +84,22 @@ __device__ __forceinline__ void store_outputs(const GemmArgs& a, int64_t m0, int
         }
         __builtin_amdgcn_sched_barrier(0);
     }
+}
+
+// Rows that start on 16-byte boundaries and hold whole pieces of 8 channels leave as aligned 16-byte stores, with the
+// non-temporal hint where output_form() says so.  Everything else takes 16-byte stores at the
+// alignment there is; only the last piece of a row of N % 8 != 0 channels goes by pairs of channels.  (1021 tokens, K = 4096:
+// N = 32000 70 us, 32001 91 us in rows of 32001 and 78 us in rows of 32008; with 2-byte stores for odd N or ldy, which from
+// this register layout go to 32 rows an instruction, 211 and 225 us, and dword stores for even N were 7-14 % slower: 2048 x
+// 12290 75.6 us, as built 65.2.)
+template <int TM, int TN, int BM, class ColBlock>
+__device__ __forceinline__ void store_outputs(const GemmArgs& a, StoreForm form, int64_t m0, int n0, int row0, int lane, const unsigned (&outv)[TM][TN][4][2], ColBlock&& col_block) {
+    if (form == StoreForm::whole_nt)
+        store_outputs_as<StoreForm::whole_nt, TM, TN, BM>(a, m0, n0, row0, lane, outv, col_block);
+    else if (form == StoreForm::whole)
+        store_outputs_as<StoreForm::whole, TM, TN, BM>(a, m0, n0, row0, lane, outv, col_block);
+    else
+        store_outputs_as<StoreForm::any, TM, TN, BM>(a, m0, n0, row0, lane, outv, col_block);
 }
 
 // The optional dump of the integer accumulators (64 * acc) into a.acc_out, rows of N int32.  As above, with one channel a
@@ -135,6 +147,24 @@ __device__ __forceinline__ void store_accumulators(const GemmArgs& a, int64_t m0
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+}
+
+// How the outputs leave.  With the non-temporal hint they don't displace the operands from the caches (4096 x
+// 28672, K = 8192: 406 us with, 420 without; 2048 x 12288, K = 4096 56 and 58; 333 x 4096 even) -- where rows are whole
+// 128-byte lines.  A line that two rows share is otherwise written in two parts (33204 x 14216, K = 256: 466 us with, 284
+// without; 5293 x 5840, K = 256 27 and 20; 2048 x 12304, K = 4096 62 and 56), which pays only where operands that are read many
+// times do not stay in the 256 MB beside the outputs (4096 x 28656, K = 8192 409 and 419; 4096 x 16432, K = 11008 348 and 370;
+// but 16384 x 9008, K = 4096 299 and 286, 3000 x 20016, K = 8192 229 and 223).
+// `hides_stores`: the kernel's other workgroups have enough to do meanwhile (the group-wise product from K = 4096 on, and with
+// half lines: 3000 x 20016, K = 4096 227 us with the hint and 236 without; 2048 x 12304, K = 512 31 and 26; 2048 x 12320, K = 1024
+// 36.6 and 37.3).
+StoreForm output_form(const GemmArgs& a, bool hides_stores) {
+    const uintptr_t y = reinterpret_cast<uintptr_t>(a.Y);
+    if ((a.ldy & 7) != 0 || (a.N & 7) != 0 || (y & 15) != 0) return StoreForm::any;
+    if (((a.ldy & 63) == 0 && (y & 127) == 0) || hides_stores) return StoreForm::whole_nt;
+    const double operands = 0.75 * a.K * ((double)a.M + a.N);
+    const bool spill = operands > (double)(128 << 20) && operands + 2.0 * (double)a.M * a.N > (double)(256 << 20);
+    return spill ? StoreForm::whole_nt : StoreForm::whole;
 }
 
 }  // namespace

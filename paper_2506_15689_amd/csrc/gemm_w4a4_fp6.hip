@@ -78,6 +78,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int swave = __builtin_amdgcn_readfirstlane(wave);
     const int ksteps = a.K / 128;
+    int store_form = (int)a.store_form;                       // fetched here: at the end it would be a memory latency
+    asm volatile("" : "+s"(store_form));
     const int rb_a = (int)((a.M + 31) >> 5), rb_w = (a.N + 31) >> 5;   // 32-row blocks per chunk of K
     const unsigned a_step = (unsigned)rb_a * BLOCK, w_step = (unsigned)rb_w * BLOCK;   // bytes from one chunk of K to the next
     const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.Aq6), 0, (int)(a_step * (unsigned)ksteps), 0x00020000);
@@ -328,7 +330,12 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         // the stages that were waited for before the previous tile's stores went out: no wait here, which would be one for
         // those stores as well
         for (; ks < landed && ks + STAGES < ksteps; ++ks) k_step(ks, yes, yes, yes, yes);
-        for (; ks + STAGES < ksteps; ++ks) k_step(ks, yes, yes, yes, no);
+        for (; ks + STAGES < ksteps; ++ks) {
+            // The step's code on a 16-byte boundary: where it begins in the middle of an 8-byte pair, which code anywhere in front
+            // of it decides, a step of one workgroup per compute unit is 1 % longer (2048 x 4096, K = 14336: 61.2 and 62.3 us).
+            asm volatile(".p2align 4");
+            k_step(ks, yes, yes, yes, no);
+        }
         if (ks + STAGES - 1 < ksteps) { k_step(ks, yes, no, yes, no); ++ks; }
         for (; ks + 1 < ksteps; ++ks) k_step(ks, no, no, yes, no);
         k_step(ks, no, no, no, no);
@@ -392,7 +399,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         // landed), and only then send the stores: a wait placed after them would have to wait for
         // the stores too, the counter being one and the same
         if (more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        store_outputs<TM, TN, BM>(a, m0, n0, wm * WM, elane, outv, col_block);
+        store_outputs<TM, TN, BM>(a, (StoreForm)store_form, m0, n0, wm * WM, elane, outv, col_block);
         if (!more) break;
         pid = next_pid; tile_m = next_m; tile_n = next_n;
     }
@@ -409,8 +416,10 @@ int launch_fp6(const GemmArgs& a, hipStream_t s) {
     const int64_t resident = 256 * (MINOCC * 4 / (WAVES_M * WAVES_N));
     static_assert(MINOCC * 4 % (WAVES_M * WAVES_N) == 0 && MINOCC * 4 >= WAVES_M * WAVES_N, "whole workgroups per compute unit");
     const int64_t grid = tm * tn < resident ? tm * tn : resident;
+    GemmArgs b = a;
+    b.store_form = output_form(a, false);
     hipLaunchKernelGGL((gemm_w4a4_fp6_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, MINOCC>), dim3((unsigned)grid),
-                       dim3(WAVES_M * WAVES_N * 64), 0, s, a, (int)tm, (int)tn);
+                       dim3(WAVES_M * WAVES_N * 64), 0, s, b, (int)tm, (int)tn);
     return check_hip(hipGetLastError(), "w4a4_gemm (fp6) launch");
 }
 

@@ -88,6 +88,8 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
     const int64_t m0 = (int64_t)tile_m * G6G_BM;
     const int n0 = tile_n * G6G_BN;
     const int ngroups = a.K / 128;
+    int store_form = (int)a.store_form;                       // fetched here: at the end it would be a memory latency
+    asm volatile("" : "+s"(store_form));
     const int rb_a = (int)((a.M + 31) >> 5), rb_w = (a.N + 31) >> 5;   // 32-row blocks per chunk of K
     const unsigned a_step = (unsigned)rb_a * G6G_BLOCK, w_step = (unsigned)rb_w * G6G_BLOCK;   // bytes from one chunk to the next
     const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.Aq6), 0, (int)(a_step * (unsigned)ngroups), 0x00020000);
@@ -275,6 +277,9 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
         group(0, cur, next, yes, yes, yes);
         advance();
         for (g = 1; g + G6G_STAGES < ngroups; ++g) {
+            // on a 16-byte boundary: beginning in the middle of an 8-byte pair, which code anywhere in front of the loop
+            // decides, costs 3 % with one workgroup per compute unit (700 x 5008, K = 8192: 39.3 and 40.5 us)
+            asm volatile(".p2align 4");
             group(g, cur, next, no, yes, yes);
             advance();
         }
@@ -327,7 +332,7 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    store_outputs<G6G_TM, G6G_TN, G6G_BM>(a, m0, n0, wm * G6G_WM, lane, outv, col_block);
+    store_outputs<G6G_TM, G6G_TN, G6G_BM>(a, (StoreForm)store_form, m0, n0, wm * G6G_WM, lane, outv, col_block);
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
@@ -346,7 +351,9 @@ int launch_gemm_grouped_fp6(const GemmArgs& a, const int32_t* w_gsum, hipStream_
     const int64_t tm = (a.M + G6G_BM - 1) / G6G_BM;
     const int64_t tn = ((int64_t)a.N + G6G_BN - 1) / G6G_BN;
     if (tm * tn > 0x7FFFFFFFll) return fail(BASQ_EINVAL, "w4a4_gemm_grouped: problem too large for one launch");
-    hipLaunchKernelGGL(gemm_w4a4_grouped_fp6_kernel, dim3((unsigned)(tm * tn)), dim3(G6G_THREADS), 0, s, a, w_gsum, (int)tm, (int)tn);
+    GemmArgs b = a;
+    b.store_form = output_form(a, a.K >= 4096 || (a.ldy & 31) == 0);
+    hipLaunchKernelGGL(gemm_w4a4_grouped_fp6_kernel, dim3((unsigned)(tm * tn)), dim3(G6G_THREADS), 0, s, b, w_gsum, (int)tm, (int)tn);
     return check_hip(hipGetLastError(), "w4a4_gemm_grouped (fp6) launch");
 }
 
