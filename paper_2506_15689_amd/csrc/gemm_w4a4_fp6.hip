@@ -458,6 +458,11 @@ const Tiling tilings[NUM_TILINGS] = {
     {64, 64, 3, 2.9, {1.3, 0.40}, {{0.7, 0.148}, {1.3, 0.221}, {1.7, 0.339}}, 0.043},
 };
 int cheapest_tiling(int64_t M, int64_t N, int K) {
+    // Few K-steps and many rounds are bound by the outputs, which the largest tiles write fastest and the table, fitted on at
+    // most seven rounds and from K = 1024 on, prices by their first rounds (23522 x 22162, K = 512: 128 x 128 519 us, 256 x
+    // 256 360; 33204 x 14216, K = 256 385 and 284; 4442 x 26256, K = 1536 140 and 120; below four rounds the table is the
+    // better guide; K = 2048 and beyond are even).
+    if (K < 2048 && ((M + 255) / 256) * ((N + 255) / 256) >= 4 * 256) return 0;
     int best = 0;
     for (int i = 1; i < NUM_TILINGS; ++i)
         if (tiling_cost(tilings[i], M, N, K) < tiling_cost(tilings[best], M, N, K)) best = i;

@@ -42,6 +42,8 @@ def test_fp6_tilings_by_name(lib):
     T = B.basq_diag_fp6_tiling
     assert T(4096, 8192, 28672) == 0 and T(2048, 4096, 12288) == 1 and T(2048, 14336, 4096) == 2
     assert T(1021, 11008, 4096) == 3 and T(260, 11008, 4096) == 4 and T(333, 4096, 4096) == 5
+    # few K-steps and four rounds of the largest tiles, and just below
+    assert T(1024, 512, 256 * 256) == 0 and T(1024, 512, 256 * 255) != 0 and T(33204, 256, 14216) == 0
     # shapes whose product runs elsewhere
     assert T(32, 4096, 28672) == T(61, 4096, 8192) == T(200, 4096 + 64, 512) == T(200, 32768 + 128, 512) == T(0, 4096, 4096) == -1
     assert T(61, 4096, 12288) >= 0 and T(65, 128, 1) >= 0
