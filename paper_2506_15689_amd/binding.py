@@ -108,6 +108,11 @@ def load() -> ctypes.CDLL:
 # handle is asked for without building a Stream object (2 us), and buffer sizes that are arithmetic are not asked of the
 # library (1 us).  One token through a 4096 x 4096 layer: 10.0 -> 6.5 us
 # a call on the host, of which about 4 are the launch.
+# (Not part of torch's documented interface: where they are missing the Stream object is built after all.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _p(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
@@ -115,9 +120,9 @@ def _p(t: Optional[torch.Tensor]) -> Optional[int]:
 def _stream(stream: Optional[torch.cuda.Stream]) -> int:
     if stream is not None:
         return stream.cuda_stream
-    if not torch.cuda.is_initialized():
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_raw_device())
 
 
 def _check(rc: int) -> None:

@@ -37,6 +37,23 @@ def test_version_and_error_text(lib):
     assert rc == B.BASQ_EINVAL and "multiple of 32" in B.basq_last_error()
 
 
+@pytest.mark.parametrize("missing", ["_raw_stream", "_raw_device"])
+def test_current_stream_without_torchs_undocumented_functions(monkeypatch, missing):
+    """The handle of the current stream comes from two functions that torch does not document; without either it is the
+    Stream object's, also once the GPU is in use."""
+    class Stream:
+        cuda_stream = 0x5678
+
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 0x1234)
+    monkeypatch.setattr(B, "_raw_device", lambda: 0)
+    monkeypatch.setattr(B.torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: Stream)
+    assert B._stream(None) == 0x1234
+    monkeypatch.setattr(B, missing, None)
+    assert B._stream(None) == 0x5678
+    assert B._stream(Stream) == 0x5678
+
+
 def test_fp6_tilings_by_name(lib):
     """Which tiling a shape takes is known without a GPU; a product by name is refused where it could not run."""
     T = B.basq_diag_fp6_tiling
