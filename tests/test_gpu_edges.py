@@ -810,3 +810,42 @@ def test_fp6_form_of_groupwise_codes_where_its_writer_changes(M, with_rot):
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
     assert not with_rot or torch.equal(got[0][2], got[1][2])
     check_fp6_copy(got[0][0], got[0][3], K, row_blocks=[0, (M // 32) - 1])
+
+
+@pytest.mark.parametrize("kind", ["ordinary", "cancelling", "wide exponents", "tiny", "large"])
+@pytest.mark.parametrize("K", [128, 384, 1024])
+def test_group_sums_bit_for_bit(K, kind):
+    """The group-wise fp6 kernel keeps F / 64 and takes z * colsum by a matrix instruction; the int8 kernel keeps F by fp32
+    multiply-adds.  All 24 bits of F must agree: with unit weight scales, no zero points and out_bias = -(what was read so far)
+    three calls bring F out in pieces of eight bits (each difference is exact: what is subtracted is the rounded sum)."""
+    announce(f"group sums K={K} {kind}")
+    M, N, G = 6, 1500, K // 128
+    A, A6, meta, W, W6, _, _, _, _ = random_product(M, N, K, seed=K + len(kind), groups=G)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    rand = lambda: torch.rand(M * G, device=DEV, generator=gen)
+    scale, lo = rand() + 0.1, -rand()
+    if kind == "cancelling":                                    # products of some 10^4 against bounds of the other sign
+        lo = -scale * (7.5 + 0.01 * rand())
+    elif kind == "wide exponents":
+        scale, lo = torch.exp2(40 * rand() - 20), torch.exp2(40 * rand() - 20) * (rand() - 0.5).sign()
+    elif kind != "ordinary":
+        f = 1e-30 if kind == "tiny" else 1e30
+        scale, lo = scale * f, lo * f
+    meta.view(torch.float32)[:, 0], meta.view(torch.float32)[:, 1] = scale, lo
+    gsum = torch.empty((G, N), dtype=torch.int32, device=DEV)
+    B.basq_group_colsums(W, 128, gsum)
+    one, zero = torch.ones(N, dtype=torch.bfloat16, device=DEV), torch.zeros(N, dtype=torch.bfloat16, device=DEV)
+    for m in range(M):
+        got = []
+        for forms in ({}, dict(Aq6=B.alloc_fp6_buffer(1, K), Wq6=W6)):
+            if forms:
+                B.basq_pack_fp6(A[m:m + 1], forms["Aq6"])
+            read = torch.zeros(N, device=DEV)
+            pieces = []
+            for _ in range(3):
+                Y = torch.empty((1, N), dtype=torch.bfloat16, device=DEV)
+                B.basq_w4a4_gemm_grouped(A[m:m + 1], meta[m * G:(m + 1) * G], 128, W, one, zero, gsum, -read, Y, **forms)
+                pieces.append(Y[0].view(torch.int16).clone())
+                read = read + Y[0].float()
+            got.append(torch.stack(pieces))
+        assert torch.equal(got[0], got[1]), f"token {m}: {int((got[0] != got[1]).sum())} pieces differ"
