@@ -200,8 +200,9 @@ size_t basq_workspace_bytes(int64_t M, int32_t K, int32_t N);
 /*
  * The whole layer in one call: basq_rotate_quant then basq_w4a4_gemm on `stream`, the codes and
  * token records living in `workspace` (256-byte aligned, >= basq_workspace_bytes(M, K, N), else
- * BASQ_EWORKSPACE).  Arguments as in the two calls above; with Wq6, M > 64 (from 33 on where the shape
- * favours it) takes the fp6 matrix-core path.
+ * BASQ_EWORKSPACE).  Arguments as in the two calls above; with Wq6, M > 128 takes the fp6 matrix-core path, and
+ * so does M > 64 (from 33 on where the shape favours it) if the quantiser writes the fp6 form itself: rot_size == K in
+ * {512, 1024, 2048, 4096, 8192, 14336}, or rot_size in {128, 256, 512} with K % 256 == 0 and K <= 16384.
  * group_size must be 0 or K here (BASQ_EUNSUPPORTED otherwise: groups go through basq_rotate_quant and
  * basq_w4a4_gemm_grouped).  With at most 4 tokens, rot_size == K in {4096, 8192}, N <= 4096 and
  * w_layout = BASQ_W_DECODE16 the whole layer is one kernel launch (same results bit for bit).  Nothing in this

@@ -442,12 +442,17 @@ double tiling_cost(const Tiling& t, int64_t M, int64_t N, int K) {
     return us;
 }
 
-// Six tilings; the cheapest by the table is within 0.3 % of the fastest in the mean over those shapes (13 % at worst).
+// Six tilings; the cheapest by the table is within 0.3 % of the fastest in the mean over those shapes (13 % at worst), whose
+// weights were in the caches.  With weights cold in memory it is as good from 334 tokens on, and 1.2 % off for 65 .. 333, where
+// a pass over the weights is what counts and 64 x 64 tiles make too many of them (192 x 8192, K = 14336: 45 us against 34 on 128 x 64,
+// with the weights in the caches 31 against 32).
 // Choosing among the first, second and fourth by how evenly their tiles fill the chip, as before, was 13 % off in the
 // mean and up to 2.6 times: it gave 129 .. 500 tokens tiles too large to occupy the chip (333 x 4096 x 4096: 96 tiles
 // of 128 x 128 take 14.1 us, 384 of 64 x 64 11.9 us), and where a round of 256 x 128 tiles fits exactly it takes
 // 58.9 us against 62.2 us for 256 x 192 and 66.4 us for 128 x 128 (2048 x 4096, K = 14336; without `fill` the table took
-// 256 x 192 there).  128 x 64 is for 65 .. 128 tokens (128 x 12288, K = 4096: 13.9 us against 17.1 us for 64 x 64).
+// 256 x 192 there).  128 x 64 is between its neighbours for a few hundred tokens, and for 65 .. 128, one row of tiles where
+// 64 x 64 makes two.  At 128 x 12288, K = 4096 the table has the two even and takes 64 x 64: 11.9 us against 11.8 with the weights in
+// the caches, 16.8 against 14.1 with cold ones.
 constexpr int NUM_TILINGS = BASQ_FP6_TILINGS;
 const Tiling tilings[NUM_TILINGS] = {
     {256, 256, 1, 2.9, {10.7, 0.774}, {{6.1, 0.477}}, 0.31},
@@ -471,12 +476,15 @@ int cheapest_tiling(int64_t M, int64_t N, int K) {
 
 }  // namespace
 
-// Against the weight-streaming kernel (gemv_w4a4.hip), weights of both forms cold in memory, 17 .. 128 tokens, N 1024 .. 28672,
-// K 1024 .. 14336.  Above 64 tokens this kernel is the faster one everywhere (128 tokens x 28672, K = 8192: 36 against
-// 64 us; x 1024, K = 4096: 8.5 against 13.8 us): the streaming kernel reads every token's codes again per 32 to 64
-// channels.  Up to 32 it never is: its weights are half as large again.  Between, it is where many channels (more than
-// the streaming kernel gives eight waves a workgroup) meet a moderate weight matrix (64 x 12288, K = 8192: 19.5 against 24.5 us; x 28672, where both stream: 36 against 34 us).  The
-// streaming kernel's time is a fit (5 %); the margin covers this kernel's on so few tiles.
+// Against the weight-streaming kernel (gemv_w4a4.hip), weights of both forms cold in memory, 17 .. 128 tokens, N 1024 ..
+// 28672, K 1024 .. 14336.  Above 64 tokens this kernel is the faster one (128 tokens x 28672, K = 8192: 37 against 63 us; x
+// 1024, K = 4096: 8.4 against 12.7 us): the streaming kernel reads every token's codes again per 16 to 64 channels.  Not so
+// up to 80 tokens with long rows of 4096 .. 8192 channels (65 x 4096, K = 14336: 28 against 22 us; with the weights in the
+// caches 21 against 19; 80 x 4096, K = 8192: 17.7 against 15.0 and 13.8 against 14.4); the line is drawn without them, the
+// caches deciding.  Up to 32 it never is: its weights are half as large again.  Between, it is where many channels (more than
+// the streaming kernel gives eight waves a workgroup) meet a moderate weight matrix (64 x 12288, K = 8192: 18.5 against 24.5
+// us; x 28672, where both stream: 36 against 34 us).  The streaming kernel's time is a fit (5 %); the margin covers this
+// kernel's on so few tiles.
 bool gemm_fp6_beats_streaming(int64_t M, int32_t N, int32_t K) {
     if (M > 64) return true;
     if (M <= 32 || N <= 8192) return false;

@@ -8,12 +8,14 @@
 //
 // One LDS stage holds exactly one group (64 packed bytes per row), so a group's integer accumulator closes with
 // the stage: it is scaled into an fp32 accumulator (convert, two multiply-adds per element) and starts again
-// from zero.  On this chip fp32 vector multiply-adds do not run alongside MFMAs (a probe: 16 of them per
-// int8 MFMA halve the MFMA rate, 16 integer instructions cost nothing), so a group costs its MFMA time
-// plus its scaling time, and wave tiles are 64 x 64 (an integer and an fp32 accumulator set must fit the
-// registers).  Running the two waves of a SIMD in opposite phases, or interleaving the scaling of group g-1 with
-// the MFMAs of group g, was measured and is no faster for that reason.  This is the path for callers without the
-// fp6 operand forms; with them gemm_w4a4_grouped_fp6.hip computes the same bits in three quarters of the time.
+// from zero.  Wave tiles are 64 x 64 (an integer and an fp32 accumulator set must fit the registers).  A group's scaling
+// is 192 vector instructions per wave, 768 issue cycles, beside 512 cycles of MFMAs: vector instructions, fp32 ones too,
+// run alongside MFMAs of the same wave as long as they do not depend on them, but here they are the longer part.  Running
+// the two waves of a SIMD in opposite phases, or interleaving the scaling of group g-1 with the MFMAs of group g,
+// was measured and no faster.  This is the path for callers without the fp6 operand forms; with them
+// gemm_w4a4_grouped_fp6.hip, whose accumulators need no conversion and whose inner multiply-add is a matrix
+// instruction, computes the same bits in half the time (2048 x 12288, K = 4096: 213 and 105 us; 4096 x 28672, K = 8192: 1765
+// and 860).
 // Operands and the per-group constants (128 token records, 128 column sums) arrive by direct-to-LDS loads.
 #include "basq_internal.h"
 
