@@ -232,9 +232,14 @@ int launch_rotate_quant_generic(const RotateQuantArgs& a, hipStream_t s);
 // 5.5 us against codes and a repacking launch, 2048 tokens 13.8 -> 11.4, 32000 tokens 93.5 -> 87.7; K = 8192: 11.1 -> 8.8,
 // 21.3 -> 19.1, 214.7 -> 202.1).  Measured up to here, which is also where the per-token form needs staged tails.  With the
 // rotation written out as well it is even from 4096 tokens and the slower from 20000 on (31000 tokens: K = 4096 250 -> 271 us,
-// K = 8192 602 -> 636).
+// K = 8192 602 -> 636).  With K = 8192 a round of all waves is 2048 tokens (half of it with s^a, which is the longer kernel
+// either way), and the workgroups that write the fp6 form own contiguous ranges of a round per XCD, so that a last round of a
+// few hundred tokens is the first XCDs' alone: 2344 tokens 29.0 us against 26.2 in two launches, 2600 30.0 and 26.9, 5000 44.4 and
+// 40.3, 7000 56.5 and 51.5, but 2060 21.4 and 24.8, 3500 31.7 and 32.2.
 constexpr int64_t GROUPED_FP6_MAX_TOKENS = 32768, GROUPED_FP6_MAX_TOKENS_ROT_OUT = 16384;
 static bool groupwise_fp6_in_one_launch(const RotateQuantArgs& a) {
+    const int64_t last_round = a.M % 2048;
+    if (a.K == 8192 && !a.act_scale && a.M > 2048 && a.M < 8192 && last_round > 64 && last_round < 1200) return false;
     return a.M < (a.rot_out ? GROUPED_FP6_MAX_TOKENS_ROT_OUT : GROUPED_FP6_MAX_TOKENS) && rotate_quant_pow2_applicable(a);
 }
 

@@ -601,7 +601,8 @@ def test_streaming_product_where_its_workgroups_change(K, M, N):
         assert torch.equal(acc.cpu(), want)
 
 
-@pytest.mark.parametrize("K,M", [(4096, 33), (4096, 2051), (8192, 70), (8192, 1030)])
+@pytest.mark.parametrize("K,M", [(4096, 33), (4096, 2051), (8192, 70), (8192, 1030), (8192, 2051), (8192, 2344), (8192, 4099),
+                                 (4096, 7000)])
 @pytest.mark.parametrize("with_bias,with_scale", [(False, False), (True, True)])
 def test_fp6_form_of_groupwise_codes(K, M, with_bias, with_scale):
     """Full rotation with groups of 128: the fp6 form that the quantiser writes beside the codes is the repacked codes, and
@@ -849,3 +850,28 @@ def test_group_sums_bit_for_bit(K, kind):
                 read = read + Y[0].float()
             got.append(torch.stack(pieces))
         assert torch.equal(got[0], got[1]), f"token {m}: {int((got[0] != got[1]).sum())} pieces differ"
+
+
+@pytest.mark.parametrize("K,M", [(8192, 2049), (8192, 2344), (8192, 3999), (8192, 5000), (4096, 8192 + 8), (4096, 9000),
+                                 (4096, 33100), (8192, 33100)])
+def test_fp6_form_of_codes_in_a_partly_filled_last_round(K, M):
+    """The one-wave kernel with a last round of tokens that only some of its workgroups have: every token's codes and records
+    are those of the call without the fp6 form, and the fp6 form, its ragged last block included, is that of the codes."""
+    announce(f"last round K={K} M={M}")
+    X, bias, _ = gpu_inputs(M, K, seed=K + M, with_bias=True, with_scale=False)
+    Aq, meta, Aq2, meta2 = (torch.full(s, 0x5E, dtype=t, device=DEV) for s, t in 2 * [((M, K // 2), torch.uint8), ((M, 4), torch.int32)])
+    A6 = B.alloc_fp6_buffer(M, K, DEV)
+    B.basq_rotate_quant(X, K, bias, None, 0.9, 0.95, Aq, meta, Aq6=A6)
+    B.basq_rotate_quant(X, K, bias, None, 0.9, 0.95, Aq2, meta2)
+    assert torch.equal(Aq, Aq2) and torch.equal(meta, meta2)
+    check_fp6_copy(Aq, A6, K, row_blocks=[0, (M // 32) - 1])
+    if M % 32:                                              # the rows of the last, ragged block: through the product with unit weights
+        N = 32
+        W = torch.full((N, K // 2), 0x11, dtype=torch.uint8, device=DEV)
+        W6 = B.alloc_fp6_buffer(N, K, DEV)
+        B.basq_pack_fp6(W, W6)
+        one, zero = torch.ones(N, dtype=torch.bfloat16, device=DEV), torch.zeros(N, dtype=torch.bfloat16, device=DEV)
+        acc = torch.full((M, N), -1, dtype=torch.int32, device=DEV)
+        Y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+        B.basq_w4a4_gemm(Aq, meta, W, one, zero, torch.zeros(N, device=DEV), None, Y, acc, Aq6=A6, Wq6=W6)
+        assert torch.equal(acc, meta[:, 2:3].expand(M, N)), "row sums of the fp6 form"
