@@ -151,15 +151,14 @@ __device__ __forceinline__ void store_accumulators(const GemmArgs& a, int64_t m0
 
 // How the outputs leave.  With the non-temporal hint they don't displace the operands from the caches (4096 x
 // 28672, K = 8192: 406 us with, 420 without; 2048 x 12288, K = 4096 56 and 58; 333 x 4096 even) -- where rows are whole
-// 128-byte lines.  A line that two rows share is otherwise written in two parts (33204 x 14216, K = 256: 466 us with, 284
-// without; 5293 x 5840, K = 256 27 and 20; 2048 x 12304, K = 4096 62 and 56), which pays only where operands that are read many
-// times do not stay in the 256 MB beside the outputs (4096 x 28656, K = 8192 409 and 419; 4096 x 16432, K = 11008 348 and 370;
-// but 16384 x 9008, K = 4096 299 and 286, 3000 x 20016, K = 8192 229 and 223).  With a reader of Y right behind (a copy of
+// 128-byte lines.  A line that two rows share is otherwise written in two parts (every product into outputs that no cache holds
+// any more: 33204 x 14216, K = 256 467 us with, 262 without; 5293 x 5840, K = 256 29 and 23; 4096 x 9008, K = 2048 65 and 54),
+// which pays only where something else takes longer: where operands that are read many times do not stay in the 256 MB beside
+// the outputs (4096 x 28656, K = 8192 409 and 419; 4096 x 16432, K = 11008 348 and 370; but 16384 x 9008, K = 4096 308 and 294,
+// 3000 x 20016, K = 8192 even), and where the launch says so.  With a reader of Y right behind (a copy of
 // it timed with the product) the hint costs 0 to 3 % up to 50 MB of outputs (333 x 4096 14.0 and 13.8 us, 2048 x 12288 78.0 and 75.7)
 // and still gains 3 % at 4096 x 28672, K = 8192.
-// `hides_stores`: the kernel's other workgroups have enough to do meanwhile (the group-wise product from K = 4096 on, and with
-// half lines: 3000 x 20016, K = 4096 227 us with the hint and 236 without; 2048 x 12304, K = 512 31 and 26; 2048 x 12320, K = 1024
-// 36.6 and 37.3).
+// `hides_stores`: the launch's other work hides what shared lines cost with the hint (each launch has its rule and figures).
 StoreForm output_form(const GemmArgs& a, bool hides_stores) {
     const uintptr_t y = reinterpret_cast<uintptr_t>(a.Y);
     if ((a.ldy & 7) != 0 || (a.N & 7) != 0 || (y & 15) != 0) return StoreForm::any;

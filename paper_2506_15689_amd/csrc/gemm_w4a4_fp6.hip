@@ -416,8 +416,19 @@ int launch_fp6(const GemmArgs& a, hipStream_t s) {
     const int64_t resident = 256 * (MINOCC * 4 / (WAVES_M * WAVES_N));
     static_assert(MINOCC * 4 % (WAVES_M * WAVES_N) == 0 && MINOCC * 4 >= WAVES_M * WAVES_N, "whole workgroups per compute unit");
     const int64_t grid = tm * tn < resident ? tm * tn : resident;
+    // Rows that share lines (output_form(); every product into outputs that no cache holds any more, us with the hint and without).
+    // Half lines pay for it only where the stores bound the kernel: largest tiles, several rounds of them, few K-steps (8000 x
+    // 14240, K = 256 70 and 63; x 28640, K = 1024 even; elsewhere it gains up to 30 %: 998 x 16160, K = 1024).
+    // Odder rows do without unless what else there is to do is long against the stores: one round of 128-channel tiles (494 x 10544,
+    // K = 11008 42 and 50; 300 x 10768, K = 512 6.6 and 6.7; seven rounds, 1884 x 26416, K = 1024, 66 and 63), one or two of the
+    // wider ones with K >= 8192 (1776 x 12496 92 and 98; below, 1884 x 14224, K = 4096 67 and 64).  64-channel tiles: up to 4 %
+    // faster without.
+    const bool half_lines = (a.ldy & 31) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 63) == 0;
+    const bool hides_stores = half_lines  ? !(BM == 256 && BN == 256 && tm * tn > resident && a.K < 1024)
+                              : BN == 128 ? tm * tn <= resident
+                                          : BN > 128 && a.K >= 8192 && tm * tn <= 2 * resident;
     GemmArgs b = a;
-    b.store_form = output_form(a, false);
+    b.store_form = output_form(a, hides_stores);
     hipLaunchKernelGGL((gemm_w4a4_fp6_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, MINOCC>), dim3((unsigned)grid),
                        dim3(WAVES_M * WAVES_N * 64), 0, s, b, (int)tm, (int)tn);
     return check_hip(hipGetLastError(), "w4a4_gemm (fp6) launch");

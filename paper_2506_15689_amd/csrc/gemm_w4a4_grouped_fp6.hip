@@ -352,7 +352,10 @@ int launch_gemm_grouped_fp6(const GemmArgs& a, const int32_t* w_gsum, hipStream_
     const int64_t tn = ((int64_t)a.N + G6G_BN - 1) / G6G_BN;
     if (tm * tn > 0x7FFFFFFFll) return fail(BASQ_EINVAL, "w4a4_gemm_grouped: problem too large for one launch");
     GemmArgs b = a;
-    b.store_form = output_form(a, a.K >= 4096 || (a.ldy & 31) == 0);
+    // shared lines: with the hint from K = 1024 on (3000 x 20016, K = 4096 225 us with and 229 without; 1000 x 26416, K = 1024 42 and
+    // 46), with half lines (2048 x 12320, K = 512 25 and 29) and where all workgroups are in flight at once (1000 x 5008, K = 512
+    // 8.9 and 9.7); otherwise the stores bound it (3000 x 20016, K = 512 58 and 52)
+    b.store_form = output_form(a, a.K >= 1024 || (a.ldy & 31) == 0 || tm * tn <= 512);
     hipLaunchKernelGGL(gemm_w4a4_grouped_fp6_kernel, dim3((unsigned)(tm * tn)), dim3(G6G_THREADS), 0, s, b, w_gsum, (int)tm, (int)tn);
     return check_hip(hipGetLastError(), "w4a4_gemm_grouped (fp6) launch");
 }
