@@ -338,13 +338,21 @@ int basq_diag_mfma_f6(float* out, int32_t blocks, int32_t iters, void* stream);
  * checking and timing them one by one: the index of that tiling (0 .. BASQ_FP6_TILINGS - 1; -1 where basq_w4a4_gemm takes
  * another kernel though both fp6 operands are given), and the product on a given one, whatever M is (the bits do not
  * depend on it).  Arguments as in basq_w4a4_gemm; both fp6 operands are needed.
+ * The same for the split tilings, in which two groups of waves share a tile's channels: basq_diag_fp6_split_tiling is the
+ * index of the one that is taken instead of the tiling above (0 .. BASQ_FP6_SPLIT_TILINGS - 1), -1 where none is.
  */
 #define BASQ_FP6_TILINGS 6
+#define BASQ_FP6_SPLIT_TILINGS 6
 int basq_diag_fp6_tiling(int64_t M, int32_t K, int32_t N);
+int basq_diag_fp6_split_tiling(int64_t M, int32_t K, int32_t N);
 int basq_diag_w4a4_gemm_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
                             const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
                             void* Y, int64_t ldy, int32_t* acc_out,
                             const uint8_t* Aq6, const uint8_t* Wq6, void* stream);
+int basq_diag_w4a4_gemm_fp6_split(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
+                                  const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
+                                  void* Y, int64_t ldy, int32_t* acc_out,
+                                  const uint8_t* Aq6, const uint8_t* Wq6, void* stream);
 
 #ifdef __cplusplus
 }

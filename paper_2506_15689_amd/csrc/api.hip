@@ -267,19 +267,27 @@ int basq_w4a4_gemm_grouped(const uint8_t* Aq, const basq_tokmeta* meta, int64_t 
     return launch_gemm_grouped(g, w_gsum, static_cast<hipStream_t>(stream));
 }
 
-int basq_diag_fp6_tiling(int64_t M, int32_t K, int32_t N) {
+static bool shape_takes_fp6(int64_t M, int32_t K, int32_t N) {
     alignas(16) static const uint8_t given[16] = {};           // stands for both operands: only whether they are given counts
     GemmArgs g{};
     g.M = M; g.K = K; g.N = N; g.Aq6 = g.Wq6 = given;
-    if (K < 1 || N < 1 || !takes_fp6(g)) return -1;
-    return gemm_fp6_tiling(M, N, K);
+    return K >= 1 && N >= 1 && takes_fp6(g);
 }
 
-int basq_diag_w4a4_gemm_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
-                            const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
-                            void* Y, int64_t ldy, int32_t* acc_out,
-                            const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {
-    if (tiling < 0 || tiling >= BASQ_FP6_TILINGS) return fail(BASQ_EINVAL, "tiling must be 0 .. %d (got %d)", BASQ_FP6_TILINGS - 1, tiling);
+int basq_diag_fp6_tiling(int64_t M, int32_t K, int32_t N) {
+    return shape_takes_fp6(M, K, N) ? gemm_fp6_tiling(M, N, K) : -1;
+}
+
+int basq_diag_fp6_split_tiling(int64_t M, int32_t K, int32_t N) {
+    return shape_takes_fp6(M, K, N) ? gemm_fp6_split_tiling(M, N, K) : -1;
+}
+
+static int run_fp6_tiling(int32_t tiling, int32_t tilings, int (*launch)(int, const GemmArgs&, hipStream_t),
+                          const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
+                          const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
+                          void* Y, int64_t ldy, int32_t* acc_out,
+                          const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {
+    if (tiling < 0 || tiling >= tilings) return fail(BASQ_EINVAL, "tiling must be 0 .. %d (got %d)", tilings - 1, tiling);
     if (!Aq6 || !Wq6) return fail(BASQ_EINVAL, "an fp6 operand is null");
     // (the 4-bit codes are not read: the fp6 operands stand in for them in the checks)
     int rc = validate_gemm(Aq6, meta, M, K, Wq6, N, BASQ_W_CANONICAL, w_scale, w_zero, w_sum, Y, ldy);
@@ -290,7 +298,23 @@ int basq_diag_w4a4_gemm_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M,
                w_sum, out_bias, static_cast<uint16_t*>(Y), ldy, acc_out, Aq6, Wq6, BASQ_W_CANONICAL};
     if (M == 0) return BASQ_OK;
     if (!gemm_fp6_applicable(g)) return fail(BASQ_EUNSUPPORTED, "no fp6 product of this shape");
-    return launch_gemm_fp6_tiling(tiling, g, static_cast<hipStream_t>(stream));
+    return launch(tiling, g, static_cast<hipStream_t>(stream));
+}
+
+int basq_diag_w4a4_gemm_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
+                            const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
+                            void* Y, int64_t ldy, int32_t* acc_out,
+                            const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {
+    return run_fp6_tiling(tiling, BASQ_FP6_TILINGS, launch_gemm_fp6_tiling, meta, M, K, N, w_scale, w_zero, w_sum, out_bias, Y, ldy,
+                          acc_out, Aq6, Wq6, stream);
+}
+
+int basq_diag_w4a4_gemm_fp6_split(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
+                                  const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
+                                  void* Y, int64_t ldy, int32_t* acc_out,
+                                  const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {
+    return run_fp6_tiling(tiling, BASQ_FP6_SPLIT_TILINGS, launch_gemm_fp6_split_tiling, meta, M, K, N, w_scale, w_zero, w_sum, out_bias,
+                          Y, ldy, acc_out, Aq6, Wq6, stream);
 }
 
 int basq_group_colsums(const uint8_t* Wq, int32_t N, int32_t K, int32_t group_size, int32_t* w_gsum, void* stream) {

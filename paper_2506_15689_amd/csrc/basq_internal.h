@@ -93,6 +93,8 @@ bool gemm_fp6_applicable(const GemmArgs& a);
 bool gemm_fp6_beats_streaming(int64_t M, int32_t N, int32_t K);   // ... the weight-streaming kernel, for M <= GEMV_MAX_TOKENS
 int gemm_fp6_tiling(int64_t M, int32_t N, int32_t K);              // which of its tilings it takes, 0 .. BASQ_FP6_TILINGS - 1
 int launch_gemm_fp6_tiling(int tiling, const GemmArgs& a, hipStream_t s);
+int gemm_fp6_split_tiling(int64_t M, int32_t N, int32_t K);        // the split tiling it takes instead, or -1
+int launch_gemm_fp6_split_tiling(int tiling, const GemmArgs& a, hipStream_t s);
 int launch_gemm_fp6(const GemmArgs& a, hipStream_t s);
 // INT4 codes [rows, K/2] -> fp6 operand form (fp6_pack.hip)
 int launch_pack_fp6(const uint8_t* codes, int64_t rows, int32_t K, uint8_t* out6, hipStream_t s);

@@ -52,13 +52,14 @@ __device__ __forceinline__ void wait_stages_and_barrier(int n) {
 #define G6_GROUP_M 4
 #endif
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MINOCC>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_kernel(GemmArgs a, int tiles_m, int tiles_n) {
+template <int BM, int BN, int WAVES_M, int WAVES_N, int KGROUPS, int STAGES, int MINOCC>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm_w4a4_fp6_kernel(GemmArgs a, int tiles_m, int tiles_n) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses device-only buffer-resource types; the host pass only needs the stub
-    constexpr int WAVES = WAVES_M * WAVES_N;
-    constexpr int THREADS = WAVES * 64;
+    constexpr int WAVES = WAVES_M * WAVES_N;                  // of one K group
+    constexpr int THREADS = WAVES * KGROUPS * 64;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int TM = WM / 32, TN = WN / 32;
+    constexpr int OWN = (TM + KGROUPS - 1) / KGROUPS;         // row blocks of its wave tile that a wave finishes
     constexpr int ROWS = BM + BN;
     constexpr int STAGE_BYTES = ROWS * CHUNK;
     constexpr int PIECES = STAGE_BYTES / 1024;                // 1 KB pieces of a stage, one wave-load each
@@ -70,20 +71,31 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
     static_assert(STAGES >= 3 && LOADS * (STAGES - 2) < 64, "the wait counter counts to 63");
     static_assert(ROWS * 16 <= STAGE_BYTES, "the epilogue constants live in the last stage");
+    static_assert(KGROUPS == 1 || (BM * BN * 4 + ROWS * 16 <= STAGES * STAGE_BYTES && TM % OWN == 0), "K groups exchange their sums through their rings");
 
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGES * STAGE_BYTES];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KGROUPS * STAGES * STAGE_BYTES];
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = (tid >> 6) % WAVES;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int swave = __builtin_amdgcn_readfirstlane(wave);
-    const int ksteps = a.K / 128;
+    // K groups: group g of the workgroup's waves takes a contiguous part of the chunks through a ring of its own.  All take
+    // the same number of steps, since they meet at the barriers; the chunks left over by the division go to the last
+    // groups, and a group that has one fewer (`idle_last`) leaves the last step's MFMAs out (what it has loaded there is
+    // its successor's first chunk).
+    const int kgroup = KGROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 6) / WAVES);
+    const int chunks = a.K / 128;
+    const int ksteps = KGROUPS == 1 ? chunks : (chunks + KGROUPS - 1) / KGROUPS;
+    const int short_groups = KGROUPS == 1 ? 0 : ksteps * KGROUPS - chunks;             // groups 0 .. short_groups - 1
+    const bool idle_last = KGROUPS > 1 && kgroup < short_groups;
+    const int chunk0 = KGROUPS == 1 ? 0 : kgroup * ksteps - (kgroup < short_groups ? kgroup : short_groups);
+    uint8_t* const lds = lds_all + kgroup * (STAGES * STAGE_BYTES);                    // this group's ring
     int store_form = (int)a.store_form;                       // fetched here: at the end it would be a memory latency
     asm volatile("" : "+s"(store_form));
     const int rb_a = (int)((a.M + 31) >> 5), rb_w = (a.N + 31) >> 5;   // 32-row blocks per chunk of K
     const unsigned a_step = (unsigned)rb_a * BLOCK, w_step = (unsigned)rb_w * BLOCK;   // bytes from one chunk of K to the next
-    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.Aq6), 0, (int)(a_step * (unsigned)ksteps), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.Wq6), 0, (int)(w_step * (unsigned)ksteps), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.Aq6), 0, (int)(a_step * (unsigned)chunks), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.Wq6), 0, (int)(w_step * (unsigned)chunks), 0x00020000);
 
     // ---- tile order (XCD-aware: workgroups congruent mod 8 run on one XCD; the tiles a workgroup takes,
     // blockIdx.x + i * gridDim.x, stay congruent when the grid is a multiple of 8 and walk a compact band)
@@ -144,12 +156,13 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         if (PIECES % WAVES != 0 && swave < PIECES % WAVES) wait_stages_and_barrier<LOADS, STAGES - 2>(ahead);
         else wait_stages_and_barrier<MIN_LOADS, STAGES - 2>(ahead);
     };
+    const unsigned kbase_a = (unsigned)chunk0 * a_step, kbase_w = (unsigned)chunk0 * w_step;
     auto issue_prologue = [&]() {
 #pragma unroll
         for (int s = 0; s < STAGES - 1; ++s)
             if (s < ksteps) {
 #pragma unroll
-                for (int i = 0; i < LOADS; ++i) issue_one(s * STAGE_BYTES, s * a_step, s * w_step, i);
+                for (int i = 0; i < LOADS; ++i) issue_one(s * STAGE_BYTES, kbase_a + s * a_step, kbase_w + s * w_step, i);
             }
     };
 
@@ -178,7 +191,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
     // Epilogue constants, one 16-byte record per row and column of the tile: in the last stage of the ring, which the next
     // tile's first loads do not touch.  Kept and read as integers: the compiler puts a wait for every direct-to-LDS load
     // in flight in front of a float-typed LDS read.
-    v4i* lrow_par = reinterpret_cast<v4i*>(lds + (STAGES - 1) * STAGE_BYTES);
+    // (with K groups, which take one tile, behind the sums that go through the first group's ring)
+    v4i* lrow_par = reinterpret_cast<v4i*>(lds_all + (KGROUPS == 1 ? (STAGES - 1) * STAGE_BYTES : STAGES * STAGE_BYTES - ROWS * 16));
     v4i* lcol_par = lrow_par + BM;
     // The raw values of one record per thread (rows first), requested a tile ahead of their use and converted only there:
     // a conversion behind the loads would wait for them.
@@ -304,7 +318,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         // of reads (a multiply chain unless it is a power of two) costs a tenth of a step.
         int prev = (STAGES - 1) * STAGE_BYTES, cur = 0, next = STAGE_BYTES;      // stages of steps ks - 1, ks, ks + 1
         asm volatile("" : "+s"(prev), "+s"(cur), "+s"(next));    // opaque: no addresses of their own for a tile's first steps
-        unsigned koff_a = (STAGES - 1) * a_step, koff_w = (STAGES - 1) * w_step;   // chunk ks + STAGES - 1
+        unsigned koff_a = kbase_a + (STAGES - 1) * a_step, koff_w = kbase_w + (STAGES - 1) * w_step;   // the group's chunk ks + STAGES - 1
         auto k_step = [&](int ks, auto loads0, auto loads1, auto has_next, auto next_landed) {
             // kb = 0, reading kb = 1 of this stage ahead
             half(0, lds + cur, 1, 1, std::true_type{}, prev, koff_a, koff_w, SPLIT, loads0);
@@ -338,14 +352,34 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         }
         if (ks + STAGES - 1 < ksteps) { k_step(ks, yes, no, yes, no); ++ks; }
         for (; ks + 1 < ksteps; ++ks) k_step(ks, no, no, yes, no);
-        k_step(ks, no, no, no, no);
+        if (!idle_last) k_step(ks, no, no, no, no);
+        else wait_stages(0);                              // (the barrier of that step)
         // every wave has passed the last step's barrier, after which nothing reads the ring: put this tile's constants there
         // and request the next tile's first stages, so that their latency hides behind this tile's epilogue
         if (tid < BM) par[2] = __float_as_int((float)par[2]);
         else { par[0] <<= 16; par[1] <<= 16; }                    // bf16 -> fp32
         if (tid < ROWS) lrow_par[tid] = par;
+        // K groups: a wave finishes the row blocks of its share, OWN of them, and hands its sums of the others to the waves
+        // of the same position in the other groups, through its own ring.  (All sums are exact: any order gives the same bits.)
+        const int own0 = kgroup * OWN;
+        auto xch_at = [&](int i, int j, int r) { return ((((wave * TM + i) * TN + j) * 4 + r) * 64 + lane) * 16; };
+        if constexpr (KGROUPS > 1) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                if (i / OWN != kgroup) {
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            v4i v;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] = __float_as_int(acc[i][j][4 * r + e]);
+                            *reinterpret_cast<v4i*>(lds + xch_at(i, j, r)) = v;
+                        }
+                }
+        }
         const int next_pid = pid + gridDim.x;
-        const bool more = next_pid < total;
+        const bool more = KGROUPS == 1 && next_pid < total;
         int next_m = 0, next_n = 0;
         if (more) {
             tile_of(next_pid, next_m, next_n);
@@ -356,25 +390,50 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
 
         // ---- epilogue (which output an accumulator register holds: gemm_fp6_store.h)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // LDS only: the next tile's loads stay in flight
+        if constexpr (KGROUPS > 1) {
+            if (own0 >= TM) return;                               // fewer row blocks than groups
+            // the first OWN blocks of `acc` become the sums of this wave's share
+#pragma unroll
+            for (int i = OWN; i < TM; ++i)
+                if (i / OWN == kgroup)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i % OWN][j] = acc[i][j];
+#pragma unroll
+            for (int o = 1; o < KGROUPS; ++o) {
+                const uint8_t* ring = lds_all + (kgroup + o < KGROUPS ? kgroup + o : kgroup + o - KGROUPS) * (STAGES * STAGE_BYTES);
+#pragma unroll
+                for (int i = 0; i < OWN; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const v4i v = *reinterpret_cast<const v4i*>(ring + xch_at(own0 + i, j, r));
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[i][j][4 * r + e] += __int_as_float(v[e]);
+                        }
+            }
+        }
+        const int row0 = wm * WM + own0 * 32;                     // of the rows this wave finishes
         // (re)derived per tile from an opaque copy of the lane index: everything computed from it below
         // would otherwise be hoisted out of the tile loop and held in registers across the main loop
         int elane = lane;
         asm volatile("" : "+v"(elane));
         const int tok = elane & 31, ehalf = elane >> 5;
-        v4i rp[TM];                                               // scale, lower bound, row sum of this lane's tokens
+        v4i rp[OWN];                                              // scale, lower bound, row sum of this lane's tokens
 #pragma unroll
-        for (int i = 0; i < TM; ++i) rp[i] = lrow_par[wm * WM + i * 32 + tok];
+        for (int i = 0; i < OWN; ++i) rp[i] = lrow_par[row0 + i * 32 + tok];
         auto dequant = [&](float s64, v4i row, v4i col) {
             // 64 * S is the integer accumulator, exactly
             const float t = fmaf(64.0f, s64, -(__int_as_float(col[1]) * __int_as_float(row[2])));
             return fmaf(__int_as_float(row[0]) * __int_as_float(col[0]), t,
                         fmaf(__int_as_float(row[1]), __int_as_float(col[2]), __int_as_float(col[3])));
         };
-        if (a.acc_out) store_accumulators<TM, TN, BM>(a, m0, n0, wm * WM, elane, acc, col_block);
+        auto& sums = reinterpret_cast<v16f(&)[OWN][TN]>(acc);
+        if (a.acc_out) store_accumulators<OWN, TN, BM>(a, m0, n0, row0, elane, sums, col_block);
         typedef float f2 __attribute__((ext_vector_type(2)));
         typedef __bf16 b2 __attribute__((ext_vector_type(2)));
         // first every output into registers (they take the accumulators' place) ...
-        unsigned outv[TM][TN][4][2];                          // [..][q][p]: channels 8q + 4*ehalf + 2p, +1
+        unsigned outv[OWN][TN][4][2];                         // [..][q][p]: channels 8q + 4*ehalf + 2p, +1
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
 #pragma unroll
@@ -383,7 +442,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
 #pragma unroll
                 for (int e = 0; e < 4; ++e) cp[e] = lcol_par[col_block(j) * 32 + 8 * q + 4 * ehalf + e];
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
+                for (int i = 0; i < OWN; ++i) {
 #pragma unroll
                     for (int p = 0; p < 2; ++p) {
                         const float y0 = dequant(acc[i][j][4 * q + 2 * p], rp[i], cp[2 * p]);
@@ -399,23 +458,25 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, MINOCC) void gemm_w4a4_fp6_
         // landed), and only then send the stores: a wait placed after them would have to wait for
         // the stores too, the counter being one and the same
         if (more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        store_outputs<TM, TN, BM>(a, (StoreForm)store_form, m0, n0, wm * WM, elane, outv, col_block);
+        store_outputs<OWN, TN, BM>(a, (StoreForm)store_form, m0, n0, row0, elane, outv, col_block);
         if (!more) break;
         pid = next_pid; tile_m = next_m; tile_n = next_n;
     }
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int MINOCC>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int KGROUPS, int STAGES, int MINOCC>
 int launch_fp6(const GemmArgs& a, hipStream_t s) {
     const int64_t tm = (a.M + BM - 1) / BM;
     const int64_t tn = ((int64_t)a.N + BN - 1) / BN;
     if (tm * tn > 0x7FFFFFFFll) return fail(BASQ_EINVAL, "w4a4_gemm: problem too large for one launch");
     // persistent workgroups: as many as the chip's 256 compute units hold at once (MINOCC waves per
     // SIMD), each walking the tiles blockIdx.x, blockIdx.x + gridDim.x, ...
-    const int64_t resident = 256 * (MINOCC * 4 / (WAVES_M * WAVES_N));
-    static_assert(MINOCC * 4 % (WAVES_M * WAVES_N) == 0 && MINOCC * 4 >= WAVES_M * WAVES_N, "whole workgroups per compute unit");
-    const int64_t grid = tm * tn < resident ? tm * tn : resident;
+    // (with K groups each takes one tile)
+    constexpr int WAVES = WAVES_M * WAVES_N * KGROUPS;
+    const int64_t resident = 256 * (MINOCC * 4 / WAVES);
+    static_assert(KGROUPS > 1 || (MINOCC * 4 % WAVES == 0 && MINOCC * 4 >= WAVES), "whole workgroups per compute unit");
+    const int64_t grid = KGROUPS > 1 || tm * tn < resident ? tm * tn : resident;
     // Rows that share lines (output_form(); every product into outputs that no cache holds any more, us with the hint and without).
     // Half lines pay for it only where the stores bound the kernel: largest tiles, several rounds of them, few K-steps (8000 x
     // 14240, K = 256 70 and 63; x 28640, K = 1024 even; elsewhere it gains up to 30 %: 998 x 16160, K = 1024).
@@ -429,8 +490,8 @@ int launch_fp6(const GemmArgs& a, hipStream_t s) {
                                           : BN > 128 && a.K >= 8192 && tm * tn <= 2 * resident;
     GemmArgs b = a;
     b.store_form = output_form(a, hides_stores);
-    hipLaunchKernelGGL((gemm_w4a4_fp6_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, MINOCC>), dim3((unsigned)grid),
-                       dim3(WAVES_M * WAVES_N * 64), 0, s, b, (int)tm, (int)tn);
+    hipLaunchKernelGGL((gemm_w4a4_fp6_kernel<BM, BN, WAVES_M, WAVES_N, KGROUPS, STAGES, MINOCC>), dim3((unsigned)grid),
+                       dim3(WAVES * 64), 0, s, b, (int)tm, (int)tn);
     return check_hip(hipGetLastError(), "w4a4_gemm (fp6) launch");
 }
 
@@ -473,6 +534,25 @@ const Tiling tilings[NUM_TILINGS] = {
     {128, 64, 2, 2.5, {2.2, 0.406}, {{2.0, 0.209}, {2.4, 0.316}}, 0.068},
     {64, 64, 3, 2.9, {1.3, 0.40}, {{0.7, 0.148}, {1.3, 0.221}, {1.7, 0.339}}, 0.043},
 };
+// The split tilings: two groups of waves share a tile's channels (KGROUPS = 2), each on a ring of its own; one workgroup a
+// compute unit.  Where every compute unit has one tile at most, its time is the chain of its K-steps -- latency of the loads,
+// the barrier, the fragment reads -- and two chains of half the length run side by side (same tile, one group against two, K =
+// 4096, weights in the caches: 64 x 64 0.86 of the time on up to 64 compute units, 0.91 on up to 256; 128 x 64 0.81 and 0.89; 128 x
+// 128 0.88 and 1.03, with cold weights 0.90 and 1.0; K >= 8192 0.78 .. 0.99; K = 1024 even; 333 x 4096 x 4096 11.3 -> 9.5 us).  With a
+// second round of tiles they are slower, 1.05 .. 1.6: two one-group workgroups on a compute unit are two chains as well, and
+// overlap their ends.  Hence tiles <= 256 and K >= 2048.  Cost: base + (step + fill * share of the chip) * K / 128, least
+// squares over 330 shapes (33 .. 4096 tokens) with most weight where a tiling is near the fastest, 4-10 %.  The choice over
+// both tables is 0.9 % off the fastest in the mean with weights in the caches and 1.4 % with cold ones, 7.0 and 6.4 % faster than
+// without these; five shapes of the 330 became slower by more than 2 %, the worst by 6 % (warm only).
+struct SplitTiling {
+    int bm, bn;
+    double base, step, fill;
+};
+constexpr int NUM_SPLIT_TILINGS = BASQ_FP6_SPLIT_TILINGS;
+const SplitTiling split_tilings[NUM_SPLIT_TILINGS] = {
+    {64, 64, 3.65, 0.103, 0.029},  {96, 64, 4.34, 0.144, 0.026}, {128, 64, 3.96, 0.146, 0.049},
+    {128, 128, 5.07, 0.155, 0.161}, {96, 96, 4.88, 0.136, 0.080}, {160, 96, 5.70, 0.151, 0.156},
+};
 int cheapest_tiling(int64_t M, int64_t N, int K) {
     // Few K-steps and many rounds are bound by the outputs, which the largest tiles write fastest and the table, fitted on at
     // most seven rounds and from K = 1024 on, prices by their first rounds (23522 x 22162, K = 512: 128 x 128 519 us, 256 x
@@ -482,6 +562,25 @@ int cheapest_tiling(int64_t M, int64_t N, int K) {
     int best = 0;
     for (int i = 1; i < NUM_TILINGS; ++i)
         if (tiling_cost(tilings[i], M, N, K) < tiling_cost(tilings[best], M, N, K)) best = i;
+    return best;
+}
+// The split tiling to take instead of the cheapest of the others, -1 if there is none.
+int cheapest_split_tiling(int64_t M, int64_t N, int K) {
+    if (K < 2048) return -1;
+    const Tiling& plain = tilings[cheapest_tiling(M, N, K)];
+    int best = -1;
+    double us = tiling_cost(plain, M, N, K);
+    // Between the two forms of one tile the tables are even on a full chip; with long rows the split form is the faster one there
+    // too (1021 x 11008 x 4096: 33.7 -> 31.7 us with the weights in the caches, 128 x 128 on 190 .. 256 compute units, K > 8192,
+    // 0.91 .. 1.03 with them, 0.86 .. 0.92 cold).
+    if (K > 8192 && plain.bm <= 128 && ((M + plain.bm - 1) / plain.bm) * ((N + plain.bn - 1) / plain.bn) <= 256) us = 1e30;
+    for (int i = 0; i < NUM_SPLIT_TILINGS; ++i) {
+        const SplitTiling& t = split_tilings[i];
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (tiles > 256) continue;
+        const double c = t.base + (t.step + t.fill * (double)tiles / 256) * (K / 128);
+        if (c < us) { us = c; best = i; }
+    }
     return best;
 }
 
@@ -518,16 +617,31 @@ int gemm_fp6_tiling(int64_t M, int32_t N, int32_t K) { return cheapest_tiling(M,
 
 int launch_gemm_fp6_tiling(int tiling, const GemmArgs& a, hipStream_t s) {
     switch (tiling) {
-        case 0: return launch_fp6<256, 256, 2, 4, 3, 2>(a, s);
-        case 1: return launch_fp6<256, 192, 4, 2, 3, 2>(a, s);
-        case 2: return launch_fp6<256, 128, 4, 2, 4, 2>(a, s);
-        case 3: return launch_fp6<128, 128, 2, 2, 3, 2>(a, s);
-        case 4: return launch_fp6<128, 64, 4, 1, 4, 2>(a, s);
-        default: return launch_fp6<64, 64, 2, 2, 4, 3>(a, s);
+        case 0: return launch_fp6<256, 256, 2, 4, 1, 3, 2>(a, s);
+        case 1: return launch_fp6<256, 192, 4, 2, 1, 3, 2>(a, s);
+        case 2: return launch_fp6<256, 128, 4, 2, 1, 4, 2>(a, s);
+        case 3: return launch_fp6<128, 128, 2, 2, 1, 3, 2>(a, s);
+        case 4: return launch_fp6<128, 64, 4, 1, 1, 4, 2>(a, s);
+        default: return launch_fp6<64, 64, 2, 2, 1, 4, 3>(a, s);
+    }
+}
+
+int gemm_fp6_split_tiling(int64_t M, int32_t N, int32_t K) { return cheapest_split_tiling(M, N, K); }
+
+int launch_gemm_fp6_split_tiling(int tiling, const GemmArgs& a, hipStream_t s) {
+    switch (tiling) {
+        case 0: return launch_fp6<64, 64, 2, 2, 2, 4, 2>(a, s);
+        case 1: return launch_fp6<96, 64, 3, 2, 2, 4, 3>(a, s);
+        case 2: return launch_fp6<128, 64, 2, 2, 2, 4, 2>(a, s);
+        case 3: return launch_fp6<128, 128, 2, 2, 2, 3, 2>(a, s);
+        case 4: return launch_fp6<96, 96, 3, 1, 2, 4, 2>(a, s);
+        default: return launch_fp6<160, 96, 5, 1, 2, 3, 3>(a, s);
     }
 }
 
 int launch_gemm_fp6(const GemmArgs& a, hipStream_t s) {
+    const int split = cheapest_split_tiling(a.M, a.N, a.K);
+    if (split >= 0) return launch_gemm_fp6_split_tiling(split, a, s);
     return launch_gemm_fp6_tiling(cheapest_tiling(a.M, a.N, a.K), a, s);
 }
 

@@ -72,6 +72,18 @@ def test_fp6_tilings_by_name(lib):
     assert call(0, K=32768 + 128) == B.BASQ_EUNSUPPORTED
 
 
+def test_fp6_split_tilings_by_name(lib):
+    """Which split tiling a shape takes, and that a product by name is refused where it could not run."""
+    T = B.basq_diag_fp6_split_tiling
+    assert T(333, 4096, 4096) in (1, 2) and T(1021, 11008, 4096) == 3 and T(61, 4096, 12288) == 0
+    # many tiles, few K-steps with many rounds, and shapes whose product runs elsewhere
+    assert T(4096, 8192, 28672) == T(2048, 4096, 12288) == T(33204, 256, 14216) == T(32, 4096, 28672) == T(0, 4096, 4096) == -1
+    call = lambda t, K=256, a=FAKE: lib.basq_diag_w4a4_gemm_fp6_split(
+        t, FAKE, 64, K, 64, FAKE, FAKE, FAKE, None, FAKE, 64, None, a, FAKE, None)
+    assert call(-1) == call(B.FP6_SPLIT_TILINGS) == call(0, a=None) == call(0, K=192) == B.BASQ_EINVAL
+    assert call(0, K=32768 + 128) == B.BASQ_EUNSUPPORTED
+
+
 FAKE = ctypes.c_void_p(0x1000)      # aligned, never dereferenced: validation fails first
 
 

@@ -708,6 +708,33 @@ def test_every_tiling_of_the_fp6_product(tiling, K):
         assert bool((buf == -7.0).all()), "wrote outside the output"
 
 
+SPLIT_TILES = [(64, 64), (96, 64), (128, 64), (128, 128), (96, 96), (160, 96)]
+
+
+@pytest.mark.parametrize("K", [128, 256, 384, 640, 896, 1024, 2176])
+@pytest.mark.parametrize("tiling", range(B.FP6_SPLIT_TILINGS))
+def test_every_split_tiling_of_the_fp6_product(tiling, K):
+    """The tilings in which two groups of waves share a tile's channels, by name: one chunk (the first group has none), odd and
+    even numbers of them around the depth of a group's ring, ragged tiles, every kind of output row, more tiles than compute
+    units: the bits of the kernels without the fp6 operands (exact sums, the same epilogue), nothing beside the output."""
+    bm, bn = SPLIT_TILES[tiling]
+    shapes = [(1, 1, 1, 0), (33, 72, 72, 0), (bm, bn, bn, 0), (bm + 1, bn - 1, bn, 8), (2 * bm - 31, 3 * bn + 32, 3 * bn + 40, 0),
+              (131, 333, 333, 1), (257, 514, 516, 2), (9 * bm - 45, 32 * bn + 8, 32 * bn + 8, 0)]
+    for M, N, ldy, offset in shapes:
+        announce(f"split tiling {tiling} M={M} N={N} K={K} ldy={ldy} offset={offset}")
+        A, A6, meta, W, W6, sw, zp, ws, c = random_product(M, N, K, seed=M + N)
+        buf, Y = output_view(M, N, ldy, offset)
+        acc = torch.full((M, N), -1, dtype=torch.int32, device=DEV)
+        B.basq_diag_w4a4_gemm_fp6(tiling, meta, K, sw, zp, ws, c, Y, acc, A6, W6, split=True)
+        want = torch.full((M, N), -7.0, dtype=torch.bfloat16, device=DEV)
+        want_acc = torch.full((M, N), -2, dtype=torch.int32, device=DEV)
+        B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, want, want_acc)
+        assert torch.equal(Y.contiguous().view(torch.int16), want.view(torch.int16))
+        assert torch.equal(acc, want_acc)
+        Y.fill_(-7.0)
+        assert bool((buf == -7.0).all()), "wrote outside the output"
+
+
 @pytest.mark.parametrize("M,K,rot,N,product", [
     (61, 4096, 4096, 12288, "fp6"), (46, 4096, 4096, 12288, "stream"), (47, 4096, 4096, 12288, "fp6"),    # the rule's edge
     (61, 4096, 4096, 8192, "stream"), (42, 4096, 4096, 8208, "fp6"), (39, 1024, 1024, 12288, "fp6"),
