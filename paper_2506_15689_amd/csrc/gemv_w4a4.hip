@@ -14,6 +14,8 @@
 // load needs contiguously, in lane order: 4 KB contiguous per workgroup step.
 #include "basq_internal.h"
 
+#include <type_traits>
+
 namespace basq {
 
 namespace {
@@ -21,7 +23,145 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int GV_ROWS = 16;                         // output channels per tile
-constexpr int GV_OUT = 256;                         // the epilogue maps one thread to each of a tile's 16 x 16 outputs
+
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+
+// The end of the kernel, a workgroup's sums to outputs, in two forms.  request() fetches the epilogue's constants and token
+// records in front of the weight stream, so that their latency overlaps it: without a branch (clamped indices) and as raw bits
+// -- a conversion there would wait for them before the first weight load is issued, and a record fetched in the epilogue is a
+// memory latency at the very end.  finish() takes the waves' accumulators: register r of lane l is weight row 4*(l/16) + r,
+// token l%16 of its tile.
+//
+// Up to 16 tokens, one or two tiles: the sums meet by LDS atomics (integer adds: any order gives the same bits) and a thread
+// finishes one output of each tile.  (As below, one wave would finish them all: 4 x 8192 x 28672 24.9 -> 25.9 us.)
+template <int WAVES, int TILES>
+struct GvFewTiles {
+    static constexpr int NT = TILES, LDS_INTS = NT * 256;
+    int orow, otok, M;
+    uint16_t sw_bits[TILES], zp_bits[TILES];
+    float ws[TILES], cb[TILES];
+    basq_tokmeta mt;
+    __device__ __forceinline__ void request(const GemmArgs& a, int n0, int tid, int* part) {
+        static_assert(WAVES * 64 == 256, "a thread per output of a tile");
+#pragma unroll
+        for (int i = 0; i < NT; ++i) part[i * 256 + tid] = 0;
+        orow = tid & 15; otok = tid >> 4; M = (int)a.M;
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            const int on = n0 + GV_ROWS * t + orow;
+            const int on_c = on < a.N ? on : a.N - 1;
+            sw_bits[t] = a.w_scale[on_c];
+            zp_bits[t] = a.w_zero[on_c];
+            ws[t] = a.w_sum[on_c];
+            cb[t] = 0.0f;
+            if (a.out_bias) cb[t] = a.out_bias[on_c];
+        }
+        mt = a.meta[otok < M ? otok : M - 1];
+    }
+    __device__ __forceinline__ void finish(const GemmArgs& a, int n0, int lane, const v4i (&acc)[NT], int* part) const {
+        __syncthreads();                                // every wave has zeroed its share of `part`
+#pragma unroll
+        for (int at = 0; at < NT; ++at)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) atomicAdd(&part[at * 256 + (4 * (lane >> 4) + r) * 16 + (lane & 15)], acc[at][r]);
+        __syncthreads();
+        if (otok >= M) return;
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            const int on = n0 + GV_ROWS * t + orow;
+            if (on >= a.N) continue;
+            const int av = part[t * 256 + orow * 16 + otok];
+            const float sw = bf16_to_f32(sw_bits[t]), zp = bf16_to_f32(zp_bits[t]);
+            const float tv = (float)av - zp * (float)mt.rowsum;
+            const float y = fmaf(mt.scale * sw, tv, fmaf(mt.lo, ws[t], cb[t]));
+            a.Y[(int64_t)otok * a.ldy + on] = f32_to_bf16(y);
+            if (a.acc_out) a.acc_out[(int64_t)otok * a.N + on] = av;
+        }
+    }
+};
+
+// More tokens: every wave puts its sums down and finishes the tiles wave, wave + WAVES, .., a lane four adjacent channels of one
+// token: 8-byte stores and vector loads of the constants.  (A thread per output, with atomics, 2-byte stores and a rounding in
+// software, spent 1300 cycles here on four tiles and 2700 on eight, 540 and 1300 as built, and 1700 instead of 1200 on the
+// constants' requests: 61 x 4096 x 12288 13.8 -> 13.2 us, 64 x 8192 x 8192 14.9 -> 13.6, 17 x 4096 x 4096 4.95 -> 4.74.)
+template <int WAVES, int TILES, int TT>
+struct GvManyTiles {
+    static constexpr int NT = TILES * TT, OWN = (NT + WAVES - 1) / WAVES, LDS_INTS = WAVES * NT * 256;
+    int wave, M;
+    bool whole;                                         // every channel of the workgroup exists
+    uint2 sw_bits[OWN], zp_bits[OWN];
+    float4 ws[OWN], cb[OWN];
+    basq_tokmeta mts[OWN];
+    __device__ __forceinline__ void request(const GemmArgs& a, int n0, int tid, int*) {
+        const int lane = tid & 63, row = lane & 15, sub = lane >> 4;
+        wave = __builtin_amdgcn_readfirstlane(tid >> 6); M = (int)a.M;
+        whole = n0 + GV_ROWS * TILES <= a.N;
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            const int at = wave + o * WAVES < NT ? wave + o * WAVES : NT - 1;      // (a wave without an o-th tile: in bounds)
+            const int tok = 16 * (at % TT) + row, on = n0 + GV_ROWS * (at / TT) + 4 * sub;
+            cb[o] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (whole) {
+                __builtin_memcpy(&sw_bits[o], a.w_scale + on, 8);
+                __builtin_memcpy(&zp_bits[o], a.w_zero + on, 8);
+                __builtin_memcpy(&ws[o], a.w_sum + on, 16);
+                if (a.out_bias) __builtin_memcpy(&cb[o], a.out_bias + on, 16);
+            } else {
+                int c[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) c[r] = on + r < a.N ? on + r : a.N - 1;
+                sw_bits[o] = make_uint2(a.w_scale[c[0]] | (uint32_t)a.w_scale[c[1]] << 16, a.w_scale[c[2]] | (uint32_t)a.w_scale[c[3]] << 16);
+                zp_bits[o] = make_uint2(a.w_zero[c[0]] | (uint32_t)a.w_zero[c[1]] << 16, a.w_zero[c[2]] | (uint32_t)a.w_zero[c[3]] << 16);
+                ws[o] = make_float4(a.w_sum[c[0]], a.w_sum[c[1]], a.w_sum[c[2]], a.w_sum[c[3]]);
+                if (a.out_bias) cb[o] = make_float4(a.out_bias[c[0]], a.out_bias[c[1]], a.out_bias[c[2]], a.out_bias[c[3]]);
+            }
+            mts[o] = a.meta[tok < M ? tok : M - 1];
+        }
+    }
+    __device__ __forceinline__ void finish(const GemmArgs& a, int n0, int lane, const v4i (&acc)[NT], int* lds) const {
+        v4i* part = reinterpret_cast<v4i*>(lds);            // [wave][tile][lane]
+        const int row = lane & 15, sub = lane >> 4;
+#pragma unroll
+        for (int at = 0; at < NT; ++at) part[(wave * NT + at) * 64 + lane] = acc[at];
+        __syncthreads();
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            const int at = wave + o * WAVES, tok = 16 * (at % TT) + row, on = n0 + GV_ROWS * (at / TT) + 4 * sub;
+            if (at >= NT) break;
+            v4i av = part[at * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) av += part[(w * NT + at) * 64 + lane];
+            if (tok >= M) continue;
+            const basq_tokmeta mt = mts[o];
+            const float rowsum = (float)mt.rowsum;
+            auto dequant = [&](int acc, float sw, float zp, float wsum, float c) {
+                return fmaf(mt.scale * sw, (float)acc - zp * rowsum, fmaf(mt.lo, wsum, c));
+            };
+            auto lo16 = [](uint32_t v) { return __uint_as_float(v << 16); };
+            auto hi16 = [](uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); };
+            const f2 y01 = {dequant(av[0], lo16(sw_bits[o].x), lo16(zp_bits[o].x), ws[o].x, cb[o].x),
+                            dequant(av[1], hi16(sw_bits[o].x), hi16(zp_bits[o].x), ws[o].y, cb[o].y)};
+            const f2 y23 = {dequant(av[2], lo16(sw_bits[o].y), lo16(zp_bits[o].y), ws[o].z, cb[o].z),
+                            dequant(av[3], hi16(sw_bits[o].y), hi16(zp_bits[o].y), ws[o].w, cb[o].w)};
+            const uint2 out = make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(y01, b2)),       // round-to-nearest-even
+                                         __builtin_bit_cast(uint32_t, __builtin_convertvector(y23, b2)));
+            uint16_t* dst = a.Y + (int64_t)tok * a.ldy + on;
+            if (whole) {
+                __builtin_memcpy(dst, &out, 8);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (on + r < a.N) dst[r] = (uint16_t)((r < 2 ? out.x : out.y) >> (16 * (r & 1)));
+            }
+            if (a.acc_out) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (on + r < a.N) a.acc_out[(int64_t)tok * a.N + on + r] = av[r];
+            }
+        }
+    }
+};
 
 // STEPS: 64-byte k-chunks per lane held in registers at once (all of their loads are in flight together).
 // TILES: 16-row weight tiles per workgroup; they share the activation operand, which at 16 tokens is as many
@@ -30,10 +170,10 @@ constexpr int GV_OUT = 256;                         // the epilogue maps one thr
 // WAVES: wavefronts per workgroup, which split K.
 template <bool STREAM_LAYOUT, int WAVES, int STEPS, int TILES, int TT>
 __global__ __launch_bounds__(WAVES * 64) void gemv_w4a4_kernel(GemmArgs a) {
-    static_assert(WAVES * 64 >= GV_OUT, "a thread per output of a tile");
     constexpr int NT = TILES * TT;                  // accumulator tiles per wave
     constexpr bool TWO_CHAINS = NT <= 2;            // few tiles: low and high nibbles on separate MFMA chains
-    __shared__ int part[NT * 256];                  // cross-wave sums (integer adds: any order gives the same bits)
+    typedef std::conditional_t<TT == 1, GvFewTiles<WAVES, TILES>, GvManyTiles<WAVES, TILES, TT>> End;
+    __shared__ __attribute__((aligned(16))) int part[End::LDS_INTS];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = blockIdx.x * (GV_ROWS * TILES);
@@ -41,9 +181,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_w4a4_kernel(GemmArgs a) {
     const int nchunks = KB / 64;               // 64-byte chunks per row (K % 128 == 0 checked by the caller)
     const int row = lane & 15, sub = lane >> 4;
     const int M = (int)a.M;
-
-#pragma unroll
-    for (int i = 0; i < NT; ++i) if (WAVES * 64 == GV_OUT || tid < GV_OUT) part[i * 256 + tid] = 0;
 
     // chunk c of this lane: canonical = 16 bytes of row n at 64c + 16sub; streaming = piece `lane` of the
     // 16-row block's c-th KB (rows past N are stored as zeros there; a whole block past N does not exist)
@@ -66,29 +203,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_w4a4_kernel(GemmArgs a) {
         arow[tt] = a.Aq + (int64_t)(t_ok[tt] ? 16 * tt + row : 0) * KB + sub * 16;
     }
 
-    // Epilogue constants and token records of the outputs this thread will finish (16 consecutive channels of one
-    // token per 16 threads, one such output per tile), requested now so that their latency overlaps the weight
-    // stream: without a branch (clamped indices) and as raw bits -- a conversion here would wait for them before
-    // the first weight load is issued, and a record fetched in the epilogue is a memory latency at the very end.
-    const int orow = tid & 15, otok = tid >> 4;
-    uint16_t sw_bits[TILES], zp_bits[TILES];
-    float ws[TILES], cb[TILES];
-#pragma unroll
-    for (int t = 0; t < TILES; ++t) {
-        const int on = n0 + GV_ROWS * t + orow;
-        const int on_c = on < a.N ? on : a.N - 1;
-        sw_bits[t] = a.w_scale[on_c];
-        zp_bits[t] = a.w_zero[on_c];
-        ws[t] = a.w_sum[on_c];
-        cb[t] = 0.0f;
-        if (a.out_bias) cb[t] = a.out_bias[on_c];
-    }
-    basq_tokmeta mts[TT];
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        const int tok = 16 * tt + otok;
-        mts[tt] = a.meta[tok < M ? tok : M - 1];
-    }
+    End end;
+    end.request(a, n0, tid, part);
 
     v4i acc[NT], acc2[TWO_CHAINS ? NT : 1];
 #pragma unroll
@@ -128,34 +244,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_w4a4_kernel(GemmArgs a) {
             }
         }
     }
-    // accumulator register r of lane l: weight row 4*(l/16) + r, token l%16
-    __syncthreads();                                // every wave has zeroed its share of `part`
+    if (TWO_CHAINS) {
 #pragma unroll
-    for (int at = 0; at < NT; ++at) {
-        if (TWO_CHAINS) acc[at] += acc2[at];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) atomicAdd(&part[at * 256 + (4 * sub + r) * 16 + row], acc[at][r]);
+        for (int at = 0; at < NT; ++at) acc[at] += acc2[at];
     }
-    __syncthreads();
-    if (WAVES * 64 > GV_OUT && tid >= GV_OUT) return;
-
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        const int tok = 16 * tt + otok;
-        if (tok >= M) continue;
-        const basq_tokmeta mt = mts[tt];
-#pragma unroll
-        for (int t = 0; t < TILES; ++t) {
-            const int on = n0 + GV_ROWS * t + orow;
-            if (on >= a.N) continue;
-            const int av = part[(t * TT + tt) * 256 + orow * 16 + otok];
-            const float sw = bf16_to_f32(sw_bits[t]), zp = bf16_to_f32(zp_bits[t]);
-            const float tv = (float)av - zp * (float)mt.rowsum;
-            const float y = fmaf(mt.scale * sw, tv, fmaf(mt.lo, ws[t], cb[t]));
-            a.Y[(int64_t)tok * a.ldy + on] = f32_to_bf16(y);
-            if (a.acc_out) a.acc_out[(int64_t)tok * a.N + on] = av;
-        }
-    }
+    end.finish(a, n0, lane, acc, part);
 }
 
 // canonical [N, K/2] -> streaming layout: one thread per 16-byte piece of the output
@@ -201,6 +294,13 @@ static void launch_gemv_tiles(const GemmArgs& a, hipStream_t s, int blocks16) {
     // one batch have no chain to shorten (17 tokens, K = 1024, N = 8192: 4.4 us with eight waves, 4.0 with four; N = 1024 3.5
     // with either; 65 tokens, K = 512, N = 8192: 6.1 against 5.6).
     const bool one_batch = a.K / 128 <= 4 * STEPS;
+    // 33 .. 64 tokens over 512 .. 1024 tiles: eight waves on the three or four tiles that give every compute unit one workgroup,
+    // which has twice the loads in flight of four waves on two (61 x 4096 x 12288 13.2 -> 9.9 us, 40 x 8192 x 12288 18.0 -> 13.8, 61 x
+    // 4096 x 16384 13.6 -> 10.7; 64 x 4096 x 20000, beyond, 19.2 and 18.3; up to 32 tokens even; rows of one batch 5.7 and 6.4).
+    if constexpr (TT == 4) {
+        if (blocks16 > 512 && blocks16 <= 768 && !one_batch) { launch_gemv_cfg<SL, 8, 4, 3, TT>(a, s, blocks16); return; }
+        if (blocks16 > 768 && blocks16 <= 1024 && !one_batch) { launch_gemv_cfg<SL, 8, 2, 4, TT>(a, s, blocks16); return; }
+    }
     if (blocks16 >= 1536) launch_gemv_cfg<SL, 4, STEPS, 4, TT>(a, s, blocks16);
     else if (blocks16 > 512 || (one_batch && blocks16 > 256)) launch_gemv_cfg<SL, 4, STEPS, 2, TT>(a, s, blocks16);
     else if (one_batch) launch_gemv_cfg<SL, 4, STEPS, 1, TT>(a, s, blocks16);

@@ -708,6 +708,30 @@ def test_every_tiling_of_the_fp6_product(tiling, K):
         assert bool((buf == -7.0).all()), "wrote outside the output"
 
 
+@pytest.mark.parametrize("M", [17, 33, 49, 64, 65])
+@pytest.mark.parametrize("N,K", [(8193, 2304), (8208, 4096), (12281, 2304), (12289, 2304), (16384, 4096), (16390, 1024), (35, 4096), (61, 384)])
+def test_streaming_product_where_waves_share_the_outputs(M, N, K):
+    """17 and more tokens: a wave finishes whole tiles, four channels a lane, on either side of the rules that choose waves and
+    tiles per workgroup, with channels past the last and rows of outputs at any alignment: the bits of the tiled int8 kernel on
+    the same tokens among 129 (exact integer sums, the same epilogue)."""
+    announce(f"streaming product M={M} N={N} K={K}")
+    A, _, meta, W, _, sw, zp, ws, c = random_product(129, N, K, seed=M + N)
+    want = torch.empty((129, N), dtype=torch.bfloat16, device=DEV)
+    want_acc = torch.empty((129, N), dtype=torch.int32, device=DEV)
+    B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, want, want_acc)
+    Wd = torch.empty(B.basq_decode_bytes(N, K), dtype=torch.uint8, device=DEV)
+    B.basq_pack_decode(W, Wd)
+    for layout, w in ((B.BASQ_W_CANONICAL, W), (B.BASQ_W_DECODE16, Wd)):
+        for ldy, offset in ((N, 0), (N + 3, 1)):
+            buf, Y = output_view(M, N, ldy, offset)
+            acc = torch.full((M, N), -1, dtype=torch.int32, device=DEV)
+            B.basq_w4a4_gemm(A[:M], meta[:M], w, sw, zp, ws, c, Y, acc, w_layout=layout, N=N)
+            assert torch.equal(Y.contiguous().view(torch.int16), want[:M].view(torch.int16))
+            assert torch.equal(acc, want_acc[:M])
+            Y.fill_(-7.0)
+            assert bool((buf == -7.0).all()), "wrote outside the output"
+
+
 SPLIT_TILES = [(64, 64), (96, 64), (128, 64), (128, 128), (96, 96), (160, 96)]
 
 
