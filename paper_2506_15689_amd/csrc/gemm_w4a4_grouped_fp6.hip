@@ -14,10 +14,12 @@
 // two 32 x 32 blocks in 64 cycles with the single rounding of fma (checked bit for bit over normal and subnormal values),
 // against 128 for 32 vector instructions, and it takes one column sum and one lower bound per lane instead of 32 sums
 // from LDS.  The outer one is 64 vector instructions (256 cycles), which run beside the MFMAs of the same wave if
-// nothing makes them wait: a column block's MFMAs are followed by the closing of the block before it, and the
-// last block of a group is closed behind the first MFMAs of the next.  With all MFMAs of a group first and 128 vector
-// multiply-adds behind them (and the constants' conversion between two more LDS waits) a group took 3380 cycles for two
-// waves of a SIMD; the kernel on 2048 x 4096 x 12288: 145 us before, 105 as built.
+// nothing makes them wait: eight behind every MFMA (32 cycles each), one block late.  With sixteen behind every second MFMA a
+// group took a wave alone on its SIMD 1230 cycles, as built 1020 (64 x 4096 x 4096 20.4 -> 17.6 us, 700 x 5008, K = 8192 38.9 ->
+// 33.7); two waves a SIMD share the loads into LDS and its reads, and gain less (2048 x 4096 x 12288 98 - 102 us, now 92 - 98; without
+// the loads 70, the multiply-adds 80, the fragment reads 82, the rank-1 updates 87).  The reads take running addresses, two
+// instructions a read less than a stage's address each time; a branch in the loop costs tens of cycles (unpeeled, with the
+// tests for the last groups inside, 24.3 us for 64 x 4096 x 4096).  256 x 128 tiles, a quarter less to load: 98.6.
 // 128 x 128 tiles, four waves of 64 x 64, two workgroups per compute unit, a ring of three stages filled by
 // direct-to-LDS loads two to three groups ahead.
 #include "gemm_fp6_store.h"
@@ -41,16 +43,20 @@ constexpr int G6G_WM = 64, G6G_TM = 2, G6G_TN = 2;
 constexpr int G6G_CHUNK = 96;                                  // bytes of one row per stage: 128 codes
 constexpr int G6G_BLOCK = 32 * G6G_CHUNK;                      // a 32-row block of a stage
 constexpr int G6G_STAGES = 3;
-constexpr int G6G_PARAMS = (G6G_BM + G6G_BN) * G6G_CHUNK;      // a stage: 24 KB of operands,
-constexpr int G6G_SUMS = G6G_PARAMS + G6G_BM * 16;             // 128 token records of 16 B,
-constexpr int G6G_STAGE_BYTES = G6G_SUMS + G6G_BN * 4;         // 128 column sums of 4 B
-constexpr int G6G_PIECES = G6G_PARAMS / 1024;                  // 1 KB pieces of operands, one wave-load each
+// LDS: the activations of all stages, then their weights, records and column sums.  A read of any stage is then one address per
+// lane plus an offset that the instruction carries (64 KB at most), not an addition per read and step.
+constexpr int G6G_A_STAGE = G6G_BM * G6G_CHUNK, G6G_B_STAGE = G6G_BN * G6G_CHUNK;      // 12 KB each
+constexpr int G6G_REC_STAGE = G6G_BM * 16, G6G_SUM_STAGE = G6G_BN * 4;
+constexpr int G6G_B_AT = G6G_STAGES * G6G_A_STAGE, G6G_REC_AT = G6G_B_AT + G6G_STAGES * G6G_B_STAGE;
+constexpr int G6G_SUM_AT = G6G_REC_AT + G6G_STAGES * G6G_REC_STAGE;
+constexpr int G6G_LDS_BYTES = G6G_SUM_AT + G6G_STAGES * G6G_SUM_STAGE;
+constexpr int G6G_PIECES = (G6G_A_STAGE + G6G_B_STAGE) / 1024; // 1 KB pieces of a stage's operands, one wave-load each
 constexpr int G6G_LOADS = G6G_PIECES / G6G_WAVES;              // operand loads per wave per stage
 constexpr int G6G_A_LOADS = (G6G_BM * G6G_CHUNK / 1024) / G6G_WAVES;   // ... of which the first ones are activations
 constexpr int G6G_ALL_LOADS = G6G_LOADS + 1;                   // ... and one more brings constants
 constexpr int G6G_NUM_XCD = 8;
 static_assert(G6G_PIECES % G6G_WAVES == 0 && (G6G_BM * G6G_CHUNK / 1024) % G6G_WAVES == 0, "whole rounds of loads");
-static_assert(2 * G6G_STAGES * G6G_STAGE_BYTES <= 160 * 1024, "two workgroups per compute unit");
+static_assert(2 * G6G_LDS_BYTES <= 160 * 1024, "two workgroups per compute unit");
 
 // Wait until at most N of this wave's direct-to-LDS loads are outstanding and its own LDS reads have returned,
 // then join the workgroup barrier (one asm block: the compiler's own barrier would wait for every load).
@@ -61,7 +67,7 @@ __device__ __forceinline__ void g6g_wait_loads_and_barrier() {
 
 __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(GemmArgs a, const int32_t* w_gsum, int tiles_m, int tiles_n) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses device-only buffer-resource types; the host pass only needs the stub
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[G6G_STAGES * G6G_STAGE_BYTES];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[G6G_LDS_BYTES];
 
     // ---- tile assignment (ids congruent mod 8 run on one XCD and walk a compact band)
     int tile_m, tile_n;
@@ -127,33 +133,34 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
         n = n < a.N ? n : a.N - 1;
         pvoff = n * 4;
     }
-    // load number i of group g's stage (byte stage_off of the ring); the last one is the constants'
-    auto issue_one = [&](int stage_off, int g, int i) {
-        uint8_t* stage = lds + stage_off;
+    // load number i of group g, into stage `stage` of the ring; the last one is the constants'
+    auto issue_one = [&](int stage, int g, int i) {
         if (i < G6G_A_LOADS)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, G6G_LDS_PTR(stage + (i * G6G_WAVES + swave) * 1024), 16, lane_off, (int)((unsigned)g * a_step + (unsigned)soff[i]), 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, G6G_LDS_PTR(lds + stage * G6G_A_STAGE + (i * G6G_WAVES + swave) * 1024), 16, lane_off, (int)((unsigned)g * a_step + (unsigned)soff[i]), 0, 0);
         else if (i < G6G_LOADS)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, G6G_LDS_PTR(stage + (i * G6G_WAVES + swave) * 1024), 16, lane_off, (int)((unsigned)g * w_step + (unsigned)soff[i]), 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, G6G_LDS_PTR(lds + G6G_B_AT + stage * G6G_B_STAGE + ((i - G6G_A_LOADS) * G6G_WAVES + swave) * 1024), 16, lane_off, (int)((unsigned)g * w_step + (unsigned)soff[i]), 0, 0);
         else if (swave < 2)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_m, G6G_LDS_PTR(stage + G6G_PARAMS + swave * 1024), 16, pvoff, g * 16, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_m, G6G_LDS_PTR(lds + G6G_REC_AT + stage * G6G_REC_STAGE + swave * 1024), 16, pvoff, g * 16, 0, 0);
         else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_c, G6G_LDS_PTR(stage + G6G_SUMS + (swave - 2) * 256), 4, pvoff, g * a.N * 4, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_c, G6G_LDS_PTR(lds + G6G_SUM_AT + stage * G6G_SUM_STAGE + (swave - 2) * 256), 4, pvoff, g * a.N * 4, 0, 0);
     };
 
     // ---- fragment addressing: lane (frow, fhalf) feeds k = 64*kb + 32*fhalf .. +31 of its row, i.e. group
     // f = 2*kb + fhalf of the row's block: 16 bytes among the pieces, 8 bytes among the tails
     const int frow = lane & 31, fhalf = lane >> 5;
-    int moff[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) moff[kb] = 64 * frow + 16 * ((2 * kb + fhalf) ^ ((frow >> 2) & 3));
     const int toff = 2048 + 256 * fhalf + 8 * frow;                        // k-block 1: 512 bytes further
     const int a_row = wm * G6G_TM * G6G_BLOCK;
-    const int b_row = (G6G_BM / 32 + wn * G6G_TN) * G6G_BLOCK;
-    // byte offsets of the 8-byte tail reads, one opaque register each: reads whose addresses share a visible base
-    // get merged into paired reads, whose result could not land in two operand tuples without register copies
-    int ta[2][G6G_TM], tb[2][G6G_TN];
+    const int b_row = G6G_B_AT + wn * G6G_TN * G6G_BLOCK;
+    // Byte addresses of the reads in stage 0.  The 8-byte tail reads have one opaque register each: reads whose addresses
+    // share a visible base get merged into paired reads, whose result could not land in two operand tuples without register
+    // copies.
+    int ma[2], mb[2], ta[2][G6G_TM], tb[2][G6G_TN];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
+        const int moff = 64 * frow + 16 * ((2 * kb + fhalf) ^ ((frow >> 2) & 3));
+        ma[kb] = a_row + moff;
+        mb[kb] = b_row + moff;
+        asm volatile("" : "+v"(ma[kb]), "+v"(mb[kb]));
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             ta[kb][i] = a_row + i * G6G_BLOCK + toff + 512 * kb;
@@ -161,6 +168,8 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
             asm volatile("" : "+v"(ta[kb][i]), "+v"(tb[kb][i]));
         }
     }
+    int rec_at = G6G_REC_AT + (wm * G6G_WM + frow) * 16, sum_at = G6G_SUM_AT + (wn * G6G_TN * 32 + frow) * 4;
+    asm volatile("" : "+v"(rec_at), "+v"(sum_at));
 
     // F / 64: facc[j] holds the row blocks i = 0, 1 of column block j, 16 registers each
     v32f facc[G6G_TN];
@@ -169,7 +178,6 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
 #pragma unroll
         for (int r = 0; r < 32; ++r) facc[j][r] = 0.0f;
     float rsum[G6G_TM] = {0.0f, 0.0f};                                     // R_m of this lane's tokens (lane % 32)
-    v16f acc[G6G_TM][G6G_TN];
     // operand registers: six consecutive VGPRs per fragment; the builtin takes eight, the fp6 form reads six
     v8i pa[2][G6G_TM], pb[2][G6G_TN];
 #pragma unroll
@@ -184,19 +192,35 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
         const v2i t = *reinterpret_cast<const v2i*>(tail_ptr);
         dst[0] = m[0]; dst[1] = m[1]; dst[2] = m[2]; dst[3] = m[3]; dst[4] = t[0]; dst[5] = t[1];
     };
-    auto read_a = [&](const uint8_t* st, int kb, int i) { read_one(pa[kb][i], st + a_row + i * G6G_BLOCK + moff[kb], st + ta[kb][i]); };
-    auto read_b = [&](const uint8_t* st, int kb, int j) { read_one(pb[kb][j], st + b_row + j * G6G_BLOCK + moff[kb], st + tb[kb][j]); };
+    auto read_a = [&](int kb, int i) { read_one(pa[kb][i], lds + ma[kb] + i * G6G_BLOCK, lds + ta[kb][i]); };
+    auto read_b = [&](int kb, int j) { read_one(pb[kb][j], lds + mb[kb] + j * G6G_BLOCK, lds + tb[kb][j]); };
     // As integers: the compiler puts a wait for every outstanding direct-to-LDS load in front of a float-typed LDS read.
-    auto read_constants = [&](const uint8_t* st, int t) {
-        rec[t] = *reinterpret_cast<const v4i*>(st + G6G_PARAMS + (wm * G6G_WM + t * 32 + frow) * 16);
-        csum[t] = *reinterpret_cast<const int*>(st + G6G_SUMS + ((wn * G6G_TN + t) * 32 + frow) * 4);
+    auto read_constants = [&](int t) {
+        rec[t] = *reinterpret_cast<const v4i*>(lds + rec_at + t * 32 * 16);
+        csum[t] = *reinterpret_cast<const int*>(lds + sum_at + t * 32 * 4);
+    };
+    int stage = 0;
+    auto next_stage = [&]() {
+        const bool wrap = stage == G6G_STAGES - 1;
+        const int d = wrap ? -(G6G_STAGES - 1) : 1;
+        static_assert(G6G_A_STAGE == G6G_B_STAGE, "one step for both operands");
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            ma[kb] += d * G6G_A_STAGE; mb[kb] += d * G6G_A_STAGE;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) { ta[kb][i] += d * G6G_A_STAGE; tb[kb][i] += d * G6G_A_STAGE; }
+        }
+        rec_at += d * G6G_REC_STAGE;
+        sum_at += d * G6G_SUM_STAGE;
+        stage = wrap ? 0 : stage + 1;
     };
     const v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // The weights are the first MFMA operand: accumulator register r of lane l belongs to token l % 32 of the row
-    // block and to output channel 8*(r/4) + 4*(l/32) + r%4 of the column block.
-    auto close_block = [&](int i, int j, float scale) {                    // F' += s_mg * S_g
+    // S_g of the four blocks (i, j).  The weights are the first MFMA operand: accumulator register r of lane l belongs to token
+    // l % 32 of the row block and to output channel 8*(r/4) + 4*(l/32) + r%4 of the column block.
+    v16f acc[G6G_TM][G6G_TN] = {{zero, zero}, {zero, zero}};
+    auto close_half = [&](int i, int j, int half, float scale) {           // F' += s_mg * S_g, eight registers
 #pragma unroll
-        for (int r = 0; r < 16; ++r) facc[j][16 * i + r] = fmaf(scale, acc[i][j][r], facc[j][16 * i + r]);
+        for (int r = 8 * half; r < 8 * half + 8; ++r) facc[j][16 * i + r] = fmaf(scale, acc[i][j][r], facc[j][16 * i + r]);
         asm volatile("" : "+v"(facc[j]));                                  // here, not where the sums are next used
     };
 
@@ -206,95 +230,80 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
     for (int g = 0; g < G6G_STAGES; ++g)
         if (g < ngroups) {
 #pragma unroll
-            for (int i = 0; i < G6G_ALL_LOADS; ++i) issue_one(g * G6G_STAGE_BYTES, g, i);
+            for (int i = 0; i < G6G_ALL_LOADS; ++i) issue_one(g, g, i);
         }
     if (ngroups > 2) g6g_wait_loads_and_barrier<2 * G6G_ALL_LOADS>();
     else if (ngroups > 1) g6g_wait_loads_and_barrier<G6G_ALL_LOADS>();
     else g6g_wait_loads_and_barrier<0>();
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-        read_b(lds, kb, 0);
-        read_a(lds, kb, 0);
-        read_constants(lds, kb);
+        read_b(kb, 0);
+        read_a(kb, 0);
+        read_constants(kb);
     }
     __builtin_amdgcn_sched_barrier(0);
 
-    // One group g, blocks (i, j) = (0,0), (1,0), (0,1), (1,1).  Fragments B0 and A0 and the constants were read during the
-    // group before; A1 and B1 are read with the first block.  Then the barrier: it ends every wave's reads of stage g,
-    // which group g + 3 refills from here on, and begins those of stage g + 1 (B0, whose last use was block (1,0), then
-    // A0, whose last use is block (0,1), and the constants).  Each block's MFMAs are followed by the closing of the
-    // block before.
-    float last_scale = 0.0f;                                               // of the group before, for its block (1,1)
-    auto group = [&](int g, int cur, int next, auto first_c, auto next_c, auto loads_c) {
-        constexpr bool has_next = decltype(next_c)::value, loads = decltype(loads_c)::value;
-        const uint8_t *here = lds + cur, *ahead = lds + next;
-        const float s0 = __int_as_float(rec[0][0]), s1 = __int_as_float(rec[1][0]);
-        const float z0 = __int_as_float(rec[0][1]), z1 = __int_as_float(rec[1][1]);
-        const float zlane = fhalf ? z1 : z0;                               // block l / 32 of the rank-1 update
-        const float c0 = 0.015625f * (float)csum[0], c1 = 0.015625f * (float)csum[1];
-        rsum[0] += fmaf(s0, (float)rec[0][2], 128.0f * z0);
-        rsum[1] += fmaf(s1, (float)rec[1][2], 128.0f * z1);
-        __builtin_amdgcn_sched_barrier(0);
+    // One group per pass: blocks (i, j) = (0,0), (1,0), (0,1), (1,1), two MFMAs each.  Fragments B0 and A0 and the constants were
+    // read during the group before; A1 and B1 are read with the first block.  The barrier, behind the first MFMA of block
+    // (0,1), ends every wave's reads of stage g, which group g + 3 refills from here on, and begins those of stage g + 1: B0
+    // and A0, whose last uses are blocks (1,0) and (0,1), with a block and a half to arrive, and the constants.
+    // Behind every MFMA go eight multiply-adds of a closing, one block late: the two pipes take 32 cycles each, side by side
+    // (sixteen behind every second MFMA left each pipe idle in turns).
+    float prev_s[2] = {0.0f, 0.0f};                                        // scales of the group before, for its blocks (., 1)
+    auto group = [&](int g, auto loads_c, auto newest_c) {
+        constexpr bool loads = decltype(loads_c)::value;
+        constexpr int newest = decltype(newest_c)::value;                  // loads that may be in flight at the barrier
+        const int here = stage;
+        float s[2] = {0.0f, 0.0f}, zlane = 0.0f, c1 = 0.0f;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const int i = (t >> 1) & 1, j = t >> 2, kb = t & 1;
-            if (t == 0) facc[0] = __builtin_amdgcn_mfma_f32_32x32x1f32(c0, zlane, facc[0], 0, 0, 0);
-            if (t == 4) facc[1] = __builtin_amdgcn_mfma_f32_32x32x1f32(c1, zlane, facc[1], 0, 0, 0);
-            if (t < 2) { read_a(here, t, 1); read_b(here, t, 1); }
-            if (t == 4 && has_next) {
-                // "loads" also says that stage g + 2 is in flight
-                if (loads || g + 2 < ngroups) g6g_wait_loads_and_barrier<G6G_ALL_LOADS>(); else g6g_wait_loads_and_barrier<0>();
-            }
+            if (t == 4) g6g_wait_loads_and_barrier<newest>();
             acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(pb[kb][j], pa[kb][i], kb == 0 ? zero : acc[i][j], 2, 2, 0, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (t >= 4 && has_next) {
-                if (t < 6) read_b(ahead, t - 4, 0); else { read_a(ahead, t - 6, 0); read_constants(ahead, t - 6); }
+            if (t == 2) {
+                // the constants, not before: they were the last to be read; out of their registers before t = 6 reads the next
+                s[0] = __int_as_float(rec[0][0]); s[1] = __int_as_float(rec[1][0]);
+                const float z0 = __int_as_float(rec[0][1]), z1 = __int_as_float(rec[1][1]);
+                zlane = fhalf ? z1 : z0;                                   // block l / 32 of the rank-1 update
+                const float c0 = 0.015625f * (float)csum[0];
+                c1 = 0.015625f * (float)csum[1];
+                rsum[0] += fmaf(s[0], (float)rec[0][2], 128.0f * z0);
+                rsum[1] += fmaf(s[1], (float)rec[1][2], 128.0f * z1);
+                asm volatile("" : "+v"(s[0]), "+v"(s[1]), "+v"(rsum[0]), "+v"(rsum[1]), "+v"(c1));
+                facc[0] = __builtin_amdgcn_mfma_f32_32x32x1f32(c0, zlane, facc[0], 0, 0, 0);
             }
+            if (t == 4) facc[1] = __builtin_amdgcn_mfma_f32_32x32x1f32(c1, zlane, facc[1], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (t < 2) { read_a(t, 1); read_b(t, 1); }
+            if (t == 2) next_stage();
+            if (t == 4) { read_b(0, 0); read_a(0, 0); }
+            if (t == 5) { read_b(1, 0); read_a(1, 0); }
+            if (t == 6) { read_constants(0); read_constants(1); }
             if (loads && t >= 4) {
-                issue_one(cur, g + G6G_STAGES, 2 * (t - 4));
-                if (2 * (t - 4) + 1 < G6G_ALL_LOADS) issue_one(cur, g + G6G_STAGES, 2 * (t - 4) + 1);
+                issue_one(here, g + G6G_STAGES, 2 * (t - 4));
+                if (2 * (t - 4) + 1 < G6G_ALL_LOADS) issue_one(here, g + G6G_STAGES, 2 * (t - 4) + 1);
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (t == 1 && !decltype(first_c)::value) close_block(1, 1, last_scale);
-            if (t == 3) close_block(0, 0, s0);
-            if (t == 5) close_block(1, 0, s1);
-            if (t == 7) close_block(0, 1, s0);
+            // behind MFMAs 2b + 1 and 2b + 2: the halves of block b - 1, of this group or of the one before
+            const int c = (t + 5) / 2 % 4;
+            close_half(c & 1, c >> 1, (t & 1) ^ 1, t >= 3 ? s[c & 1] : prev_s[c & 1]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        last_scale = s1;
+        prev_s[0] = s[0];
+        prev_s[1] = s[1];
     };
-    constexpr std::true_type yes{};
-    constexpr std::false_type no{};
-    int cur = 0, next = G6G_STAGE_BYTES;
-    auto advance = [&]() {
-        cur = next;
-        next = next == (G6G_STAGES - 1) * G6G_STAGE_BYTES ? 0 : next + G6G_STAGE_BYTES;
-    };
-    // The first group closes nothing, the last three request nothing, the last one reads nothing ahead: all peeled off the
-    // loop, so that the compiler's LDS waits count only the operands in use.
+    constexpr std::integral_constant<int, G6G_ALL_LOADS> one_stage{};
+    constexpr std::integral_constant<int, 0> none{};
     int g = 0;
-    if (ngroups > G6G_STAGES) {
-        group(0, cur, next, yes, yes, yes);
-        advance();
-        for (g = 1; g + G6G_STAGES < ngroups; ++g) {
-            // on a 16-byte boundary: beginning in the middle of an 8-byte pair, which code anywhere in front of the loop
-            // decides, costs 3 % with one workgroup per compute unit (700 x 5008, K = 8192: 39.3 and 40.5 us)
-            asm volatile(".p2align 4");
-            group(g, cur, next, no, yes, yes);
-            advance();
-        }
-    } else if (ngroups > 1) {
-        group(0, cur, next, yes, yes, no);
-        advance();
-        g = 1;
+    for (; g + G6G_STAGES < ngroups; ++g) {
+        asm volatile(".p2align 4");
+        group(g, std::true_type{}, one_stage);
     }
-    for (; g + 1 < ngroups; ++g) {
-        group(g, cur, next, no, yes, no);
-        advance();
-    }
-    if (g > 0) group(g, cur, next, no, no, no);
-    else group(g, cur, next, yes, no, no);
-    close_block(1, 1, last_scale);
+    for (; g + 2 < ngroups; ++g) group(g, std::false_type{}, one_stage);
+    for (; g < ngroups; ++g) group(g, std::false_type{}, none);
+    close_half(0, 1, 1, prev_s[0]);
+    close_half(1, 1, 0, prev_s[1]);
+    close_half(1, 1, 1, prev_s[1]);
     __syncthreads();
 
     // ---- epilogue: column constants through LDS (sw, sw * zp, c), rows already in registers
