@@ -75,7 +75,7 @@ def test_fp6_tilings_by_name(lib):
 def test_fp6_split_tilings_by_name(lib):
     """Which split tiling a shape takes, and that a product by name is refused where it could not run."""
     T = B.basq_diag_fp6_split_tiling
-    assert T(333, 4096, 4096) in (1, 2) and T(1021, 11008, 4096) == 3 and T(61, 4096, 12288) == 0
+    assert T(333, 4096, 4096) == 1 and T(1021, 11008, 4096) == 3 and T(61, 4096, 12288) == 0
     # many tiles, few K-steps with many rounds, and shapes whose product runs elsewhere
     assert T(4096, 8192, 28672) == T(2048, 4096, 12288) == T(33204, 256, 14216) == T(32, 4096, 28672) == T(0, 4096, 4096) == -1
     call = lambda t, K=256, a=FAKE: lib.basq_diag_w4a4_gemm_fp6_split(
