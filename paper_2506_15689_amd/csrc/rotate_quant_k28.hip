@@ -24,10 +24,14 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef int v6i __attribute__((ext_vector_type(6)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+#define K28_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 constexpr int K28 = 14336;
-// Workgroups of four waves (two tokens), two per compute unit, while one 64 KB vector (b^c or s^a) is
-// staged in LDS; with both vectors staged, eight waves (four tokens) and one workgroup per unit.
+constexpr int K28_CUS = 256;
+constexpr int K28_VEC_BYTES = K28 * 4;              // b^c or s^a in LDS
+constexpr int K28_BLOCK_BYTES = 8 * 1024;           // a column block of a token in LDS: 32 rows x 128 columns in bf16
 
 struct H28Cols {
     uint32_t col[28];   // bit i of col[j] set  <=>  H28[i][j] == -1
@@ -67,61 +71,55 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int K28_WAVES, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
-__global__ __launch_bounds__(K28_WAVES * 64, 8 / K28_WAVES) void rotate_quant_k28_kernel(RotateQuantArgs a, float norm, H28Cols hc) {
+// Wait until at most N of this wave's memory operations are outstanding (they complete in the order they were issued).
+template <int N>
+__device__ __forceinline__ void wait_memory() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// A 4-byte LDS write that the compiler does not see as one: it would wait for every direct load into LDS in flight.
+__device__ __forceinline__ void lds_write(const void* p, int v) {
+    asm volatile("ds_write_b32 %0, %1" ::"v"((int)(uintptr_t)K28_LDS_PTR(p)), "v"(v) : "memory");
+}
+
+// What bounds it: 2450 vector instructions per wave and token, 17 us for 2048 tokens, if the memory is busy beside them.
+//
+// The vectors b^c and s^a go to LDS by direct loads requested behind the first token's and not waited for before they are
+// used.  (A loop of loads and LDS writes in front of everything was 16 memory latencies in a row: one token 10.5 us, as built
+// 8.2; 1024 tokens 20.4 and 17.7; 64 with both vectors 16.7 and 10.8.)
+//
+// STAGED: the column blocks 1 .. STAGED of the next token are requested straight into LDS as soon as both waves of the token
+// have read them, and are there when it begins, as is block 0, in registers; 0: the launch has one round, a wave one token at
+// most.  With block 0 alone requested ahead every round began with a memory latency and 20 KB a token: 2048 tokens, two rounds,
+// 34.7 us, as built 33.1; 8192 120.5, as built 110.2 (3.0 TB/s).  Four tokens and one vector take 152 KB of LDS, so four tokens (eight waves) share
+// a workgroup; with both vectors there is room for one block of a token.
+template <int TOKENS, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT, int STAGED>
+__global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCALE) ? 2 : 1) void rotate_quant_k28_kernel(RotateQuantArgs a, float norm, H28Cols hc) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses device-only buffer-resource types; the host pass only needs the stub
-    // bias (and s^a) laid out so that for a piece index q the 64 lanes of a wave half read consecutive float4s
-    constexpr int K28_THREADS = K28_WAVES * 64;
-    constexpr int VEC_WORDS = 2 * 32 * 64 * 4;
-    constexpr int BIAS_WORDS = HAS_BIAS ? VEC_WORDS : 0;
-    constexpr int SCALE_WORDS = HAS_SCALE ? VEC_WORDS : 0;
-    __shared__ __attribute__((aligned(16))) float lds[BIAS_WORDS + SCALE_WORDS + 64];
-    float* red = lds + BIAS_WORDS + SCALE_WORDS;   // [parity][token in block][half][mn, mx, sum, -]
+    constexpr int WAVES = 2 * TOKENS;
+    constexpr int VECTORS = (HAS_BIAS ? 1 : 0) + (HAS_SCALE ? 1 : 0);
+    constexpr int SCALE_AT = HAS_BIAS ? K28_VEC_BYTES : 0;
+    constexpr int STAGE_AT = VECTORS * K28_VEC_BYTES;
+    constexpr int RED_AT = STAGE_AT + TOKENS * STAGED * K28_BLOCK_BYTES;
+    constexpr int VEC_PIECES = K28_VEC_BYTES / 1024 / WAVES;           // 1 KB pieces of a vector that a wave brings
+    static_assert(K28_VEC_BYTES % (1024 * WAVES) == 0, "whole rounds of direct loads");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[RED_AT + 2 * TOKENS * 32];
+    int* red = reinterpret_cast<int*>(lds + RED_AT);   // [parity][token in block][half][mn, mx, sum, -]
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = wave & 1, tok_in_blk = wave >> 1;
     const int g = lane >> 4, m16 = lane & 15;
     const int ip = 16 * half + m16;                // output row i'
     const bool row_valid = ip < 28;
-
-    if (HAS_BIAS || HAS_SCALE) {
-        float4* dst = reinterpret_cast<float4*>(lds);
-        for (int f = threadIdx.x; f < 2 * 32 * 64; f += K28_THREADS) {
-            const int ln = f & 63, q = (f >> 6) & 31, hh = f >> 11;
-            const int row = 16 * hh + (ln & 15);
-            const int ch = row * 512 + 128 * (ln >> 4) + 4 * q;
-            if (HAS_BIAS)
-                dst[f] = row < 28 ? *reinterpret_cast<const float4*>(a.bias + ch) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (HAS_SCALE)
-                dst[BIAS_WORDS / 4 + f] = row < 28 ? *reinterpret_cast<const float4*>(a.act_scale + ch) : make_float4(1.f, 1.f, 1.f, 1.f);
-        }
-    }
-    __syncthreads();
-    const float4* lbias = reinterpret_cast<const float4*>(lds) + half * 32 * 64;
-    const float4* lscale = reinterpret_cast<const float4*>(lds + BIAS_WORDS) + half * 32 * 64;
-
-    // B operand: H_28[k = 8g + t][n = ip], zero outside 28 x 28
-    v8bf bop;
-    {
-        typedef short v8s __attribute__((ext_vector_type(8)));
-        v8s tmp;
-        const uint32_t mask = row_valid ? hc.col[ip] : 0u;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int i = 8 * g + t;
-            short v = 0;
-            if (row_valid && i < 28) v = (short)(((mask >> i) & 1u) ? 0xBF80 : 0x3F80);
-            tmp[t] = v;
-        }
-        bop = __builtin_bit_cast(v8bf, tmp);
-    }
+    const uint32_t signs = hc.col[row_valid ? ip : 27];  // requested first: a wait for it waits for nothing else
 
     // 16-byte loads of column block jb of a token: rows 8g .. 8g+7.  Buffer loads on a descriptor that ends with
     // the token: rows >= 28 lie past its end and read as zero without a branch -- with a branch per row the paths
     // that meet afterwards carry different numbers of loads in flight and every wait becomes a wait for all of them,
-    // the prefetched block of the next token included.  `tok` is uniform over the wave.
-    auto load_block = [&](v4u (&R)[8], int64_t tok, int jb) {
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.X + tok * a.ldx), 0, K28 * 2, 0x00020000);
+    // the prefetched block of the next token included.  `tok` is uniform over the wave.  (`bytes` = 0: a token that does not
+    // exist, nothing is read.)
+    auto load_block = [&](v4u (&R)[8], int64_t tok, int jb, int bytes) {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.X + tok * a.ldx), 0, bytes, 0x00020000);
         const int voff = 8192 * g + 16 * m16 + 256 * jb;                 // bytes; row i = 8g + t starts at 1024 i
 #pragma unroll
         for (int t = 0; t < 8; ++t)
@@ -133,31 +131,100 @@ __global__ __launch_bounds__(K28_WAVES * 64, 8 / K28_WAVES) void rotate_quant_k2
     int vblock = blockIdx.x;
     if ((gridDim.x & 127) == 0) vblock = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     const int64_t rb6 = (a.M + 31) >> 5;                    // 32-row blocks per chunk of the fp6 output
-    const int tokens_per_round = gridDim.x * (K28_WAVES / 2);
-    const int64_t m_first = (int64_t)vblock * (K28_WAVES / 2);
+    const int tokens_per_round = gridDim.x * TOKENS;
+    const int64_t m_first = (int64_t)vblock * TOKENS;
+    // Blocks 1 .. STAGED of a token straight into LDS, in the lanes' order: wave half h brings rows 8g + 4h .. 8g + 4h + 3.
+    uint8_t* const staged = lds + STAGE_AT + tok_in_blk * STAGED * K28_BLOCK_BYTES;
+    auto stage_blocks = [&](int64_t tok, int bytes) {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.X + tok * a.ldx), 0, bytes, 0x00020000);
+        const int voff = 8192 * g + 16 * m16 + 4096 * half;
+#pragma unroll
+        for (int jb = 1; jb <= STAGED; ++jb)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, K28_LDS_PTR(staged + (jb - 1) * K28_BLOCK_BYTES + (4 * half + t) * 1024), 16,
+                                                         voff + 256 * jb + 1024 * t, 0, 0, 2 /* non-temporal */);
+    };
     v4u R[4][8];
     {
         const int64_t m = m_first + tok_in_blk;
-        load_block(R[0], m < a.M ? m : a.M - 1, 0);
+        const int64_t mm = m < a.M ? m : a.M - 1;
+        if (STAGED > 0 && half == 1 && g == 3) {
+            // rows 28 .. 31 lie past the token's end: zeros, also if such a load should write nothing
+#pragma unroll
+            for (int jb = 0; jb < STAGED; ++jb)
+#pragma unroll
+                for (int t = 4; t < 8; ++t) *reinterpret_cast<v4i*>(staged + jb * K28_BLOCK_BYTES + t * 1024 + lane * 16) = v4i{0, 0, 0, 0};
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        load_block(R[0], mm, 0, K28 * 2);
+        if (STAGED > 0) stage_blocks(mm, K28 * 2);
+        else
+#pragma unroll
+            for (int jb = 1; jb < 4; ++jb) load_block(R[jb], mm, jb, K28 * 2);
+    }
+    // b^c and s^a: 16 bytes q of the 512-byte run of channels 512 i' + 128 g + 4 q .. + 3 stand at place q ^ (i' % 16), so that 16
+    // lanes of a read (i' = 0 .. 15) spread over the banks, and a direct load reads whole lines.
+#pragma unroll
+    for (int i = 0; i < VEC_PIECES; ++i) {
+        const int piece = i * WAVES + wave;
+        const int voff = (lane >> 5) * 512 + 16 * ((lane & 31) ^ ((piece >> 1) & 15));
+        if (HAS_BIAS)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.bias), 0, K28_VEC_BYTES, 0x00020000),
+                                                     K28_LDS_PTR(lds + piece * 1024), 16, voff, piece * 1024, 0, 0);
+        if (HAS_SCALE)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.act_scale), 0, K28_VEC_BYTES, 0x00020000),
+                                                     K28_LDS_PTR(lds + SCALE_AT + piece * 1024), 16, voff, piece * 1024, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int vec_row = row_valid ? ip : 27;           // (rows past the matrix: any values, they go nowhere)
+    int vec_at = vec_row * 2048 + g * 512 + 16 * (vec_row & 15);
+    // As integers: the compiler puts a wait for every outstanding direct load in front of a float-typed LDS read.
+    auto vec4 = [&](int base, int q) { return *reinterpret_cast<const v4i*>(lds + base + ((vec_at ^ (16 * (q & 15))) + 256 * (q >> 4))); };
+
+    // B operand: H_28[k = 8g + t][n = ip], zero outside 28 x 28
+    v8bf bop;
+    {
+        typedef short v8s __attribute__((ext_vector_type(8)));
+        v8s tmp;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int i = 8 * g + t;
+            short v = 0;
+            if (row_valid && i < 28) v = (short)(((signs >> i) & 1u) ? 0xBF80 : 0x3F80);
+            tmp[t] = v;
+        }
+        bop = __builtin_bit_cast(v8bf, tmp);
+    }
+
+    if (STAGED > 0) {
+        wait_memory<VECTORS * VEC_PIECES>();
+        lds_barrier();
     }
     // The row sums of the two halves meet one token late, at the next token's barrier, so that a token
     // costs one barrier: red is double buffered by token parity.
     int parity = 0;
     int64_t prev_m = -1;
     float prev_s = 0.f, prev_lo = 0.f;
-    for (int64_t m0 = m_first; m0 < a.M; m0 += tokens_per_round, parity ^= 1) {
+    for (int64_t m0 = m_first;; m0 += tokens_per_round, parity ^= 1) {
         const int64_t m = m0 + tok_in_blk;
         const bool tok_valid = m < a.M;
         const int64_t mm = tok_valid ? m : a.M - 1;      // keep every wave on the same barrier schedule
 
-        // ---- H_28 on the matrix core.  Block 0 was requested one token ago; blocks 1..3 are requested
-        // together now, while the accumulators that will replace them are not live yet.
+        // ---- H_28 on the matrix core.  Blocks that were not requested a token ago are requested together now, while the
+        // accumulators that will replace them are not live yet.
         float d[4][8][4];                                  // [jb][jj][r]
+        if (STAGED > 0) {
 #pragma unroll
-        for (int jb = 1; jb < 4; ++jb) load_block(R[jb], mm, jb);
-        __builtin_amdgcn_sched_barrier(0);
+            for (int jb = STAGED + 1; jb < 4; ++jb) load_block(R[jb], mm, jb, K28 * 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int jb = 0; jb < 4; ++jb) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (jb >= 1 && jb <= STAGED)
+                    R[jb][t] = __builtin_bit_cast(v4u, *reinterpret_cast<const v4i*>(staged + (jb - 1) * K28_BLOCK_BYTES + t * 1024 + lane * 16));
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) {
                 v4u A;
@@ -175,11 +242,10 @@ __global__ __launch_bounds__(K28_WAVES * 64, 8 / K28_WAVES) void rotate_quant_k2
             }
         }
         // first block of this wave's next token: its latency hides behind the butterflies below
-        {
-            const int64_t mn_tok = m + tokens_per_round;
-            load_block(R[0], mn_tok < a.M ? mn_tok : a.M - 1, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        const bool more = STAGED > 0 && m0 + tokens_per_round < a.M;
+        const int64_t next = m + tokens_per_round < a.M ? m + tokens_per_round : a.M - 1;
+        if (STAGED > 0) load_block(R[0], next, 0, more ? K28 * 2 : 0);
+        __builtin_amdgcn_sched_barrier(0);
 
         // ---- H_512: register stages jj (j0..2), r (j3..4), jb (j7..8) ------------------------------------
 #pragma unroll
@@ -222,7 +288,12 @@ __global__ __launch_bounds__(K28_WAVES * 64, 8 / K28_WAVES) void rotate_quant_k2
 
         // ---- this lane owns channels ip*512 + 128*g + c, c = 32*jb + 8*r + jj ---------------------------
         const int ch0 = ip * 512 + 128 * g;
+        if (VECTORS > 0 && m0 == m_first) {                // the vectors have arrived, every wave's part of them
+            wait_memory<(STAGED > 0 ? 8 : 0)>();             // (behind them only the next token's block 0)
+            lds_barrier();
+        }
         float mn = INFINITY, mx = -INFINITY;
+        asm volatile("" : "+v"(vec_at));                   // (32 addresses kept over the tokens would be spilled)
 #pragma unroll
         for (int jb = 0; jb < 4; ++jb)
 #pragma unroll
@@ -230,17 +301,16 @@ __global__ __launch_bounds__(K28_WAVES * 64, 8 / K28_WAVES) void rotate_quant_k2
 #pragma unroll
                 for (int q2 = 0; q2 < 2; ++q2) {
                     const int c = 32 * jb + 8 * r + 4 * q2;
-                    float4 bb = make_float4(0.f, 0.f, 0.f, 0.f), ss = make_float4(1.f, 1.f, 1.f, 1.f);
-                    if (HAS_BIAS) bb = lbias[(c >> 2) * 64 + lane];
-                    if (HAS_SCALE) ss = lscale[(c >> 2) * 64 + lane];
-                    const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
-                    const float sv[4] = {ss.x, ss.y, ss.z, ss.w};
+                    v4i bb = {0, 0, 0, 0}, ss = {0, 0, 0, 0};
+                    if (HAS_BIAS) bb = vec4(0, c >> 2);
+                    if (HAS_SCALE) ss = vec4(SCALE_AT, c >> 2);
                     float rr[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float rv = d[jb][4 * q2 + e][r] * norm;
                         rr[e] = rv;
-                        const float v = HAS_SCALE ? fmaf(rv, sv[e], -bv[e]) : rv - bv[e];
+                        const float bv = __int_as_float(bb[e]);
+                        const float v = HAS_SCALE ? fmaf(rv, __int_as_float(ss[e]), -bv) : rv - bv;
                         d[jb][4 * q2 + e][r] = v;
                         mn = fminf(mn, v);
                         mx = fmaxf(mx, v);
@@ -264,19 +334,26 @@ __global__ __launch_bounds__(K28_WAVES * 64, 8 / K28_WAVES) void rotate_quant_k2
             mn = fminf(fminf(lo4[0], lo4[1]), fminf(lo4[2], lo4[3]));
             mx = fmaxf(fmaxf(hi4[0], hi4[1]), fmaxf(hi4[2], hi4[3]));
         }
-        float* myred = red + (parity * (K28_WAVES / 2) + tok_in_blk) * 8;
-        float* otherred = red + ((parity ^ 1) * (K28_WAVES / 2) + tok_in_blk) * 8;
-        if (lane == 0) { myred[half * 4 + 0] = mn; myred[half * 4 + 1] = mx; }
+        const int* myred = red + (parity * TOKENS + tok_in_blk) * 8;
+        const int* otherred = red + ((parity ^ 1) * TOKENS + tok_in_blk) * 8;
+        if (lane == 0) {
+            lds_write(myred + half * 4, __float_as_int(mn));
+            lds_write(myred + half * 4 + 1, __float_as_int(mx));
+        }
         lds_barrier();
-        mn = fminf(myred[0], myred[4]);
-        mx = fmaxf(myred[1], myred[5]);
+        mn = fminf(__int_as_float(myred[0]), __int_as_float(myred[4]));
+        mx = fmaxf(__int_as_float(myred[1]), __int_as_float(myred[5]));
         if (half == 0 && lane == 0 && prev_m >= 0) {       // finish the previous token
             basq_tokmeta mt;
             mt.scale = prev_s; mt.lo = prev_lo;
-            mt.rowsum = reinterpret_cast<int*>(otherred)[2] + reinterpret_cast<int*>(otherred)[6];
+            mt.rowsum = otherred[2] + otherred[6];
             mt.reserved = 0;
             a.meta[prev_m] = mt;
         }
+        // Behind the barrier every wave has read its token's blocks: the next one's may come.  (Also where there is none: the
+        // compiler counts the requests behind block 0, and with a branch here it would wait for the code stores as well.)
+        if (STAGED > 0) stage_blocks(next, more ? K28 * 2 : 0);
+        __builtin_amdgcn_sched_barrier(0);
 
         const float lo = a.clip_lo * mn;
         const float hi = a.clip_hi * mx;
@@ -348,13 +425,19 @@ __global__ __launch_bounds__(K28_WAVES * 64, 8 / K28_WAVES) void rotate_quant_k2
         sum += dppi<0x140>(sum);
         sum = __builtin_amdgcn_readlane(sum, 0) + __builtin_amdgcn_readlane(sum, 16) +
               __builtin_amdgcn_readlane(sum, 32) + __builtin_amdgcn_readlane(sum, 48);
-        if (lane == 0) reinterpret_cast<int*>(myred)[half * 4 + 2] = sum;
+        if (lane == 0) lds_write(myred + half * 4 + 2, sum);
         prev_m = tok_valid ? m : -1;
         prev_s = s; prev_lo = lo;
+        if (!more) break;
+        // The next token's blocks are in LDS.  Behind their requests this wave stored at least four pieces of codes (its token
+        // exists, or there would be no more), which may still be on their way.
+        wait_memory<4>();
+        lds_barrier();
     }
+    if (STAGED > 0) wait_memory<0>();                      // nothing may be on its way into LDS when the workgroup ends
     lds_barrier();
     if (half == 0 && lane == 0 && prev_m >= 0) {
-        const int* lastred = reinterpret_cast<const int*>(red + ((parity ^ 1) * (K28_WAVES / 2) + tok_in_blk) * 8);
+        const int* lastred = red + (parity * TOKENS + tok_in_blk) * 8;
         basq_tokmeta mt;
         mt.scale = prev_s; mt.lo = prev_lo;
         mt.rowsum = lastred[2] + lastred[6];
@@ -364,18 +447,24 @@ __global__ __launch_bounds__(K28_WAVES * 64, 8 / K28_WAVES) void rotate_quant_k2
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
+template <int TOKENS, bool HB, bool HS, int STAGED>
+int launch_k28_form(const RotateQuantArgs& a, hipStream_t s, float norm, const H28Cols& hc, int max_blocks) {
+    const int64_t want = (a.M + TOKENS - 1) / TOKENS;
+    const unsigned blocks = (unsigned)(want < max_blocks ? want : max_blocks);
+    if (a.rot_out)
+        hipLaunchKernelGGL((rotate_quant_k28_kernel<TOKENS, HB, HS, true, STAGED>), dim3(blocks), dim3(TOKENS * 128), 0, s, a, norm, hc);
+    else
+        hipLaunchKernelGGL((rotate_quant_k28_kernel<TOKENS, HB, HS, false, STAGED>), dim3(blocks), dim3(TOKENS * 128), 0, s, a, norm, hc);
+    return check_hip(hipGetLastError(), "rotate_quant (28x512) launch");
+}
+
+// Calls that fit one round of two-token workgroups (two per compute unit, one where both vectors fill its LDS) take them: they
+// spread over twice the compute units.  More tokens: four to a workgroup, and the next ones' blocks by way of LDS.
 template <bool HB, bool HS>
 int launch_k28_flags(const RotateQuantArgs& a, hipStream_t s, float norm, const H28Cols& hc) {
-    constexpr int WAVES = (HB && HS) ? 8 : 4;
-    constexpr int TOKENS = WAVES / 2;
-    constexpr int MAX_BLOCKS = 256 * (8 / WAVES);
-    const int64_t want = (a.M + TOKENS - 1) / TOKENS;
-    const unsigned blocks = (unsigned)(want < MAX_BLOCKS ? want : MAX_BLOCKS);
-    if (a.rot_out)
-        hipLaunchKernelGGL((rotate_quant_k28_kernel<WAVES, HB, HS, true>), dim3(blocks), dim3(WAVES * 64), 0, s, a, norm, hc);
-    else
-        hipLaunchKernelGGL((rotate_quant_k28_kernel<WAVES, HB, HS, false>), dim3(blocks), dim3(WAVES * 64), 0, s, a, norm, hc);
-    return check_hip(hipGetLastError(), "rotate_quant (28x512) launch");
+    constexpr int PER_CU = (HB && HS) ? 1 : 2;
+    if (a.M <= 2 * PER_CU * K28_CUS) return launch_k28_form<2, HB, HS, 0>(a, s, norm, hc, PER_CU * K28_CUS);
+    return launch_k28_form<4, HB, HS, (HB && HS) ? 1 : 3>(a, s, norm, hc, K28_CUS);
 }
 
 }  // namespace
