@@ -2,7 +2,7 @@
 // H_28 (x) H_512 (Paley type-I H_28; paper Sec. 5.2 splits a large non-power-of-two rotation in one
 // Cooley-Tukey step).  Channel k = i*512 + j, i the H_28 index.
 //
-// Two wavefronts share a token; wave half h owns output rows i' in [16h, 16h+16) (rows >= 28 idle).
+// Two wavefronts share a token (four up to 256 tokens, see the split kernel); wave half h owns output rows i' in [16h, 16h+16) (rows >= 28 idle).
 //   1. H_28 along i on the matrix core, exact: lane (g = l/16, m = l%16) loads rows i = 8g+t, t = 0..7,
 //      columns j = 128*jb + 8m .. +8 (16 B each), transposes the 8x8 bf16 block in registers
 //      (v_perm), and feeds it as A (row = column group m, k = i) to one bf16 MFMA per column
@@ -14,6 +14,8 @@
 //   3. Every lane now owns 128 consecutive channels: normalise, bias (from LDS), min/max, the two
 //      waves of the token combine their ranges through LDS, quantise, pack, store.
 #include "basq_internal.h"
+
+#include <type_traits>
 
 namespace basq {
 
@@ -82,16 +84,161 @@ __device__ __forceinline__ void lds_write(const void* p, int v) {
     asm volatile("ds_write_b32 %0, %1" ::"v"((int)(uintptr_t)K28_LDS_PTR(p)), "v"(v) : "memory");
 }
 
+#if defined(__HIP_DEVICE_COMPILE__)   // device-only buffer-resource types
+// 16-byte loads of column block jb of a token: rows 8g .. 8g+7.  Buffer loads on a descriptor that ends with
+// the token: rows >= 28 lie past its end and read as zero without a branch -- with a branch per row the paths
+// that meet afterwards carry different numbers of loads in flight and every wait becomes a wait for all of them,
+// the prefetched block of the next token included.  `x` is uniform over the wave.  (`bytes` = 0: a token that does not
+// exist, nothing is read.)
+__device__ __forceinline__ void k28_load_block(v4u (&R)[8], const uint16_t* x, int jb, int bytes, int lane) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x), 0, bytes, 0x00020000);
+    const int voff = 8192 * (lane >> 4) + 16 * (lane & 15) + 256 * jb;   // bytes; row i = 8g + t starts at 1024 i
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+        R[t] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 1024 * t, 0, 2 /* non-temporal */));
+}
+
+// b^c and s^a into LDS by direct loads: 16 bytes q of the 512-byte run of channels 512 i' + 128 g + 4 q .. + 3 stand at place
+// q ^ (i' % 16), so that 16 lanes of a read (i' = 0 .. 15) spread over the banks, and a direct load reads whole lines.
+template <int WAVES, bool HAS_BIAS, bool HAS_SCALE>
+__device__ __forceinline__ void k28_stage_vectors(const RotateQuantArgs& a, uint8_t* lds, int wave, int lane) {
+    static_assert(K28_VEC_BYTES % (1024 * WAVES) == 0, "whole rounds of direct loads");
+#pragma unroll
+    for (int i = 0; i < K28_VEC_BYTES / 1024 / WAVES; ++i) {
+        const int piece = i * WAVES + wave;
+        const int voff = (lane >> 5) * 512 + 16 * ((lane & 31) ^ ((piece >> 1) & 15));
+        if (HAS_BIAS)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.bias), 0, K28_VEC_BYTES, 0x00020000),
+                                                     K28_LDS_PTR(lds + piece * 1024), 16, voff, piece * 1024, 0, 0);
+        if (HAS_SCALE)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.act_scale), 0, K28_VEC_BYTES, 0x00020000),
+                                                     K28_LDS_PTR(lds + (HAS_BIAS ? K28_VEC_BYTES : 0) + piece * 1024), 16, voff, piece * 1024, 0, 0);
+    }
+}
+
+// B operand: H_28[k = 8g + t][n = ip], zero outside 28 x 28; `signs`: column ip of the matrix
+__device__ __forceinline__ v8bf k28_bop(uint32_t signs, bool row_valid, int g) {
+    typedef short v8s __attribute__((ext_vector_type(8)));
+    v8s tmp;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const int i = 8 * g + t;
+        short v = 0;
+        if (row_valid && i < 28) v = (short)(((signs >> i) & 1u) ? 0xBF80 : 0x3F80);
+        tmp[t] = v;
+    }
+    return __builtin_bit_cast(v8bf, tmp);
+}
+
+// H_28 of one column block: d[jj][r]
+__device__ __forceinline__ void k28_h28_block(const v4u (&R)[8], v8bf bop, float (&d)[8][4]) {
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+        v4u A;
+        const int w = jj >> 1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            // bytes of (hi, lo) = (R[2u+1][w], R[2u][w]); even jj takes the low halves, odd jj the high halves
+            A[u] = (jj & 1) ? __builtin_amdgcn_perm(R[2 * u + 1][w], R[2 * u][w], 0x07060302u)
+                            : __builtin_amdgcn_perm(R[2 * u + 1][w], R[2 * u][w], 0x05040100u);
+        }
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, A), bop, acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d[jj][r] = acc[r];
+    }
+}
+
+// the stages over jj (j0..2) and r (j3..4) of one column block
+__device__ __forceinline__ void k28_block_stages(float (&d)[8][4]) {
+#pragma unroll
+    for (int s = 1; s < 8; s <<= 1)
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj)
+            if ((jj & s) == 0)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) BFLY28(d[jj][r], d[jj + s][r]);
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+        BFLY28(d[jj][0], d[jj][1]);
+        BFLY28(d[jj][2], d[jj][3]);
+        BFLY28(d[jj][0], d[jj][2]);
+        BFLY28(d[jj][1], d[jj][3]);
+    }
+}
+
+// Range of a wave's values, the same in every lane
+__device__ __forceinline__ void k28_wave_range(float& mn, float& mx) {
+    mn = fminf(mn, dppf<0xB1>(mn)); mx = fmaxf(mx, dppf<0xB1>(mx));
+    mn = fminf(mn, dppf<0x4E>(mn)); mx = fmaxf(mx, dppf<0x4E>(mx));
+    mn = fminf(mn, dppf<0x141>(mn)); mx = fmaxf(mx, dppf<0x141>(mx));
+    mn = fminf(mn, dppf<0x140>(mn)); mx = fmaxf(mx, dppf<0x140>(mx));
+    float lo4[4], hi4[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        lo4[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mn), 16 * q));
+        hi4[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), 16 * q));
+    }
+    mn = fminf(fminf(lo4[0], lo4[1]), fminf(lo4[2], lo4[3]));
+    mx = fmaxf(fmaxf(hi4[0], hi4[1]), fmaxf(hi4[2], hi4[3]));
+}
+
+__device__ __forceinline__ int k28_wave_sum(int sum) {
+    sum += dppi<0xB1>(sum);
+    sum += dppi<0x4E>(sum);
+    sum += dppi<0x141>(sum);
+    sum += dppi<0x140>(sum);
+    return __builtin_amdgcn_readlane(sum, 0) + __builtin_amdgcn_readlane(sum, 16) +
+           __builtin_amdgcn_readlane(sum, 32) + __builtin_amdgcn_readlane(sum, 48);
+}
+
+// Codes of the 32 channels d[jj][r] of group jb of a lane (chunk 4*i' + g of the fp6 layout): 16 bytes in the 4-bit form, their sum, and
+// with `store6` the fp6 form, stored.
+__device__ __forceinline__ void k28_quantise_group(const RotateQuantArgs& a, const float (&d)[8][4], float inv, float nlo, bool row_valid,
+                                                   bool store6, int64_t m, int64_t rb6, int chunk, int jb, uint32_t (&words)[4], int& sum) {
+    v16f qe, qo;                                           // the clamped values before rounding: low / high nibbles
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        uint32_t ev = 0, od = 0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const float t0 = __builtin_amdgcn_fmed3f(fmaf(d[2 * p][r], inv, nlo), 0.0f, 15.0f);
+            const float t1 = __builtin_amdgcn_fmed3f(fmaf(d[2 * p + 1][r], inv, nlo), 0.0f, 15.0f);
+            ev = __builtin_amdgcn_cvt_pk_u8_f32(t0, p, ev);
+            od = __builtin_amdgcn_cvt_pk_u8_f32(t1, p, od);
+            qe[4 * r + p] = t0;
+            qo[4 * r + p] = t1;
+        }
+        if (row_valid) {
+            sum = __builtin_amdgcn_udot4(ev, 0x01010101u, sum, false);
+            sum = __builtin_amdgcn_udot4(od, 0x01010101u, sum, false);
+        }
+        words[r] = ev | (od << 4);
+    }
+    if (store6) {
+        // The 32 codes once more, as e2m3 numbers q/8, straight from the clamped values: the
+        // packed conversion divides by its scale operand, rounds to nearest-even (on the e2m3 grid below 2
+        // that is t/8 -> rint(t)/8, ties as in the integer conversion) and interleaves its two sources.
+        const v6i f6 = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(qe, qo, 8.0f);
+        const int rr = (int)(m & 31);
+        uint8_t* blk = a.Aq6 + ((int64_t)chunk * rb6 + (m >> 5)) * 3072;
+        *reinterpret_cast<uint4*>(blk + 64 * rr + 16 * (jb ^ ((rr >> 2) & 3))) =
+            make_uint4((uint32_t)f6[0], (uint32_t)f6[1], (uint32_t)f6[2], (uint32_t)f6[3]);
+        *reinterpret_cast<uint2*>(blk + 2048 + 256 * jb + 8 * rr) = make_uint2((uint32_t)f6[4], (uint32_t)f6[5]);
+    }
+}
+#endif  // __HIP_DEVICE_COMPILE__
+
 // What bounds it: 2450 vector instructions per wave and token, 17 us for 2048 tokens, if the memory is busy beside them.
 //
 // The vectors b^c and s^a go to LDS by direct loads requested behind the first token's and not waited for before they are
-// used.  (A loop of loads and LDS writes in front of everything was 16 memory latencies in a row: one token 10.5 us, as built
-// 8.2; 1024 tokens 20.4 and 17.7; 64 with both vectors 16.7 and 10.8.)
+// used.  (A loop of loads and LDS writes in front of everything was 16 memory latencies in a row: one token 10.5 us, without
+// 8.2; 1024 tokens 20.4 and 17.5; 64 with both vectors 16.7 and 10.8.)
 //
 // STAGED: the column blocks 1 .. STAGED of the next token are requested straight into LDS as soon as both waves of the token
 // have read them, and are there when it begins, as is block 0, in registers; 0: the launch has one round, a wave one token at
 // most.  With block 0 alone requested ahead every round began with a memory latency and 20 KB a token: 2048 tokens, two rounds,
-// 34.7 us, as built 33.1; 8192 120.5, as built 110.2 (3.0 TB/s).  Four tokens and one vector take 152 KB of LDS, so four tokens (eight waves) share
+// 34.7 us, as built 32.4; 8192 120.5, as built 110.2 (3.0 TB/s).  Four tokens and one vector take 152 KB of LDS, so four tokens (eight waves) share
 // a workgroup; with both vectors there is room for one block of a token.
 template <int TOKENS, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT, int STAGED>
 __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCALE) ? 2 : 1) void rotate_quant_k28_kernel(RotateQuantArgs a, float norm, H28Cols hc) {
@@ -102,7 +249,6 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
     constexpr int STAGE_AT = VECTORS * K28_VEC_BYTES;
     constexpr int RED_AT = STAGE_AT + TOKENS * STAGED * K28_BLOCK_BYTES;
     constexpr int VEC_PIECES = K28_VEC_BYTES / 1024 / WAVES;           // 1 KB pieces of a vector that a wave brings
-    static_assert(K28_VEC_BYTES % (1024 * WAVES) == 0, "whole rounds of direct loads");
     __shared__ __attribute__((aligned(1024))) uint8_t lds[RED_AT + 2 * TOKENS * 32];
     int* red = reinterpret_cast<int*>(lds + RED_AT);   // [parity][token in block][half][mn, mx, sum, -]
 
@@ -112,19 +258,6 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
     const int ip = 16 * half + m16;                // output row i'
     const bool row_valid = ip < 28;
     const uint32_t signs = hc.col[row_valid ? ip : 27];  // requested first: a wait for it waits for nothing else
-
-    // 16-byte loads of column block jb of a token: rows 8g .. 8g+7.  Buffer loads on a descriptor that ends with
-    // the token: rows >= 28 lie past its end and read as zero without a branch -- with a branch per row the paths
-    // that meet afterwards carry different numbers of loads in flight and every wait becomes a wait for all of them,
-    // the prefetched block of the next token included.  `tok` is uniform over the wave.  (`bytes` = 0: a token that does not
-    // exist, nothing is read.)
-    auto load_block = [&](v4u (&R)[8], int64_t tok, int jb, int bytes) {
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.X + tok * a.ldx), 0, bytes, 0x00020000);
-        const int voff = 8192 * g + 16 * m16 + 256 * jb;                 // bytes; row i = 8g + t starts at 1024 i
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-            R[t] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 1024 * t, 0, 2 /* non-temporal */));
-    };
 
     // Workgroups g, g+8, ... share an XCD; renumbered so that an XCD owns a contiguous range, 32
     // consecutive tokens (one block of the fp6 output) meet in one L2 and their pieces merge there.
@@ -145,6 +278,7 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, K28_LDS_PTR(staged + (jb - 1) * K28_BLOCK_BYTES + (4 * half + t) * 1024), 16,
                                                          voff + 256 * jb + 1024 * t, 0, 0, 2 /* non-temporal */);
     };
+    auto load_block = [&](v4u (&R)[8], int64_t tok, int jb, int bytes) { k28_load_block(R, a.X + tok * a.ldx, jb, bytes, lane); };
     v4u R[4][8];
     {
         const int64_t m = m_first + tok_in_blk;
@@ -163,40 +297,14 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
 #pragma unroll
             for (int jb = 1; jb < 4; ++jb) load_block(R[jb], mm, jb, K28 * 2);
     }
-    // b^c and s^a: 16 bytes q of the 512-byte run of channels 512 i' + 128 g + 4 q .. + 3 stand at place q ^ (i' % 16), so that 16
-    // lanes of a read (i' = 0 .. 15) spread over the banks, and a direct load reads whole lines.
-#pragma unroll
-    for (int i = 0; i < VEC_PIECES; ++i) {
-        const int piece = i * WAVES + wave;
-        const int voff = (lane >> 5) * 512 + 16 * ((lane & 31) ^ ((piece >> 1) & 15));
-        if (HAS_BIAS)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.bias), 0, K28_VEC_BYTES, 0x00020000),
-                                                     K28_LDS_PTR(lds + piece * 1024), 16, voff, piece * 1024, 0, 0);
-        if (HAS_SCALE)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.act_scale), 0, K28_VEC_BYTES, 0x00020000),
-                                                     K28_LDS_PTR(lds + SCALE_AT + piece * 1024), 16, voff, piece * 1024, 0, 0);
-    }
+    k28_stage_vectors<WAVES, HAS_BIAS, HAS_SCALE>(a, lds, wave, lane);
     __builtin_amdgcn_sched_barrier(0);
     const int vec_row = row_valid ? ip : 27;           // (rows past the matrix: any values, they go nowhere)
     int vec_at = vec_row * 2048 + g * 512 + 16 * (vec_row & 15);
     // As integers: the compiler puts a wait for every outstanding direct load in front of a float-typed LDS read.
     auto vec4 = [&](int base, int q) { return *reinterpret_cast<const v4i*>(lds + base + ((vec_at ^ (16 * (q & 15))) + 256 * (q >> 4))); };
 
-    // B operand: H_28[k = 8g + t][n = ip], zero outside 28 x 28
-    v8bf bop;
-    {
-        typedef short v8s __attribute__((ext_vector_type(8)));
-        v8s tmp;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int i = 8 * g + t;
-            short v = 0;
-            if (row_valid && i < 28) v = (short)(((signs >> i) & 1u) ? 0xBF80 : 0x3F80);
-            tmp[t] = v;
-        }
-        bop = __builtin_bit_cast(v8bf, tmp);
-    }
-
+    const v8bf bop = k28_bop(signs, row_valid, g);
     if (STAGED > 0) {
         wait_memory<VECTORS * VEC_PIECES>();
         lds_barrier();
@@ -225,21 +333,7 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
             for (int t = 0; t < 8; ++t)
                 if (jb >= 1 && jb <= STAGED)
                     R[jb][t] = __builtin_bit_cast(v4u, *reinterpret_cast<const v4i*>(staged + (jb - 1) * K28_BLOCK_BYTES + t * 1024 + lane * 16));
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) {
-                v4u A;
-                const int w = jj >> 1;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    // bytes of (hi, lo) = (R[2u+1][w], R[2u][w]); even jj takes the low halves, odd jj the high halves
-                    A[u] = (jj & 1) ? __builtin_amdgcn_perm(R[jb][2 * u + 1][w], R[jb][2 * u][w], 0x07060302u)
-                                    : __builtin_amdgcn_perm(R[jb][2 * u + 1][w], R[jb][2 * u][w], 0x05040100u);
-                }
-                v4f acc = {0.f, 0.f, 0.f, 0.f};
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, A), bop, acc, 0, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) d[jb][jj][r] = acc[r];
-            }
+            k28_h28_block(R[jb], bop, d[jb]);
         }
         // first block of this wave's next token: its latency hides behind the butterflies below
         const bool more = STAGED > 0 && m0 + tokens_per_round < a.M;
@@ -249,22 +343,7 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
 
         // ---- H_512: register stages jj (j0..2), r (j3..4), jb (j7..8) ------------------------------------
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb) {
-#pragma unroll
-            for (int s = 1; s < 8; s <<= 1)
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj)
-                    if ((jj & s) == 0)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) BFLY28(d[jb][jj][r], d[jb][jj + s][r]);
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) {
-                BFLY28(d[jb][jj][0], d[jb][jj][1]);
-                BFLY28(d[jb][jj][2], d[jb][jj][3]);
-                BFLY28(d[jb][jj][0], d[jb][jj][2]);
-                BFLY28(d[jb][jj][1], d[jb][jj][3]);
-            }
-        }
+        for (int jb = 0; jb < 4; ++jb) k28_block_stages(d[jb]);
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj)
 #pragma unroll
@@ -319,21 +398,7 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
                         *reinterpret_cast<float4*>(a.rot_out + m * (int64_t)K28 + ch0 + c) = make_float4(rr[0], rr[1], rr[2], rr[3]);
                 }
         if (!row_valid) { mn = INFINITY; mx = -INFINITY; }
-        // wave reduction, then the two halves of the token through LDS
-        mn = fminf(mn, dppf<0xB1>(mn)); mx = fmaxf(mx, dppf<0xB1>(mx));
-        mn = fminf(mn, dppf<0x4E>(mn)); mx = fmaxf(mx, dppf<0x4E>(mx));
-        mn = fminf(mn, dppf<0x141>(mn)); mx = fmaxf(mx, dppf<0x141>(mx));
-        mn = fminf(mn, dppf<0x140>(mn)); mx = fmaxf(mx, dppf<0x140>(mx));
-        {
-            float lo4[4], hi4[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                lo4[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mn), 16 * q));
-                hi4[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), 16 * q));
-            }
-            mn = fminf(fminf(lo4[0], lo4[1]), fminf(lo4[2], lo4[3]));
-            mx = fmaxf(fmaxf(hi4[0], hi4[1]), fmaxf(hi4[2], hi4[3]));
-        }
+        k28_wave_range(mn, mx);                            // then the two halves of the token through LDS
         const int* myred = red + (parity * TOKENS + tok_in_blk) * 8;
         const int* otherred = red + ((parity ^ 1) * TOKENS + tok_in_blk) * 8;
         if (lane == 0) {
@@ -365,39 +430,8 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
         int sum = 0;
         uint32_t words[4][4];                              // [jb][r]: 16 bytes of codes per jb
 #pragma unroll
-        for (int jb = 0; jb < 4; ++jb) {
-            v16f qe, qo;                                   // the clamped values before rounding: low / high nibbles
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                uint32_t ev = 0, od = 0;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    const float t0 = __builtin_amdgcn_fmed3f(fmaf(d[jb][2 * p][r], inv, nlo), 0.0f, 15.0f);
-                    const float t1 = __builtin_amdgcn_fmed3f(fmaf(d[jb][2 * p + 1][r], inv, nlo), 0.0f, 15.0f);
-                    ev = __builtin_amdgcn_cvt_pk_u8_f32(t0, p, ev);
-                    od = __builtin_amdgcn_cvt_pk_u8_f32(t1, p, od);
-                    qe[4 * r + p] = t0;
-                    qo[4 * r + p] = t1;
-                }
-                if (row_valid) {
-                    sum = __builtin_amdgcn_udot4(ev, 0x01010101u, sum, false);
-                    sum = __builtin_amdgcn_udot4(od, 0x01010101u, sum, false);
-                }
-                words[jb][r] = ev | (od << 4);
-            }
-            if (a.Aq6 && row_valid && tok_valid) {
-                // The 32 codes of group jb once more, as e2m3 numbers q/8, straight from the clamped values: the
-                // packed conversion divides by its scale operand, rounds to nearest-even (on the e2m3 grid below 2
-                // that is t/8 -> rint(t)/8, ties as in the integer conversion) and interleaves its two sources.
-                // A lane's 128 channels are one 128-code chunk of the fp6 layout: chunk 4*i' + g, group jb.
-                const v6i f6 = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(qe, qo, 8.0f);
-                const int rr = (int)(m & 31);
-                uint8_t* blk = a.Aq6 + ((int64_t)(4 * ip + g) * rb6 + (m >> 5)) * 3072;
-                *reinterpret_cast<uint4*>(blk + 64 * rr + 16 * (jb ^ ((rr >> 2) & 3))) =
-                    make_uint4((uint32_t)f6[0], (uint32_t)f6[1], (uint32_t)f6[2], (uint32_t)f6[3]);
-                *reinterpret_cast<uint2*>(blk + 2048 + 256 * jb + 8 * rr) = make_uint2((uint32_t)f6[4], (uint32_t)f6[5]);
-            }
-        }
+        for (int jb = 0; jb < 4; ++jb)
+            k28_quantise_group(a, d[jb], inv, nlo, row_valid, a.Aq6 && row_valid && tok_valid, m, rb6, 4 * ip + g, jb, words[jb], sum);
         // A lane holds 64 consecutive output bytes as four 16-byte pieces.  Transposing the pieces over
         // (jb, g) lets every store instruction write whole 64-byte segments (piece jb of lane g goes to
         // register g of lane jb), instead of four partial writes per segment.
@@ -419,12 +453,7 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
                     nt_store16(orow + 64 * j, make_uint4(words[j][0], words[j][1], words[j][2], words[j][3]));
             }
         }
-        sum += dppi<0xB1>(sum);
-        sum += dppi<0x4E>(sum);
-        sum += dppi<0x141>(sum);
-        sum += dppi<0x140>(sum);
-        sum = __builtin_amdgcn_readlane(sum, 0) + __builtin_amdgcn_readlane(sum, 16) +
-              __builtin_amdgcn_readlane(sum, 32) + __builtin_amdgcn_readlane(sum, 48);
+        sum = k28_wave_sum(sum);
         if (lane == 0) lds_write(myred + half * 4 + 2, sum);
         prev_m = tok_valid ? m : -1;
         prev_s = s; prev_lo = lo;
@@ -447,6 +476,173 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
+// Few tokens: one to a workgroup, four waves.  A call this small is all latency -- a wave alone on its SIMD takes five to six cycles
+// an instruction, 5.6 us for the 2450 of half a token -- and the split divides the chain: wave (half, part) takes output rows
+// [16 half, 16 half + 16) of column blocks 2 part and 2 part + 1.  Parts exchange by way of LDS in front of the stage over the
+// upper block bit, after which a wave has columns jj = 4 part .. + 3 of all four blocks, and behind the range, after which it
+// has its two blocks' 32-channel groups whole again.  Every sum is that of the two-wave kernel, in its order.
+// With two waves a token one took 8.2 us, 64 9.5 and 256 10.9; as built 6.1, 6.9 and 8.4 (64 with both vectors 10.8 and 8.0).  LDS holds
+// one workgroup per compute unit, so more than 256 tokens would take two rounds (257 .. 512 on two waves 10.9 - 12.6).
+template <bool HAS_BIAS, bool HAS_SCALE>
+__global__ __launch_bounds__(256, 1) void rotate_quant_k28_split_kernel(RotateQuantArgs a, float norm, H28Cols hc) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int VECTORS = (HAS_BIAS ? 1 : 0) + (HAS_SCALE ? 1 : 0);
+    constexpr int SCALE_AT = HAS_BIAS ? K28_VEC_BYTES : 0;
+    constexpr int XCH_AT = VECTORS * K28_VEC_BYTES, RED_AT = XCH_AT + 4 * 8 * 1024;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[RED_AT + 4 * 16];
+    int* red = reinterpret_cast<int*>(lds + RED_AT);       // [wave][mn, mx, sum, -]
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int half = wave & 1, part = wave >> 1;
+    const int g = lane >> 4, m16 = lane & 15;
+    const int ip = 16 * half + m16;
+    const bool row_valid = ip < 28;
+    const uint32_t signs = hc.col[row_valid ? ip : 27];    // requested first: a wait for it waits for nothing else
+    int64_t m = blockIdx.x;                                // 32 consecutive tokens on one XCD, as in the two-wave kernel
+    if ((gridDim.x & 127) == 0) m = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    v4u R[2][8];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) k28_load_block(R[b], a.X + m * a.ldx, 2 * part + b, K28 * 2, lane);
+    k28_stage_vectors<4, HAS_BIAS, HAS_SCALE>(a, lds, wave, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    const v8bf bop = k28_bop(signs, row_valid, g);
+
+    float d[2][8][4];                                      // [jb - 2 part][jj][r]
+#pragma unroll
+    for (int b = 0; b < 2; ++b) k28_h28_block(R[b], bop, d[b]);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) k28_block_stages(d[b]);
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) BFLY28(d[0][jj][r], d[1][jj][r]);
+
+    v4i* const mine = reinterpret_cast<v4i*>(lds + XCH_AT) + wave * 512 + lane;
+    const v4i* const theirs = reinterpret_cast<const v4i*>(lds + XCH_AT) + (wave ^ 2) * 512 + lane;
+    auto put = [&](int slot, const float (&v)[4]) {
+        mine[64 * slot] = v4i{__float_as_int(v[0]), __float_as_int(v[1]), __float_as_int(v[2]), __float_as_int(v[3])};
+    };
+    float e[4][4][4];                                      // [jb][jj - 4 part][r]
+    auto exchange_columns = [&](auto part_c) {
+        constexpr int P = decltype(part_c)::value;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) put(4 * b + k, d[b][4 * (1 - P) + k]);
+        lds_barrier();
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const v4i o = theirs[64 * (4 * b + k)];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float own = d[b][4 * P + k][r], other = __int_as_float(o[r]);
+                    e[b][k][r] = P ? other : own;
+                    e[2 + b][k][r] = P ? own : other;
+                    BFLY28(e[b][k][r], e[2 + b][k][r]);
+                }
+            }
+    };
+    if (part) exchange_columns(std::integral_constant<int, 1>{});
+    else exchange_columns(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            cross_lane_bfly<false>(e[0][k][r], e[1][k][r]);
+            cross_lane_bfly<false>(e[2][k][r], e[3][k][r]);
+            cross_lane_bfly<true>(e[0][k][r], e[2][k][r]);
+            cross_lane_bfly<true>(e[1][k][r], e[3][k][r]);
+        }
+
+    // the vectors have arrived, every wave's part of them, and every wave has read its partner's columns
+    wait_memory<0>();
+    lds_barrier();
+    const int vec_row = row_valid ? ip : 27;               // (rows past the matrix: any values, they go nowhere)
+    const int vec_at = vec_row * 2048 + g * 512 + 16 * ((vec_row & 15) ^ part);
+    float mn = INFINITY, mx = -INFINITY;
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int q = 8 * jb + 2 * r;                  // + part
+            const uint8_t* const at = lds + ((vec_at ^ (16 * (q & 15))) + 256 * (q >> 4));
+            v4i bb = {0, 0, 0, 0}, ss = {0, 0, 0, 0};
+            if (HAS_BIAS) bb = *reinterpret_cast<const v4i*>(at);
+            if (HAS_SCALE) ss = *reinterpret_cast<const v4i*>(at + SCALE_AT);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float rv = e[jb][k][r] * norm, bv = __int_as_float(bb[k]);
+                const float v = HAS_SCALE ? fmaf(rv, __int_as_float(ss[k]), -bv) : rv - bv;
+                e[jb][k][r] = v;
+                mn = fminf(mn, v);
+                mx = fmaxf(mx, v);
+            }
+        }
+    if (!row_valid) { mn = INFINITY; mx = -INFINITY; }
+    k28_wave_range(mn, mx);
+    if (lane == 0) {
+        red[4 * wave] = __float_as_int(mn);
+        red[4 * wave + 1] = __float_as_int(mx);
+    }
+    auto exchange_blocks = [&](auto part_c) {
+        constexpr int P = decltype(part_c)::value;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) put(4 * b + k, e[2 * (1 - P) + b][k]);
+        lds_barrier();
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const v4i o = theirs[64 * (4 * b + k)];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    d[b][4 * P + k][r] = e[2 * P + b][k][r];
+                    d[b][4 * (1 - P) + k][r] = __int_as_float(o[r]);
+                }
+            }
+    };
+    if (part) exchange_blocks(std::integral_constant<int, 1>{});
+    else exchange_blocks(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        mn = fminf(mn, __int_as_float(red[4 * w]));
+        mx = fmaxf(mx, __int_as_float(red[4 * w + 1]));
+    }
+
+    const float lo = a.clip_lo * mn;
+    const float hi = a.clip_hi * mx;
+    float s = __fdiv_rn(hi - lo, 15.0f);
+    if (!(s > 0.0f && s < INFINITY)) s = 1.0f;
+    const float inv = __fdiv_rn(1.0f, s);
+    const float nlo = -(lo * inv);
+    int sum = 0;
+    const int64_t rb6 = (a.M + 31) >> 5;
+    uint32_t words[2][4];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+        k28_quantise_group(a, d[b], inv, nlo, row_valid, a.Aq6 && row_valid, m, rb6, 4 * ip + g, 2 * part + b, words[b], sum);
+    if (a.Aq && row_valid) {
+        uint8_t* dst = a.Aq + m * (int64_t)(K28 / 2) + ip * 256 + 64 * g + 32 * part;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) *reinterpret_cast<uint4*>(dst + 16 * b) = make_uint4(words[b][0], words[b][1], words[b][2], words[b][3]);
+    }
+    sum = k28_wave_sum(sum);
+    if (lane == 0) red[4 * wave + 2] = sum;
+    lds_barrier();
+    if (threadIdx.x == 0) {
+        basq_tokmeta mt;
+        mt.scale = s; mt.lo = lo;
+        mt.rowsum = red[2] + red[6] + red[10] + red[14];
+        mt.reserved = 0;
+        a.meta[m] = mt;
+    }
+#endif  // __HIP_DEVICE_COMPILE__
+}
+
 template <int TOKENS, bool HB, bool HS, int STAGED>
 int launch_k28_form(const RotateQuantArgs& a, hipStream_t s, float norm, const H28Cols& hc, int max_blocks) {
     const int64_t want = (a.M + TOKENS - 1) / TOKENS;
@@ -458,10 +654,14 @@ int launch_k28_form(const RotateQuantArgs& a, hipStream_t s, float norm, const H
     return check_hip(hipGetLastError(), "rotate_quant (28x512) launch");
 }
 
-// Calls that fit one round of two-token workgroups (two per compute unit, one where both vectors fill its LDS) take them: they
+// Up to a token a compute unit (without the fp32 rotation written out): four waves a token.  Calls that fit one round of two-token workgroups (two per compute unit, one where both vectors fill its LDS) take them: they
 // spread over twice the compute units.  More tokens: four to a workgroup, and the next ones' blocks by way of LDS.
 template <bool HB, bool HS>
 int launch_k28_flags(const RotateQuantArgs& a, hipStream_t s, float norm, const H28Cols& hc) {
+    if (a.M <= K28_CUS && !a.rot_out) {
+        hipLaunchKernelGGL((rotate_quant_k28_split_kernel<HB, HS>), dim3((unsigned)a.M), dim3(256), 0, s, a, norm, hc);
+        return check_hip(hipGetLastError(), "rotate_quant (28x512, split) launch");
+    }
     constexpr int PER_CU = (HB && HS) ? 1 : 2;
     if (a.M <= 2 * PER_CU * K28_CUS) return launch_k28_form<2, HB, HS, 0>(a, s, norm, hc, PER_CU * K28_CUS);
     return launch_k28_form<4, HB, HS, (HB && HS) ? 1 : 3>(a, s, norm, hc, K28_CUS);
