@@ -115,13 +115,30 @@ __global__ __launch_bounds__(RH_THREADS) void rotate_quant_head_kernel(RotateQua
     if (m < a.M) request(m, c);                                // before the staging below, whose barrier would wait for more
 
     if (HAS_BIAS || HAS_SCALE) {
-        for (int f = threadIdx.x; f < K / 2; f += RH_THREADS) {
-            // float2 number f of the staged copy: lane f%64, r = (f/64)%4, c = f/256
-            const int ln = f & 63, r = (f >> 6) & 3, cc = f >> 8;
-            const int e = 512 * cc + 128 * (ln >> 4) + 32 * r + 2 * (ln & 15);
-            if (HAS_BIAS) lbias[f] = *reinterpret_cast<const float2*>(a.bias + e);
-            if (HAS_SCALE) lscale[f] = *reinterpret_cast<const float2*>(a.act_scale + e);
-        }
+        // Up to eight pieces requested before the first is written (a piece at a time is a memory latency each, eight in a row in
+        // front of everything at K = 4096: 1 token 3.35 -> 2.72 us, 1024 6.9 -> 6.1, 8192 23.1 -> 22.3; K = 8192, 512 tokens 7.9 -> 6.6).
+        static_assert(RH_THREADS == 256, "a piece is an item: float2 number f of the staged copy is lane f%64, r = (f/64)%4, c = f/256");
+        const int at = threadIdx.x, items = K / 512;
+        const int e = 128 * ((at & 63) >> 4) + 32 * (at >> 6) + 2 * (at & 15);
+        auto stage = [&](int c0, auto count_c) {
+            constexpr int COUNT = decltype(count_c)::value;
+            float2 bv[COUNT], sv[COUNT];
+#pragma unroll
+            for (int i = 0; i < COUNT; ++i) {
+                if (HAS_BIAS) bv[i] = *reinterpret_cast<const float2*>(a.bias + 512 * (c0 + i) + e);
+                if (HAS_SCALE) sv[i] = *reinterpret_cast<const float2*>(a.act_scale + 512 * (c0 + i) + e);
+            }
+#pragma unroll
+            for (int i = 0; i < COUNT; ++i) {
+                if (HAS_BIAS) lbias[256 * (c0 + i) + at] = bv[i];
+                if (HAS_SCALE) lscale[256 * (c0 + i) + at] = sv[i];
+            }
+        };
+        int c0 = 0;
+        for (; c0 + 8 <= items; c0 += 8) stage(c0, std::integral_constant<int, 8>{});
+        if (items & 4) { stage(c0, std::integral_constant<int, 4>{}); c0 += 4; }
+        if (items & 2) { stage(c0, std::integral_constant<int, 2>{}); c0 += 2; }
+        if (items & 1) stage(c0, std::integral_constant<int, 1>{});
         __syncthreads();
     }
 
