@@ -104,7 +104,7 @@ __global__ __launch_bounds__(LD_THREADS, 1) void linear_decode_kernel(RotateQuan
     float cb = 0.0f;
     if (g.out_bias) cb = g.out_bias[on_c];
     __builtin_amdgcn_sched_barrier(0);
-    {                                                     // the staged layout of p2_stage_bias
+    {                                                     // the staged layout of p2_stage_vectors
         float4* dstb = reinterpret_cast<float4*>(lbias_s);
         float4* dsts = reinterpret_cast<float4*>(lscale_s);
 #define LD_VEC_STAGE(i) do { \

@@ -133,10 +133,37 @@ __device__ __forceinline__ void p2_stage_bias(float* lds_bias, const float* bias
     }
 }
 
+// Both vectors, four pieces of each requested before the first is written: in the loop above a piece is a memory latency, two to
+// eight in a row in front of the kernel.  K = 4096, 16 tokens 4.49 -> 4.34 us, 333 with both vectors 6.28 -> 6.14, 2048 10.05 -> 9.85,
+// with groups of 128 11.65 -> 10.9; K = 8192, 64 tokens 5.46 -> 5.37.  The one-wave kernel of K = 8192, whose token is requested
+// behind them, keeps the loop: 333 tokens 9.79, 9.89 with batches of four, 10.03 with eight at once.
+template <int K, int THREADS, bool HAS_BIAS, bool HAS_SCALE>
+__device__ __forceinline__ void p2_stage_vectors(float* lds_bias, const float* bias, float* lds_scale, const float* scale, int tid) {
+    constexpr int PIECES = K / 4 / THREADS, BATCH = PIECES < 4 ? PIECES : 4;
+    static_assert(PIECES % BATCH == 0 && PIECES * THREADS * 4 == K, "whole batches of whole pieces");
+#pragma unroll
+    for (int b = 0; b < PIECES; b += BATCH) {
+        float4 bv[BATCH], sv[BATCH];
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) {
+            if (HAS_BIAS) bv[i] = *reinterpret_cast<const float4*>(bias + 4 * (tid + (b + i) * THREADS));
+            if (HAS_SCALE) sv[i] = *reinterpret_cast<const float4*>(scale + 4 * (tid + (b + i) * THREADS));
+        }
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) {
+            const int e = 4 * (tid + (b + i) * THREADS);   // channels e .. e+3 belong to lane (e%2048)/32, piece (e%32)/4
+            const int at = ((e >> 11) * 8 + ((e & 31) >> 2)) * 64 + ((e & 2047) >> 5);
+            if (HAS_BIAS) reinterpret_cast<float4*>(lds_bias)[at] = bv[i];
+            if (HAS_SCALE) reinterpret_cast<float4*>(lds_scale)[at] = sv[i];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 struct P2Meta { float scale, lo; int rowsum; };
 
 // raw: the token as loaded with P2Lane::chunk (raw[c] = 16 bytes at channel 512*c + 8*chunk).  wl: this wave's
-// P2_LDS_WORDS floats.  lbias, lscale: b^c and s^a as staged by p2_stage_bias (s^a read from memory here would be
+// P2_LDS_WORDS floats.  lbias, lscale: b^c and s^a as staged by p2_stage_vectors (s^a read from memory here would be
 // a load per 16 bytes behind whatever the caller has in flight -- its prefetched next token, a weight stream --
 // and loads complete in issue order).  rot_row: where the fp32 rotation of this token goes (ROT_OUT).
 // after_mfma(): called once raw[] is dead.  sink(hf, b, words, te, to): the 32 codes of channels

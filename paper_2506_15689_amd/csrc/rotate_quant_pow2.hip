@@ -71,8 +71,12 @@ __global__ __launch_bounds__(WAVES * 64, p2_waves_per_simd(NC, WAVES, ROT_OUT, G
     // 64 registers live around the loop and the kernel spills)
     int64_t m = wave_id;
     if (PREFETCH && m < a.M) load_token(m);
-    if (HAS_BIAS) p2_stage_bias<K>(lds, a.bias, threadIdx.x, THREADS);
-    if (HAS_SCALE) p2_stage_bias<K>(lds + BIAS_WORDS, a.act_scale, threadIdx.x, THREADS);
+    if (PREFETCH) {
+        p2_stage_vectors<K, THREADS, HAS_BIAS, HAS_SCALE>(lds, a.bias, lds + BIAS_WORDS, a.act_scale, threadIdx.x);
+    } else {
+        if (HAS_BIAS) p2_stage_bias<K>(lds, a.bias, threadIdx.x, THREADS);
+        if (HAS_SCALE) p2_stage_bias<K>(lds + BIAS_WORDS, a.act_scale, threadIdx.x, THREADS);
+    }
     if (HAS_BIAS || HAS_SCALE) __syncthreads();
 
     // One round per iteration: the workgroup's waves take WAVES consecutive tokens (a whole number of rounds for
@@ -169,8 +173,7 @@ __global__ __launch_bounds__(256) void rotate_quant_pow2_split_kernel(RotateQuan
 #pragma unroll
         for (int j = 0; j < 4; ++j) raw4[j] = nt_load16(x + 512 * j);
     }
-    if (HAS_BIAS) p2_stage_bias<K>(lbias_s, a.bias, tid, 256);          // complete behind the routine's first barrier
-    if (HAS_SCALE) p2_stage_bias<K>(lscale_s, a.act_scale, tid, 256);
+    p2_stage_vectors<K, 256, HAS_BIAS, HAS_SCALE>(lbias_s, a.bias, lscale_s, a.act_scale, tid);   // complete behind the routine's first barrier
     const P2Meta tm = p2_token_split<NWAY, NC == 8, HAS_BIAS, HAS_SCALE>(
         active, part, raw4, bop, tr + wave * P2_LDS_WORDS, xch + tl * (NWAY * 512), lred + tl * (NWAY * 2),
         reinterpret_cast<const float4*>(lbias_s), reinterpret_cast<const float4*>(lscale_s), norm, a.clip_lo, a.clip_hi, lane,
