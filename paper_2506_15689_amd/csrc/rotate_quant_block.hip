@@ -213,12 +213,29 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
     }
 
     // ---- pass 1: rotate, bias, range ---------------------------------------------------------------------------
+    // b^c and s^a of a piece are requested a piece ahead, without a branch (past the token: its first piece's once more):
+    // requested where they are used they were a cache latency in front of every piece (K = 11008: 1 token 5.9 -> 4.3 us, 256 8.4 -> 6.7,
+    // 2048 25.8 -> 24.2, 4096 49.2 -> 45.6).  The token's loads without their branches, on a descriptor that ends with it: 4.4, 6.9,
+    // 24.6, 46.9.
+    float2 bb[2][4], ss[2][4];
+    auto request_vectors = [&](int p) {
+        const int e0 = 512 * (wave + RB_WAVES * p) + eout;
+        const int e1 = e0 < K ? e0 : eout;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (HAS_BIAS) bb[p & 1][r] = *reinterpret_cast<const float2*>(a.bias + e1 + 8 * r);
+            if (HAS_SCALE) ss[p & 1][r] = *reinterpret_cast<const float2*>(a.act_scale + e1 + 8 * r);
+        }
+    };
+    request_vectors(0);
     float v[RB_PMAX][2][4];
     float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
     for (int p = 0; p < RB_PMAX; ++p) {
         const int c = wave + RB_WAVES * p;
         if (c < np) {                                  // uniform over the wave
+            if (p + 1 < RB_PMAX) request_vectors(p + 1);
+            __builtin_amdgcn_sched_barrier(0);
             float d[2][4];
             rb_rotate_piece(raw[p], bop, d);
             const int e0 = 512 * c + eout;
@@ -226,14 +243,12 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int e = e0 + 8 * r;              // channels e (h = 0) and e + 1 (h = 1)
-                float2 bb = make_float2(0.f, 0.f), ss = make_float2(1.f, 1.f);
-                if (HAS_BIAS && ok) bb = *reinterpret_cast<const float2*>(a.bias + e);
-                if (HAS_SCALE && ok) ss = *reinterpret_cast<const float2*>(a.act_scale + e);
+                const float2 b2 = HAS_BIAS ? bb[p & 1][r] : make_float2(0.f, 0.f), s2 = HAS_SCALE ? ss[p & 1][r] : make_float2(1.f, 1.f);
                 float r0 = d[0][r], r1 = d[1][r];
                 if (!FOLD_NORM) { r0 = r0 * norm; r1 = r1 * norm; }
                 if (ROT_OUT && ok) *reinterpret_cast<float2*>(a.rot_out + m * (int64_t)K + e) = make_float2(r0, r1);
-                const float v0 = HAS_SCALE ? fmaf(r0, ss.x, -bb.x) : r0 - bb.x;
-                const float v1 = HAS_SCALE ? fmaf(r1, ss.y, -bb.y) : r1 - bb.y;
+                const float v0 = HAS_SCALE ? fmaf(r0, s2.x, -b2.x) : r0 - b2.x;
+                const float v1 = HAS_SCALE ? fmaf(r1, s2.y, -b2.y) : r1 - b2.y;
                 v[p][0][r] = v0;
                 v[p][1][r] = v1;
                 if (ok) {
