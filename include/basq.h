@@ -302,7 +302,7 @@ int basq_calibrate_bias(const void* X, int64_t M, int32_t K, int64_t ldx, int32_
  * int8 (Paley type-I construction over GF(27) = GF(3)[t]/(t^3 + 2t + 1)). */
 int basq_hadamard28(int8_t* out_host);
 
-/* ---- diagnostics: what this machine sustains (used by the benchmark's measured ceilings), single tilings ---- */
+/* ---- diagnostics: what this machine sustains (used by the benchmark's measured ceilings), single tilings, bounds ---- */
 
 /*
  * Pure streaming kernel with the access pattern of basq_rotate_quant (the paper's fused quant kernel,
@@ -353,6 +353,13 @@ int basq_diag_w4a4_gemm_fp6_split(int32_t tiling, const basq_tokmeta* meta, int6
                                   const void* w_scale, const void* w_zero, const float* w_sum, const float* out_bias,
                                   void* Y, int64_t ldy, int32_t* acc_out,
                                   const uint8_t* Aq6, const uint8_t* Wq6, void* stream);
+
+/*
+ * The blockwise rotations with per-token ranges request bias and act_scale without a test for the token's end.  Computed on the
+ * host with the kernel's own index: one past the last channel that it requests of either, for a token of K channels, K a
+ * multiple of 256 up to 16384 (otherwise BASQ_EINVAL); at most K.
+ */
+int basq_diag_block_vector_channels(int32_t K);
 
 #ifdef __cplusplus
 }

@@ -24,7 +24,8 @@ STREAM_MAX_TOKENS = 128      # calls of more tokens never take the weight-stream
 EXPORTS = ["basq_version", "basq_last_error", "basq_rotate_quant", "basq_w4a4_gemm", "basq_workspace_bytes",
            "basq_w4a4_gemm_grouped", "basq_group_colsums", "basq_fp6_bytes", "basq_pack_fp6", "basq_decode_bytes", "basq_pack_decode", "basq_linear_fused", "basq_linear_fused_static", "basq_rotate_weights", "basq_quantize_weights", "basq_fused_bias", "basq_prepare_weights", "basq_calibrate_bias",
            "basq_hadamard28", "basq_diag_stream", "basq_diag_read", "basq_diag_mfma_i8", "basq_diag_mfma_f6",
-           "basq_diag_fp6_tiling", "basq_diag_w4a4_gemm_fp6", "basq_diag_fp6_split_tiling", "basq_diag_w4a4_gemm_fp6_split"]
+           "basq_diag_fp6_tiling", "basq_diag_w4a4_gemm_fp6", "basq_diag_fp6_split_tiling", "basq_diag_w4a4_gemm_fp6_split",
+           "basq_diag_block_vector_channels"]
 
 
 class BasqError(RuntimeError):
@@ -101,6 +102,8 @@ def load() -> ctypes.CDLL:
     for name in ("basq_diag_w4a4_gemm_fp6", "basq_diag_w4a4_gemm_fp6_split"):
         getattr(lib, name).restype = c.c_int
         getattr(lib, name).argtypes = [i32, vp, i64, i32, i32, vp, vp, vp, vp, vp, i64, vp, vp, vp, vp]
+    lib.basq_diag_block_vector_channels.restype = c.c_int
+    lib.basq_diag_block_vector_channels.argtypes = [i32]
     _lib = lib
     return lib
 
@@ -372,6 +375,11 @@ def basq_diag_w4a4_gemm_fp6(tiling: int, meta: torch.Tensor, K: int, w_scale: to
     run = load().basq_diag_w4a4_gemm_fp6_split if split else load().basq_diag_w4a4_gemm_fp6
     _check(run(tiling, _p(meta), M, K, N, _p(w_scale), _p(w_zero), _p(w_sum), _p(out_bias),
                _p(Y), Y.stride(0) if M > 0 else N, _p(acc_out), _p(Aq6), _p(Wq6), _stream(stream)))
+
+
+def basq_diag_block_vector_channels(K: int) -> int:
+    """One past the last channel of bias and act_scale that the blockwise rotation requests for tokens of K channels."""
+    return int(load().basq_diag_block_vector_channels(K))
 
 
 # ---- allocation helpers (device memory only; no arithmetic) ----------------------------------

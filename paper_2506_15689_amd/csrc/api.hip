@@ -267,6 +267,11 @@ int basq_w4a4_gemm_grouped(const uint8_t* Aq, const basq_tokmeta* meta, int64_t 
     return launch_gemm_grouped(g, w_gsum, static_cast<hipStream_t>(stream));
 }
 
+int basq_diag_block_vector_channels(int32_t K) {
+    if (K < 256 || K > 16384 || K % 256 != 0) return fail(BASQ_EINVAL, "K must be a multiple of 256 up to 16384 (got %d)", K);
+    return rotate_quant_block_vector_channels(K);
+}
+
 static bool shape_takes_fp6(int64_t M, int32_t K, int32_t N) {
     alignas(16) static const uint8_t given[16] = {};           // stands for both operands: only whether they are given counts
     GemmArgs g{};

@@ -41,6 +41,7 @@ int launch_rotate_quant_head(const RotateQuantArgs& a, hipStream_t s);
 // blockwise rotations of 128, 256 or 512 channels with per-token ranges, K <= 16384 (rotate_quant_block.hip)
 bool rotate_quant_block_applicable(const RotateQuantArgs& a);
 int launch_rotate_quant_block(const RotateQuantArgs& a, hipStream_t s);
+int rotate_quant_block_vector_channels(int32_t K);               // one past the last channel of b^c and s^a that it requests
 // rot_size == K in {512, 1024, 2048}: one wave per token (rotate_quant_block.hip)
 bool rotate_quant_small_applicable(const RotateQuantArgs& a);
 int launch_rotate_quant_small(const RotateQuantArgs& a, hipStream_t s);

@@ -106,9 +106,16 @@ __device__ __forceinline__ void rb_rotate_piece(const uint4& raw, const v8bf (&b
 }
 
 // where a lane's values of a piece end up: e = rb_eout + h + 8*r0 + 16*r1
-__device__ __forceinline__ int rb_eout(int lane) {
+__host__ __device__ __forceinline__ int rb_eout(int lane) {
     return 2 * (lane & 1) + 4 * ((lane >> 1) & 1) + 128 * ((lane >> 2) & 1) + 256 * ((lane >> 3) & 1) +
            32 * ((lane >> 4) & 1) + 64 * ((lane >> 5) & 1);
+}
+// The channel from which a lane requests its values of b^c and s^a for piece p of its wave, two at +8*r, r = 0..3.  Past the
+// token (the missing half of a last piece, pieces that do not exist) the values are not used: channels of the first 256, which
+// the smallest token has too.
+__host__ __device__ __forceinline__ int rb_vector_at(int K, int wave, int p, int eout) {
+    const int e0 = 512 * (wave + RB_WAVES * p) + eout;
+    return e0 < K ? e0 : eout & 255;
 }
 // the 32-channel segment of the piece whose codes the lane's quad holds
 __device__ __forceinline__ int rb_segment(int lane) {
@@ -213,18 +220,17 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
     }
 
     // ---- pass 1: rotate, bias, range ---------------------------------------------------------------------------
-    // b^c and s^a of a piece are requested a piece ahead, without a branch (past the token: its first piece's once more):
+    // b^c and s^a of a piece are requested a piece ahead, without a branch (past the token: see rb_vector_at):
     // requested where they are used they were a cache latency in front of every piece (K = 11008: 1 token 5.9 -> 4.3 us, 256 8.4 -> 6.7,
     // 2048 25.8 -> 24.2, 4096 49.2 -> 45.6).  The token's loads without their branches, on a descriptor that ends with it: 4.4, 6.9,
     // 24.6, 46.9.
     float2 bb[2][4], ss[2][4];
     auto request_vectors = [&](int p) {
-        const int e0 = 512 * (wave + RB_WAVES * p) + eout;
-        const int e1 = e0 < K ? e0 : eout;
+        const int at = rb_vector_at(K, wave, p, eout);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            if (HAS_BIAS) bb[p & 1][r] = *reinterpret_cast<const float2*>(a.bias + e1 + 8 * r);
-            if (HAS_SCALE) ss[p & 1][r] = *reinterpret_cast<const float2*>(a.act_scale + e1 + 8 * r);
+            if (HAS_BIAS) bb[p & 1][r] = *reinterpret_cast<const float2*>(a.bias + at + 8 * r);
+            if (HAS_SCALE) ss[p & 1][r] = *reinterpret_cast<const float2*>(a.act_scale + at + 8 * r);
         }
     };
     request_vectors(0);
@@ -431,6 +437,18 @@ bool rotate_quant_block_applicable(const RotateQuantArgs& a) {
     return a.group == a.K && !a.has28 && (a.rot_size == 128 || a.rot_size == 256 || a.rot_size == 512) &&
            a.K % 256 == 0 && a.K % a.rot_size == 0 && a.K <= RB_WAVES * RB_PMAX * 512 &&
            (a.Aq != nullptr || a.Aq6 != nullptr) && a.meta != nullptr && a.M <= 0x7FFFFFFFll;
+}
+
+int rotate_quant_block_vector_channels(int32_t K) {
+    int end = 0;
+    const int np = (K + 511) / 512;
+    for (int wave = 0; wave < RB_WAVES; ++wave)
+        for (int p = 0; p < RB_PMAX && (p == 0 || wave + RB_WAVES * (p - 1) < np); ++p)    // piece p is requested with piece p - 1
+            for (int lane = 0; lane < 64; ++lane) {
+                const int last = rb_vector_at(K, wave, p, rb_eout(lane)) + 8 * 3 + 1;
+                if (last >= end) end = last + 1;
+            }
+    return end;
 }
 
 bool rotate_quant_small_applicable(const RotateQuantArgs& a) {

@@ -84,6 +84,14 @@ def test_fp6_split_tilings_by_name(lib):
     assert call(0, K=32768 + 128) == B.BASQ_EUNSUPPORTED
 
 
+def test_blockwise_rotation_requests_no_channel_past_the_token(lib):
+    """b^c and s^a have K values each; what is requested for the missing half of a last piece, and for pieces that do not
+    exist, must lie inside them too, down to the smallest token (K = 256, half a piece)."""
+    for K in range(256, 16384 + 1, 256):
+        assert B.basq_diag_block_vector_channels(K) == K
+    assert [lib.basq_diag_block_vector_channels(K) for K in (0, 128, 384, 16640)] == [B.BASQ_EINVAL] * 4
+
+
 FAKE = ctypes.c_void_p(0x1000)      # aligned, never dereferenced: validation fails first
 
 
