@@ -63,9 +63,16 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     constexpr int ROWS = BM + BN;
     constexpr int STAGE_BYTES = ROWS * CHUNK;
     constexpr int PIECES = STAGE_BYTES / 1024;                // 1 KB pieces of a stage, one wave-load each
-    constexpr int LOADS = (PIECES + WAVES - 1) / WAVES;       // direct loads per thread per stage (the last one may read nothing)
-    constexpr bool PARTIAL = PIECES % WAVES != 0;
     constexpr int A_PIECES = BM * CHUNK / 1024;               // pieces 0 .. A_PIECES-1 of a stage are activations
+    // Direct loads per wave per stage, the same number for all waves: whole pieces, and of the last PIECES % WAVES pieces an equal
+    // share, SHARES times 256 bytes (4 a lane); where they do not divide so, or a round holds pieces of both operands as well,
+    // the waves without a piece in the last round load nothing there (see issue_one).
+    constexpr int WHOLE = PIECES / WAVES, LEFT = PIECES % WAVES;
+    constexpr bool SHARED = LEFT != 0 && LEFT * 4 % WAVES == 0 && A_PIECES % WAVES == 0;
+    constexpr bool PADDED = LEFT != 0 && !SHARED;
+    constexpr int SHARES = SHARED ? LEFT * 4 / WAVES : 0;
+    constexpr int LOADS = WHOLE + (PADDED ? 1 : SHARES);
+    static_assert(LEFT == 0 || WHOLE * WAVES >= A_PIECES, "the last pieces are weights");
     static_assert(STAGE_BYTES % 1024 == 0, "a stage is a whole number of 1 KB pieces");
     static_assert(BM % 32 == 0 && BN % 32 == 0, "tiles are made of 32-row blocks");
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
@@ -73,7 +80,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     static_assert(ROWS * 16 <= STAGE_BYTES, "the epilogue constants live in the last stage");
     static_assert(KGROUPS == 1 || (BM * BN * 4 + ROWS * 16 <= STAGES * STAGE_BYTES && TM % OWN == 0), "K groups exchange their sums through their rings");
 
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KGROUPS * STAGES * STAGE_BYTES + (PARTIAL ? 1024 : 0)];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KGROUPS * STAGES * STAGE_BYTES + (PADDED ? 1024 : 0)];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = (tid >> 6) % WAVES;
@@ -124,7 +131,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     auto set_tile = [&](int tile_m, int tile_n) {
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
-            const int piece = i * WAVES + swave;
+            const int share = swave * SHARES + i - WHOLE;      // number of the 256 bytes among the last pieces
+            const int piece = SHARED && i >= WHOLE ? WHOLE * WAVES + share / 4 : i * WAVES + swave;
             int blk = piece / 3;
             const int part = piece % 3;
             if (piece < A_PIECES) {
@@ -134,22 +142,31 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
                 blk += tile_n * (BN / 32) - BM / 32;
                 blk = blk < rb_w ? blk : rb_w - 1;
             }
-            soff[i] = blk * BLOCK + part * 1024;
+            soff[i] = blk * BLOCK + part * 1024 + (SHARED && i >= WHOLE ? share % 4 * 256 : 0);
         }
     };
     // load number i of a K-step: into the stage at byte stage_off of the ring, from chunk offsets koff_a / koff_w (unsigned
-    // 32-bit byte offsets).  No branches, which cost tens of cycles each: where only some waves have an i-th piece, the others'
-    // lanes point past the end of the operand, so that the load reads nothing, and at a place in LDS that nobody reads; where a
-    // round holds pieces of both operands, descriptor and offset are selected (333 x 4096 x 4096 on 96 x 64: 10.3 -> 9.4 us; with a
-    // partial last round alone even).
-    const int last_off = PARTIAL && (LOADS - 1) * WAVES + swave >= PIECES ? (int)0xFFFFFF00u : lane_off;
+    // 32-bit byte offsets).  No branches, which cost tens of cycles a step: where a round holds pieces of both operands,
+    // descriptor and offset are selected; waves without a piece in a padded last round load from past the end of the operand,
+    // so that nothing is read, to a place in LDS that nobody reads (96 x 64, 333 x 4096 x 4096: 10.3 -> 9.4 us).  Loads of nothing take the
+    // time of loads all the same, though, which shows with weights from memory: shares instead where the pieces divide (us with
+    // weights from memory; in the caches.  256 x 192, six of eight waves without a piece: 2048 x 4096 x 12288 padded 61.5; 57.9, by
+    // shares 60.1; 57.9, with a branch 59.8; 58.0; 1021 x 8192 x 11008 54.7; 47.3, 52.6; 47.1, 52.3; 47.8.  256 x 128, four of eight:
+    // 777 x 14336 x 5008 52.9; 46.4, 50.0; 46.7, 51.1; 47.1; 2048 x 14336 x 4096 69.9; 60.6, 69.3; 61.2, 68.8; 62.7.  96 x 64:
+    // 333 x 4096 x 4096 padded 11.2; 8.4, by shares 11.1; 8.9).
+    const int last_off = PADDED && WHOLE * WAVES + swave >= PIECES ? (int)0xFFFFFF00u : lane_off;
     auto issue_one = [&](int stage_off, unsigned koff_a, unsigned koff_w, int i) {
-        const bool some = (i + 1) * WAVES > PIECES;            // of the waves have this piece
+        if (SHARED && i >= WHOLE) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, LDS_PTR(lds + stage_off + WHOLE * WAVES * 1024 + (swave * SHARES + i - WHOLE) * 256), 4, lane * 4,
+                                                     (int)(koff_w + (unsigned)soff[i]), 0, 0);
+            return;
+        }
+        const bool last = i >= WHOLE;
         const bool mixed = i * WAVES < A_PIECES && (i + 1) * WAVES > A_PIECES;
         const bool is_a = mixed ? i * WAVES + swave < A_PIECES : i * WAVES < A_PIECES;
         uint8_t* dst = lds + stage_off + swave * 1024 + i * WAVES * 1024;
-        if (some) dst = i * WAVES + swave < PIECES ? dst : lds_all + KGROUPS * STAGES * STAGE_BYTES;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? rsrc_a : rsrc_w, LDS_PTR(dst), 16, some ? last_off : lane_off,
+        if (last) dst = i * WAVES + swave < PIECES ? dst : lds_all + KGROUPS * STAGES * STAGE_BYTES;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? rsrc_a : rsrc_w, LDS_PTR(dst), 16, last ? last_off : lane_off,
                                                  (int)((is_a ? koff_a : koff_w) + (unsigned)soff[i]), 0, 0);
     };
     constexpr int SPLIT = (LOADS + 1) / 2;                     // the first half of a stage's loads (see `half` below)
