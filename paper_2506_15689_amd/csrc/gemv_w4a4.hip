@@ -2,7 +2,7 @@
 // pass over the packed 4-bit weights, bound by HBM bandwidth up to about 64 tokens.  Same arithmetic as the
 // prefill GEMM (ACC in INT32, fused de-quantisation).
 //
-// A workgroup owns 16 or 32 output channels; its waves split K.  Each lane issues a batch of 16-byte weight
+// A workgroup owns one to four tiles of 16 output channels; its waves split K.  Each lane issues a batch of 16-byte weight
 // loads before it consumes any, so the whole weight matrix is in flight at once.  The 16 x 16 x 64 int8 MFMA
 // takes 16 weight rows as one operand and 16 (zero padded) tokens as the other; more tokens are more token
 // tiles against the same weight registers.  Nibbles are split into low/high words exactly as in the prefill
@@ -81,42 +81,56 @@ struct GvFewTiles {
     }
 };
 
-// More tokens: every wave puts its sums down and finishes the tiles wave, wave + WAVES, .., a lane four adjacent channels of one
-// token: 8-byte stores and vector loads of the constants.  (A thread per output, with atomics, 2-byte stores and a rounding in
-// software, spent 1300 cycles here on four tiles and 2700 on eight, 540 and 1300 as built, and 1700 instead of 1200 on the
-// constants' requests: 61 x 4096 x 12288 13.8 -> 13.2 us, 64 x 8192 x 8192 14.9 -> 13.6, 17 x 4096 x 4096 4.95 -> 4.74.)
+// More tokens: every wave puts its sums down and finishes whole tiles, a lane four adjacent channels of one token: 8-byte stores
+// and vector loads of the constants.  (A thread per output, with atomics, 2-byte stores and a rounding in software, spent 1300
+// cycles here on four tiles and 2700 on eight, 540 and 1300 as built: 17 x 4096 x 4096 5.2 -> 4.8 us, 64 x 8192 x 8192 15.2 -> 14.3,
+// 128 x 8192 x 28672 63.3 -> 59.3.)  A wave keeps to the token tiles wave % TT (and, TT > WAVES, every WAVES-th from there), over all weight
+// tiles or a share of them, so that it requests a record per token tile and the constants per weight tile.  With both per output
+// tile, up to 40 loads a lane in front of the weights, calls that fill few of their token tiles were slower than with a thread
+// per output (65 x 1024 x 28672 19.0 us, per output 18.0, as built 17.3); with the constants channel by channel in a workgroup that
+// has channels past the last, that workgroup alone took 2 us longer (65 x 1024 x 8208 8.9, 7.1, as built 6.9).
 template <int WAVES, int TILES, int TT>
 struct GvManyTiles {
-    static constexpr int NT = TILES * TT, OWN = (NT + WAVES - 1) / WAVES, LDS_INTS = WAVES * NT * 256;
-    int wave, M;
+    static constexpr int NT = TILES * TT, LDS_INTS = WAVES * NT * 256;
+    static constexpr int OWN_TT = TT > WAVES ? TT / WAVES : 1;             // token tiles of a wave, WAVES apart
+    static constexpr int T_STEP = TT < WAVES ? WAVES / TT : 1;             // its weight tiles are T_STEP apart
+    static constexpr int OWN_T = (TILES + T_STEP - 1) / T_STEP;
+    static_assert(TT > WAVES ? TT % WAVES == 0 : WAVES % TT == 0, "every wave has as many token tiles");
+    int wave, tt0, t0, M;
     bool whole;                                         // every channel of the workgroup exists
-    uint2 sw_bits[OWN], zp_bits[OWN];
-    float4 ws[OWN], cb[OWN];
-    basq_tokmeta mts[OWN];
+    uint2 sw_bits[OWN_T], zp_bits[OWN_T];
+    float4 ws[OWN_T], cb[OWN_T];
+    basq_tokmeta mts[OWN_TT];
     __device__ __forceinline__ void request(const GemmArgs& a, int n0, int tid, int*) {
         const int lane = tid & 63, row = lane & 15, sub = lane >> 4;
         wave = __builtin_amdgcn_readfirstlane(tid >> 6); M = (int)a.M;
+        tt0 = wave % TT; t0 = wave / TT;
         whole = n0 + GV_ROWS * TILES <= a.N;
 #pragma unroll
-        for (int o = 0; o < OWN; ++o) {
-            const int at = wave + o * WAVES < NT ? wave + o * WAVES : NT - 1;      // (a wave without an o-th tile: in bounds)
-            const int tok = 16 * (at % TT) + row, on = n0 + GV_ROWS * (at / TT) + 4 * sub;
-            cb[o] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (whole) {
-                __builtin_memcpy(&sw_bits[o], a.w_scale + on, 8);
-                __builtin_memcpy(&zp_bits[o], a.w_zero + on, 8);
-                __builtin_memcpy(&ws[o], a.w_sum + on, 16);
-                if (a.out_bias) __builtin_memcpy(&cb[o], a.out_bias + on, 16);
+        for (int k = 0; k < OWN_T; ++k) {
+            const int t = t0 + k * T_STEP < TILES ? t0 + k * T_STEP : TILES - 1;   // (a wave without a k-th tile: in bounds)
+            const int on = n0 + GV_ROWS * t + 4 * sub;
+            cb[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (a.N >= 4) {
+                const int at4 = on < a.N - 4 ? on : a.N - 4;       // past the last four channels: those, put in their places by finish()
+                __builtin_memcpy(&sw_bits[k], a.w_scale + at4, 8);
+                __builtin_memcpy(&zp_bits[k], a.w_zero + at4, 8);
+                __builtin_memcpy(&ws[k], a.w_sum + at4, 16);
+                if (a.out_bias) __builtin_memcpy(&cb[k], a.out_bias + at4, 16);
             } else {
                 int c[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) c[r] = on + r < a.N ? on + r : a.N - 1;
-                sw_bits[o] = make_uint2(a.w_scale[c[0]] | (uint32_t)a.w_scale[c[1]] << 16, a.w_scale[c[2]] | (uint32_t)a.w_scale[c[3]] << 16);
-                zp_bits[o] = make_uint2(a.w_zero[c[0]] | (uint32_t)a.w_zero[c[1]] << 16, a.w_zero[c[2]] | (uint32_t)a.w_zero[c[3]] << 16);
-                ws[o] = make_float4(a.w_sum[c[0]], a.w_sum[c[1]], a.w_sum[c[2]], a.w_sum[c[3]]);
-                if (a.out_bias) cb[o] = make_float4(a.out_bias[c[0]], a.out_bias[c[1]], a.out_bias[c[2]], a.out_bias[c[3]]);
+                sw_bits[k] = make_uint2(a.w_scale[c[0]] | (uint32_t)a.w_scale[c[1]] << 16, a.w_scale[c[2]] | (uint32_t)a.w_scale[c[3]] << 16);
+                zp_bits[k] = make_uint2(a.w_zero[c[0]] | (uint32_t)a.w_zero[c[1]] << 16, a.w_zero[c[2]] | (uint32_t)a.w_zero[c[3]] << 16);
+                ws[k] = make_float4(a.w_sum[c[0]], a.w_sum[c[1]], a.w_sum[c[2]], a.w_sum[c[3]]);
+                if (a.out_bias) cb[k] = make_float4(a.out_bias[c[0]], a.out_bias[c[1]], a.out_bias[c[2]], a.out_bias[c[3]]);
             }
-            mts[o] = a.meta[tok < M ? tok : M - 1];
+        }
+#pragma unroll
+        for (int s = 0; s < OWN_TT; ++s) {
+            const int tok = 16 * (tt0 + s * WAVES) + row;
+            mts[s] = a.meta[tok < M ? tok : M - 1];
         }
     }
     __device__ __forceinline__ void finish(const GemmArgs& a, int n0, int lane, const v4i (&acc)[NT], int* lds) const {
@@ -126,38 +140,55 @@ struct GvManyTiles {
         for (int at = 0; at < NT; ++at) part[(wave * NT + at) * 64 + lane] = acc[at];
         __syncthreads();
 #pragma unroll
-        for (int o = 0; o < OWN; ++o) {
-            const int at = wave + o * WAVES, tok = 16 * (at % TT) + row, on = n0 + GV_ROWS * (at / TT) + 4 * sub;
-            if (at >= NT) break;
-            v4i av = part[at * 64 + lane];
-#pragma unroll
-            for (int w = 1; w < WAVES; ++w) av += part[(w * NT + at) * 64 + lane];
-            if (tok >= M) continue;
-            const basq_tokmeta mt = mts[o];
-            const float rowsum = (float)mt.rowsum;
-            auto dequant = [&](int acc, float sw, float zp, float wsum, float c) {
-                return fmaf(mt.scale * sw, (float)acc - zp * rowsum, fmaf(mt.lo, wsum, c));
-            };
-            auto lo16 = [](uint32_t v) { return __uint_as_float(v << 16); };
-            auto hi16 = [](uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); };
-            const f2 y01 = {dequant(av[0], lo16(sw_bits[o].x), lo16(zp_bits[o].x), ws[o].x, cb[o].x),
-                            dequant(av[1], hi16(sw_bits[o].x), hi16(zp_bits[o].x), ws[o].y, cb[o].y)};
-            const f2 y23 = {dequant(av[2], lo16(sw_bits[o].y), lo16(zp_bits[o].y), ws[o].z, cb[o].z),
-                            dequant(av[3], hi16(sw_bits[o].y), hi16(zp_bits[o].y), ws[o].w, cb[o].w)};
-            const uint2 out = make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(y01, b2)),       // round-to-nearest-even
-                                         __builtin_bit_cast(uint32_t, __builtin_convertvector(y23, b2)));
-            uint16_t* dst = a.Y + (int64_t)tok * a.ldy + on;
-            if (whole) {
-                __builtin_memcpy(dst, &out, 8);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (on + r < a.N) dst[r] = (uint16_t)((r < 2 ? out.x : out.y) >> (16 * (r & 1)));
+        for (int k = 0; k < OWN_T; ++k) {
+            const int t = t0 + k * T_STEP, on = n0 + GV_ROWS * t + 4 * sub;
+            if (t >= TILES) break;
+            uint2 sw2 = sw_bits[k], zp2 = zp_bits[k];
+            float4 ws4 = ws[k], cb4 = cb[k];
+            const int shift = on - (a.N - 4);                      // 1 .. 3: that many of the lane's channels lie past the last
+            if (!whole && a.N >= 4 && shift > 0) {
+                auto down16 = [&](uint2 v) {
+                    const uint64_t w = ((uint64_t)v.y << 32 | v.x) >> (16 * (shift & 3));
+                    return make_uint2((uint32_t)w, (uint32_t)(w >> 32));
+                };
+                auto down32 = [&](float4 v) {
+                    return make_float4(shift == 1 ? v.y : shift == 2 ? v.z : v.w, shift == 1 ? v.z : v.w, v.w, v.w);
+                };
+                sw2 = down16(sw2); zp2 = down16(zp2);
+                ws4 = down32(ws4); cb4 = down32(cb4);
             }
-            if (a.acc_out) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (on + r < a.N) a.acc_out[(int64_t)tok * a.N + on + r] = av[r];
+            for (int s = 0; s < OWN_TT; ++s) {
+                const int tt = tt0 + s * WAVES, at = t * TT + tt, tok = 16 * tt + row;
+                if (16 * tt >= M) continue;                        // no token there
+                v4i av = part[at * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < WAVES; ++w) av += part[(w * NT + at) * 64 + lane];
+                if (tok >= M) continue;
+                const basq_tokmeta mt = mts[s];
+                const float rowsum = (float)mt.rowsum;
+                auto dequant = [&](int acc, float sw, float zp, float wsum, float c) {
+                    return fmaf(mt.scale * sw, (float)acc - zp * rowsum, fmaf(mt.lo, wsum, c));
+                };
+                auto lo16 = [](uint32_t v) { return __uint_as_float(v << 16); };
+                auto hi16 = [](uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); };
+                const f2 y01 = {dequant(av[0], lo16(sw2.x), lo16(zp2.x), ws4.x, cb4.x), dequant(av[1], hi16(sw2.x), hi16(zp2.x), ws4.y, cb4.y)};
+                const f2 y23 = {dequant(av[2], lo16(sw2.y), lo16(zp2.y), ws4.z, cb4.z), dequant(av[3], hi16(sw2.y), hi16(zp2.y), ws4.w, cb4.w)};
+                const uint2 out = make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(y01, b2)),       // round-to-nearest-even
+                                             __builtin_bit_cast(uint32_t, __builtin_convertvector(y23, b2)));
+                uint16_t* dst = a.Y + (int64_t)tok * a.ldy + on;
+                if (whole || on + 4 <= a.N) {
+                    __builtin_memcpy(dst, &out, 8);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (on + r < a.N) dst[r] = (uint16_t)((r < 2 ? out.x : out.y) >> (16 * (r & 1)));
+                }
+                if (a.acc_out) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (on + r < a.N) a.acc_out[(int64_t)tok * a.N + on + r] = av[r];
+                }
             }
         }
     }

@@ -733,6 +733,15 @@ def test_streaming_product_where_waves_share_the_outputs(M, N, K):
             assert bool((buf == -7.0).all()), "wrote outside the output"
 
 
+@pytest.mark.parametrize("M,N,K", [(M, N, 1152) for M in (17, 32, 65, 113, 128) for N in (24560, 24561, 24577)] +
+                         [(128, N, 2304) for N in (8193, 12289, 16390)] +
+                         [(M, N, 256) for M in (17, 48, 128) for N in (1, 2, 3, 4, 5, 7, 18, 31)])
+def test_streaming_product_on_the_widest_and_narrowest_outputs(M, N, K):
+    """The same around 1535 and 1536 tiles of channels, where four of them go to a workgroup, with all token tiles filled,
+    and with fewer channels than a lane finishes."""
+    test_streaming_product_where_waves_share_the_outputs(M, N, K)
+
+
 SPLIT_TILES = [(64, 64), (96, 64), (128, 64), (128, 128), (96, 96), (160, 96)]
 
 
