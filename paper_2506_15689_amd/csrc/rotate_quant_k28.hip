@@ -235,11 +235,12 @@ __device__ __forceinline__ void k28_quantise_group(const RotateQuantArgs& a, con
 // used.  (A loop of loads and LDS writes in front of everything was 16 memory latencies in a row: one token 10.5 us, without
 // 8.2; 1024 tokens 20.4 and 17.5; 64 with both vectors 16.7 and 10.8.)
 //
-// STAGED: the column blocks 1 .. STAGED of the next token are requested straight into LDS as soon as both waves of the token
-// have read them, and are there when it begins, as is block 0, in registers; 0: the launch has one round, a wave one token at
-// most.  With block 0 alone requested ahead every round began with a memory latency and 20 KB a token: 2048 tokens, two rounds,
-// 34.7 us, as built 32.4; 8192 120.5, as built 110.2 (3.0 TB/s).  Four tokens and one vector take 152 KB of LDS, so four tokens (eight waves) share
-// a workgroup; with both vectors there is room for one block of a token.
+// STAGED = 0: a wave has one token, and a compute unit takes the next workgroup when it has done with one.
+// STAGED > 0: workgroups stay and walk over the tokens.  The column blocks 1 .. STAGED of the next token are requested straight
+// into LDS as soon as both waves of the token have read them, and are there when it begins, as is block 0, in registers.  (With
+// block 0 alone requested ahead every round began with a memory latency and 20 KB a token.)  Four tokens and one vector take
+// 152 KB of LDS, so four tokens (eight waves) share a workgroup; with both vectors there is room for one block of a token.
+// Which one is taken where: launch_k28_flags().
 template <int TOKENS, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT, int STAGED>
 __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCALE) ? 2 : 1) void rotate_quant_k28_kernel(RotateQuantArgs a, float norm, H28Cols hc) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses device-only buffer-resource types; the host pass only needs the stub
@@ -259,12 +260,16 @@ __global__ __launch_bounds__(TOKENS * 128, TOKENS == 2 && !(HAS_BIAS && HAS_SCAL
     const bool row_valid = ip < 28;
     const uint32_t signs = hc.col[row_valid ? ip : 27];  // requested first: a wait for it waits for nothing else
 
-    // Workgroups g, g+8, ... share an XCD; renumbered so that an XCD owns a contiguous range, 32
-    // consecutive tokens (one block of the fp6 output) meet in one L2 and their pieces merge there.
+    // Workgroups g, g+8, ... share an XCD; renumbered so that 32 consecutive tokens (one block of the fp6 output) go to one,
+    // meet in its L2 and their pieces merge there: runs of 32 / TOKENS workgroups, as far as all XCDs have one.
+    constexpr int RUN = 32 / TOKENS;
     int vblock = blockIdx.x;
-    if ((gridDim.x & 127) == 0) vblock = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (vblock < (int)gridDim.x / (8 * RUN) * (8 * RUN)) {
+        const int xcd = vblock & 7, i = vblock >> 3;
+        vblock = ((i / RUN) * 8 + xcd) * RUN + i % RUN;
+    }
     const int64_t rb6 = (a.M + 31) >> 5;                    // 32-row blocks per chunk of the fp6 output
-    const int tokens_per_round = gridDim.x * TOKENS;
+    const int64_t tokens_per_round = (int64_t)gridDim.x * TOKENS;
     const int64_t m_first = (int64_t)vblock * TOKENS;
     // Blocks 1 .. STAGED of a token straight into LDS, in the lanes' order: wave half h brings rows 8g + 4h .. 8g + 4h + 3.
     uint8_t* const staged = lds + STAGE_AT + tok_in_blk * STAGED * K28_BLOCK_BYTES;
@@ -643,28 +648,37 @@ __global__ __launch_bounds__(256, 1) void rotate_quant_k28_split_kernel(RotateQu
 #endif  // __HIP_DEVICE_COMPILE__
 }
 
-template <int TOKENS, bool HB, bool HS, int STAGED>
-int launch_k28_form(const RotateQuantArgs& a, hipStream_t s, float norm, const H28Cols& hc, int max_blocks) {
-    const int64_t want = (a.M + TOKENS - 1) / TOKENS;
-    const unsigned blocks = (unsigned)(want < max_blocks ? want : max_blocks);
-    if (a.rot_out)
-        hipLaunchKernelGGL((rotate_quant_k28_kernel<TOKENS, HB, HS, true, STAGED>), dim3(blocks), dim3(TOKENS * 128), 0, s, a, norm, hc);
-    else
-        hipLaunchKernelGGL((rotate_quant_k28_kernel<TOKENS, HB, HS, false, STAGED>), dim3(blocks), dim3(TOKENS * 128), 0, s, a, norm, hc);
+template <int TOKENS, bool HB, bool HS, bool ROT_OUT, int STAGED>
+int launch_k28_form(const RotateQuantArgs& a, hipStream_t s, float norm, const H28Cols& hc) {
+    int64_t blocks = (a.M + TOKENS - 1) / TOKENS;
+    if (STAGED > 0 && blocks > K28_CUS) blocks = K28_CUS;
+    if (blocks > 0x7FFFFFFFll) return fail(BASQ_EINVAL, "rotate_quant (28x512): too many tokens for one launch");
+    hipLaunchKernelGGL((rotate_quant_k28_kernel<TOKENS, HB, HS, ROT_OUT, STAGED>), dim3((unsigned)blocks), dim3(TOKENS * 128), 0, s, a, norm, hc);
     return check_hip(hipGetLastError(), "rotate_quant (28x512) launch");
 }
 
-// Up to a token a compute unit (without the fp32 rotation written out): four waves a token.  Calls that fit one round of two-token workgroups (two per compute unit, one where both vectors fill its LDS) take them: they
-// spread over twice the compute units.  More tokens: four to a workgroup, and the next ones' blocks by way of LDS.
+// Up to a token a compute unit: four waves a token.  Otherwise two tokens to a workgroup of one round (two of them fit a compute
+// unit, one with both vectors in LDS), but workgroups of four tokens that stay where they are faster:
+//  - with both vectors, from 513 tokens on;
+//  - with at most one for codes in the 4-bit form alone, if the last round of 1024 tokens leaves at most a tenth of all rounds empty
+//    (b^c given, staying workgroups and two-token ones: 1400 tokens 25.2 and 21.7 us, 1800 26.2 and 26.0, 2048 26.9 and 27.7,
+//    2049 34.1 and 29.6, 2600 36.4 and 35.7, 2800 36.5 and 37.1, 4100 55.4 and 51.5, 5000 57.8 and 60.5, 8192 86.4 and 96.4).
+//    Calls that write the fp6 form are faster on two-token workgroups (1025 26.4 and 20.1, 2048 31.8 and 31.6, 3000 45.0 and 43.9,
+//    8192 109.7 and 105.2, 16384 218 and 205), as are those that write the rotation out, where the staying ones spill (2048 98.9
+//    and 66.9; 8192 417 and 270).
 template <bool HB, bool HS>
 int launch_k28_flags(const RotateQuantArgs& a, hipStream_t s, float norm, const H28Cols& hc) {
-    if (a.M <= K28_CUS && !a.rot_out) {
+    if (a.rot_out) return launch_k28_form<2, HB, HS, true, 0>(a, s, norm, hc);
+    if (a.M <= K28_CUS) {
         hipLaunchKernelGGL((rotate_quant_k28_split_kernel<HB, HS>), dim3((unsigned)a.M), dim3(256), 0, s, a, norm, hc);
         return check_hip(hipGetLastError(), "rotate_quant (28x512, split) launch");
     }
-    constexpr int PER_CU = (HB && HS) ? 1 : 2;
-    if (a.M <= 2 * PER_CU * K28_CUS) return launch_k28_form<2, HB, HS, 0>(a, s, norm, hc, PER_CU * K28_CUS);
-    return launch_k28_form<4, HB, HS, (HB && HS) ? 1 : 3>(a, s, norm, hc, K28_CUS);
+    constexpr bool BOTH = HB && HS;
+    constexpr int64_t ROUND = 4 * K28_CUS;
+    const int64_t room = (a.M + ROUND - 1) / ROUND * ROUND;
+    const bool stay = BOTH ? a.M > 2 * K28_CUS : !a.Aq6 && a.M > ROUND && room - a.M <= room / 10;
+    if (stay) return launch_k28_form<4, HB, HS, false, BOTH ? 1 : 3>(a, s, norm, hc);
+    return launch_k28_form<2, HB, HS, false, 0>(a, s, norm, hc);
 }
 
 }  // namespace

@@ -87,12 +87,13 @@ def check_fp6_copy(Aq, A6, K, row_blocks):
 # eight-wave workgroups up to 32767, and from 32768 tokens on with the fp6 copy the staged tails.
 # K = 8192: split up to 256, four waves to 2047, eight waves to 4096, four waves beyond, staged tails from 32768;
 # with s^a (staged in LDS beside b^c) eight waves from 1025 tokens on.
-# K = 14336: four waves per token up to 256 tokens, then two; one round of two-token workgroups up to 1024 (512 with both b^c and s^a), beyond it
-# rounds of 1024 tokens in four-token workgroups.
+# K = 14336: four waves per token up to 256 tokens, then two: workgroups of two tokens, and of four that stay for several rounds
+# with both b^c and s^a from 513 tokens on, otherwise for codes alone where the last round of 1024 tokens is filled well enough
+# (1844 and not 1843).
 SWITCH_CASES = [
     (4096, 12), (4096, 512), (4096, 513), (4096, 2047), (4096, 2048), (4096, 2061), (4096, 32768 + 13),
     (8192, 11), (8192, 256), (8192, 257), (8192, 1024), (8192, 1025), (8192, 2047), (8192, 2048), (8192, 4096), (8192, 4097), (8192, 12301), (8192, 32768 + 13),
-    (14336, 11), (14336, 131), (14336, 256), (14336, 257), (14336, 512), (14336, 513), (14336, 1024), (14336, 1025), (14336, 1030), (14336, 2048 + 5),
+    (14336, 11), (14336, 131), (14336, 256), (14336, 257), (14336, 512), (14336, 513), (14336, 1024), (14336, 1025), (14336, 1030), (14336, 1843), (14336, 1844), (14336, 2048 + 5), (14336, 3071),
 ]
 
 
