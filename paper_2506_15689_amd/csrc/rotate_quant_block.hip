@@ -195,7 +195,8 @@ struct RbFp6 {
     }
 };
 
-template <int LOG2N, bool FP6, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
+// PMAX: pieces that a wave has at most.
+template <int LOG2N, bool FP6, int PMAX, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
 __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQuantArgs a, float norm) {
     constexpr bool FOLD_NORM = LOG2N == 8;           // 1/sqrt(256) = 2^-4 sits in the MFMA operand
     __shared__ float red_mn[RB_WAVES], red_mx[RB_WAVES];
@@ -212,9 +213,9 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
 
     // ---- all of this wave's pieces are requested at once ------------------------------------------------------
     const uint16_t* x = a.X + m * a.ldx;
-    uint4 raw[RB_PMAX];
+    uint4 raw[PMAX];
 #pragma unroll
-    for (int p = 0; p < RB_PMAX; ++p) {
+    for (int p = 0; p < PMAX; ++p) {
         const int ein = 512 * (wave + RB_WAVES * p) + 8 * pl.chunk;
         raw[p] = ein < K ? nt_load16(x + ein) : make_uint4(0, 0, 0, 0);
     }
@@ -233,14 +234,14 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
             if (HAS_SCALE) ss[p & 1][r] = *reinterpret_cast<const float2*>(a.act_scale + at + 8 * r);
         }
     };
-    request_vectors(0);
-    float v[RB_PMAX][2][4];
+    if (PMAX > 1 || wave < np) request_vectors(0);
+    float v[PMAX][2][4];
     float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
-    for (int p = 0; p < RB_PMAX; ++p) {
+    for (int p = 0; p < PMAX; ++p) {
         const int c = wave + RB_WAVES * p;
         if (c < np) {                                  // uniform over the wave
-            if (p + 1 < RB_PMAX) request_vectors(p + 1);
+            if (p + 1 < PMAX) request_vectors(p + 1);
             __builtin_amdgcn_sched_barrier(0);
             float d[2][4];
             rb_rotate_piece(raw[p], bop, d);
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
     uint8_t* orow = codes ? a.Aq + m * (int64_t)(K / 2) + 16 * seg + 4 * q4 : nullptr;
     const RbFp6 f6(a, m, seg);
 #pragma unroll
-    for (int p = 0; p < RB_PMAX; ++p) {
+    for (int p = 0; p < PMAX; ++p) {
         const int c = wave + RB_WAVES * p;
         if (c < np) {
             const bool ok = 512 * c + eout < K;
@@ -395,17 +396,32 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_small_kernel(RotateQu
     }
 }
 
-template <int LOG2N, bool FP6>
-int launch_rb_form(const RotateQuantArgs& a, hipStream_t s, float norm) {
+template <int LOG2N, bool FP6, int PMAX>
+int launch_rb_pieces(const RotateQuantArgs& a, hipStream_t s, float norm) {
     const bool hb = a.bias != nullptr, hs = a.act_scale != nullptr, ro = a.rot_out != nullptr;
     const dim3 grid((unsigned)a.M), block(RB_THREADS);
-#define RB_LAUNCH(HB, HS, RO) hipLaunchKernelGGL((rotate_quant_block_kernel<LOG2N, FP6, HB, HS, RO>), grid, block, 0, s, a, norm)
+#define RB_LAUNCH(HB, HS, RO) hipLaunchKernelGGL((rotate_quant_block_kernel<LOG2N, FP6, PMAX, HB, HS, RO>), grid, block, 0, s, a, norm)
     if (hb && hs) { if (ro) RB_LAUNCH(true, true, true); else RB_LAUNCH(true, true, false); }
     else if (hb) { if (ro) RB_LAUNCH(true, false, true); else RB_LAUNCH(true, false, false); }
     else if (hs) { if (ro) RB_LAUNCH(false, true, true); else RB_LAUNCH(false, true, false); }
     else { if (ro) RB_LAUNCH(false, false, true); else RB_LAUNCH(false, false, false); }
 #undef RB_LAUNCH
     return check_hip(hipGetLastError(), "rotate_quant (blockwise) launch");
+}
+
+// A kernel for each number of pieces a wave has, up to three (K <= 6144): the vectors requested for a piece that does not exist, and
+// the registers of eight pieces, cost short tokens 3 - 11 % where the chip is full (both vectors, requested in place, a piece ahead in the
+// kernel for eight pieces, as built: K = 512 in blocks of 128, 2048 tokens 5.8, 6.2, 3.8 us, 16384 34.0, 35.7, 18.2; K = 2048, 1021
+// tokens 4.8, 5.2, 4.6; K = 4096 6.9, 7.2, 6.6; K = 5632 8.2, 8.8, 8.2).  With four pieces one of its own is the faster one with b^c (K = 8192,
+// 4096 tokens 26.0 -> 24.2) and the slower one for both forms of the codes without (26.6 -> 27.6); beyond, one less in eight counts
+// little.
+template <int LOG2N, bool FP6>
+int launch_rb_form(const RotateQuantArgs& a, hipStream_t s, float norm) {
+    const int pieces = (a.K + 512 * RB_WAVES - 1) / (512 * RB_WAVES);
+    if (pieces == 1) return launch_rb_pieces<LOG2N, FP6, 1>(a, s, norm);
+    if (pieces == 2) return launch_rb_pieces<LOG2N, FP6, 2>(a, s, norm);
+    if (pieces == 3) return launch_rb_pieces<LOG2N, FP6, 3>(a, s, norm);
+    return launch_rb_pieces<LOG2N, FP6, RB_PMAX>(a, s, norm);
 }
 
 // A kernel of its own for codes alone: with the fp6 form behind a test of its pointer they took 3-9 % longer (K = 512 in blocks
