@@ -588,7 +588,8 @@ int cheapest_split_tiling(int64_t M, int64_t N, int K) {
     double us = tiling_cost(plain, M, N, K);
     // Between the two forms of one tile the tables are even on a full chip; with long rows the split form is the faster one there
     // too (1021 x 11008 x 4096: 33.7 -> 31.7 us with the weights in the caches, 128 x 128 on 190 .. 256 compute units, K > 8192,
-    // 0.91 .. 1.03 with them, 0.86 .. 0.92 cold).
+    // 0.91 .. 1.03 with them, 0.86 .. 0.92 cold; 128 x 64 on 192 .. 256 0.94 .. 0.97 with them, 1.03 .. 1.04 cold, 128 x 11008 x 12288
+    // 22.2 -> 21.5 and 30.7 -> 31.8 us).
     if (K > 8192 && plain.bm <= 128 && ((M + plain.bm - 1) / plain.bm) * ((N + plain.bn - 1) / plain.bn) <= 256) us = 1e30;
     for (int i = 0; i < NUM_SPLIT_TILINGS; ++i) {
         const SplitTiling& t = split_tilings[i];
@@ -603,14 +604,17 @@ int cheapest_split_tiling(int64_t M, int64_t N, int K) {
 }  // namespace
 
 // Against the weight-streaming kernel (gemv_w4a4.hip), weights of both forms cold in memory, 17 .. 128 tokens, N 1024 ..
-// 28672, K 1024 .. 14336.  Above 64 tokens this kernel is the faster one (128 tokens x 28672, K = 8192: 37 against 63 us; x
-// 1024, K = 4096: 8.4 against 12.7 us): the streaming kernel reads every token's codes again per 16 to 64 channels.  Not so
-// up to 80 tokens with long rows of 4096 .. 8192 channels (65 x 4096, K = 14336: 28 against 22 us; with the weights in the
-// caches 21 against 19; 80 x 4096, K = 8192: 17.7 against 15.0 and 13.8 against 14.4); the line is drawn without them, the
-// caches deciding.  Up to 32 it never is: its weights are half as large again.  Between, it is where many channels (more than
-// the streaming kernel gives eight waves a workgroup) meet a moderate weight matrix (64 x 12288, K = 8192: 18.5 against 24.5
-// us; x 28672, where both stream: 36 against 34 us).  The streaming kernel's time is a fit (5 %); the margin covers this
-// kernel's on so few tiles.
+// 28672, K 1024 .. 14336.  Above 64 tokens this kernel is the faster one (128 tokens x 28672, K = 8192: 35 against 59 us; x
+// 1024, K = 4096: 7.2 against 11.2 us): the streaming kernel reads every token's codes again per 16 to 64 channels.  Not quite so
+// up to 80 tokens with long rows of 4096 .. 8192 channels (65 x 4096, K = 14336: 23.1 against 20.8 us); the line is drawn without
+// them.  Up to 32 it never is: its weights are half as large again.
+// Between, the line was fitted (5 %) to a streaming kernel that took four waves a workgroup beyond 8192 channels, against this
+// kernel's tilings without the split ones.  Both have become faster since, the streaming kernel the more with cold weights.
+// Where the line stands: 33, 40, 48, 56 and 64 tokens, N 8208 .. 28672, K 1024 .. 14336, the kernel taken is 2.3 % off the
+// faster one in the mean with cold weights and 7 % with weights in the caches.  Cold, calls that take this one lose up to 25 %
+// at 40 and 48 tokens (40 x 8208, K = 8192: 17.8 against 14.2 us) and little at 64 (x 12288, K = 4096 11.5 against 10.8, K = 8192
+// 18.6 against 17.9; K = 1024 4.9 against 6.5); in the caches this one is ahead at 64 tokens throughout (x 20480, K = 14336,
+// which streams: 39.5 against 59.8; cold 55.5 against 60.7).
 bool gemm_fp6_beats_streaming(int64_t M, int32_t N, int32_t K) {
     if (M > 64) return true;
     if (M <= 32 || N <= 8192) return false;

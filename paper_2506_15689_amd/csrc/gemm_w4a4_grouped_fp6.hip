@@ -244,7 +244,7 @@ __global__ __launch_bounds__(G6G_THREADS, 2) void gemm_w4a4_grouped_fp6_kernel(G
     __builtin_amdgcn_sched_barrier(0);
 
     // One group per pass: blocks (i, j) = (0,0), (1,0), (0,1), (1,1), two MFMAs each.  Fragments B0 and A0 and the constants were
-    // read during the group before; A1 and B1 are read with the first block.  The barrier, behind the first MFMA of block
+    // read during the group before; A1 and B1 are read with the first block.  The barrier, in front of the first MFMA of block
     // (0,1), ends every wave's reads of stage g, which group g + 3 refills from here on, and begins those of stage g + 1: B0
     // and A0, whose last uses are blocks (1,0) and (0,1), with a block and a half to arrive, and the constants.
     // Behind every MFMA go eight multiply-adds of a closing, one block late: the two pipes take 32 cycles each, side by side

@@ -326,8 +326,8 @@ static void launch_gemv_tiles(const GemmArgs& a, hipStream_t s, int blocks16) {
     // with either; 65 tokens, K = 512, N = 8192: 6.1 against 5.6).
     const bool one_batch = a.K / 128 <= 4 * STEPS;
     // 33 .. 64 tokens over 512 .. 1024 tiles: eight waves on the three or four tiles that give every compute unit one workgroup,
-    // which has twice the loads in flight of four waves on two (61 x 4096 x 12288 13.2 -> 9.9 us, 40 x 8192 x 12288 18.0 -> 13.8, 61 x
-    // 4096 x 16384 13.6 -> 10.7; 64 x 4096 x 20000, beyond, 19.2 and 18.3; up to 32 tokens even; rows of one batch 5.7 and 6.4).
+    // which has twice the loads in flight of four waves on two (cold weights: 64 x 4096 x 12288 14.1 -> 10.7 us, x 16384 14.5 -> 11.7,
+    // 64 x 8192 x 12288 24.3 -> 17.8; 64 x 4096 x 20000, beyond, 19.2 and 18.3; up to 32 tokens even; rows of one batch 5.7 and 6.4).
     if constexpr (TT == 4) {
         if (blocks16 > 512 && blocks16 <= 768 && !one_batch) { launch_gemv_cfg<SL, 8, 4, 3, TT>(a, s, blocks16); return; }
         if (blocks16 > 768 && blocks16 <= 1024 && !one_batch) { launch_gemv_cfg<SL, 8, 2, 4, TT>(a, s, blocks16); return; }

@@ -82,9 +82,9 @@ __device__ __forceinline__ float rh_item(float v, int t) {
 // the next step's are requested before this step's are worked on, and what is per head -- two divisions and the rest of the
 // range arithmetic, 30 instructions that one item repeats on the 16 lanes of a head -- is done for the NI items on
 // different lanes at once.  What bounds it is vector-instruction issue, about 145 per item (170 with one item a step).
-// K = 4096, one item a step and nothing requested ahead -> as built: 1024 tokens 8.0 -> 6.5 us, 4096 tokens 15.7 -> 13.7,
-// 8192 tokens 25.4 -> 21.2 (4.1 TB/s), 65536 tokens 156 -> 127; K = 8192, 16384 tokens 102 -> 69.  (NI = 2 throughout: 24.1 us
-// at 8192 tokens; eight workgroups per compute unit: 16.5 us at 4096.)
+// K = 4096, one item a step and nothing requested ahead -> with both: 1024 tokens 8.0 -> 6.5 us, 4096 tokens 15.7 -> 13.7,
+// 8192 tokens 25.4 -> 21.2, 65536 tokens 156 -> 127; K = 8192, 16384 tokens 102 -> 69 (before the staging below took its present
+// form; another box than its figures).  NI = 2 throughout: 24.1 us at 8192 tokens; eight workgroups per compute unit: 16.5 us at 4096.
 template <int NI, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
 __global__ __launch_bounds__(RH_THREADS) void rotate_quant_head_kernel(RotateQuantArgs a, float norm) {
     // bias and s^a laid out so that lane l of piece (c, r) reads the float2 at ((c*4 + r)*64 + l)
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(RH_THREADS) void rotate_quant_head_kernel(RotateQua
 
     if (HAS_BIAS || HAS_SCALE) {
         // Up to eight pieces requested before the first is written (a piece at a time is a memory latency each, eight in a row in
-        // front of everything at K = 4096: 1 token 3.35 -> 2.72 us, 1024 6.9 -> 6.1, 8192 23.1 -> 22.3; K = 8192, 512 tokens 7.9 -> 6.6).
+        // front of everything at K = 4096: 1 token 3.2 -> 2.6 us, 1024 6.5 -> 5.7, 8192 23.0 -> 21.3; K = 8192, 333 tokens 6.9 -> 5.8).
         static_assert(RH_THREADS == 256, "a piece is an item: float2 number f of the staged copy is lane f%64, r = (f/64)%4, c = f/256");
         const int at = threadIdx.x, items = K / 512;
         const int e = 128 * ((at & 63) >> 4) + 32 * (at >> 6) + 2 * (at & 15);
