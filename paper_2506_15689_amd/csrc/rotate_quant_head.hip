@@ -84,7 +84,7 @@ __device__ __forceinline__ float rh_item(float v, int t) {
 // different lanes at once.  What bounds it is vector-instruction issue, about 145 per item (170 with one item a step).
 // K = 4096, one item a step and nothing requested ahead -> with both: 1024 tokens 8.0 -> 6.5 us, 4096 tokens 15.7 -> 13.7,
 // 8192 tokens 25.4 -> 21.2, 65536 tokens 156 -> 127; K = 8192, 16384 tokens 102 -> 69 (before the staging below took its present
-// form; another box than its figures).  NI = 2 throughout: 24.1 us at 8192 tokens; eight workgroups per compute unit: 16.5 us at 4096.
+// form, and on another machine than its figures).  NI = 2 throughout: 24.1 us at 8192 tokens; eight workgroups per compute unit: 16.5 us at 4096.
 template <int NI, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
 __global__ __launch_bounds__(RH_THREADS) void rotate_quant_head_kernel(RotateQuantArgs a, float norm) {
     // bias and s^a laid out so that lane l of piece (c, r) reads the float2 at ((c*4 + r)*64 + l)
