@@ -355,6 +355,16 @@ int basq_diag_w4a4_gemm_fp6_split(int32_t tiling, const basq_tokmeta* meta, int6
                                   const uint8_t* Aq6, const uint8_t* Wq6, void* stream);
 
 /*
+ * The fp6 product of basq_w4a4_gemm_grouped has two tilings: 0, 128 x 128, and 1, 256 x 192, which needs N % 4 == 0, w_gsum on
+ * a 16-byte boundary and K >= 384.  The one that is taken for a shape whose w_gsum is aligned (-1 where there is none), and the
+ * product on a given one (the bits do not depend on it); arguments as in basq_w4a4_gemm_grouped, group_size = 128.
+ */
+int basq_diag_grouped_tiling(int64_t M, int32_t K, int32_t N);
+int basq_diag_w4a4_gemm_grouped_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
+                                    const void* w_scale, const void* w_zero, const int32_t* w_gsum, const float* out_bias,
+                                    void* Y, int64_t ldy, const uint8_t* Aq6, const uint8_t* Wq6, void* stream);
+
+/*
  * The blockwise rotations with per-token ranges request bias and act_scale without a test for the token's end.  Computed on the
  * host with the kernel's own index: one past the last channel that it requests of either, for a token of K channels, K a
  * multiple of 256 up to 16384 (otherwise BASQ_EINVAL); at most K.

@@ -25,7 +25,7 @@ EXPORTS = ["basq_version", "basq_last_error", "basq_rotate_quant", "basq_w4a4_ge
            "basq_w4a4_gemm_grouped", "basq_group_colsums", "basq_fp6_bytes", "basq_pack_fp6", "basq_decode_bytes", "basq_pack_decode", "basq_linear_fused", "basq_linear_fused_static", "basq_rotate_weights", "basq_quantize_weights", "basq_fused_bias", "basq_prepare_weights", "basq_calibrate_bias",
            "basq_hadamard28", "basq_diag_stream", "basq_diag_read", "basq_diag_mfma_i8", "basq_diag_mfma_f6",
            "basq_diag_fp6_tiling", "basq_diag_w4a4_gemm_fp6", "basq_diag_fp6_split_tiling", "basq_diag_w4a4_gemm_fp6_split",
-           "basq_diag_block_vector_channels"]
+           "basq_diag_grouped_tiling", "basq_diag_w4a4_gemm_grouped_fp6", "basq_diag_block_vector_channels"]
 
 
 class BasqError(RuntimeError):
@@ -96,12 +96,14 @@ def load() -> ctypes.CDLL:
     lib.basq_diag_mfma_i8.argtypes = [vp, i32, i32, vp]
     lib.basq_diag_mfma_f6.restype = c.c_int
     lib.basq_diag_mfma_f6.argtypes = [vp, i32, i32, vp]
-    for name in ("basq_diag_fp6_tiling", "basq_diag_fp6_split_tiling"):
+    for name in ("basq_diag_fp6_tiling", "basq_diag_fp6_split_tiling", "basq_diag_grouped_tiling"):
         getattr(lib, name).restype = c.c_int
         getattr(lib, name).argtypes = [i64, i32, i32]
     for name in ("basq_diag_w4a4_gemm_fp6", "basq_diag_w4a4_gemm_fp6_split"):
         getattr(lib, name).restype = c.c_int
         getattr(lib, name).argtypes = [i32, vp, i64, i32, i32, vp, vp, vp, vp, vp, i64, vp, vp, vp, vp]
+    lib.basq_diag_w4a4_gemm_grouped_fp6.restype = c.c_int
+    lib.basq_diag_w4a4_gemm_grouped_fp6.argtypes = [i32, vp, i64, i32, i32, vp, vp, vp, vp, vp, i64, vp, vp, vp]
     lib.basq_diag_block_vector_channels.restype = c.c_int
     lib.basq_diag_block_vector_channels.argtypes = [i32]
     _lib = lib
@@ -375,6 +377,24 @@ def basq_diag_w4a4_gemm_fp6(tiling: int, meta: torch.Tensor, K: int, w_scale: to
     run = load().basq_diag_w4a4_gemm_fp6_split if split else load().basq_diag_w4a4_gemm_fp6
     _check(run(tiling, _p(meta), M, K, N, _p(w_scale), _p(w_zero), _p(w_sum), _p(out_bias),
                _p(Y), Y.stride(0) if M > 0 else N, _p(acc_out), _p(Aq6), _p(Wq6), _stream(stream)))
+
+
+def basq_diag_grouped_tiling(M: int, K: int, N: int) -> int:
+    """Index of the tiling that the fp6 form of basq_w4a4_gemm_grouped takes, -1 where there is none."""
+    return int(load().basq_diag_grouped_tiling(M, K, N))
+
+
+def basq_diag_w4a4_gemm_grouped_fp6(tiling: int, meta: torch.Tensor, K: int, w_scale: torch.Tensor, w_zero: torch.Tensor,
+                                    w_gsum: torch.Tensor, out_bias: Optional[torch.Tensor], Y: torch.Tensor,
+                                    Aq6: torch.Tensor, Wq6: torch.Tensor, *, stream: Optional[torch.cuda.Stream] = None) -> None:
+    """The fp6 form of basq_w4a4_gemm_grouped on the given tiling; M, N = Y.shape."""
+    M, N = Y.shape
+    _need(meta, 16 * M * (K // 128), "meta")
+    _need(w_gsum, 4 * N * (K // 128), "w_gsum")
+    _need_fp6(Aq6, M, K, "Aq6")
+    _need_fp6(Wq6, N, K, "Wq6")
+    _check(load().basq_diag_w4a4_gemm_grouped_fp6(tiling, _p(meta), M, K, N, _p(w_scale), _p(w_zero), _p(w_gsum), _p(out_bias),
+                                                  _p(Y), Y.stride(0) if M > 0 else N, _p(Aq6), _p(Wq6), _stream(stream)))
 
 
 def basq_diag_block_vector_channels(K: int) -> int:

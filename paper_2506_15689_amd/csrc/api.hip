@@ -247,10 +247,9 @@ int basq_w4a4_gemm(const uint8_t* Aq, const basq_tokmeta* meta, int64_t M, int32
     return run_gemm(g, static_cast<hipStream_t>(stream));
 }
 
-int basq_w4a4_gemm_grouped(const uint8_t* Aq, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t group_size,
-                           const uint8_t* Wq, int32_t N, const void* w_scale, const void* w_zero,
-                           const int32_t* w_gsum, const float* out_bias, void* Y, int64_t ldy,
-                           const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {
+static int validate_grouped(const uint8_t* Aq, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t group_size,
+                            const uint8_t* Wq, int32_t N, const void* w_scale, const void* w_zero,
+                            const int32_t* w_gsum, void* Y, int64_t ldy, const uint8_t* Aq6, const uint8_t* Wq6) {
     const float dummy = 0.0f;   // validate_gemm wants the per-token weight sums, which this formula does not use
     int rc = validate_gemm(Aq, meta, M, K, Wq, N, BASQ_W_CANONICAL, w_scale, w_zero, &dummy, Y, ldy);
     if (rc != BASQ_OK) return rc;
@@ -258,7 +257,14 @@ int basq_w4a4_gemm_grouped(const uint8_t* Aq, const basq_tokmeta* meta, int64_t 
     if (K % 128 != 0) return fail(BASQ_EINVAL, "group-wise GEMM: K must be a multiple of 128 (got %d)", K);
     if (!w_gsum) return fail(BASQ_EINVAL, "w_gsum is null");
     if ((reinterpret_cast<uintptr_t>(w_gsum) & 3u) != 0) return fail(BASQ_EINVAL, "w_gsum must be 4-byte aligned");
-    rc = validate_fp6(Aq6, Wq6, true, K);
+    return validate_fp6(Aq6, Wq6, true, K);
+}
+
+int basq_w4a4_gemm_grouped(const uint8_t* Aq, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t group_size,
+                           const uint8_t* Wq, int32_t N, const void* w_scale, const void* w_zero,
+                           const int32_t* w_gsum, const float* out_bias, void* Y, int64_t ldy,
+                           const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {
+    const int rc = validate_grouped(Aq, meta, M, K, group_size, Wq, N, w_scale, w_zero, w_gsum, Y, ldy, Aq6, Wq6);
     if (rc != BASQ_OK) return rc;
     GemmArgs g{Aq, meta, M, K, Wq, N, static_cast<const uint16_t*>(w_scale), static_cast<const uint16_t*>(w_zero),
                nullptr, out_bias, static_cast<uint16_t*>(Y), ldy, nullptr, Aq6, Wq6, BASQ_W_CANONICAL};
@@ -304,6 +310,27 @@ static int run_fp6_tiling(int32_t tiling, int32_t tilings, int (*launch)(int, co
     if (M == 0) return BASQ_OK;
     if (!gemm_fp6_applicable(g)) return fail(BASQ_EUNSUPPORTED, "no fp6 product of this shape");
     return launch(tiling, g, static_cast<hipStream_t>(stream));
+}
+
+int basq_diag_grouped_tiling(int64_t M, int32_t K, int32_t N) {
+    if (M < 1 || N < 1 || K < 128 || K % 128 != 0) return -1;
+    return N % 4 == 0 && gemm_grouped_wide_is_faster(M, N, K) ? 1 : 0;
+}
+
+int basq_diag_w4a4_gemm_grouped_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
+                                    const void* w_scale, const void* w_zero, const int32_t* w_gsum, const float* out_bias,
+                                    void* Y, int64_t ldy, const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {
+    if (tiling < 0 || tiling > 1) return fail(BASQ_EINVAL, "tiling must be 0 or 1 (got %d)", tiling);
+    if (!Aq6 || !Wq6) return fail(BASQ_EINVAL, "an fp6 operand is null");
+    // (the 4-bit codes are not read: the fp6 operands stand in for them in the checks)
+    const int rc = validate_grouped(Aq6, meta, M, K, 128, Wq6, N, w_scale, w_zero, w_gsum, Y, ldy, Aq6, Wq6);
+    if (rc != BASQ_OK) return rc;
+    GemmArgs g{nullptr, meta, M, K, nullptr, N, static_cast<const uint16_t*>(w_scale), static_cast<const uint16_t*>(w_zero),
+               nullptr, out_bias, static_cast<uint16_t*>(Y), ldy, nullptr, Aq6, Wq6, BASQ_W_CANONICAL};
+    if (M == 0) return BASQ_OK;
+    if (tiling == 0 ? !gemm_grouped_fp6_applicable(g) : !gemm_grouped_wide_applicable(g, w_gsum))
+        return fail(BASQ_EUNSUPPORTED, "this tiling does not take the call");
+    return (tiling == 0 ? launch_gemm_grouped_fp6_narrow : launch_gemm_grouped_wide)(g, w_gsum, static_cast<hipStream_t>(stream));
 }
 
 int basq_diag_w4a4_gemm_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,

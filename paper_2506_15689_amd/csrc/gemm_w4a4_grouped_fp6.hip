@@ -357,6 +357,11 @@ bool gemm_grouped_fp6_applicable(const GemmArgs& a) {
 
 int launch_gemm_grouped_fp6(const GemmArgs& a, const int32_t* w_gsum, hipStream_t s) {
     if (a.M == 0) return BASQ_OK;
+    if (gemm_grouped_wide_applicable(a, w_gsum) && gemm_grouped_wide_is_faster(a.M, a.N, a.K)) return launch_gemm_grouped_wide(a, w_gsum, s);
+    return launch_gemm_grouped_fp6_narrow(a, w_gsum, s);
+}
+
+int launch_gemm_grouped_fp6_narrow(const GemmArgs& a, const int32_t* w_gsum, hipStream_t s) {
     const int64_t tm = (a.M + G6G_BM - 1) / G6G_BM;
     const int64_t tn = ((int64_t)a.N + G6G_BN - 1) / G6G_BN;
     if (tm * tn > 0x7FFFFFFFll) return fail(BASQ_EINVAL, "w4a4_gemm_grouped: problem too large for one launch");

@@ -743,6 +743,59 @@ def test_streaming_product_on_the_widest_and_narrowest_outputs(M, N, K):
     test_streaming_product_where_waves_share_the_outputs(M, N, K)
 
 
+@pytest.mark.parametrize("K", [384, 512, 640, 1152])
+def test_wide_tiles_of_the_group_wise_product(K):
+    """The 256 x 192 tiling by name: lengths of the loop over the groups from the depth of the ring on, tiles ragged in both
+    directions, fewer tokens and channels than a tile, every kind of output row, more tiles than compute units (a workgroup goes on
+    to another tile), constants from very small to very large: the int8 kernel's bits, nothing beside the output.  The tables
+    that it reads by direct loads may end anywhere, but its column sums start on a 16-byte boundary; where they do not, or N
+    is no multiple of 4, the call takes the other tiling."""
+    G = K // 128
+    shapes = [(1, 4, 4, 0), (33, 72, 72, 0), (256, 192, 192, 0), (257, 188, 192, 8), (481, 612, 620, 0), (300, 1000, 1001, 1),
+              (515, 196, 198, 2), (9 * 256 - 45, 30 * 192 + 8, 30 * 192 + 8, 0)]
+    for M, N, ldy, offset in shapes:
+        announce(f"wide group-wise tiling M={M} N={N} K={K} ldy={ldy} offset={offset}")
+        A, A6, meta, W, W6, sw, zp, _, c = random_product(M, N, K, seed=M + N, groups=G)
+        rows = torch.arange(M, device=DEV).repeat_interleave(G)
+        meta.view(torch.float32)[:, :2] *= torch.pow(2.0, ((rows * 7) % 5 - 2).float() * 24)[:, None]
+        gsum = torch.empty((G, N), dtype=torch.int32, device=DEV)
+        B.basq_group_colsums(W, 128, gsum)
+        want = torch.full((M, N), -7.0, dtype=torch.bfloat16, device=DEV)
+        B.basq_w4a4_gemm_grouped(A, meta, 128, W, sw, zp, gsum, c, want)
+        for bias in (c, None):
+            buf, Y = output_view(M, N, ldy, offset)
+            B.basq_diag_w4a4_gemm_grouped_fp6(1, meta, K, sw, zp, gsum, bias, Y, A6, W6)
+            if bias is None:
+                B.basq_w4a4_gemm_grouped(A, meta, 128, W, sw, zp, gsum, None, want)
+            assert torch.equal(Y.contiguous().view(torch.int16), want.view(torch.int16))
+            Y.fill_(-7.0)
+            assert bool((buf == -7.0).all()), "wrote outside the output"
+        shifted = torch.empty(G * N + 1, dtype=torch.int32, device=DEV)[1:].view(G, N).copy_(gsum)
+        with pytest.raises(B.BasqError):
+            B.basq_diag_w4a4_gemm_grouped_fp6(1, meta, K, sw, zp, shifted, None, want, A6, W6)
+        got = torch.empty_like(want)
+        B.basq_w4a4_gemm_grouped(A, meta, 128, W, sw, zp, shifted, None, got, Aq6=A6, Wq6=W6)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+def test_group_wise_products_on_either_tiling():
+    """Shapes on both sides of the rule that chooses between the tilings, through the public call."""
+    chosen = set()
+    for M, N, K in [(256, 2048, 1024), (1024, 12288, 1024), (1020, 12292, 4096), (1020, 12290, 4096), (3345, 2720, 2048)]:
+        announce(f"group-wise product M={M} N={N} K={K}")
+        chosen.add(B.basq_diag_grouped_tiling(M, K, N))
+        A, A6, meta, W, W6, sw, zp, _, c = random_product(M, N, K, seed=M + N, groups=K // 128)
+        gsum = torch.empty((K // 128, N), dtype=torch.int32, device=DEV)
+        B.basq_group_colsums(W, 128, gsum)
+        got = []
+        for forms in ({"Aq6": A6, "Wq6": W6}, {}):
+            Y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+            B.basq_w4a4_gemm_grouped(A, meta, 128, W, sw, zp, gsum, c, Y, **forms)
+            got.append(Y.view(torch.int16))
+        assert torch.equal(*got)
+    assert chosen == {0, 1}
+
+
 SPLIT_TILES = [(64, 64), (96, 64), (128, 64), (128, 128), (96, 96), (160, 96)]
 
 
