@@ -37,11 +37,11 @@ constexpr int P2_LDS_WORDS = 2048;          // transpose buffer per wave, in flo
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
 __device__ __forceinline__ int dpp_i(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
 }
 constexpr int DPP_QUAD_XOR1 = 0xB1;         // quad_perm [1,0,3,2]
 constexpr int DPP_QUAD_XOR2 = 0x4E;         // quad_perm [2,3,0,1]

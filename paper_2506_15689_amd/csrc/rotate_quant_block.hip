@@ -79,7 +79,7 @@ __device__ __forceinline__ void rb_make_bop(int lane, v8bf (&bop)[2]) {
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t rb_dpp_u(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
 }
 
 // The stages of one piece: MFMA, then e5, e6 in registers, then e3, e4 across lane bits 4 and 5.
@@ -139,13 +139,11 @@ __device__ __forceinline__ uint32_t rb_codes(const float (&v)[2][4], float inv, 
     }
     // byte r of `w`: the row's byte at 256*c + 16*seg + q4 + 4*r.  Quad transpose: lane q4 ends with the bytes
     // q4 of its quad's four words, i.e. the aligned dword at ... + 4*q4.
-    const int q4 = lane & 3;                                             // position in the quad
-    const uint32_t sel = (uint32_t)q4 | ((uint32_t)(4 + q4) << 8);       // v_perm: byte q4 of each of two dwords
     const uint32_t w = ev | (od << 4);
-    const uint32_t w0 = rb_dpp_u<0x00>(w), w1 = rb_dpp_u<0x55>(w), w2 = rb_dpp_u<0xAA>(w), w3 = rb_dpp_u<0xFF>(w);
-    const uint32_t lo2 = __builtin_amdgcn_perm(w1, w0, sel);             // bytes (w0[q4], w1[q4], -, -)
-    const uint32_t hi2 = __builtin_amdgcn_perm(w3, w2, sel);
-    return __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
+    // with the neighbour: bytes 0, 2 (even lanes) or 1, 3 of both; with the lane after that: one 16-bit half of both
+    const uint32_t sel1 = lane & 1 ? 0x03070105u : 0x06020400u, sel2 = lane & 2 ? 0x03020706u : 0x05040100u;
+    const uint32_t x = __builtin_amdgcn_perm(rb_dpp_u<0xB1>(w), w, sel1);
+    return __builtin_amdgcn_perm(rb_dpp_u<0x4E>(x), x, sel2);
 }
 
 // The same codes in the fp6 operand form (fp6_pack.hip): the four lanes of a quad hold a group of 32 codes, whose
@@ -196,8 +194,11 @@ struct RbFp6 {
 };
 
 // PMAX: pieces that a wave has at most.
+// (Two waves a SIMD: allowed more than 256 registers, the compiler gives the MFMAs' results to accumulation registers, and a move each
+// brings them back.  With that, DPP moves without an old value, and a quad's bytes transposed in two steps: K = 11008, 1021 tokens
+// 13.54 -> 13.13 us, 64 5.43 -> 5.13; rotate_quant_small_kernel, K = 1024, 4096 tokens 5.11 -> 4.82.)
 template <int LOG2N, bool FP6, int PMAX, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
-__global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQuantArgs a, float norm) {
+__global__ __launch_bounds__(RB_THREADS, 2) void rotate_quant_block_kernel(RotateQuantArgs a, float norm) {
     constexpr bool FOLD_NORM = LOG2N == 8;           // 1/sqrt(256) = 2^-4 sits in the MFMA operand
     __shared__ float red_mn[RB_WAVES], red_mx[RB_WAVES];
     __shared__ int red_sum[RB_WAVES];
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(RB_THREADS) void rotate_quant_block_kernel(RotateQu
 // waves, so there is no LDS and no barrier, and the four waves of a workgroup take four tokens.  b^c and s^a stay in
 // registers over a wave's tokens, the next token is requested before the current one is worked on.
 template <int NP, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
-__global__ __launch_bounds__(RB_THREADS) void rotate_quant_small_kernel(RotateQuantArgs a, float norm) {
+__global__ __launch_bounds__(RB_THREADS, 2) void rotate_quant_small_kernel(RotateQuantArgs a, float norm) {
     constexpr bool FOLD_NORM = NP == 2;                // 1/sqrt(1024) = 2^-5 sits in the MFMA operand
     constexpr int K = 512 * NP;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

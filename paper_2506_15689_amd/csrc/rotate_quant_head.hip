@@ -27,13 +27,14 @@ typedef short v8s __attribute__((ext_vector_type(8)));
 constexpr int RH_WAVES = 4;
 constexpr int RH_THREADS = RH_WAVES * 64;
 
+// (every CTRL used takes each lane's value from a lane of the row: no old value to keep)
 template <int CTRL>
 __device__ __forceinline__ float rh_dppf(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
 __device__ __forceinline__ int rh_dppi(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
 }
 #define RH_BFLY(x, y) do { const float _a = (x), _b = (y); (x) = _a + _b; (y) = _a - _b; } while (0)
 
@@ -81,12 +82,14 @@ __device__ __forceinline__ float rh_item(float v, int t) {
 // NI consecutive items of a token per step of a wave (NI divides the items per token): their loads are in flight together,
 // the next step's are requested before this step's are worked on, and what is per head -- two divisions and the rest of the
 // range arithmetic, 30 instructions that one item repeats on the 16 lanes of a head -- is done for the NI items on
-// different lanes at once.  What bounds it is vector-instruction issue, about 145 per item (170 with one item a step).
+// different lanes at once.  What bounds it is vector-instruction issue, 100 per item: 120 while the compiler, allowed more than 256
+// registers a lane, kept the MFMAs' results in accumulation registers, and every DPP move had a zero put into its result first;
+// 8192 tokens of K = 4096 20.5 -> 19.2 us.
 // K = 4096, one item a step and nothing requested ahead -> with both: 1024 tokens 8.0 -> 6.5 us, 4096 tokens 15.7 -> 13.7,
 // 8192 tokens 25.4 -> 21.2, 65536 tokens 156 -> 127; K = 8192, 16384 tokens 102 -> 69 (before the staging below took its present
 // form, and on another machine than its figures).  NI = 2 throughout: 24.1 us at 8192 tokens; eight workgroups per compute unit: 16.5 us at 4096.
 template <int NI, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
-__global__ __launch_bounds__(RH_THREADS) void rotate_quant_head_kernel(RotateQuantArgs a, float norm) {
+__global__ __launch_bounds__(RH_THREADS, 2) void rotate_quant_head_kernel(RotateQuantArgs a, float norm) {
     // bias and s^a laid out so that lane l of piece (c, r) reads the float2 at ((c*4 + r)*64 + l)
     extern __shared__ __attribute__((aligned(16))) float rh_lds[];
     const int K = a.K;
@@ -155,10 +158,10 @@ __global__ __launch_bounds__(RH_THREADS) void rotate_quant_head_kernel(RotateQua
         }
         bop[h] = __builtin_bit_cast(v8bf, tmp);
     }
-    // byte transpose inside a quad: lane i of the quad collects byte i of the four lanes
+    // byte transpose inside a quad, lane i collects byte i of the four lanes: with the neighbour bytes 0, 2 (even lanes) or 1, 3
+    // of both, then with the lane after that one 16-bit half of both
     const int qi = lane & 3;
-    const unsigned sel01 = 0x0C0C0000u | (unsigned)qi | ((unsigned)(4 + qi) << 8);
-    const unsigned sel23 = 0x00000C0Cu | ((unsigned)qi << 16) | ((unsigned)(4 + qi) << 24);
+    const unsigned sel1 = lane & 1 ? 0x03070105u : 0x06020400u, sel2 = lane & 2 ? 0x03020706u : 0x05040100u;
 
     while (m < a.M) {
         float d[NI][2][4];
@@ -229,9 +232,8 @@ __global__ __launch_bounds__(RH_THREADS) void rotate_quant_head_kernel(RotateQua
             const int sum = __builtin_amdgcn_udot4(ev, 0x01010101u, 0, false);
             sums[t] = __builtin_amdgcn_udot4(od, 0x01010101u, sum, false);
             const uint32_t mine = ev | (od << 4);                   // byte r = the packed byte at 256*item + 64g + 16r + col
-            const uint32_t x0 = (uint32_t)rh_dppi<0x00>((int)mine), x1 = (uint32_t)rh_dppi<0x55>((int)mine);
-            const uint32_t x2 = (uint32_t)rh_dppi<0xAA>((int)mine), x3 = (uint32_t)rh_dppi<0xFF>((int)mine);
-            const uint32_t word = __builtin_amdgcn_perm(x1, x0, sel01) | __builtin_amdgcn_perm(x3, x2, sel23);
+            const uint32_t x = __builtin_amdgcn_perm((unsigned)rh_dppi<0xB1>((int)mine), mine, sel1);
+            const uint32_t word = __builtin_amdgcn_perm((unsigned)rh_dppi<0x4E>((int)x), x, sel2);
             // lane (quad q = col/4, i = col%4) now holds bytes 256*item + 64g + 16i + 4q .. +3
             *reinterpret_cast<uint32_t*>(a.Aq + m * (int64_t)(K / 2) + 256 * (NI * c + t) + 64 * g + 16 * qi + 4 * (col >> 2)) = word;
         }
