@@ -1,14 +1,14 @@
 // The group-wise INT4 x INT4 GEMM of gemm_w4a4_grouped_fp6.hip (same operands, same sums in the same order, same bits) on
 // 256 x 192 tiles, for products large enough to fill the chip with them.
 //
-// What bounds it: 2240 cycles a group, of which the vector units work 1500 -- the closings' 96 multiply-adds a lane and the rest, 127
+// What bounds it: 2200 cycles a group, of which the vector units work 1460 -- the closings' 96 multiply-adds a lane and the rest, 122
 // instructions of 4.4 cycles for each of two waves, and the rank-1 updates: an fp32 MFMA runs beside no fp32 vector
 // instruction (64 of them 280 cycles, two of the updates 130, both 423), where the fp6 ones do -- and the matrix units 770 more
 // beside them.  No single part is the rest: without the loads, the fragment reads, the multiply-adds or the rank-1 updates a
 // product is 11 .. 17 % shorter each.  Against 128 x 128 tiles, two workgroups per compute unit, the tile needs 55 % of the direct
-// loads and 83 % of the fragment reads per output, which is what it gains: 2048 x 4096 x 12288 98 -> 84 us, 4096 x 4096 x 28672
-// 465 -> 397, 1024 x 4096 x 12288 50 -> 42.  (Twelve waves of 64 x 64 outputs on the same tile, three a SIMD: 92 us; their reads
-// of LDS stand in the way.)
+// loads and 83 % of the fragment reads per output, which is what it gains: 2048 x 4096 x 12288 98 -> 80 us, 4096 x 4096 x 28672
+// 465 -> 386, 1024 x 4096 x 12288 50 -> 42.  (Twelve waves of 64 x 64 outputs on the same tile, three a SIMD: 92 us; their reads
+// of LDS stand in the way.  Column blocks in LDS in the order of the operand, four more running addresses: 82.)
 //
 // Eight waves of 64 x 96 outputs, one workgroup per compute unit that walks its tiles; a ring of three stages, one group each,
 // filled by direct loads three groups ahead, across the ends of tiles: a tile's last three groups request the next tile's first
@@ -93,10 +93,17 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
     // matrix are clamped to its last block).  The fourth brings the last six pieces of weights (waves 0 .. 5), the group's
     // token records (6 .. 9, 64 rows each) or its column sums (10 and 11, both the same), rows and columns clamped likewise.
     int lane_off = lane * 16;
-    auto block_off = [&](int piece, int first, int tile_block, int blocks) {
-        int blk = (piece - first) / 3 + tile_block;
-        blk = blk < blocks ? blk : blocks - 1;
-        return (unsigned)(blk * GW_BLOCK + (piece - first) % 3 * 1024);
+    auto a_off = [&](int piece, int tile_m) {
+        int blk = piece / 3 + tile_m * (GW_BM / 32);
+        blk = blk < rb_a ? blk : rb_a - 1;
+        return (unsigned)(blk * GW_BLOCK + piece % 3 * 1024);
+    };
+    // (the column blocks stand in LDS as the waves own them, one wave's three behind each other: see col_block)
+    auto b_off = [&](int piece, int tile_n) {
+        const int slot = (piece - GW_A_PIECES) / 3, own = slot % GW_TN, w = slot / GW_TN;
+        int blk = (own < 2 ? 2 * w + own : 2 * GW_WAVES_N + w) + tile_n * (GW_BN / 32);
+        blk = blk < rb_w ? blk : rb_w - 1;
+        return (unsigned)(blk * GW_BLOCK + piece % 3 * 1024);
     };
     const int last_piece = (GW_LOADS - 1) * GW_WAVES + (swave < GW_WAVES - 2 ? swave : GW_WAVES - 2);
     const bool last_w = last_piece < GW_REC_PIECE, last_rec = !last_w && last_piece < GW_SUM_PIECE;
@@ -109,15 +116,15 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
     auto request_from = [&](int tile_m, int tile_n) {                      // the next group to request is the first of this tile
 #pragma unroll
         for (int i = 0; i < GW_LOADS - 1; ++i)
-            soff[i] = i * GW_WAVES < GW_A_PIECES ? block_off(i * GW_WAVES + swave, 0, tile_m * (GW_BM / 32), rb_a)
-                                                 : block_off(i * GW_WAVES + swave, GW_A_PIECES, tile_n * (GW_BN / 32), rb_w);
+            soff[i] = i * GW_WAVES < GW_A_PIECES ? a_off(i * GW_WAVES + swave, tile_m) : b_off(i * GW_WAVES + swave, tile_n);
         int64_t m = (int64_t)tile_m * GW_BM + 64 * (last_piece - GW_REC_PIECE) + lane;
         m = m < a.M ? m : a.M - 1;
-        int n = tile_n * GW_BN + 4 * lane;
+        const int slot = lane >> 3, own = slot % GW_TN, w = slot / GW_TN;      // (lanes 48 .. 63: what nobody reads)
+        int n = tile_n * GW_BN + 32 * (own < 2 ? 2 * w + own : 2 * GW_WAVES_N + w) + 4 * (lane & 7);
         n = n < a.N - 4 ? n : a.N - 4;
         last_voff = last_w ? lane_off : last_rec ? (int)(m * ngroups * 16) : n * 4;
         koff_a = koff_w = 0;
-        koff_l = last_w ? block_off(last_piece, GW_A_PIECES, tile_n * (GW_BN / 32), rb_w) : 0;
+        koff_l = last_w ? b_off(last_piece, tile_n) : 0;
     };
     auto issue_one = [&](int stage_off, int i) {
         const int at = stage_off + (i * GW_WAVES + swave) * 1024;
@@ -137,19 +144,18 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
     const int a_row = wm * GW_TM * GW_BLOCK;
     // a wave's column blocks: a pair of adjacent ones (64 columns, a 128-byte line of outputs), and one from behind all pairs
     auto col_block = [&](int j) { return j < 2 ? wn * 2 + j : GW_WAVES_N * 2 + wn; };
-    const int b_row = GW_A_PIECES * 1024 + col_block(0) * GW_BLOCK, b2_row = (col_block(2) - col_block(0)) * GW_BLOCK;
+    const int b_row = GW_A_PIECES * 1024 + wn * GW_TN * GW_BLOCK;
     // running byte addresses of the reads: of the stage that is read next
-    int ma[2], mb[2], mb2[2], ta = a_row + toff, tb = b_row + toff, tb2 = b_row + b2_row + toff;
+    int ma[2], mb[2], ta = a_row + toff, tb = b_row + toff;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
         const int moff = 64 * frow + 16 * ((2 * kb + fhalf) ^ ((frow >> 2) & 3));
         ma[kb] = a_row + moff;
         mb[kb] = b_row + moff;
-        mb2[kb] = b_row + b2_row + moff;
-        asm volatile("" : "+v"(ma[kb]), "+v"(mb[kb]), "+v"(mb2[kb]));
+        asm volatile("" : "+v"(ma[kb]), "+v"(mb[kb]));
     }
-    int rec_at = GW_REC_PIECE * 1024 + (wm * GW_TM * 32 + frow) * 16, sum_at = GW_SUM_PIECE * 1024 + (col_block(0) * 32 + frow) * 4, sum2_at = GW_SUM_PIECE * 1024 + (col_block(2) * 32 + frow) * 4;
-    asm volatile("" : "+v"(ta), "+v"(tb), "+v"(tb2), "+v"(rec_at), "+v"(sum_at), "+v"(sum2_at));
+    int rec_at = GW_REC_PIECE * 1024 + (wm * GW_TM * 32 + frow) * 16, sum_at = GW_SUM_PIECE * 1024 + (wn * GW_TN * 32 + frow) * 4;
+    asm volatile("" : "+v"(ta), "+v"(tb), "+v"(rec_at), "+v"(sum_at));
 
     // Column constants (sw, sw * zp, c) of a tile.  Requested as raw bits on every path, so that no conversion, with a wait for
     // everything in flight in front of it, stands behind the request.
@@ -196,24 +202,20 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
         asm volatile("" ::: "memory");
     };
     auto read_a = [&](int kb, int i) { read_one(pa[kb][i], lds + ma[kb] + i * GW_BLOCK, lds + ta + i * GW_BLOCK + 512 * kb); };
-    auto read_b = [&](int kb, int j) {
-        if (j < 2) read_one(pb[kb][j], lds + mb[kb] + j * GW_BLOCK, lds + tb + j * GW_BLOCK + 512 * kb);
-        else read_one(pb[kb][0], lds + mb2[kb], lds + tb2 + 512 * kb);
-    };
+    auto read_b = [&](int kb, int j) { read_one(pb[kb][j & 1], lds + mb[kb] + j * GW_BLOCK, lds + tb + j * GW_BLOCK + 512 * kb); };
     // As integers: the compiler puts a wait for every outstanding direct-to-LDS load in front of a float-typed LDS read.
     auto read_records = [&](int t) { rec[t] = *reinterpret_cast<const v4i*>(lds + rec_at + t * 32 * 16); };
     auto read_sums = [&]() {
-        csum[0] = *reinterpret_cast<const int*>(lds + sum_at);
-        csum[1] = *reinterpret_cast<const int*>(lds + sum_at + 32 * 4);
-        csum[2] = *reinterpret_cast<const int*>(lds + sum2_at);
+#pragma unroll
+        for (int j = 0; j < GW_TN; ++j) csum[j] = *reinterpret_cast<const int*>(lds + sum_at + j * 32 * 4);
     };
     int stage = 0;                                                         // byte offset of the stage being read
     auto next_stage = [&]() {
         const bool wrap = stage == (GW_STAGES - 1) * GW_STAGE;
         const int d = wrap ? -(GW_STAGES - 1) * GW_STAGE : GW_STAGE;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) { ma[kb] += d; mb[kb] += d; mb2[kb] += d; }
-        ta += d; tb += d; tb2 += d; rec_at += d; sum_at += d; sum2_at += d;
+        for (int kb = 0; kb < 2; ++kb) { ma[kb] += d; mb[kb] += d; }
+        ta += d; tb += d; rec_at += d; sum_at += d;
         stage += d;
     };
     const v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -246,8 +248,8 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
     __builtin_amdgcn_sched_barrier(0);
 
     float prev_s[2] = {0.0f, 0.0f};                                        // scales of the group before
-    // One group per pass: blocks (i, j) = (0,0), (1,0), (0,1), (1,1), (0,2), (1,2), two MFMAs each.  The barrier, in front of block
-    // (1,1), ends every wave's reads of this stage, which the group three further on refills from here on, and begins those
+    // One group per pass: blocks (i, j) = (0,0), (1,0), (1,1), (0,1), (0,2), (1,2), two MFMAs each.  The barrier, in front of block
+    // (0,1), ends every wave's reads of this stage, which the group three further on refills from here on, and begins those
     // of the next one: each fragment as soon as its registers have had their last use.  Behind every MFMA go eight multiply-adds
     // of a closing, one block late.
     auto group = [&]() {
@@ -255,7 +257,7 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
         float s[2] = {0.0f, 0.0f}, zlane = 0.0f, c1 = 0.0f, c2 = 0.0f;
 #pragma unroll
         for (int t = 0; t < 4 * GW_TN; ++t) {
-            const int i = (t >> 1) & 1, j = t >> 2, kb = t & 1;
+            const int j = t >> 2, i = ((t >> 1) ^ j) & 1, kb = t & 1;
             if (t == 6) gw_wait_loads_and_barrier<GW_LOADS>();
             acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(pb[kb][j & 1], pa[kb][i], kb == 0 ? zero : acc[i][j], 2, 2, 0, 0, 0, 0);
             if (t == 2) {
@@ -288,7 +290,8 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
             // behind MFMAs 2b + 1 and 2b + 2: the halves of block b - 1, of this group or of the one before
             constexpr int BLOCKS = GW_TM * GW_TN;
             const int c = (t - 1 + 2 * BLOCKS) / 2 % BLOCKS == 0 ? BLOCKS - 1 : (t - 1 + 2 * BLOCKS) / 2 % BLOCKS - 1;
-            close_half(c & 1, c >> 1, (t & 1) ^ 1, t >= 3 ? s[c & 1] : prev_s[c & 1]);
+            const int ci = (c ^ (c >> 1)) & 1;
+            close_half(ci, c >> 1, (t & 1) ^ 1, t >= 3 ? s[ci] : prev_s[ci]);
             __builtin_amdgcn_sched_barrier(0);
         }
         prev_s[0] = s[0];
