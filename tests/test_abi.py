@@ -84,6 +84,19 @@ def test_fp6_split_tilings_by_name(lib):
     assert call(0, K=32768 + 128) == B.BASQ_EUNSUPPORTED
 
 
+def test_grouped_tilings_by_name(lib):
+    """Which tiling a group-wise shape takes, and that a product by name is refused where it could not run."""
+    T = B.basq_diag_grouped_tiling
+    assert T(2048, 4096, 12288) == T(3345, 8192, 2720) == 1
+    # odd output widths, rows shorter than the ring, too few tiles, and a second round of them just begun
+    assert T(2048, 4096, 12290) == T(2048, 256, 12288) == T(333, 4096, 4096) == T(1775, 4096, 8176) == 0
+    assert T(0, 4096, 4096) == T(4, 192, 4096) == -1
+    call = lambda t, K=512, N=64, a=FAKE, gs=FAKE: lib.basq_diag_w4a4_gemm_grouped_fp6(
+        t, FAKE, 64, K, N, FAKE, FAKE, gs, None, FAKE, 64, a, FAKE, None)
+    assert call(-1) == call(2) == call(0, a=None) == call(1, gs=None) == call(0, K=192) == B.BASQ_EINVAL
+    assert call(1, K=256) == call(1, N=62) == call(1, gs=ctypes.c_void_p(0x1004)) == B.BASQ_EUNSUPPORTED
+
+
 def test_blockwise_rotation_requests_no_channel_past_the_token(lib):
     """b^c and s^a have K values each; what is requested for the missing half of a last piece, and for pieces that do not
     exist, must lie inside them too, down to the smallest token (K = 256, half a piece)."""
