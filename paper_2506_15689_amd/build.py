@@ -18,6 +18,13 @@ SOURCES = ["api.hip", "hadamard28.hip", "rotate_quant.hip", "rotate_quant_pow2.h
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 
+# Kernels with 32 .. 128 MFMA results a lane that vector instructions take up at once: without this the compiler puts the results
+# into accumulation registers wherever a kernel may have more than 256 registers (workgroups of four waves with much LDS), and
+# moves each back, 4-5 % of all instructions (61 tokens of K = 4096 4.78 -> 4.58 us, 256 of K = 14336 7.60 -> 7.38, 600 of K =
+# 8192 with s^a 12.6 -> 11.5).  The one-launch decode kernel is 1 % slower with it.
+MFMA_VGPR_SOURCES = {"rotate_quant_pow2.hip", "rotate_quant_k28.hip"}
+MFMA_VGPR_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+
 
 def _hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
@@ -28,7 +35,7 @@ def _hipcc() -> str:
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), *HIPCC_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [_hipcc(), *HIPCC_FLAGS, *(MFMA_VGPR_FLAGS if src in MFMA_VGPR_SOURCES else []), "-c", os.path.join(CSRC, src), "-o", obj]
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in proc.stdout.splitlines() if "packed-fp32-ops" not in l)
     if proc.returncode != 0:

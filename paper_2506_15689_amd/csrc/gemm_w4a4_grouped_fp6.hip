@@ -13,13 +13,14 @@
 // an outer product of tokens and channels, so it is a rank-1 update on the matrix cores: v_mfma_f32_32x32x1_2b_f32 does
 // two 32 x 32 blocks in 64 cycles with the single rounding of fma (checked bit for bit over normal and subnormal values),
 // against 128 for 32 vector instructions, and it takes one column sum and one lower bound per lane instead of 32 sums
-// from LDS.  The outer one is 64 vector instructions (256 cycles), which run beside the MFMAs of the same wave if
-// nothing makes them wait: eight behind every MFMA (32 cycles each), one block late.  With sixteen behind every second MFMA a
+// from LDS (it runs beside no fp32 vector instruction: 64 of them 280 cycles, two updates 130, both 423).  The outer one is 64
+// vector instructions (256 cycles), which run beside the fp6 MFMAs of the same wave if nothing makes them wait: eight behind every MFMA (32 cycles each), one block late.  With sixteen behind every second MFMA a
 // group took a wave alone on its SIMD 1230 cycles, as built 1020 (64 x 4096 x 4096 20.4 -> 17.6 us, 700 x 5008, K = 8192 38.9 ->
 // 33.7); two waves a SIMD share the loads into LDS and its reads, and gain less (2048 x 4096 x 12288 98 - 102 us, now 92 - 98; without
 // the loads 70, the multiply-adds 80, the fragment reads 82, the rank-1 updates 87).  The reads take running addresses, two
 // instructions a read less than a stage's address each time; a branch in the loop costs tens of cycles (unpeeled, with the
 // tests for the last groups inside, 24.3 us for 64 x 4096 x 4096).  256 x 128 tiles, a quarter less to load: 98.6.
+// Products that fill the chip with 256 x 192 tiles take those (gemm_w4a4_grouped_wide.hip).  Here
 // 128 x 128 tiles, four waves of 64 x 64, two workgroups per compute unit, a ring of three stages filled by
 // direct-to-LDS loads two to three groups ahead.
 #include "gemm_fp6_store.h"
