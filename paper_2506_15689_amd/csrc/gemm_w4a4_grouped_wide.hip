@@ -405,7 +405,7 @@ int launch_gemm_grouped_wide(const GemmArgs& a, const int32_t* w_gsum, hipStream
     const int64_t tm = (a.M + GW_BM - 1) / GW_BM, tn = ((int64_t)a.N + GW_BN - 1) / GW_BN;
     if (tm * tn > 0x7FFFFFFFll) return fail(BASQ_EINVAL, "w4a4_gemm_grouped: problem too large for one launch");
     GemmArgs b = a;
-    b.store_form = output_form(a, true);                          // (shared lines with the hint as on the small tiles from K = 1024 on)
+    b.store_form = output_form(a, a.K >= 1024 || (a.ldy & 31) == 0 || tm * tn <= 256);        // as on the small tiles (gemm_w4a4_grouped_fp6.hip)
     const int64_t grid = tm * tn < 256 ? tm * tn : 256;           // persistent workgroups, one per compute unit
     hipLaunchKernelGGL(gemm_w4a4_grouped_wide_kernel, dim3((unsigned)grid), dim3(GW_THREADS), 0, s, b, w_gsum, (int)tm, (int)tn);
     return check_hip(hipGetLastError(), "w4a4_gemm_grouped (wide) launch");
