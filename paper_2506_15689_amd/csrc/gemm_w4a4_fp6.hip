@@ -450,11 +450,13 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         typedef __bf16 b2 __attribute__((ext_vector_type(2)));
         // Outputs into registers, where they take the accumulators' place, then the stores.  With one workgroup per compute unit in
         // two halves of the row blocks: the first half's stores go out while the other is worked on (together with the order of
-        // the MFMAs: 2048 x 4096 x 12288 60.2 -> 58.8 us, with cached weights 59.5 -> 57.0; 4096 x 14336 x 8192 199 -> 197; with
-        // two workgroups, whose ends overlap as it is, 128 x 128 tiles 14.7 -> 14.9).  In front of the first stores a wait for the
-        // next tile's first stages (requested before this epilogue, so mostly landed): behind them it would be one for the stores
-        // too, the counter being one and the same.
-        constexpr int FIRST = KGROUPS == 1 && MINOCC * 4 == WAVES ? (OWN + 1) / 2 : OWN;
+        // the MFMAs: 2048 x 4096 x 12288 60.2 -> 58.8 us, with cached weights 59.5 -> 57.0).  In front of the first stores a wait for
+        // the next tile's first stages (requested before this epilogue, so mostly landed): behind them it would be one for the
+        // stores too, the counter being one and the same.  256 x 256 tiles in one go: their stages are longer on the way, and with
+        // weights from memory the earlier wait costs what the earlier stores gain (4096 x 8192 x 28672 422 and 426, with cached weights
+        // 417 and 412; layer calls between other work 448 and 453).  Nor with two workgroups per compute unit, whose ends overlap
+        // as it is (128 x 128 tiles 14.7 and 14.9).
+        constexpr int FIRST = KGROUPS == 1 && MINOCC * 4 == WAVES && BN < 256 ? (OWN + 1) / 2 : OWN;
         auto finish = [&](auto first_c, auto count_c) {
             constexpr int i0 = decltype(first_c)::value, count = decltype(count_c)::value;
             unsigned outv[count][TN][4][2];                   // [..][q][p]: channels 8q + 4*ehalf + 2p, +1

@@ -5,7 +5,7 @@
 // instructions of 4.4 cycles for each of two waves, and the rank-1 updates: an fp32 MFMA runs beside no fp32 vector
 // instruction (64 of them 280 cycles, two of the updates 130, both 423), where the fp6 ones do -- and the matrix units 770 more
 // beside them.  No single part is the rest: without the loads, the fragment reads, the multiply-adds or the rank-1 updates a
-// product is 11 .. 17 % shorter each.  Against 128 x 128 tiles, two workgroups per compute unit, the tile needs 55 % of the direct
+// product is 11 .. 17 % shorter each.  Against 128 x 128 tiles, two workgroups per compute unit, the tile needs 58 % of the direct
 // loads and 83 % of the fragment reads per output, which is what it gains: 2048 x 4096 x 12288 98 -> 80 us, 4096 x 4096 x 28672
 // 465 -> 386, 1024 x 4096 x 12288 50 -> 42.  (Twelve waves of 64 x 64 outputs on the same tile, three a SIMD: 92 us; their reads
 // of LDS stand in the way.  Column blocks in LDS in the order of the operand, four more running addresses: 82.)
