@@ -365,6 +365,13 @@ int basq_diag_w4a4_gemm_grouped_fp6(int32_t tiling, const basq_tokmeta* meta, in
                                     void* Y, int64_t ldy, const uint8_t* Aq6, const uint8_t* Wq6, void* stream);
 
 /*
+ * The 256 x 192 tiling goes on requesting behind a workgroup's last tile, from lane offsets that the bounds check of the load drops.
+ * Counted on the host with the kernel's own offsets: the requests of an M x K x N product that leave their table, or are not
+ * dropped behind a last tile; 0 in a sound kernel, -1 for a shape that the tiling does not take.
+ */
+int64_t basq_diag_grouped_wide_strays(int64_t M, int32_t K, int32_t N);
+
+/*
  * The blockwise rotations with per-token ranges request bias and act_scale without a test for the token's end.  Computed on the
  * host with the kernel's own index: one past the last channel that it requests of either, for a token of K channels, K a
  * multiple of 256 up to 16384 (otherwise BASQ_EINVAL); at most K.

@@ -25,7 +25,7 @@ EXPORTS = ["basq_version", "basq_last_error", "basq_rotate_quant", "basq_w4a4_ge
            "basq_w4a4_gemm_grouped", "basq_group_colsums", "basq_fp6_bytes", "basq_pack_fp6", "basq_decode_bytes", "basq_pack_decode", "basq_linear_fused", "basq_linear_fused_static", "basq_rotate_weights", "basq_quantize_weights", "basq_fused_bias", "basq_prepare_weights", "basq_calibrate_bias",
            "basq_hadamard28", "basq_diag_stream", "basq_diag_read", "basq_diag_mfma_i8", "basq_diag_mfma_f6",
            "basq_diag_fp6_tiling", "basq_diag_w4a4_gemm_fp6", "basq_diag_fp6_split_tiling", "basq_diag_w4a4_gemm_fp6_split",
-           "basq_diag_grouped_tiling", "basq_diag_w4a4_gemm_grouped_fp6", "basq_diag_block_vector_channels"]
+           "basq_diag_grouped_tiling", "basq_diag_w4a4_gemm_grouped_fp6", "basq_diag_grouped_wide_strays", "basq_diag_block_vector_channels"]
 
 
 class BasqError(RuntimeError):
@@ -104,6 +104,8 @@ def load() -> ctypes.CDLL:
         getattr(lib, name).argtypes = [i32, vp, i64, i32, i32, vp, vp, vp, vp, vp, i64, vp, vp, vp, vp]
     lib.basq_diag_w4a4_gemm_grouped_fp6.restype = c.c_int
     lib.basq_diag_w4a4_gemm_grouped_fp6.argtypes = [i32, vp, i64, i32, i32, vp, vp, vp, vp, vp, i64, vp, vp, vp]
+    lib.basq_diag_grouped_wide_strays.restype = i64
+    lib.basq_diag_grouped_wide_strays.argtypes = [i64, i32, i32]
     lib.basq_diag_block_vector_channels.restype = c.c_int
     lib.basq_diag_block_vector_channels.argtypes = [i32]
     _lib = lib
@@ -382,6 +384,11 @@ def basq_diag_w4a4_gemm_fp6(tiling: int, meta: torch.Tensor, K: int, w_scale: to
 def basq_diag_grouped_tiling(M: int, K: int, N: int) -> int:
     """Index of the tiling that the fp6 form of basq_w4a4_gemm_grouped takes, -1 where there is none."""
     return int(load().basq_diag_grouped_tiling(M, K, N))
+
+
+def basq_diag_grouped_wide_strays(M: int, K: int, N: int) -> int:
+    """Requests of the 256 x 192 group-wise tiling that leave their table, or are not dropped behind a last tile (on the host)."""
+    return int(load().basq_diag_grouped_wide_strays(M, K, N))
 
 
 def basq_diag_w4a4_gemm_grouped_fp6(tiling: int, meta: torch.Tensor, K: int, w_scale: torch.Tensor, w_zero: torch.Tensor,

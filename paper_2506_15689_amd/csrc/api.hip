@@ -317,6 +317,11 @@ int basq_diag_grouped_tiling(int64_t M, int32_t K, int32_t N) {
     return N % 4 == 0 && gemm_grouped_wide_is_faster(M, N, K) ? 1 : 0;
 }
 
+int64_t basq_diag_grouped_wide_strays(int64_t M, int32_t K, int32_t N) {
+    if (M < 1 || N < 4 || N % 4 != 0 || K < 384 || K % 128 != 0 || M > 1 << 20 || N > 1 << 20 || K > 1 << 15) return -1;
+    return gemm_grouped_wide_strays(M, N, K);
+}
+
 int basq_diag_w4a4_gemm_grouped_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
                                     const void* w_scale, const void* w_zero, const int32_t* w_gsum, const float* out_bias,
                                     void* Y, int64_t ldy, const uint8_t* Aq6, const uint8_t* Wq6, void* stream) {

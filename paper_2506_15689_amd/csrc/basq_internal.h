@@ -88,6 +88,7 @@ int launch_gemm_grouped_fp6_narrow(const GemmArgs& a, const int32_t* w_gsum, hip
 bool gemm_grouped_wide_applicable(const GemmArgs& a, const int32_t* w_gsum);
 bool gemm_grouped_wide_is_faster(int64_t M, int32_t N, int32_t K);
 int launch_gemm_grouped_wide(const GemmArgs& a, const int32_t* w_gsum, hipStream_t s);
+int64_t gemm_grouped_wide_strays(int64_t M, int32_t N, int32_t K);
 constexpr int GEMV_MAX_TOKENS = 128;                          // above it the tiled GEMMs take over
 int launch_gemv_decode(const GemmArgs& a, hipStream_t s);   // M <= GEMV_MAX_TOKENS, K % 128 == 0
 // one launch for the whole layer at decode size (linear_decode.hip)

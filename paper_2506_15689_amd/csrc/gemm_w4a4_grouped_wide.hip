@@ -55,6 +55,46 @@ __device__ __forceinline__ void gw_wait_loads_and_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// ---- what a wave requests, as byte offsets; on the host too, where gemm_grouped_wide_strays() holds all of it against the tables.
+// Load i < 5 of wave w brings piece 8 i + w of a stage, three of activations and two of weights (three pieces make one 32-row
+// block; which block is uniform over the wave and goes into the scalar offset; blocks past the matrix are clamped to its
+// last block).  The sixth brings the last two pieces of weights (waves 0 and 1), the group's token records (2 .. 5, 64 rows
+// each) or its column sums (6 and 7, both the same), rows and columns clamped likewise.
+#define GW_BOTH __host__ __device__ __forceinline__
+GW_BOTH int gw_last_piece(int wave) { return (GW_LOADS - 1) * GW_WAVES + (wave < GW_WAVES - 2 ? wave : GW_WAVES - 2); }
+GW_BOTH unsigned gw_a_off(int piece, int tile_m, int rb_a) {
+    int blk = piece / 3 + tile_m * (GW_BM / 32);
+    blk = blk < rb_a ? blk : rb_a - 1;
+    return (unsigned)(blk * GW_BLOCK + piece % 3 * 1024);
+}
+// (the column blocks stand in LDS as the waves own them, one wave's three behind each other: see col_block)
+GW_BOTH int gw_slot_block(int slot) {
+    const int own = slot % GW_TN, w = slot / GW_TN;
+    return own < 2 ? 2 * w + own : 2 * GW_WAVES_N + w;
+}
+GW_BOTH unsigned gw_b_off(int piece, int tile_n, int rb_w) {
+    int blk = gw_slot_block((piece - GW_A_PIECES) / 3) + tile_n * (GW_BN / 32);
+    blk = blk < rb_w ? blk : rb_w - 1;
+    return (unsigned)(blk * GW_BLOCK + piece % 3 * 1024);
+}
+GW_BOTH int gw_record_off(int piece, int lane, int tile_m, int64_t M, int ngroups) {
+    int64_t m = (int64_t)tile_m * GW_BM + 64 * (piece - GW_REC_PIECE) + lane;
+    m = m < M ? m : M - 1;
+    return (int)(m * ngroups * 16);
+}
+GW_BOTH int gw_sum_off(int lane, int tile_n, int N) {                      // (lanes 48 .. 63: what nobody reads)
+    int n = tile_n * GW_BN + 32 * gw_slot_block(lane >> 3) + 4 * (lane & 7);
+    n = n < N - 4 ? n : N - 4;
+    return n * 4;
+}
+// Behind the last tile: nothing, from lane offsets past the end of any table.  A lane is left out where its offset reaches the table's
+// size less the scalar offset, and that difference must not wrap: the scalar offsets go back to the first groups, of which every
+// table has the GW_STAGES that are requested here.
+GW_BOTH void gw_request_nothing(int& lane_off, int& last_voff, unsigned& koff_a, unsigned& koff_w, unsigned& koff_l) {
+    lane_off = last_voff = (int)0xFFFFFF00u;
+    koff_a = koff_w = koff_l = 0;
+}
+
 __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(GemmArgs a, const int32_t* w_gsum, int tiles_m, int tiles_n) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses device-only buffer-resource types; the host pass only needs the stub
     __shared__ __attribute__((aligned(1024))) uint8_t lds[GW_LDS_BYTES];
@@ -88,24 +128,9 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
     const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.Aq6), 0, (int)(a_step * (unsigned)ngroups), 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a.Wq6), 0, (int)(w_step * (unsigned)ngroups), 0x00020000);
 
-    // ---- direct loads, four of 1 KB per wave and stage: load i < 3 of wave w brings piece 12 i + w of the operands (three
-    // pieces make one 32-row block; which block is uniform over the wave and goes into the scalar offset; blocks past the
-    // matrix are clamped to its last block).  The fourth brings the last six pieces of weights (waves 0 .. 5), the group's
-    // token records (6 .. 9, 64 rows each) or its column sums (10 and 11, both the same), rows and columns clamped likewise.
+    // ---- direct loads: six of 1 KB per wave and stage (which ones: gw_last_piece and below)
     int lane_off = lane * 16;
-    auto a_off = [&](int piece, int tile_m) {
-        int blk = piece / 3 + tile_m * (GW_BM / 32);
-        blk = blk < rb_a ? blk : rb_a - 1;
-        return (unsigned)(blk * GW_BLOCK + piece % 3 * 1024);
-    };
-    // (the column blocks stand in LDS as the waves own them, one wave's three behind each other: see col_block)
-    auto b_off = [&](int piece, int tile_n) {
-        const int slot = (piece - GW_A_PIECES) / 3, own = slot % GW_TN, w = slot / GW_TN;
-        int blk = (own < 2 ? 2 * w + own : 2 * GW_WAVES_N + w) + tile_n * (GW_BN / 32);
-        blk = blk < rb_w ? blk : rb_w - 1;
-        return (unsigned)(blk * GW_BLOCK + piece % 3 * 1024);
-    };
-    const int last_piece = (GW_LOADS - 1) * GW_WAVES + (swave < GW_WAVES - 2 ? swave : GW_WAVES - 2);
+    const int last_piece = gw_last_piece(swave);
     const bool last_w = last_piece < GW_REC_PIECE, last_rec = !last_w && last_piece < GW_SUM_PIECE;
     const unsigned last_step = last_w ? w_step : last_rec ? 16u : (unsigned)a.N * 4u;
     const __amdgpu_buffer_rsrc_t rsrc_l = __builtin_amdgcn_make_buffer_rsrc(
@@ -116,15 +141,11 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
     auto request_from = [&](int tile_m, int tile_n) {                      // the next group to request is the first of this tile
 #pragma unroll
         for (int i = 0; i < GW_LOADS - 1; ++i)
-            soff[i] = i * GW_WAVES < GW_A_PIECES ? a_off(i * GW_WAVES + swave, tile_m) : b_off(i * GW_WAVES + swave, tile_n);
-        int64_t m = (int64_t)tile_m * GW_BM + 64 * (last_piece - GW_REC_PIECE) + lane;
-        m = m < a.M ? m : a.M - 1;
-        const int slot = lane >> 3, own = slot % GW_TN, w = slot / GW_TN;      // (lanes 48 .. 63: what nobody reads)
-        int n = tile_n * GW_BN + 32 * (own < 2 ? 2 * w + own : 2 * GW_WAVES_N + w) + 4 * (lane & 7);
-        n = n < a.N - 4 ? n : a.N - 4;
-        last_voff = last_w ? lane_off : last_rec ? (int)(m * ngroups * 16) : n * 4;
+            soff[i] = i * GW_WAVES < GW_A_PIECES ? gw_a_off(i * GW_WAVES + swave, tile_m, rb_a) : gw_b_off(i * GW_WAVES + swave, tile_n, rb_w);
+        const int rec = gw_record_off(last_piece, lane, tile_m, a.M, ngroups), sum = gw_sum_off(lane, tile_n, a.N);
+        last_voff = last_w ? lane_off : last_rec ? rec : sum;
         koff_a = koff_w = 0;
-        koff_l = last_w ? b_off(last_piece, tile_n) : 0;
+        koff_l = last_w ? gw_b_off(last_piece, tile_n, rb_w) : 0;
     };
     auto issue_one = [&](int stage_off, int i) {
         const int at = stage_off + (i * GW_WAVES + swave) * 1024;
@@ -318,7 +339,7 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
                 tile_of(next_pid, next_m, next_n);
                 request_from(next_m, next_n);
             } else {
-                lane_off = last_voff = (int)0xFFFFFF00u;
+                gw_request_nothing(lane_off, last_voff, koff_a, koff_w, koff_l);
             }
         }
         const Column next_column = load_column(more ? next_n : tile_n);
@@ -379,6 +400,43 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
 }
 
 }  // namespace
+
+// The requests of an M x K x N product that leave their table, in any byte of a lane's 16, or are not dropped behind a last tile:
+// counted on the host, with the kernel's own offsets.
+int64_t gemm_grouped_wide_strays(int64_t M, int32_t N, int32_t K) {
+    const int ngroups = K / 128, tiles_m = (int)((M + GW_BM - 1) / GW_BM), tiles_n = (N + GW_BN - 1) / GW_BN;
+    const int rb_a = (int)((M + 31) >> 5), rb_w = (N + 31) >> 5;
+    const unsigned a_step = (unsigned)rb_a * GW_BLOCK, w_step = (unsigned)rb_w * GW_BLOCK;
+    const uint64_t a_size = (uint64_t)a_step * ngroups, w_size = (uint64_t)w_step * ngroups;
+    const uint64_t rec_size = (uint64_t)M * ngroups * 16, sum_size = (uint64_t)ngroups * N * 4;
+    int64_t strays = 0;
+    auto check = [&](uint64_t size, unsigned scalar, int lane_offset, bool wanted) {
+        const unsigned vector = (unsigned)lane_offset;
+        strays += scalar > size || (wanted ? scalar + (uint64_t)vector + 16 > size : vector < size - scalar);
+    };
+    for (int tile = 0; tile < tiles_m * tiles_n; ++tile)
+        for (int wave = 0; wave < GW_WAVES; ++wave)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int tile_m = tile % tiles_m, tile_n = tile / tiles_m, last_piece = gw_last_piece(wave);
+                const bool last_w = last_piece < GW_REC_PIECE, last_rec = !last_w && last_piece < GW_SUM_PIECE;
+                int lane_off = lane * 16;
+                int last_voff = last_w ? lane_off : last_rec ? gw_record_off(last_piece, lane, tile_m, M, ngroups) : gw_sum_off(lane, tile_n, N);
+                unsigned koff_a = 0, koff_w = 0, koff_l = last_w ? gw_b_off(last_piece, tile_n, rb_w) : 0;
+                for (int g = 0; g < ngroups + GW_STAGES; ++g) {
+                    if (g == ngroups) gw_request_nothing(lane_off, last_voff, koff_a, koff_w, koff_l);
+                    for (int i = 0; i < GW_LOADS - 1; ++i) {
+                        const bool of_a = i * GW_WAVES < GW_A_PIECES;
+                        const int piece = i * GW_WAVES + wave;
+                        check(of_a ? a_size : w_size, of_a ? koff_a + gw_a_off(piece, tile_m, rb_a) : koff_w + gw_b_off(piece, tile_n, rb_w), lane_off, g < ngroups);
+                    }
+                    check(last_w ? w_size : last_rec ? rec_size : sum_size, koff_l, last_voff, g < ngroups);
+                    koff_a += a_step;
+                    koff_w += w_step;
+                    koff_l += last_w ? w_step : last_rec ? 16u : (unsigned)N * 4u;
+                }
+            }
+    return strays;
+}
 
 bool gemm_grouped_wide_applicable(const GemmArgs& a, const int32_t* w_gsum) {
     // four column sums a lane and load: their rows start on 16-byte boundaries

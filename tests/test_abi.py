@@ -97,6 +97,16 @@ def test_grouped_tilings_by_name(lib):
     assert call(1, K=256) == call(1, N=62) == call(1, gs=ctypes.c_void_p(0x1004)) == B.BASQ_EUNSUPPORTED
 
 
+def test_wide_group_wise_tiling_requests_nothing_outside_its_tables(lib):
+    """Blocks, records and sums past the matrix are clamped to its last ones, and what is requested behind a workgroup's last tile
+    is dropped, which takes scalar offsets inside the table: one token, few channels and the shortest rows are the tables that
+    such an offset leaves first."""
+    for K in (384, 512, 1152):
+        for M, N in [(1, 4), (1, 64), (1, 200), (2, 4), (33, 60), (257, 188), (300, 388)]:
+            assert B.basq_diag_grouped_wide_strays(M, K, N) == 0, (M, K, N)
+    assert [B.basq_diag_grouped_wide_strays(*s) for s in [(0, 384, 4), (1, 256, 4), (1, 384, 6), (1, 400, 4)]] == [-1] * 4
+
+
 def test_blockwise_rotation_requests_no_channel_past_the_token(lib):
     """b^c and s^a have K values each; what is requested for the missing half of a last piece, and for pieces that do not
     exist, must lie inside them too, down to the smallest token (K = 256, half a piece)."""
