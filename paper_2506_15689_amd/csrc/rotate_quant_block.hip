@@ -196,9 +196,11 @@ struct RbFp6 {
 // PMAX: pieces that a wave has at most.
 // (Two waves a SIMD: allowed more than 256 registers, the compiler gives the MFMAs' results to accumulation registers, and a move each
 // brings them back.  With that, DPP moves without an old value, and a quad's bytes transposed in two steps: K = 11008, 1021 tokens
-// 13.54 -> 13.13 us, 64 5.43 -> 5.13; rotate_quant_small_kernel, K = 1024, 4096 tokens 5.11 -> 4.82.)
+// 13.54 -> 13.13 us, 64 5.43 -> 5.13; rotate_quant_small_kernel, K = 1024, 4096 tokens 5.11 -> 4.82.  Not where the rotation is
+// written out: the registers saved let one more wave in, and the memory is slower with that many rows of fp32 under way: without b^c
+// and s^a, K = 11008, 1777 tokens 38.5 us with two and 31.9 as built, K = 8192 in blocks of 128, 9000 tokens 110.5 and 99.4.)
 template <int LOG2N, bool FP6, int PMAX, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
-__global__ __launch_bounds__(RB_THREADS, 2) void rotate_quant_block_kernel(RotateQuantArgs a, float norm) {
+__global__ __launch_bounds__(RB_THREADS, ROT_OUT ? 1 : 2) void rotate_quant_block_kernel(RotateQuantArgs a, float norm) {
     constexpr bool FOLD_NORM = LOG2N == 8;           // 1/sqrt(256) = 2^-4 sits in the MFMA operand
     __shared__ float red_mn[RB_WAVES], red_mx[RB_WAVES];
     __shared__ int red_sum[RB_WAVES];
@@ -312,9 +314,13 @@ __global__ __launch_bounds__(RB_THREADS, 2) void rotate_quant_block_kernel(Rotat
 // holds (8 values per lane per piece).  The stages over e9 (, e10) pair its pieces register by register; nothing crosses
 // waves, so there is no LDS and no barrier, and the four waves of a workgroup take four tokens.  b^c and s^a stay in
 // registers over a wave's tokens, the next token is requested before the current one is worked on.
+// Registers as in the blockwise kernel, but two waves a SIMD do not pay for K = 2048 with both vectors either (4000 tokens 11.5 us, as
+// built 9.3; three waves fit both ways), and with one of them and the rotation written out a fourth wave is kept away, as above
+// (20000 tokens, fp6 form too, 80.9 and 76.7 us).
 template <int NP, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
-__global__ __launch_bounds__(RB_THREADS, 2) void rotate_quant_small_kernel(RotateQuantArgs a, float norm) {
+__global__ __launch_bounds__(RB_THREADS, ROT_OUT || (NP == 4 && HAS_BIAS && HAS_SCALE) ? 1 : 2) void rotate_quant_small_kernel(RotateQuantArgs a, float norm) {
     constexpr bool FOLD_NORM = NP == 2;                // 1/sqrt(1024) = 2^-5 sits in the MFMA operand
+    if (NP == 4 && ROT_OUT && HAS_BIAS != HAS_SCALE) asm volatile("" ::: "v128");
     constexpr int K = 512 * NP;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const P2Lane pl = p2_lane(lane);

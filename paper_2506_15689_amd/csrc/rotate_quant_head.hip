@@ -84,12 +84,13 @@ __device__ __forceinline__ float rh_item(float v, int t) {
 // range arithmetic, 30 instructions that one item repeats on the 16 lanes of a head -- is done for the NI items on
 // different lanes at once.  What bounds it is vector-instruction issue, 100 per item: 120 while the compiler, allowed more than 256
 // registers a lane, kept the MFMAs' results in accumulation registers, and every DPP move had a zero put into its result first;
-// 8192 tokens of K = 4096 20.5 -> 19.2 us.
+// 8192 tokens of K = 4096 20.5 -> 19.2 us.  Where the rotation is written out they may stay there: a wave a SIMD more is slower then
+// (1777 tokens with s^a 11.5 us, as built 11.2).
 // K = 4096, one item a step and nothing requested ahead -> with both: 1024 tokens 8.0 -> 6.5 us, 4096 tokens 15.7 -> 13.7,
 // 8192 tokens 25.4 -> 21.2, 65536 tokens 156 -> 127; K = 8192, 16384 tokens 102 -> 69 (before the staging below took its present
 // form, and on another machine than its figures).  NI = 2 throughout: 24.1 us at 8192 tokens; eight workgroups per compute unit: 16.5 us at 4096.
 template <int NI, bool HAS_BIAS, bool HAS_SCALE, bool ROT_OUT>
-__global__ __launch_bounds__(RH_THREADS, 2) void rotate_quant_head_kernel(RotateQuantArgs a, float norm) {
+__global__ __launch_bounds__(RH_THREADS, ROT_OUT ? 1 : 2) void rotate_quant_head_kernel(RotateQuantArgs a, float norm) {
     // bias and s^a laid out so that lane l of piece (c, r) reads the float2 at ((c*4 + r)*64 + l)
     extern __shared__ __attribute__((aligned(16))) float rh_lds[];
     const int K = a.K;
