@@ -278,11 +278,17 @@ int basq_diag_block_vector_channels(int32_t K) {
     return rotate_quant_block_vector_channels(K);
 }
 
-static bool shape_takes_fp6(int64_t M, int32_t K, int32_t N) {
-    alignas(16) static const uint8_t given[16] = {};           // stands for both operands: only whether they are given counts
+alignas(16) static const int32_t given[4] = {};                // stands for an operand or table: only that it is given, and aligned, counts
+
+static GemmArgs fp6_shape(int64_t M, int32_t K, int32_t N) {
     GemmArgs g{};
-    g.M = M; g.K = K; g.N = N; g.Aq6 = g.Wq6 = given;
-    return K >= 1 && N >= 1 && takes_fp6(g);
+    g.M = M; g.K = K; g.N = N;
+    g.Aq6 = g.Wq6 = reinterpret_cast<const uint8_t*>(given);
+    return g;
+}
+
+static bool shape_takes_fp6(int64_t M, int32_t K, int32_t N) {
+    return K >= 1 && N >= 1 && takes_fp6(fp6_shape(M, K, N));
 }
 
 int basq_diag_fp6_tiling(int64_t M, int32_t K, int32_t N) {
@@ -313,8 +319,10 @@ static int run_fp6_tiling(int32_t tiling, int32_t tilings, int (*launch)(int, co
 }
 
 int basq_diag_grouped_tiling(int64_t M, int32_t K, int32_t N) {
-    if (M < 1 || N < 1 || K < 128 || K % 128 != 0) return -1;
-    return N % 4 == 0 && gemm_grouped_wide_is_faster(M, N, K) ? 1 : 0;
+    if (M < 1 || N < 1 || K < 1) return -1;
+    const GemmArgs g = fp6_shape(M, K, N);
+    if (!gemm_grouped_fp6_applicable(g)) return -1;
+    return gemm_grouped_wide_applicable(g, given) && gemm_grouped_wide_is_faster(M, N, K) ? 1 : 0;
 }
 
 int64_t basq_diag_grouped_wide_strays(int64_t M, int32_t K, int32_t N) {

@@ -91,6 +91,9 @@ def test_grouped_tilings_by_name(lib):
     # odd output widths, rows shorter than the ring, too few tiles, and a second round of them just begun
     assert T(2048, 4096, 12290) == T(2048, 256, 12288) == T(333, 4096, 4096) == T(1775, 4096, 8176) == 0
     assert T(0, 4096, 4096) == T(4, 192, 4096) == -1
+    # an operand or a table of 4 GiB, which the fp6 form cannot address: the largest that it takes, and one more of each
+    assert T(256, 32768, 174752) >= 0 and T(174752, 32768, 256) >= 0
+    assert T(256, 32768, 174752 + 32) == T(174752 + 32, 32768, 256) == -1
     call = lambda t, K=512, N=64, a=FAKE, gs=FAKE: lib.basq_diag_w4a4_gemm_grouped_fp6(
         t, FAKE, 64, K, N, FAKE, FAKE, gs, None, FAKE, 64, a, FAKE, None)
     assert call(-1) == call(2) == call(0, a=None) == call(1, gs=None) == call(0, K=192) == B.BASQ_EINVAL
