@@ -113,6 +113,16 @@ def traffic_of(table, workload, kernel, field="bytes_per_launch"):
     return None
 
 
+def product_kernel(M, K, N, grouped, fp6):
+    """Name of the tiled kernel that a product takes."""
+    from paper_2506_15689_amd import binding as B
+    if not grouped:
+        return "gemm_w4a4_fp6_kernel" if fp6 else "gemm_w4a4_direct_kernel"
+    if not fp6:
+        return "gemm_w4a4_grouped_kernel"
+    return ("gemm_w4a4_grouped_kernel", "gemm_w4a4_grouped_fp6_kernel", "gemm_w4a4_grouped_wide_kernel")[1 + B.basq_diag_grouped_tiling(M, K, N)]
+
+
 # ---- CPU oracle leg (runs in a child process so that its thread count can be set; never touches the GPU) -----------
 
 def cpu_baseline_child(config, sample_tokens):
@@ -438,8 +448,7 @@ def run_workload(args, config, steps, warmup, *, with_ceilings, traffic_table, M
     else:
         ach = ops / (gemm_ms * 1e-3) / 1e12
         peak = FP6_PEAK_TOPS if (use_fp6 or g_fp6) else INT8_PEAK_TOPS
-        kname = ("gemm_w4a4_fp6_kernel" if use_fp6 else
-                 (("gemm_w4a4_grouped_fp6_kernel" if g_fp6 else "gemm_w4a4_grouped_kernel") if grouped else "gemm_w4a4_direct_kernel"))
+        kname = product_kernel(M, K, N, grouped, use_fp6 or g_fp6)
         roof = {"kernel": kname, "bound": "mfma", "achieved": ach, "peak": peak, "unit": "TOP/s", "frac": ach / peak,
                 "traffic": traffic_of(table, config, kname), "algorithmic_ops": ops, "algorithmic_bytes": gemm_bytes,
                 **spread(t_gemm)}

@@ -35,6 +35,17 @@ def test_algorithmic_bytes_follow_the_stated_formulas():
     assert bench.algorithmic_bytes_gemm(16, 4096, 4096, False) == 4096 * 2048 + 4096 * 12 + 16 * (2048 + 16) + 2 * 16 * 4096
 
 
+def test_the_kernel_named_is_the_one_that_the_product_takes():
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.product_kernel(4096, 8192, 28672, True, True) == "gemm_w4a4_grouped_wide_kernel"
+    assert bench.product_kernel(2048, 4096, 12290, True, True) == "gemm_w4a4_grouped_fp6_kernel"     # (N % 4 != 0)
+    assert bench.product_kernel(256, 32768, 174784, True, True) == "gemm_w4a4_grouped_kernel"        # (weights of 4 GiB)
+    assert bench.product_kernel(4096, 8192, 28672, True, False) == "gemm_w4a4_grouped_kernel"
+    assert bench.product_kernel(4096, 8192, 28672, False, True) == "gemm_w4a4_fp6_kernel"
+    assert bench.product_kernel(4096, 8192, 28672, False, False) == "gemm_w4a4_direct_kernel"
+
+
 import json
 
 import pytest
