@@ -21,7 +21,8 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-cont
 # Kernels with 32 .. 128 MFMA results a lane that vector instructions take up at once: without this the compiler puts the results
 # into accumulation registers wherever a kernel may have more than 256 registers (workgroups of four waves with much LDS), and
 # moves each back, 4-5 % of all instructions (61 tokens of K = 4096 4.78 -> 4.58 us, 256 of K = 14336 7.60 -> 7.38, 600 of K =
-# 8192 with s^a 12.6 -> 11.5).  The one-launch decode kernel is 1 % slower with it.
+# 8192 with s^a 12.6 -> 11.5).  The one-launch decode kernel is 1 % slower with it.  An option of LLVM that it does not document: a
+# compiler without it builds the same kernels, slower.
 MFMA_VGPR_SOURCES = {"rotate_quant_pow2.hip", "rotate_quant_k28.hip"}
 MFMA_VGPR_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
 
@@ -33,9 +34,21 @@ def _hipcc() -> str:
     return "hipcc"
 
 
+def _takes(flags) -> bool:
+    """Whether the compiler knows `flags` (tried on an empty program)."""
+    cmd = [_hipcc(), "--offload-arch=gfx950", *flags, "--cuda-device-only", "-nogpuinc", "-nogpulib", "-fsyntax-only", "-x", "hip", os.devnull]
+    return subprocess.run(cmd, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL).returncode == 0
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), *HIPCC_FLAGS, *(MFMA_VGPR_FLAGS if src in MFMA_VGPR_SOURCES else []), "-c", os.path.join(CSRC, src), "-o", obj]
+    flags = list(HIPCC_FLAGS)
+    if src in MFMA_VGPR_SOURCES:
+        if _takes(MFMA_VGPR_FLAGS):
+            flags += MFMA_VGPR_FLAGS
+        else:
+            sys.stderr.write(f"{src}: the compiler does not know {MFMA_VGPR_FLAGS[-1]}, built without it\n")
+    cmd = [_hipcc(), *flags, "-c", os.path.join(CSRC, src), "-o", obj]
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in proc.stdout.splitlines() if "packed-fp32-ops" not in l)
     if proc.returncode != 0:
