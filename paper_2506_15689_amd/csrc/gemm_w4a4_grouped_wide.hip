@@ -463,7 +463,12 @@ int launch_gemm_grouped_wide(const GemmArgs& a, const int32_t* w_gsum, hipStream
     const int64_t tm = (a.M + GW_BM - 1) / GW_BM, tn = ((int64_t)a.N + GW_BN - 1) / GW_BN;
     if (tm * tn > 0x7FFFFFFFll) return fail(BASQ_EINVAL, "w4a4_gemm_grouped: problem too large for one launch");
     GemmArgs b = a;
-    b.store_form = output_form(a, a.K >= 1024 || (a.ldy & 31) == 0 || tm * tn <= 256);        // as on the small tiles (gemm_w4a4_grouped_fp6.hip)
+    // Rows of half lines with the hint, odder ones without, whatever K and the number of tiles: one workgroup per compute unit does not
+    // hide what the hint costs there (outputs that no cache holds any more, us with and without; 128 x 128 tiles.  Half lines: 2567 x
+    // 4000, K = 384 11.9 and 14.0; 12.1; 1585 x 27872, K = 2048 90.8 and 104.9; 103.5; 917 x 12256, K = 4096 44.3 and 46.3; 55.0.  Odder:
+    // 3132 x 3536, K = 512 18.0 and 13.3; 14.4; 2591 x 4176, K = 1024 20.5 and 16.8; 18.7; 2739 x 14224, K = 4096 160.8 and 152.1;
+    // 156.8; 4020 x 8784, K = 8192 226.9 and 224.6; 267.3; but 385 x 19792, K = 384 13.5 and 14.2; 14.1).
+    b.store_form = output_form(a, (a.ldy & 31) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 63) == 0);
     const int64_t grid = tm * tn < 256 ? tm * tn : 256;           // persistent workgroups, one per compute unit
     hipLaunchKernelGGL(gemm_w4a4_grouped_wide_kernel, dim3((unsigned)grid), dim3(GW_THREADS), 0, s, b, w_gsum, (int)tm, (int)tn);
     return check_hip(hipGetLastError(), "w4a4_gemm_grouped (wide) launch");
