@@ -445,7 +445,12 @@ bool gemm_grouped_wide_applicable(const GemmArgs& a, const int32_t* w_gsum) {
 
 // Microseconds of both tilings, least squares over 120 shapes (100 .. 4096 tokens, N 1024 .. 28672, K 1024 .. 14336, 90 and more
 // of the large tiles), 6-7 %: rounds in which every compute unit is full, and a last one by the number of tiles a compute unit
-// holds there and the share of the chip that they fill.  The choice is 0.3 % off the faster one in the mean (worst 6 %).
+// holds there and the share of the chip that they fill.  Rows of odd lines cost the large tiles more with outputs that no cache
+// holds (their stores wait on nobody else's work), so there they have to be 4 % cheaper: without that 2552 x 10224, K = 8192 205 us
+// against 201, 377 x 24208, K = 1024 19.0 against 18.2, 334 x 23824 5 % off.  Over 304 shapes (100 .. 4096 tokens, N 1024 .. 28672, K 384 ..
+// 14336, 100 and more of the large tiles) the large tiles are then nowhere more than 2 % behind the small ones where they are
+// taken; the small ones are taken where the large are up to 22 % faster (4091 x 24512, K = 1536 173 and 141; K < 1024 and
+// several rounds of tiles), with cold weights the choice is 0.8 % off the faster tiling in the mean.
 // Where they are even: one round of large tiles, three quarters full (K = 4096: 2272 x 3584, 171 tiles, 36.0 us narrow and 40.9;
 // 3816 x 2480, 195 tiles, 47.9 and 41.9); a second one just begun loses (1775 x 8176, 301 tiles, 60.8 and 78.1).
 bool gemm_grouped_wide_is_faster(int64_t M, int32_t N, int32_t K) {
@@ -456,7 +461,7 @@ bool gemm_grouped_wide_is_faster(int64_t M, int32_t N, int32_t K) {
     double narrow = 2.9 + (double)(small / 512) * (3.0 + 0.882 * g), wide = 4.5 + (double)(large / 256) * (7.5 + 1.068 * g);
     if (small_left > 0) narrow += (small_left == 1 ? 2.3 + 0.386 * g : 3.0 + 0.639 * g) + 0.266 * g * (double)small_over / 512;
     if (large_over > 0) wide += 4.5 + 0.653 * g + 0.469 * g * (double)large_over / 256;
-    return wide < narrow;
+    return wide < (N % 32 != 0 ? 0.96 : 1.0) * narrow;
 }
 
 int launch_gemm_grouped_wide(const GemmArgs& a, const int32_t* w_gsum, hipStream_t s) {

@@ -90,6 +90,9 @@ def test_grouped_tilings_by_name(lib):
     assert T(2048, 4096, 12288) == T(3345, 8192, 2720) == 1
     # odd output widths, rows shorter than the ring, too few tiles, and a second round of them just begun
     assert T(2048, 4096, 12290) == T(2048, 256, 12288) == T(333, 4096, 4096) == T(1775, 4096, 8176) == 0
+    # rows of odd lines, where the large tiles have to be the cheaper ones by a margin; the same in rows of whole and half lines
+    assert T(279, 1024, 24272) == T(2552, 8192, 10224) == T(1729, 1536, 27280) == 0
+    assert T(279, 1024, 24256) == T(279, 1024, 24288) == T(3684, 1024, 3088) == 1
     assert T(0, 4096, 4096) == T(4, 192, 4096) == -1
     # an operand or a table of 4 GiB, which the fp6 form cannot address: the largest that it takes, and one more of each
     assert T(256, 32768, 174752) >= 0 and T(174752, 32768, 256) >= 0
