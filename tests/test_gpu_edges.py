@@ -778,6 +778,41 @@ def test_wide_tiles_of_the_group_wise_product(K):
         assert torch.equal(got.view(torch.int16), want.view(torch.int16))
 
 
+@pytest.mark.parametrize("K", [384, 512, 640])
+def test_wide_group_wise_tiles_of_three_to_a_workgroup(K):
+    """More than two tiles for each compute unit: a workgroup takes back the first buffer of column constants and hands its ring
+    over twice, from each position that the number of groups can leave it in."""
+    M, N, G = 17 * 256 - 45, 31 * 192, K // 128
+    announce(f"three wide group-wise tiles a workgroup K={K}")
+    A, A6, meta, W, W6, sw, zp, _, c = random_product(M, N, K, seed=K, groups=G)
+    gsum = torch.empty((G, N), dtype=torch.int32, device=DEV)
+    B.basq_group_colsums(W, 128, gsum)
+    want, got = (torch.full((M, N), -7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    B.basq_w4a4_gemm_grouped(A, meta, 128, W, sw, zp, gsum, c, want)
+    B.basq_diag_w4a4_gemm_grouped_fp6(1, meta, K, sw, zp, gsum, c, got, A6, W6)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("K", [128, 256, 384, 640, 1152])
+def test_small_tiles_of_the_group_wise_product(K):
+    """The 128 x 128 tiling by name, which large products no longer take by themselves: from one group on, ragged tiles, odd rows,
+    more tiles than are in flight at once."""
+    G = K // 128
+    for M, N, ldy, offset in [(1, 1, 1, 0), (33, 72, 72, 0), (128, 128, 128, 0), (129, 127, 130, 1), (481, 612, 620, 0), (300, 1001, 1001, 3),
+                              (9 * 256 - 45, 30 * 192 + 8, 30 * 192 + 8, 0)]:
+        announce(f"small group-wise tiling M={M} N={N} K={K} ldy={ldy} offset={offset}")
+        A, A6, meta, W, W6, sw, zp, _, c = random_product(M, N, K, seed=M + N, groups=G)
+        gsum = torch.empty((G, N), dtype=torch.int32, device=DEV)
+        B.basq_group_colsums(W, 128, gsum)
+        want = torch.full((M, N), -7.0, dtype=torch.bfloat16, device=DEV)
+        B.basq_w4a4_gemm_grouped(A, meta, 128, W, sw, zp, gsum, c, want)
+        buf, Y = output_view(M, N, ldy, offset)
+        B.basq_diag_w4a4_gemm_grouped_fp6(0, meta, K, sw, zp, gsum, c, Y, A6, W6)
+        assert torch.equal(Y.contiguous().view(torch.int16), want.view(torch.int16))
+        Y.fill_(-7.0)
+        assert bool((buf == -7.0).all()), "wrote outside the output"
+
+
 def test_group_wise_products_on_either_tiling():
     """Shapes on both sides of the rule that chooses between the tilings, through the public call."""
     chosen = set()
@@ -931,8 +966,8 @@ def test_fp6_form_of_groupwise_codes_where_its_writer_changes(M, with_rot):
 @pytest.mark.parametrize("kind", ["ordinary", "cancelling", "wide exponents", "tiny", "large"])
 @pytest.mark.parametrize("K", [128, 384, 1024])
 def test_group_sums_bit_for_bit(K, kind):
-    """The group-wise fp6 kernel keeps F / 64 and takes z * colsum by a matrix instruction; the int8 kernel keeps F by fp32
-    multiply-adds.  All 24 bits of F must agree: with unit weight scales, no zero points and out_bias = -(what was read so far)
+    """The group-wise fp6 kernels keep F / 64 and take z * colsum by a matrix instruction; the int8 kernel keeps F by fp32
+    multiply-adds.  On either tiling of the fp6 product (the large one from three groups on) all 24 bits of F must agree: with unit weight scales, no zero points and out_bias = -(what was read so far)
     three calls bring F out in pieces of eight bits (each difference is exact: what is subtracted is the rounded sum)."""
     announce(f"group sums K={K} {kind}")
     M, N, G = 6, 1500, K // 128
@@ -953,18 +988,24 @@ def test_group_sums_bit_for_bit(K, kind):
     one, zero = torch.ones(N, dtype=torch.bfloat16, device=DEV), torch.zeros(N, dtype=torch.bfloat16, device=DEV)
     for m in range(M):
         got = []
-        for forms in ({}, dict(Aq6=B.alloc_fp6_buffer(1, K), Wq6=W6)):
-            if forms:
-                B.basq_pack_fp6(A[m:m + 1], forms["Aq6"])
+        a6, mt = B.alloc_fp6_buffer(1, K), meta[m * G:(m + 1) * G]
+        B.basq_pack_fp6(A[m:m + 1], a6)
+        # the int8 kernel, the call with the fp6 forms, which takes the small tiles for one token, and the large ones by name
+        for tiling in (None, 0, 1) if G >= 3 else (None, 0):
             read = torch.zeros(N, device=DEV)
             pieces = []
             for _ in range(3):
                 Y = torch.empty((1, N), dtype=torch.bfloat16, device=DEV)
-                B.basq_w4a4_gemm_grouped(A[m:m + 1], meta[m * G:(m + 1) * G], 128, W, one, zero, gsum, -read, Y, **forms)
+                if tiling == 1:
+                    B.basq_diag_w4a4_gemm_grouped_fp6(1, mt, K, one, zero, gsum, -read, Y, a6, W6)
+                else:
+                    forms = {} if tiling is None else dict(Aq6=a6, Wq6=W6)
+                    B.basq_w4a4_gemm_grouped(A[m:m + 1], mt, 128, W, one, zero, gsum, -read, Y, **forms)
                 pieces.append(Y[0].view(torch.int16).clone())
                 read = read + Y[0].float()
             got.append(torch.stack(pieces))
-        assert torch.equal(got[0], got[1]), f"token {m}: {int((got[0] != got[1]).sum())} pieces differ"
+        for tiling, pieces in enumerate(got[1:]):
+            assert torch.equal(got[0], pieces), f"token {m}, tiling {tiling}: {int((got[0] != pieces).sum())} pieces differ"
 
 
 @pytest.mark.parametrize("K,M", [(8192, 2049), (8192, 2344), (8192, 3999), (8192, 5000), (4096, 8192 + 8), (4096, 9000),
