@@ -452,10 +452,13 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         // two halves of the row blocks: the first half's stores go out while the other is worked on (together with the order of
         // the MFMAs: 2048 x 4096 x 12288 60.2 -> 58.8 us, with cached weights 59.5 -> 57.0).  In front of the first stores a wait for
         // the next tile's first stages (requested before this epilogue, so mostly landed): behind them it would be one for the
-        // stores too, the counter being one and the same.  256 x 256 tiles in one go: their stages are longer on the way, and with
-        // weights from memory the earlier wait costs what the earlier stores gain (4096 x 8192 x 28672 422 and 426, with cached weights
-        // 417 and 412; layer calls between other work 448 and 453).  Nor with two workgroups per compute unit, whose ends overlap
-        // as it is (128 x 128 tiles 14.7 and 14.9).
+        // stores too, the counter being one and the same.  (4000 x 2048 x 12288 79.1 -> 75.2; x 6144 on 256 x 128 tiles 45.0 -> 42.6;
+        // even from K = 8192 on.)  256 x 256 tiles in one go: their stages are longer on the way, and with long rows and weights from memory the
+        // earlier wait costs more than the earlier stores gain (in one go and in halves; with cached weights: 4096 x 8192 x 28672 420.2 and
+        // 424.3; 405.2 and 402.4; 2048 x 8192 x 28672 230.5 and 236.9; 221.3 and 219.8; 4096 x 11008 x 16384 308.8 and 312.5; 298.5 and
+        // 296.5).  With shorter rows they would gain too (4096 x 4096 x 28672 232.1 and 226.2, 8192 x 512 x 16384 92.0 and 87.4), which would
+        // take a second copy of the epilogue.  Nor with two workgroups per compute unit, whose ends overlap as it is (128 x 128
+        // tiles 14.7 and 14.9).
         constexpr int FIRST = KGROUPS == 1 && MINOCC * 4 == WAVES && BN < 256 ? (OWN + 1) / 2 : OWN;
         auto finish = [&](auto first_c, auto count_c) {
             constexpr int i0 = decltype(first_c)::value, count = decltype(count_c)::value;
@@ -543,7 +546,9 @@ double tiling_cost(const Tiling& t, int64_t M, int64_t N, int K) {
 // Six tilings; the cheapest by the table is within 0.3 % of the fastest in the mean over those shapes (13 % at worst), whose
 // weights were in the caches.  With weights cold in memory it is as good from 334 tokens on, and 1.2 % off for 65 .. 333, where
 // a pass over the weights is what counts and 64 x 64 tiles make too many of them (192 x 8192, K = 14336: 45 us against 34 on 128 x 64,
-// with the weights in the caches 31 against 32).
+// with the weights in the caches 31 against 32).  Over 200 other shapes (129 .. 4096 tokens, same N and K) at the present kernels, whose
+// 256-row tiles finish in halves: 0.4 % off with weights in the caches (12 % at worst), 0.8 % with cold ones (24 %: 556 x 24368, K = 14336
+// on 128 x 128, where 256 x 192 is the faster one), so the fit stands.
 // Choosing among the first, second and fourth by how evenly their tiles fill the chip, as before, was 13 % off in the
 // mean and up to 2.6 times: it gave 129 .. 500 tokens tiles too large to occupy the chip (333 x 4096 x 4096: 96 tiles
 // of 128 x 128 take 14.1 us, 384 of 64 x 64 11.9 us), and where a round of 256 x 128 tiles fits exactly it takes

@@ -322,7 +322,9 @@ __global__ __launch_bounds__(GW_THREADS, 2) void gemm_w4a4_grouped_wide_kernel(G
     while (true) {
         // Every group requests the one three further on: the last three those of the next tile, whose first fragments are read
         // with the last group, or nothing, from past the end of the operands.  The second and third group of a later tile
-        // have landed before the stores of the tile in front went out: a wait would be one for those stores.
+        // have landed before the stores of the tile in front go out (the wait in `finish`).  Its first two groups need no wait for
+        // loads, then, but the one copy of their code has it, and there it is a wait for those stores: for all but six of them in the
+        // first group, for the rest in the second.
         const int next_pid = pid + gridDim.x;
         const bool more = next_pid < total;
         int next_m = 0, next_n = 0;
