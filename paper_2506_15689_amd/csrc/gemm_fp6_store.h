@@ -149,6 +149,106 @@ __device__ __forceinline__ void store_accumulators(const GemmArgs& a, int64_t m0
         }
 }
 
+// The same out of 16 x 16 blocks: accumulator register r of lane l belongs to token l % 16 and channel 4*(l/16) + r of a block,
+// outv[i][j][p] = channels 4*(l/16) + 2p, +1 of row block i, column block j of 16 (j / 2 of 32: col_block).  Lane bit 4 (channel)
+// trades places with the low bit of j, and in a pair of 32-column blocks lane bit 3 (token) with the block: as above a lane owns 16 bytes of
+// one token's row and a store covers whole lines of eight rows, at half the swaps between lanes.
+template <StoreForm FORM, int TM, int TN, int BM, class ColBlock>
+__device__ __forceinline__ void store_outputs16_as(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const unsigned (&outv)[TM][TN][2], ColBlock&& col_block) {
+    const int piece = 2 * ((lane >> 4) & 1) + (lane >> 5);
+    const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;       // of the matrix, from the tile's start
+    auto store16 = [&](int row, int col, unsigned o0, unsigned o1, unsigned o2, unsigned o3) {      // within the tile
+        if (row >= row_end || col >= col_end) return;
+        uint16_t* dst = a.Y + (m0 + row) * a.ldy + n0 + col;
+        const basq_v4u v = {o0, o1, o2, o3};
+        if (FORM == StoreForm::whole_nt) {
+            nt_store16(dst, make_uint4(o0, o1, o2, o3));
+        } else if (FORM == StoreForm::whole) {
+            *reinterpret_cast<basq_v4u*>(dst) = v;
+        } else if (col + 8 <= col_end) {
+            __builtin_memcpy(dst, &v, 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (col + 2 * e + 1 < col_end) { const unsigned d = v[e]; __builtin_memcpy(dst + 2 * e, &d, 4); }
+                else if (col + 2 * e < col_end) dst[2 * e] = (uint16_t)v[e];
+            }
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        unsigned z[TN / 2][4];                                // 16 bytes: piece `piece` of token l % 16
+#pragma unroll
+        for (int j = 0; j < TN / 2; ++j)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const auto u = __builtin_amdgcn_permlane16_swap(outv[i][2 * j][p], outv[i][2 * j + 1][p], false, false);
+                z[j][p] = u[0]; z[j][2 + p] = u[1];
+            }
+#pragma unroll
+        for (int j = 0; j < TN / 2; j += 2) {
+            if (j + 1 < TN / 2) {
+                unsigned lo[4], hi[4];                        // tokens 0..7 and 8..15 of the sixteen (row rotation by 8 lanes)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    lo[e] = (unsigned)__builtin_amdgcn_update_dpp((int)z[j][e], (int)z[j + 1][e], 0x128, 0xF, 0xC, false);
+                    hi[e] = (unsigned)__builtin_amdgcn_update_dpp((int)z[j + 1][e], (int)z[j][e], 0x128, 0xF, 0x3, false);
+                }
+                const int row = row0 + i * 16 + (lane & 7), col = (col_block(j) + ((lane >> 3) & 1)) * 32 + 8 * piece;
+                store16(row, col, lo[0], lo[1], lo[2], lo[3]);
+                store16(row + 8, col, hi[0], hi[1], hi[2], hi[3]);
+            } else {
+                store16(row0 + i * 16 + (lane & 15), col_block(j) * 32 + 8 * piece, z[j][0], z[j][1], z[j][2], z[j][3]);
+            }
+        }
+        if (i & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+template <int TM, int TN, int BM, class ColBlock>
+__device__ __forceinline__ void store_outputs16(const GemmArgs& a, StoreForm form, int64_t m0, int n0, int row0, int lane, const unsigned (&outv)[TM][TN][2], ColBlock&& col_block) {
+    if (form == StoreForm::whole_nt)
+        store_outputs16_as<StoreForm::whole_nt, TM, TN, BM>(a, m0, n0, row0, lane, outv, col_block);
+    else if (form == StoreForm::whole)
+        store_outputs16_as<StoreForm::whole, TM, TN, BM>(a, m0, n0, row0, lane, outv, col_block);
+    else
+        store_outputs16_as<StoreForm::any, TM, TN, BM>(a, m0, n0, row0, lane, outv, col_block);
+}
+
+typedef float fp6_acc4_t __attribute__((ext_vector_type(4)));
+
+template <int TM, int TN, int BM, class ColBlock>
+__device__ __forceinline__ void store_accumulators16(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const fp6_acc4_t (&acc)[TM][TN], ColBlock&& col_block) {
+    const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;
+    auto store16 = [&](int row, int col, const int (&v)[4]) {
+        if (row >= row_end) return;
+        int32_t* dst = a.acc_out + (m0 + row) * a.N + n0 + col;
+        if (col + 4 <= col_end) {
+            __builtin_memcpy(dst, v, 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (col + e < col_end) dst[e] = v[e];
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; j += 2) {
+            int lo[4], hi[4];                                 // tokens 0..7 and 8..15 of the sixteen (row rotation by 8 lanes)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int v0 = __float2int_rn(64.0f * acc[i][j][e]), v1 = __float2int_rn(64.0f * acc[i][j + 1][e]);
+                lo[e] = __builtin_amdgcn_update_dpp(v0, v1, 0x128, 0xF, 0xC, false);
+                hi[e] = __builtin_amdgcn_update_dpp(v1, v0, 0x128, 0xF, 0x3, false);
+            }
+            const int row = row0 + i * 16 + (lane & 7), col = col_block(j / 2) * 32 + 16 * ((lane >> 3) & 1) + 4 * (lane >> 4);
+            store16(row, col, lo);
+            store16(row + 8, col, hi);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+}
+
 // How the outputs leave.  With the non-temporal hint they don't displace the operands from the caches (4096 x
 // 28672, K = 8192: 406 us with, 420 without; 2048 x 12288, K = 4096 56 and 58; 333 x 4096 even) -- where rows are whole
 // 128-byte lines.  A line that two rows share is otherwise written in two parts (every product into outputs that no cache holds

@@ -1,15 +1,22 @@
 // Prefill INT4 x INT4 -> INT32 GEMM on the f8f6f4 matrix-core path (paper Sec. 5.2; Fig. 6; Eq. 14).
 //
 // Both operands arrive in the fp6 operand form of fp6_pack.hip: code q stored as the e2m3 number q/8.
-// v_mfma_f32_32x32x64_f8f6f4 with two fp6 operands runs at twice the int8 rate and its fp32 accumulator
+// v_mfma_f32_16x16x128_f8f6f4 with two fp6 operands runs at twice the int8 rate and its fp32 accumulator
 // holds S = sum_k (qa/8)(qb/8) exactly (multiples of 1/64, S < 2^17 for K <= 32768).  The integer
 // accumulator of the INT4 product is ACC = 64*S; the epilogue de-quantises exactly as the int8 kernels do.
+// (16 x 16 x 128 and not 32 x 32 x 64: the chip's power sets the clock under such a loop, and a register-resident one on
+// code-valued operands runs at 8.7 POP/s in this shape, 7.6 in the other.  Products with the weights in the caches, this kernel
+// against its predecessor on 32 x 32 x 64, us: 4096 x 8192 x 28672 413 -> 390, 2048 x 4096 x 12288 54.7 -> 51.6, 2048 x 14336 x 4096
+// 59.5 -> 54.2, 256 x 4096 x 8192 on 128 x 64 tiles 11.0 -> 9.4.)
 //
-// Structure as in gemm_w4a4_direct.hip: direct-to-LDS buffer loads into a ring of stages, fragments
-// read one step ahead into two register sets, XCD-aware tile order.  A stage holds 128 codes per row.
-// The operands are stored as 3 KB blocks of 32 rows x 128 codes that already are the LDS image (see
-// fp6_pack.hip): a stage is filled by contiguous 1 KB copies of whole cache lines, and both the 16-byte
-// and the 8-byte fragment reads are free of bank conflicts.  No unpacking: LDS -> registers -> MFMA.
+// Structure: direct-to-LDS buffer loads into a ring of stages, fragments read ahead, XCD-aware tile order.  A stage holds
+// 128 codes per row.  The operands are stored as 3 KB blocks of 32 rows x 128 codes (see fp6_pack.hip): a stage is filled by
+// 1 KB copies of whole cache lines.  No unpacking: LDS -> registers -> MFMA.
+//
+// What a K-step's code looks like matters as much as what it moves.  Eight waves of a compute unit, 32 MFMAs and 12 fragments (24
+// reads) a wave and step, operands in LDS: 1040 cycles with the MFMAs alone, 1066 with six direct loads a wave, 1120 with the
+// reads, 1295 with a vector instruction for the address of each read.  So reads and loads stand evenly between the MFMAs, and a
+// step's addresses are constants: it knows its ring stage at compile time.
 #include "gemm_fp6_store.h"
 #include <type_traits>
 
@@ -19,8 +26,8 @@ namespace {
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef int v6i __attribute__((ext_vector_type(6)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int NUM_XCD = 8;
 constexpr int CHUNK = 96;              // bytes of one row per stage: 128 codes
@@ -52,14 +59,19 @@ __device__ __forceinline__ void wait_stages_and_barrier(int n) {
 #define G6_GROUP_M 4
 #endif
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int KGROUPS, int STAGES, int MINOCC>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int KGROUPS, int STAGES, int MINOCC, bool SHORT>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm_w4a4_fp6_kernel(GemmArgs a, int tiles_m, int tiles_n) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses device-only buffer-resource types; the host pass only needs the stub
     constexpr int WAVES = WAVES_M * WAVES_N;                  // of one K group
     constexpr int THREADS = WAVES * KGROUPS * 64;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int TM = WM / 32, TN = WN / 32;
+    constexpr int TM = WM / 16, TN = WN / 16;                 // blocks of 16 rows and of 16 columns
     constexpr int OWN = (TM + KGROUPS - 1) / KGROUPS;         // row blocks of its wave tile that a wave finishes
+    // The operand with more blocks is the outer one: its fragments are read half a step ahead, those of the inner one
+    // as soon as their last MFMA of a step has gone (see k_step)
+    constexpr bool ROWS_OUTER = TM >= TN;
+    constexpr int TO = ROWS_OUTER ? TM : TN, TI = ROWS_OUTER ? TN : TM;
+    constexpr int PART0 = TO / 2;                             // outer blocks of a step's first part
     constexpr int ROWS = BM + BN;
     constexpr int STAGE_BYTES = ROWS * CHUNK;
     constexpr int PIECES = STAGE_BYTES / 1024;                // 1 KB pieces of a stage, one wave-load each
@@ -68,6 +80,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     // share, SHARES times 256 bytes (4 a lane); where they do not divide so, or a round holds pieces of both operands as well,
     // the waves without a piece in the last round load nothing there (see issue_one).
     constexpr int WHOLE = PIECES / WAVES, LEFT = PIECES % WAVES;
+    constexpr bool BY_BLOCK = LEFT == 0 && WHOLE % 3 == 0 && A_PIECES % WHOLE == 0;      // whole 32-row blocks of one operand a wave
     constexpr bool SHARED = LEFT != 0 && LEFT * 4 % WAVES == 0 && A_PIECES % WAVES == 0;
     constexpr bool PADDED = LEFT != 0 && !SHARED;
     constexpr int SHARES = SHARED ? LEFT * 4 / WAVES : 0;
@@ -83,9 +96,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KGROUPS * STAGES * STAGE_BYTES + (PADDED ? 1024 : 0)];
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = (tid >> 6) % WAVES;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-    const int swave = __builtin_amdgcn_readfirstlane(wave);
+    const int lane = tid & 63, swave = __builtin_amdgcn_readfirstlane((tid >> 6) % WAVES);
+    const int wm = swave / WAVES_N, wn = swave % WAVES_N;
     // K groups: group g of the workgroup's waves takes a contiguous part of the chunks through a ring of its own.  All take
     // the same number of steps, since they meet at the barriers; the chunks left over by the division go to the last
     // groups, and a group that has one fewer (`idle_last`) leaves the last step's MFMAs out (what it has loaded there is
@@ -124,15 +136,17 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
 
     // ---- direct loads: load i of wave w copies the 1 KB piece number i*WAVES + w of the stage; three
     // pieces make one 32-row block.  Which block a piece comes from is uniform over the wave, so it goes
-    // into the scalar offset of the load; the only per-lane part is 16 * lane.  Blocks past the matrix
-    // are clamped to its last block.
-    const int lane_off = lane * 16;
+    // into the scalar offset of the load; the per-lane part is 16 * lane, except for the 1 KB of 8-byte tails: there the 128
+    // bytes of rows 0 .. 15 and of rows 16 .. 31 trade places for the groups 2 and 3, see the fragment addressing.
+    // BY_BLOCK: a wave's pieces are whole blocks of one operand, so it needs one descriptor, and an address per block
+    // (256 x 4096 x 8192 on 128 x 128 tiles 12.0 -> 11.6 us, 700 x 384 x 3000 5.7 -> 5.4).
+    // Blocks past the matrix are clamped to its last block.
     int soff[LOADS];                                           // scalar: block and part of each of this wave's pieces
     auto set_tile = [&](int tile_m, int tile_n) {
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
             const int share = swave * SHARES + i - WHOLE;      // number of the 256 bytes among the last pieces
-            const int piece = SHARED && i >= WHOLE ? WHOLE * WAVES + share / 4 : i * WAVES + swave;
+            const int piece = BY_BLOCK ? swave * WHOLE + i : SHARED && i >= WHOLE ? WHOLE * WAVES + share / 4 : i * WAVES + swave;
             int blk = piece / 3;
             const int part = piece % 3;
             if (piece < A_PIECES) {
@@ -145,7 +159,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
             soff[i] = blk * BLOCK + part * 1024 + (SHARED && i >= WHOLE ? share % 4 * 256 : 0);
         }
     };
-    // load number i of a K-step: into the stage at byte stage_off of the ring, from chunk offsets koff_a / koff_w (unsigned
+    // issue_one: load number i of a K-step: into the stage at byte stage_off of the ring, from chunk offsets koff_a / koff_w (unsigned
     // 32-bit byte offsets).  No branches, which cost tens of cycles a step: where a round holds pieces of both operands,
     // descriptor and offset are selected; waves without a piece in a padded last round load from past the end of the operand,
     // so that nothing is read, to a place in LDS that nobody reads (96 x 64, 333 x 4096 x 4096: 10.3 -> 9.4 us).  Loads of nothing take the
@@ -154,65 +168,106 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     // shares 60.1; 57.9, with a branch 59.8; 58.0; 1021 x 8192 x 11008 54.7; 47.3, 52.6; 47.1, 52.3; 47.8.  256 x 128, four of eight:
     // 777 x 14336 x 5008 52.9; 46.4, 50.0; 46.7, 51.1; 47.1; 2048 x 14336 x 4096 69.9; 60.6, 69.3; 61.2, 68.8; 62.7.  96 x 64:
     // 333 x 4096 x 4096 padded 11.2; 8.4, by shares 11.1; 8.9).
-    const int last_off = PADDED && WHOLE * WAVES + swave >= PIECES ? (int)0xFFFFFF00u : lane_off;
+    // per-lane source offsets of load i (parts of blocks repeat every three loads) and of the shares
+    int src_off[3], share_off[SHARES > 0 ? SHARES : 1];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) src_off[i] = 16 * ((BY_BLOCK ? i : (i * WAVES + swave) % 3) == 2 ? lane ^ (lane >> 5) * 8 : lane);
+#pragma unroll
+    for (int i = 0; i < SHARES; ++i) {
+        const int share = swave * SHARES + i;
+        share_off[i] = 4 * ((WHOLE * WAVES + share / 4) % 3 == 2 && share % 4 >= 2 ? lane ^ 32 : lane);
+    }
+    const int last_off = PADDED && WHOLE * WAVES + swave >= PIECES ? (int)0xFFFFFF00u : src_off[WHOLE % 3];
+    int wave_at = kgroup * (STAGES * STAGE_BYTES) + swave * (BY_BLOCK ? WHOLE * 1024 : 1024);
+    const bool loads_a = swave * WHOLE < A_PIECES;             // (BY_BLOCK)
+    const __amdgpu_buffer_rsrc_t rsrc_own = loads_a ? rsrc_a : rsrc_w;
     auto issue_one = [&](int stage_off, unsigned koff_a, unsigned koff_w, int i) {
         if (SHARED && i >= WHOLE) {
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, LDS_PTR(lds + stage_off + WHOLE * WAVES * 1024 + (swave * SHARES + i - WHOLE) * 256), 4, lane * 4,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, LDS_PTR(lds + stage_off + WHOLE * WAVES * 1024 + (swave * SHARES + i - WHOLE) * 256), 4, share_off[i - WHOLE],
                                                      (int)(koff_w + (unsigned)soff[i]), 0, 0);
+            return;
+        }
+        if constexpr (BY_BLOCK) {
+            // the parts of a block by the load's own offset, which counts in memory and in LDS
+            const unsigned at = (loads_a ? koff_a : koff_w) + (unsigned)soff[i / 3 * 3];
+            uint8_t* dst = lds_all + wave_at + stage_off + i / 3 * BLOCK;
+            if (i % 3 == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_own, LDS_PTR(dst), 16, src_off[0], (int)at, 0, 0);
+            else if (i % 3 == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_own, LDS_PTR(dst), 16, src_off[1], (int)at, 1024, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_own, LDS_PTR(dst), 16, src_off[2], (int)at, 2048, 0);
             return;
         }
         const bool last = i >= WHOLE;
         const bool mixed = i * WAVES < A_PIECES && (i + 1) * WAVES > A_PIECES;
         const bool is_a = mixed ? i * WAVES + swave < A_PIECES : i * WAVES < A_PIECES;
-        uint8_t* dst = lds + stage_off + swave * 1024 + i * WAVES * 1024;
+        uint8_t* dst = lds_all + wave_at + stage_off + i * WAVES * 1024;
         if (last) dst = i * WAVES + swave < PIECES ? dst : lds_all + KGROUPS * STAGES * STAGE_BYTES;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? rsrc_a : rsrc_w, LDS_PTR(dst), 16, last ? last_off : lane_off,
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? rsrc_a : rsrc_w, LDS_PTR(dst), 16, last ? last_off : src_off[i % 3],
                                                  (int)((is_a ? koff_a : koff_w) + (unsigned)soff[i]), 0, 0);
     };
-    constexpr int SPLIT = (LOADS + 1) / 2;                     // the first half of a stage's loads (see `half` below)
+    constexpr int SPLIT = (LOADS + 1) / 2;                     // the first half of a stage's loads (see k_step)
     // Wait until the oldest stage in flight has landed, `ahead` stages having been requested behind it at most
     auto wait_stages = [&](int ahead) { wait_stages_and_barrier<LOADS, STAGES - 2>(ahead); };
+    // A tile's first step takes stage `start` of the ring, so that its last STAGES steps take stages 0 .. STAGES - 1: behind `lead`
+    // steps that reckon their stage, the others have it at compile time.  Tiles of fewer steps than stages (SHORT) have a
+    // kernel of their own: as a second path it cost the others registers (spilled, 256 x 256).
+    constexpr int LEAD = STAGES - 2;                           // of a later tile, whose stages have landed already
+    constexpr bool ROUNDS = !SHORT;                            // at least STAGES steps
+    const int lead = !ROUNDS ? 0 : ksteps >= LEAD + STAGES ? LEAD + (ksteps - LEAD) % STAGES : ksteps % STAGES;
+    const int start = (STAGES * 2 - lead) % STAGES;
     const unsigned kbase_a = (unsigned)chunk0 * a_step, kbase_w = (unsigned)chunk0 * w_step;
     auto issue_prologue = [&]() {
 #pragma unroll
         for (int s = 0; s < STAGES - 1; ++s)
             if (s < ksteps) {
 #pragma unroll
-                for (int i = 0; i < LOADS; ++i) issue_one(s * STAGE_BYTES, kbase_a + s * a_step, kbase_w + s * w_step, i);
+                for (int i = 0; i < LOADS; ++i) issue_one((start + s >= STAGES ? start + s - STAGES : start + s) * STAGE_BYTES, kbase_a + s * a_step, kbase_w + s * w_step, i);
             }
     };
 
-    // ---- fragment addressing: lane (frow, fhalf) feeds k = 64*kb + 32*fhalf .. +31 of its row, i.e.
-    // group f = 2*kb + fhalf of the row's block: 16 bytes among the pieces, 8 bytes among the tails
-    const int frow = lane & 31, fhalf = lane >> 5;
-    int moff[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) moff[kb] = 64 * frow + 16 * ((2 * kb + fhalf) ^ ((frow >> 2) & 3));
-    const int toff = 2048 + 256 * fhalf + 8 * frow;            // k-block 1: 512 bytes further
-    const int a_row = (wm * WM / 32) * BLOCK;
-    // A wave's TN column blocks: pairs of adjacent ones (64 columns, a 128-byte line of outputs), and the odd one left over
+    // ---- fragment addressing: lane (frow, fgroup) feeds k = 32*fgroup .. +31 of row frow of a 16-row half of a block:
+    // 16 bytes among the pieces, 8 bytes among the tails.  LDS serves 16-byte reads of lanes {0-3, 12-15, 20-27}, {4-11, 16-19,
+    // 28-31} and the same of the upper half together, 8-byte reads of 32 lanes at once.  With the groups 0, 3, 1, 2 on lanes
+    // 0-15, 16-31, .. (any order will do, if both operands have the same) the first are free of bank conflicts; the second
+    // are because the halves of the groups 2 and 3 have traded places.  (In the order 0, 1, 2, 3 half of the LDS cycles were conflicts.)
+    const int frow = lane & 15, fgroup = (0x9C >> (2 * (lane >> 4))) & 3;      // 0, 3, 1, 2
+    const int moff = 64 * frow + 16 * (fgroup ^ (frow >> 2));
+    const int toff = 2048 + 256 * fgroup + 8 * frow, tflip = fgroup >> 1;
+    // A wave's WN / 32 column blocks of 32: pairs of adjacent ones (64 columns, a 128-byte line of outputs), and the odd one left over
     // from behind all pairs of the tile.
-    constexpr int PAIRED = TN / 2 * 2;
+    constexpr int PAIRED = WN / 64 * 2;
     auto col_block = [&](int j) { return j < PAIRED ? wn * PAIRED + j : WAVES_N * PAIRED + wn; };
-    auto b_row = [&](int j) { return (BM / 32 + col_block(j)) * BLOCK; };
-    // Byte offsets of the 8-byte tail reads, one opaque register each: reads whose addresses share a
-    // visible base get merged into paired reads, whose result could not land in two operand tuples
-    // without register copies.
-    int ta[TM], tb[TN];
+    // LDS addresses of the 16-byte reads and of the 8-byte reads of either half of a block, for activations, weights and the odd
+    // column block, in every second stage: everything else about a read, also the stage behind, fits its 16-bit offset.
+    constexpr int BASES = (STAGES + 1) / 2;
+    constexpr bool ODD = WN / 32 != PAIRED;
+    struct Base { int main, tail[2]; };
+    Base base_a[BASES], base_b[BASES], base_c[ODD ? BASES : 1];
+    auto set_base = [&](Base& x, int b, int block) {
+        const int at = kgroup * (STAGES * STAGE_BYTES) + 2 * b * STAGE_BYTES + block * BLOCK;
+        x.main = at + moff;
+        x.tail[0] = at + toff + 128 * tflip;
+        x.tail[1] = at + toff + 128 * (1 - tflip);
+        asm volatile("" : "+v"(x.main), "+v"(x.tail[0]), "+v"(x.tail[1]));
+    };
 #pragma unroll
-    for (int i = 0; i < TM; ++i) { ta[i] = a_row + i * BLOCK + toff; asm volatile("" : "+v"(ta[i])); }
-#pragma unroll
-    for (int j = 0; j < TN; ++j) { tb[j] = b_row(j) + toff; asm volatile("" : "+v"(tb[j])); }
+    for (int b = 0; b < BASES; ++b) {
+        set_base(base_a[b], b, wm * (WM / 32));
+        set_base(base_b[b], b, BM / 32 + wn * PAIRED);
+        if (ODD) set_base(base_c[b], b, BM / 32 + WAVES_N * PAIRED + wn);
+    }
+    static_assert(STAGE_BYTES + (WM / 32) * BLOCK <= 65536 && STAGE_BYTES + (WN / 32) * BLOCK <= 65536, "reach of an offset");
 
     // Epilogue constants, one 16-byte record per row and column of the tile: in the last stage of the ring, which the next
     // tile's first loads do not touch.  Kept and read as integers: the compiler puts a wait for every direct-to-LDS load
     // in flight in front of a float-typed LDS read.
     // (with K groups, which take one tile, behind the sums that go through the first group's ring)
-    v4i* lrow_par = reinterpret_cast<v4i*>(lds_all + (KGROUPS == 1 ? (STAGES - 1) * STAGE_BYTES : STAGES * STAGE_BYTES - ROWS * 16));
+    v4i* lrow_par = reinterpret_cast<v4i*>(lds_all + (KGROUPS == 1 ? (start + STAGES - 1) % STAGES * STAGE_BYTES : STAGES * STAGE_BYTES - ROWS * 16));
     v4i* lcol_par = lrow_par + BM;
     // The raw values of one record per thread (rows first), requested a tile ahead of their use and converted only there:
     // a conversion behind the loads would wait for them.
     auto load_par = [&](int tile_m, int tile_n) -> v4i {
+        int tid = threadIdx.x;                                // (opaque: nothing derived from it is kept across the main loop)
+        asm volatile("" : "+v"(tid));
         v4i raw = {0, 0, 0, 0};
         if (tid < BM) {
             int64_t m = (int64_t)tile_m * BM + tid;
@@ -241,45 +296,49 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     while (true) {
         const int64_t m0 = (int64_t)tile_m * BM;
         const int n0 = tile_n * BN;
-        v16f acc[TM][TN];
-        // Operand registers: six consecutive VGPRs per fragment (the builtin takes eight; the fp6 form of
-        // the instruction reads the first six).  The two LDS reads of a fragment land in them directly.
-        v8i pa[2][TM], pb[2][TN];
-    #pragma unroll
-        for (int set = 0; set < 2; ++set) {
-    #pragma unroll
-            for (int i = 0; i < TM; ++i) pa[set][i] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
-    #pragma unroll
-            for (int j = 0; j < TN; ++j) pb[set][j] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
-        }
-        auto read_one = [&](v8i& dst, const uint8_t* main_ptr, const uint8_t* tail_ptr) {
+        v4f acc[TM][TN];
+        // Operand registers: six consecutive VGPRs per fragment (the builtin takes eight, of which the instruction reads the
+        // first six in this form).  The two LDS reads of a fragment land in them directly.
+        v6i pa[TM], pb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) pa[i] = v6i{0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < TN; ++j) pb[j] = v6i{0, 0, 0, 0, 0, 0};
+        auto read_one = [&](v6i& dst, const uint8_t* main_ptr, const uint8_t* tail_ptr) {
             const v4i m = *reinterpret_cast<const v4i*>(main_ptr);
             const v2i t = *reinterpret_cast<const v2i*>(tail_ptr);
             dst[0] = m[0]; dst[1] = m[1]; dst[2] = m[2]; dst[3] = m[3]; dst[4] = t[0]; dst[5] = t[1];
         };
-        // fragment number t of the read order B0, A0, B1, .., B(TN-1), A1, .., A(TM-1): the order in which the MFMAs
-        // (row block outer, column block inner) first need them
-        auto read_nth = [&](int t, const uint8_t* st, int kb, int set) {
-            if (t == 0) read_one(pb[set][0], st + b_row(0) + moff[kb], st + 512 * kb + tb[0]);
-            else if (t == 1) read_one(pa[set][0], st + a_row + moff[kb], st + 512 * kb + ta[0]);
-            else if (t < TN + 1) read_one(pb[set][t - 1], st + b_row(t - 1) + moff[kb], st + 512 * kb + tb[t - 1]);
-            else read_one(pa[set][t - TN], st + a_row + (t - TN) * BLOCK + moff[kb], st + 512 * kb + ta[t - TN]);
-        };
-        auto read_frags = [&](const uint8_t* st, int kb, int set) {
-    #pragma unroll
-            for (int t = 0; t < TM + TN; ++t) {
-                read_nth(t, st, kb, set);
-                __builtin_amdgcn_sched_barrier(0);        // keep the order of the main loop (its waits count reads)
+        // half-block number n of an operand, in a stage given by its number (known at compile time) or by its byte offset in the ring
+        auto read_half = [&](v6i& dst, const Base* base, auto stage, int n) {
+            const int at = n / 2 * BLOCK;
+            if constexpr (std::is_same_v<decltype(stage), int>) {
+                read_one(dst, lds_all + stage + base[0].main + (at + 1024 * (n & 1)), lds_all + stage + base[0].tail[n & 1] + at);
+            } else {
+                const Base& x = base[stage / 2];
+                read_one(dst, lds_all + x.main + (stage % 2 * STAGE_BYTES + at + 1024 * (n & 1)), lds_all + x.tail[n & 1] + (stage % 2 * STAGE_BYTES + at));
             }
+            __builtin_amdgcn_sched_barrier(0);                // one at a time: neighbours would become one read with registers to be moved
         };
-
+        auto read_a = [&](auto stage, int i) { read_half(pa[i], base_a, stage, i); };
+        auto read_b = [&](auto stage, int j) {
+            if (ODD && j >= 2 * PAIRED) read_half(pb[j], base_c, stage, j - 2 * PAIRED);
+            else read_half(pb[j], base_b, stage, j);
+        };
+        auto read_outer = [&](auto st, int o) { if (ROWS_OUTER) read_a(st, o); else read_b(st, o); };
+        auto read_inner = [&](auto st, int i) { if (ROWS_OUTER) read_b(st, i); else read_a(st, i); };
+        auto operand = [](v6i x) { return __builtin_shufflevector(x, x, 0, 1, 2, 3, 4, 5, -1, -1); };
+        auto mfma = [&](int o, int n) {
+            const int i = ROWS_OUTER ? o : n, j = ROWS_OUTER ? n : o;
+            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(operand(pb[j]), operand(pa[i]), acc[i][j], 2, 2, 0, 0, 0, 0);
+        };
 
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
 
         // Stage 0 must have landed: on the first tile the loads of stage 1 may stay in flight; on later
         // tiles both stages were waited for before the previous epilogue's stores went out.  The barrier
@@ -292,106 +351,145 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         // stages this tile starts with that have landed already (beyond stage 0)
         const int landed = first ? 0 : STAGES - 2;
         first = false;
-        read_frags(lds, 0, 0);
+        auto stage_at = [&](int i) { return (i >= STAGES ? i - STAGES : i) * STAGE_BYTES; };
+        int prev = stage_at(start + STAGES - 1), cur = stage_at(start), next = stage_at(start + 1);      // stages of steps ks - 1, ks, ks + 1
+        asm volatile("" : "+s"(prev), "+s"(cur), "+s"(next));    // opaque: no addresses of their own for a tile's first steps
+        // the fragments the first step begins with, in the order in which its MFMAs need them
+        read_inner(cur, 0);
+#pragma unroll
+        for (int t = 0; t < PART0; ++t) read_outer(cur, t);
+#pragma unroll
+        for (int t = 1; t < TI; ++t) read_inner(cur, t);
 
-        // Half a K-step: the TM*TN MFMAs of one k-block.  Between them go the fragment reads of the NEXT k-block, one
-        // fragment (two LDS reads) in front of each MFMA in the order in which the next half will need them (B0, A0,
-        // B1 .. , A1 ..), and half of a stage's direct loads, one behind each MFMA.  Issuing all reads first and all
-        // MFMAs after made every wave of the compute unit queue at the LDS at the same time while the matrix cores
-        // idled, and then run its MFMAs while the LDS idled; and a compute unit accepts one direct load (1 KB) per 16
-        // cycles, so a burst of them blocks its waves while the matrix cores idle (a step of the 128 x 128 tile
-        // alone on its compute unit: 256 cycles of MFMAs, 384 of load issue, 850 in all with the loads in a burst).
-        auto half = [&](int use_set, const uint8_t* rd_stage, int rd_kb, int rd_set, auto do_reads, int fill, unsigned koff_a, unsigned koff_w, int from, auto do_loads) {
-            constexpr int MFMAS = TM * TN;
-            constexpr int READS = (TM + TN + MFMAS - 1) / MFMAS;                      // fragments read per MFMA
-            constexpr int PER = (SPLIT + MFMAS - 1) / MFMAS;                            // loads issued per MFMA
-    #pragma unroll
+        // Part of a K-step: the MFMAs of the outer blocks from .. from + COUNT - 1.
+        auto part = [&](auto from_c, auto count_c, auto&& before, auto do_loads, int fill, unsigned koff_a, unsigned koff_w, int first_load, int loads) {
+            constexpr int FROM = decltype(from_c)::value, COUNT = decltype(count_c)::value, MFMAS = COUNT * TI;
+#pragma unroll
             for (int t = 0; t < MFMAS; ++t) {
-                if (decltype(do_reads)::value) {
-    #pragma unroll
-                    for (int u = 0; u < READS; ++u)
-                        if (t * READS + u < TM + TN) read_nth(t * READS + u, rd_stage, rd_kb, rd_set);
-                }
-                const int i = t / TN, j = i & 1 ? TN - 1 - t % TN : t % TN;     // back and forth: each shares an operand with the one before
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(pb[use_set][j], pa[use_set][i], acc[i][j], 2, 2, 0, 0, 0, 0);
+                before(t);
+                const int n = t / COUNT, o = FROM + (n & 1 ? COUNT - 1 - t % COUNT : t % COUNT);   // back and forth: each shares an operand with the one before
+                mfma(o, n);
                 __builtin_amdgcn_sched_barrier(0);
                 if (decltype(do_loads)::value) {
-    #pragma unroll
-                    for (int u = 0; u < PER; ++u)
-                        if (t * PER + u < SPLIT && from + t * PER + u < LOADS) issue_one(fill, koff_a, koff_w, from + t * PER + u);
+#pragma unroll
+                    for (int u = 0; u < loads; ++u)
+                        if ((2 * u + 1) * MFMAS / (2 * loads) == t) issue_one(fill, koff_a, koff_w, first_load + u);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
         };
         // One K-step.  A stage is refilled from the moment every wave has passed the barrier behind its last reads: the
-        // first half of the loads of stage ks + STAGES goes out with the second block of MFMAs of step ks, the other
-        // half with the first block of step ks + 1.  The last steps, which request nothing, and the very last, which
-        // reads no next stage, are peeled off the loop: with these tests inside it, two paths met in front of a block
-        // of MFMAs, and the compiler then waited for every outstanding LDS read there -- including the ones just
-        // issued -- instead of only for the operands the MFMAs use (a bubble of an LDS latency per step).
-        //
-        // Ring positions and chunk offsets are carried along: a remainder by the number of stages in front of each block
-        // of reads (a multiply chain unless it is a power of two) costs a tenth of a step.
-        int prev = (STAGES - 1) * STAGE_BYTES, cur = 0, next = STAGE_BYTES;      // stages of steps ks - 1, ks, ks + 1
-        asm volatile("" : "+s"(prev), "+s"(cur), "+s"(next));    // opaque: no addresses of their own for a tile's first steps
+        // first half of the loads of stage ks + STAGES goes out with the second part of step ks, the other
+        // half with the first part of step ks + 1.  The last steps, which request nothing, and the very last, which
+        // reads no next stage, are copies of their own: with these tests inside a loop, two paths meet in front of MFMAs, and the
+        // compiler then waits for every outstanding LDS read there -- including the ones just issued -- instead of only for the
+        // operands the MFMAs use (a bubble of an LDS latency per step).
+        // Reads and loads evenly between the MFMAs: all waves pass the barrier together, and with a read in front of each of the
+        // first MFMAs and a load behind it LDS and loads were what they all waited for (4096 x 8192 x 28672 402 and 390 us).
         unsigned koff_a = kbase_a + (STAGES - 1) * a_step, koff_w = kbase_w + (STAGES - 1) * w_step;   // the group's chunk ks + STAGES - 1
-        auto k_step = [&](int ks, auto loads0, auto loads1, auto has_next, auto next_landed) {
-            // kb = 0, reading kb = 1 of this stage ahead
-            half(0, lds + cur, 1, 1, std::true_type{}, prev, koff_a, koff_w, SPLIT, loads0);
+        auto k_step = [&](auto here, auto behind, auto fill0, auto fill1, auto loads0, auto loads1, auto has_next, auto&& wait) {
+            constexpr int REST = TO - PART0;
+            asm volatile("" : "+s"(wave_at));               // no LDS address of its own for every load of every stage
+            // first part: reads the outer blocks of the second
+            part(std::integral_constant<int, 0>{}, std::integral_constant<int, PART0>{},
+                 [&](int t) {
+#pragma unroll
+                     for (int u = 0; u < REST; ++u)
+                         if (u * (3 * PART0 * TI) / (4 * REST) == t) read_outer(here, PART0 + u);
+                 }, loads0, fill0, koff_a, koff_w, SPLIT, LOADS - SPLIT);
             koff_a += a_step;
             koff_w += w_step;
             // every read of this stage has been issued; pass the barrier (next stage complete and visible: all but
-            // the newest STAGES-2 loads have landed), then kb = 1, reading the next stage's kb = 0 ahead
-            if (decltype(next_landed)::value) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            else wait_stages(decltype(loads0)::value ? STAGES - 2 : ksteps - 2 - ks);
-            half(1, lds + next, 0, 0, has_next, cur, koff_a, koff_w, 0, loads1);
+            // the newest STAGES-2 stages have landed)
+            wait();
+            // second part: reads the next stage's outer blocks of its first part, and every inner block when its last MFMA has gone
+            part(std::integral_constant<int, PART0>{}, std::integral_constant<int, REST>{},
+                 [&](int t) {
+                     if (!decltype(has_next)::value) return;
+#pragma unroll
+                     for (int u = 0; u < PART0; ++u)
+                         if (u * (3 * REST * TI) / (4 * PART0) == t) read_outer(behind, u);
+                     if (t > 0 && t % REST == 0) read_inner(behind, t / REST - 1);
+                 }, loads1, fill1, koff_a, koff_w, 0, SPLIT);
+            if (decltype(has_next)::value) read_inner(behind, TI - 1);
+        };
+        auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+        // a step on stages reckoned at run time
+        auto any_step = [&](auto loads0, auto loads1, auto has_next, auto&& wait) {
+            k_step(cur, next, prev, cur, loads0, loads1, has_next, wait);
             prev = cur;
             cur = next;
             next = next == (STAGES - 1) * STAGE_BYTES ? 0 : next + STAGE_BYTES;
         };
+        // ... and on stage S
+        auto step_on = [&](auto S, auto loads0, auto loads1, auto has_next, auto&& wait) {
+            constexpr int here = decltype(S)::value, behind = (here + 1) % STAGES, before = (here + STAGES - 1) % STAGES;
+            k_step(S, std::integral_constant<int, behind>{}, before * STAGE_BYTES, here * STAGE_BYTES, loads0, loads1, has_next, wait);
+        };
         constexpr std::true_type yes{};
         constexpr std::false_type no{};
-        if (STAGES - 1 < ksteps) {
+        if (ROUNDS || STAGES - 1 < ksteps) {
 #pragma unroll
             for (int i = 0; i < SPLIT; ++i) issue_one(prev, koff_a, koff_w, i);
         }
         __builtin_amdgcn_sched_barrier(0);
-        int ks = 0;
-        // the stages that were waited for before the previous tile's stores went out: no wait here, which would be one for
-        // those stores as well
-        for (; ks < landed && ks + STAGES < ksteps; ++ks) k_step(ks, yes, yes, yes, yes);
-        for (; ks + STAGES < ksteps; ++ks) {
-            // The step's code on a 16-byte boundary: where it begins in the middle of an 8-byte pair, which code anywhere in front
-            // of it decides, a step of one workgroup per compute unit is 1 % longer (2048 x 4096, K = 14336: 61.2 and 62.3 us).
-            asm volatile(".p2align 4");
-            k_step(ks, yes, yes, yes, no);
+        if constexpr (ROUNDS) {
+            // the stages that were waited for before the previous tile's stores went out: no wait here, which would be one for
+            // those stores as well
+            int ks = 0;
+            for (; ks < lead; ++ks)
+                any_step(yes, yes, yes, [&]() { if (ks < landed) lds_barrier(); else wait_loads_and_barrier<LOADS * (STAGES - 2)>(); });
+            auto round = [&](auto self, auto S) {
+                step_on(S, yes, yes, yes, [&]() { wait_loads_and_barrier<LOADS * (STAGES - 2)>(); });
+                if constexpr (decltype(S)::value + 1 < STAGES) self(self, std::integral_constant<int, decltype(S)::value + 1>{});
+            };
+            for (; ks + STAGES < ksteps; ks += STAGES) {
+                // The step's code on a 16-byte boundary: where it begins in the middle of an 8-byte pair, which code anywhere in front
+                // of it decides, a step of one workgroup per compute unit is 1 % longer (2048 x 4096, K = 14336: 61.2 and 62.3 us).
+                asm volatile(".p2align 4");
+                round(round, std::integral_constant<int, 0>{});
+            }
+            // the last STAGES steps, whose requests run out
+            auto last = [&](auto self, auto S) {
+                constexpr int s = decltype(S)::value;
+                if constexpr (s + 1 < STAGES) {
+                    auto wait = [&]() { wait_loads_and_barrier<LOADS * (STAGES - 2 - s)>(); };
+                    if constexpr (s == 0) step_on(S, yes, no, yes, wait);
+                    else step_on(S, no, no, yes, wait);
+                    self(self, std::integral_constant<int, s + 1>{});
+                } else if (!idle_last) {
+                    step_on(S, no, no, no, [&]() { wait_loads_and_barrier<0>(); });
+                } else {
+                    wait_loads_and_barrier<0>();
+                }
+            };
+            last(last, std::integral_constant<int, 0>{});
+        } else {
+            int ks = 0;
+            auto wait = [&]() { wait_stages(ksteps - 2 - ks); };
+            for (; ks + STAGES < ksteps; ++ks) any_step(yes, yes, yes, [&]() { wait_stages(STAGES - 2); });
+            if (ks + STAGES - 1 < ksteps) { any_step(yes, no, yes, wait); ++ks; }
+            for (; ks + 1 < ksteps; ++ks) any_step(no, no, yes, wait);
+            if (!idle_last) any_step(no, no, no, wait);
+            else wait_stages(0);
         }
-        if (ks + STAGES - 1 < ksteps) { k_step(ks, yes, no, yes, no); ++ks; }
-        for (; ks + 1 < ksteps; ++ks) k_step(ks, no, no, yes, no);
-        if (!idle_last) k_step(ks, no, no, no, no);
-        else wait_stages(0);                              // (the barrier of that step)
         // every wave has passed the last step's barrier, after which nothing reads the ring: put this tile's constants there
         // and request the next tile's first stages, so that their latency hides behind this tile's epilogue
-        if (tid < BM) par[2] = __float_as_int((float)par[2]);
+        int etid = tid;
+        asm volatile("" : "+v"(etid));
+        if (etid < BM) par[2] = __float_as_int((float)par[2]);
         else { par[0] <<= 16; par[1] <<= 16; }                    // bf16 -> fp32
-        if (tid < ROWS) lrow_par[tid] = par;
+        if (etid < ROWS) lrow_par[etid] = par;
         // K groups: a wave finishes the row blocks of its share, OWN of them, and hands its sums of the others to the waves
         // of the same position in the other groups, through its own ring.  (All sums are exact: any order gives the same bits.)
         const int own0 = kgroup * OWN;
-        auto xch_at = [&](int i, int j, int r) { return ((((wave * TM + i) * TN + j) * 4 + r) * 64 + lane) * 16; };
+        auto xch_at = [&](int i, int j) { return (((swave * TM + i) * TN + j) * 64 + lane) * 16; };
         if constexpr (KGROUPS > 1) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
                 if (i / OWN != kgroup) {
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            v4i v;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) v[e] = __float_as_int(acc[i][j][4 * r + e]);
-                            *reinterpret_cast<v4i*>(lds + xch_at(i, j, r)) = v;
-                        }
+                    for (int j = 0; j < TN; ++j) *reinterpret_cast<v4i*>(lds + xch_at(i, j)) = __builtin_bit_cast(v4i, acc[i][j]);
                 }
         }
         const int next_pid = pid + gridDim.x;
@@ -420,32 +518,31 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
 #pragma unroll
                 for (int i = 0; i < OWN; ++i)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
+                    for (int j = 0; j < TN; ++j) {
+                        const v4i v = *reinterpret_cast<const v4i*>(ring + xch_at(own0 + i, j));
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const v4i v = *reinterpret_cast<const v4i*>(ring + xch_at(own0 + i, j, r));
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[i][j][4 * r + e] += __int_as_float(v[e]);
-                        }
+                        for (int e = 0; e < 4; ++e) acc[i][j][e] += __int_as_float(v[e]);
+                    }
             }
         }
-        const int row0 = wm * WM + own0 * 32;                     // of the rows this wave finishes
+        const int row0 = wm * WM + own0 * 16;                     // of the rows this wave finishes
         // (re)derived per tile from an opaque copy of the lane index: everything computed from it below
         // would otherwise be hoisted out of the tile loop and held in registers across the main loop
-        int elane = lane;
+        int elane = tid;
         asm volatile("" : "+v"(elane));
-        const int tok = elane & 31, ehalf = elane >> 5;
+        elane &= 63;
+        const int tok = elane & 15, quad = elane >> 4;
         v4i rp[OWN];                                              // scale, lower bound, row sum of this lane's tokens
 #pragma unroll
-        for (int i = 0; i < OWN; ++i) rp[i] = lrow_par[row0 + i * 32 + tok];
+        for (int i = 0; i < OWN; ++i) rp[i] = lrow_par[row0 + i * 16 + tok];
         auto dequant = [&](float s64, v4i row, v4i col) {
             // 64 * S is the integer accumulator, exactly
             const float t = fmaf(64.0f, s64, -(__int_as_float(col[1]) * __int_as_float(row[2])));
             return fmaf(__int_as_float(row[0]) * __int_as_float(col[0]), t,
                         fmaf(__int_as_float(row[1]), __int_as_float(col[2]), __int_as_float(col[3])));
         };
-        auto& sums = reinterpret_cast<v16f(&)[OWN][TN]>(acc);
-        if (a.acc_out) store_accumulators<OWN, TN, BM>(a, m0, n0, row0, elane, sums, col_block);
+        auto& sums = reinterpret_cast<v4f(&)[OWN][TN]>(acc);
+        if (a.acc_out) store_accumulators16<OWN, TN, BM>(a, m0, n0, row0, elane, sums, col_block);
         typedef float f2 __attribute__((ext_vector_type(2)));
         typedef __bf16 b2 __attribute__((ext_vector_type(2)));
         // Outputs into registers, where they take the accumulators' place, then the stores.  With one workgroup per compute unit in
@@ -462,29 +559,26 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         constexpr int FIRST = KGROUPS == 1 && MINOCC * 4 == WAVES && BN < 256 ? (OWN + 1) / 2 : OWN;
         auto finish = [&](auto first_c, auto count_c) {
             constexpr int i0 = decltype(first_c)::value, count = decltype(count_c)::value;
-            unsigned outv[count][TN][4][2];                   // [..][q][p]: channels 8q + 4*ehalf + 2p, +1
+            unsigned outv[count][TN][2];                      // [..][p]: channels 4*quad + 2p, +1
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
+                v4i cp[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    v4i cp[4];
+                for (int e = 0; e < 4; ++e) cp[e] = lcol_par[col_block(j / 2) * 32 + 16 * (j & 1) + 4 * quad + e];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) cp[e] = lcol_par[col_block(j) * 32 + 8 * q + 4 * ehalf + e];
+                for (int i = 0; i < count; ++i) {
 #pragma unroll
-                    for (int i = 0; i < count; ++i) {
-#pragma unroll
-                        for (int p = 0; p < 2; ++p) {
-                            const float y0 = dequant(acc[i0 + i][j][4 * q + 2 * p], rp[i0 + i], cp[2 * p]);
-                            const float y1 = dequant(acc[i0 + i][j][4 * q + 2 * p + 1], rp[i0 + i], cp[2 * p + 1]);
-                            outv[i][j][q][p] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){y0, y1}, b2));   // hardware round-to-nearest-even
-                            asm volatile("" : "+v"(outv[i][j][q][p]));   // computed here: one set of column constants at a time
-                        }
+                    for (int p = 0; p < 2; ++p) {
+                        const float y0 = dequant(acc[i0 + i][j][2 * p], rp[i0 + i], cp[2 * p]);
+                        const float y1 = dequant(acc[i0 + i][j][2 * p + 1], rp[i0 + i], cp[2 * p + 1]);
+                        outv[i][j][p] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){y0, y1}, b2));   // hardware round-to-nearest-even
+                        asm volatile("" : "+v"(outv[i][j][p]));   // computed here: one set of column constants at a time
                     }
-                    __builtin_amdgcn_sched_barrier(0);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
             if (i0 == 0 && more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            store_outputs<count, TN, BM>(a, (StoreForm)store_form, m0, n0, row0 + 32 * i0, elane, outv, col_block);
+            store_outputs16<count, TN, BM>(a, (StoreForm)store_form, m0, n0, row0 + 16 * i0, elane, outv, col_block);
         };
         finish(std::integral_constant<int, 0>{}, std::integral_constant<int, FIRST>{});
         if constexpr (FIRST < OWN) finish(std::integral_constant<int, FIRST>{}, std::integral_constant<int, OWN - FIRST>{});
@@ -519,8 +613,12 @@ int launch_fp6(const GemmArgs& a, hipStream_t s) {
                                           : BN > 128 && a.K >= 8192 && tm * tn <= 2 * resident;
     GemmArgs b = a;
     b.store_form = output_form(a, hides_stores);
-    hipLaunchKernelGGL((gemm_w4a4_fp6_kernel<BM, BN, WAVES_M, WAVES_N, KGROUPS, STAGES, MINOCC>), dim3((unsigned)grid),
-                       dim3(WAVES * 64), 0, s, b, (int)tm, (int)tn);
+    if ((a.K / 128 + KGROUPS - 1) / KGROUPS < STAGES)
+        hipLaunchKernelGGL((gemm_w4a4_fp6_kernel<BM, BN, WAVES_M, WAVES_N, KGROUPS, STAGES, MINOCC, true>), dim3((unsigned)grid),
+                           dim3(WAVES * 64), 0, s, b, (int)tm, (int)tn);
+    else
+        hipLaunchKernelGGL((gemm_w4a4_fp6_kernel<BM, BN, WAVES_M, WAVES_N, KGROUPS, STAGES, MINOCC, false>), dim3((unsigned)grid),
+                           dim3(WAVES * 64), 0, s, b, (int)tm, (int)tn);
     return check_hip(hipGetLastError(), "w4a4_gemm (fp6) launch");
 }
 

@@ -831,6 +831,23 @@ def test_group_wise_products_on_either_tiling():
     assert chosen == {0, 1}
 
 
+@pytest.mark.parametrize("steps", [8, 9, 10, 11, 12, 13])
+@pytest.mark.parametrize("tiling", range(B.FP6_TILINGS))
+def test_fp6_tiles_of_every_number_of_steps_around_the_ring(tiling, steps):
+    """A tile's first steps reckon their ring stage, the others have it fixed in rounds of as many as there are stages: every remainder
+    of the rounds, at least one of them, and more tiles than are resident, so that a workgroup begins anew where the tile in front
+    has left the ring.  Exact sums: the bits of the kernels without the fp6 operands."""
+    bm, bn, _ = FP6_TILES[tiling]
+    K = 128 * steps
+    for M, N in [(bm + 3, bn + 8), (9 * bm - 45, (30 if bn > 128 else 100) * bn + 8)]:
+        announce(f"tiling {tiling} steps={steps} M={M} N={N}")
+        A, A6, meta, W, W6, sw, zp, ws, c = random_product(M, N, K, seed=steps)
+        Y, want = (torch.full((M, N), -7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+        B.basq_diag_w4a4_gemm_fp6(tiling, meta, K, sw, zp, ws, c, Y, None, A6, W6)
+        B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, want)
+        assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
+
+
 SPLIT_TILES = [(64, 64), (96, 64), (128, 64), (128, 128), (96, 96), (160, 96)]
 
 
