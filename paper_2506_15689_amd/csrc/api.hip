@@ -168,6 +168,7 @@ int linear_fused_impl(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t 
         return fail(BASQ_EUNSUPPORTED, "more than 128 tokens with the streaming weight layout need the fp6 operands "
                                         "(the int8 kernels read canonical weights)");
     if (linear_decode_applicable(a, g)) return launch_linear_decode(a, g, s);      // a few tokens: one launch
+    if (linear_small_applicable(a, g)) return launch_linear_small(a, g, s);
     rc = launch_rotate_quant(a, s);
     if (rc != BASQ_OK) return rc;
     return run_gemm(g, s);

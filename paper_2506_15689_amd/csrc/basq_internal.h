@@ -94,6 +94,9 @@ int launch_gemv_decode(const GemmArgs& a, hipStream_t s);   // M <= GEMV_MAX_TOK
 // one launch for the whole layer at decode size (linear_decode.hip)
 bool linear_decode_applicable(const RotateQuantArgs& q, const GemmArgs& g);
 int launch_linear_decode(const RotateQuantArgs& q, const GemmArgs& g, hipStream_t s);
+// the same for few tokens of 512, 1024 or 2048 channels (linear_small.hip)
+bool linear_small_applicable(const RotateQuantArgs& q, const GemmArgs& g);
+int launch_linear_small(const RotateQuantArgs& q, const GemmArgs& g, hipStream_t s);
 int launch_pack_decode16(const uint8_t* Wq, int32_t N, int32_t K, uint8_t* out, hipStream_t s);
 // f8f6f4 MFMA kernel on the fp6 operand form, K % 128 == 0 (gemm_w4a4_fp6.hip)
 bool gemm_fp6_applicable(const GemmArgs& a);

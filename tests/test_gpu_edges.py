@@ -1048,3 +1048,41 @@ def test_fp6_form_of_codes_in_a_partly_filled_last_round(K, M):
         Y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
         B.basq_w4a4_gemm(Aq, meta, W, one, zero, torch.zeros(N, device=DEV), None, Y, acc, Aq6=A6, Wq6=W6)
         assert torch.equal(acc, meta[:, 2:3].expand(M, N)), "row sums of the fp6 form"
+
+
+@pytest.mark.parametrize("K", [512, 1024, 2048])
+def test_small_tokens_in_one_launch(K):
+    """The one-launch layer of few small tokens against the two calls (the quantiser, then the product on canonical weights): four tokens
+    and 64 channels to a workgroup, so token and channel counts around multiples of these, up to the most that it takes and one
+    beyond; with and without b^c, s^a and the layer bias, rows of every alignment, tokens of a wider matrix, dead and NaN tokens."""
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    rand = lambda *shape: torch.rand(*shape, device=DEV, generator=gen)
+    most = (256 if K == 2048 else 512) * 64
+    for M, N, ldy, offset, vectors in [(1, 1, 1, 0, 3), (1, 16, 17, 1, 0), (3, 15, 15, 3, 1), (4, 64, 64, 0, 2), (5, 63, 68, 4, 3), (7, 65, 66, 2, 0), (64, 1000, 1000, 0, 3),
+                                       (33, 130, 132, 0, 1), (128, 200, 201, 0, 2), (127, 77, 80, 8, 3), (4, most, most, 0, 1), (4, most + 1, most + 1, 0, 3)]:
+        announce(f"small tokens in one launch M={M} N={N} K={K} ldy={ldy} offset={offset} vectors={vectors}")
+        _, _, _, W, W6, sw, zp, ws, c = random_product(M, N, K, seed=M + N)
+        wide = torch.randn((M, K + 24), device=DEV, generator=gen).to(torch.bfloat16)
+        if M > 3:
+            wide[1] = 0
+            wide[M - 1, 5] = float("nan")
+            wide[2, 7] = float("inf")
+        X = wide[:, :K]
+        bias = rand(K) - 0.5 if vectors & 1 else None
+        scale = rand(K) + 0.5 if vectors & 2 else None
+        out_bias = c if vectors & 1 else None
+        Wd = torch.empty(B.basq_decode_bytes(N, K), dtype=torch.uint8, device=DEV)
+        B.basq_pack_decode(W, Wd)
+        A, meta = B.alloc_activation_buffers(M, K, DEV)
+        want = torch.full((M, N), -7.0, dtype=torch.bfloat16, device=DEV)
+        B.basq_rotate_quant(X, K, bias, scale, 0.9, 0.8, A, meta)
+        B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, out_bias, want)
+        workspace = torch.empty(B.basq_workspace_bytes(M, K, N), dtype=torch.uint8, device=DEV)
+        for six in (None, W6):
+            buf, Y = output_view(M, N, ldy, offset)
+            B.basq_linear_fused(X, K, bias, scale, 0.9, 0.8, Wd, sw, zp, ws, out_bias, Y, workspace, Wq6=six, w_layout=B.BASQ_W_DECODE16, N=N)
+            got = Y.contiguous()
+            assert torch.equal(got.isnan(), want.isnan())
+            assert torch.equal(got.nan_to_num(0.0).view(torch.int16), want.nan_to_num(0.0).view(torch.int16))
+            Y.fill_(-7.0)
+            assert bool((buf == -7.0).all()), "wrote outside the output"
