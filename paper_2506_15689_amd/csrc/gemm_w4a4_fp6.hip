@@ -6,7 +6,7 @@
 // accumulator of the INT4 product is ACC = 64*S; the epilogue de-quantises exactly as the int8 kernels do.
 // (16 x 16 x 128 and not 32 x 32 x 64: the chip's power sets the clock under such a loop, and a register-resident one on
 // code-valued operands runs at 8.7 POP/s in this shape, 7.6 in the other.  Products with the weights in the caches, this kernel
-// against its predecessor on 32 x 32 x 64, us: 4096 x 8192 x 28672 413 -> 390, 2048 x 4096 x 12288 54.7 -> 51.6, 2048 x 14336 x 4096
+// against its predecessor on 32 x 32 x 64, us: 4096 x 8192 x 28672 408 -> 377, 2048 x 4096 x 12288 54.7 -> 50.6, 2048 x 14336 x 4096
 // 59.5 -> 54.2, 256 x 4096 x 8192 on 128 x 64 tiles 11.0 -> 9.4.)
 //
 // Structure: direct-to-LDS buffer loads into a ring of stages, fragments read ahead, XCD-aware tile order.  A stage holds
@@ -71,7 +71,11 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     // as soon as their last MFMA of a step has gone (see k_step)
     constexpr bool ROWS_OUTER = TM >= TN;
     constexpr int TO = ROWS_OUTER ? TM : TN, TI = ROWS_OUTER ? TN : TM;
-    constexpr int PART0 = TO / 2;                             // outer blocks of a step's first part
+    // Outer blocks of a step's first part: half of them, one fewer where there are more outer than inner blocks (six at least),
+    // which leaves the barrier, at a part's end, farther from the reads of the next step's operands.  us, half and one fewer: 256 x 256
+    // 4096 x 8192 x 28672 381.4 and 376.7, 256 x 192 2048 x 8192 x 12288 88.2 and 86.9.  (96 x 96, as many of either: no
+    // difference, 320 x 4096 x 4096 9.1.)
+    constexpr int PART0 = TO >= 6 && TO > TI ? TO / 2 - 1 : TO / 2;
     constexpr int ROWS = BM + BN;
     constexpr int STAGE_BYTES = ROWS * CHUNK;
     constexpr int PIECES = STAGE_BYTES / 1024;                // 1 KB pieces of a stage, one wave-load each
