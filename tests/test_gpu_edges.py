@@ -1086,3 +1086,23 @@ def test_small_tokens_in_one_launch(K):
             assert torch.equal(got.nan_to_num(0.0).view(torch.int16), want.nan_to_num(0.0).view(torch.int16))
             Y.fill_(-7.0)
             assert bool((buf == -7.0).all()), "wrote outside the output"
+
+
+@pytest.mark.parametrize("M,K,shift", [(64, 1024, 0), (128, 512, 0), (31, 1024, 8), (16, 2048, 0)])
+def test_small_layers_in_place(M, K, shift):
+    """Outputs over the layer's own tokens, or over the tokens shifted by some channels: as with outputs elsewhere."""
+    gen = torch.Generator(device=DEV).manual_seed(M + K)
+    _, _, _, W, _, sw, zp, ws, c = random_product(M, K, K, seed=M + K)
+    Wd = torch.empty(B.basq_decode_bytes(K, K), dtype=torch.uint8, device=DEV)
+    B.basq_pack_decode(W, Wd)
+    X = torch.randn((M, K), device=DEV, generator=gen).to(torch.bfloat16)
+    workspace = torch.empty(B.basq_workspace_bytes(M, K, K), dtype=torch.uint8, device=DEV)
+    layer = lambda x, y: B.basq_linear_fused(x, K, None, None, 0.9, 0.8, Wd, sw, zp, ws, c, y, workspace, w_layout=B.BASQ_W_DECODE16, N=K)
+    want = torch.empty_like(X)
+    layer(X, want)
+    for _ in range(20):
+        buf = torch.zeros(M * K + shift, dtype=torch.bfloat16, device=DEV)
+        x, y = buf[shift:].view(M, K), buf[:M * K].view(M, K)
+        x.copy_(X)
+        layer(x, y)
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
