@@ -95,9 +95,14 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
     static_assert(STAGES >= 3 && LOADS * (STAGES - 2) < 64, "the wait counter counts to 63");
     static_assert(ROWS * 16 <= STAGE_BYTES, "the epilogue constants live in the last stage");
+    // With 128 sums a lane (256 x 256) no registers are left to carry the next tile's constants across the K loop: they go to LDS of their
+    // own, two tiles' worth beside the ring.  (Carried, they were spilled, and fetched again behind a tile's last MFMA with a full
+    // wait.  Whole layers, us: 4096 x 8192 x 28672 447 -> 440, 4096 x 4096 x 28672 252.7 -> 246.7, 8000 x 512 x 14240 94.3 -> 86.7.)
+    constexpr bool APART = TM * TN * 4 >= 128;
+    static_assert(!APART || (KGROUPS == 1 && !PADDED), "nothing else stands behind the ring");
     static_assert(KGROUPS == 1 || (BM * BN * 4 + ROWS * 16 <= STAGES * STAGE_BYTES && TM % OWN == 0), "K groups exchange their sums through their rings");
 
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KGROUPS * STAGES * STAGE_BYTES + (PADDED ? 1024 : 0)];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KGROUPS * STAGES * STAGE_BYTES + (PADDED ? 1024 : APART ? 2 * ROWS * 16 : 0)];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, swave = __builtin_amdgcn_readfirstlane((tid >> 6) % WAVES);
@@ -262,13 +267,12 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     static_assert(STAGE_BYTES + (WM / 32) * BLOCK <= 65536 && STAGE_BYTES + (WN / 32) * BLOCK <= 65536, "reach of an offset");
 
     // Epilogue constants, one 16-byte record per row and column of the tile: in the last stage of the ring, which the next
-    // tile's first loads do not touch.  Kept and read as integers: the compiler puts a wait for every direct-to-LDS load
-    // in flight in front of a float-typed LDS read.
+    // tile's first loads do not touch, or in this tile's half of the LDS behind it (APART).  Kept and read as integers: the compiler
+    // puts a wait for every direct-to-LDS load in flight in front of a float-typed LDS read.
     // (with K groups, which take one tile, behind the sums that go through the first group's ring)
-    v4i* lrow_par = reinterpret_cast<v4i*>(lds_all + (KGROUPS == 1 ? (start + STAGES - 1) % STAGES * STAGE_BYTES : STAGES * STAGE_BYTES - ROWS * 16));
-    v4i* lcol_par = lrow_par + BM;
-    // The raw values of one record per thread (rows first), requested a tile ahead of their use and converted only there:
-    // a conversion behind the loads would wait for them.
+    int par_at = APART ? STAGES * STAGE_BYTES : KGROUPS == 1 ? (start + STAGES - 1) % STAGES * STAGE_BYTES : STAGES * STAGE_BYTES - ROWS * 16;
+    // The raw values of one record per thread (rows first), requested a tile ahead of their use and converted only where they are put
+    // down: a conversion behind the loads would wait for them.
     auto load_par = [&](int tile_m, int tile_n) -> v4i {
         int tid = threadIdx.x;                                // (opaque: nothing derived from it is kept across the main loop)
         asm volatile("" : "+v"(tid));
@@ -288,6 +292,13 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         return raw;
     };
     static_assert(ROWS <= THREADS, "one record per thread");
+    auto put_par = [&](v4i raw, int at) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        if (tid < BM) raw[2] = __float_as_int((float)raw[2]);
+        else { raw[0] <<= 16; raw[1] <<= 16; }                    // bf16 -> fp32
+        if (ROWS == THREADS || tid < ROWS) reinterpret_cast<v4i*>(lds_all + at)[tid] = raw;
+    };
 
     // ---- persistent loop over this workgroup's tiles
     int pid = blockIdx.x;
@@ -296,6 +307,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     set_tile(tile_m, tile_n);
     v4i par = load_par(tile_m, tile_n);
     issue_prologue();
+    if (APART) put_par(par, par_at);
     bool first = true;
     while (true) {
         const int64_t m0 = (int64_t)tile_m * BM;
@@ -478,12 +490,9 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
             else wait_stages(0);
         }
         // every wave has passed the last step's barrier, after which nothing reads the ring: put this tile's constants there
-        // and request the next tile's first stages, so that their latency hides behind this tile's epilogue
-        int etid = tid;
-        asm volatile("" : "+v"(etid));
-        if (etid < BM) par[2] = __float_as_int((float)par[2]);
-        else { par[0] <<= 16; par[1] <<= 16; }                    // bf16 -> fp32
-        if (etid < ROWS) lrow_par[etid] = par;
+        // (APART: they stand behind it since the tile in front) and request the next tile's first stages, so that their latency
+        // hides behind this tile's epilogue
+        if (!APART) put_par(par, par_at);
         // K groups: a wave finishes the row blocks of its share, OWN of them, and hands its sums of the others to the waves
         // of the same position in the other groups, through its own ring.  (All sums are exact: any order gives the same bits.)
         const int own0 = kgroup * OWN;
@@ -499,15 +508,16 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         const int next_pid = pid + gridDim.x;
         const bool more = KGROUPS == 1 && next_pid < total;
         int next_m = 0, next_n = 0;
+        v4i next_par = {0, 0, 0, 0};
         if (more) {
             tile_of(next_pid, next_m, next_n);
             set_tile(next_m, next_n);
-            par = load_par(next_m, next_n);
+            (APART ? next_par : par) = load_par(next_m, next_n);
             issue_prologue();
         }
 
         // ---- epilogue (which output an accumulator register holds: gemm_fp6_store.h)
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // LDS only: the next tile's loads stay in flight
+        if (!APART) lds_barrier();                                // LDS only: the next tile's loads stay in flight
         if constexpr (KGROUPS > 1) {
             if (own0 >= TM) return;                               // fewer row blocks than groups
             // the first OWN blocks of `acc` become the sums of this wave's share
@@ -536,6 +546,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         asm volatile("" : "+v"(elane));
         elane &= 63;
         const int tok = elane & 15, quad = elane >> 4;
+        const v4i* const lrow_par = reinterpret_cast<const v4i*>(lds_all + par_at);
+        const v4i* const lcol_par = lrow_par + BM;
         v4i rp[OWN];                                              // scale, lower bound, row sum of this lane's tokens
 #pragma unroll
         for (int i = 0; i < OWN; ++i) rp[i] = lrow_par[row0 + i * 16 + tok];
@@ -581,7 +593,11 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (i0 == 0 && more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (i0 == 0 && (more || APART)) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (i0 == 0 && APART) {                           // behind the last tile too: from a branch the compiler takes waits along in front of the stores
+                par_at = 2 * STAGES * STAGE_BYTES + ROWS * 16 - par_at;      // the other half of the LDS behind the ring
+                put_par(next_par, par_at);
+            }
             store_outputs16<count, TN, BM>(a, (StoreForm)store_form, m0, n0, row0 + 16 * i0, elane, outv, col_block);
         };
         finish(std::integral_constant<int, 0>{}, std::integral_constant<int, FIRST>{});

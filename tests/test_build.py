@@ -1,5 +1,8 @@
-"""How the library is compiled."""
+"""How the library is compiled, and what the compiler made of it."""
 import os
+import re
+import struct
+import subprocess
 
 import pytest
 
@@ -20,3 +23,34 @@ def test_an_option_that_the_compiler_does_not_know_is_left_out(tmp_path, monkeyp
     compiled = [line for line in (tmp_path / "calls").read_text().splitlines() if " -c " in line]
     assert [option in line for line in compiled] == [knows] * len(build.MFMA_VGPR_SOURCES)
     assert ("built without it" in capfd.readouterr().err) == (not knows)
+
+
+def kernel_resources():
+    """Name, spilled vector registers and bytes of scratch a lane of every kernel of the built library, from its code objects' notes."""
+    if not os.path.exists(build.LIB):
+        build.build_lib(verbose=False)
+    with open(build.LIB, "rb") as f:
+        blob = f.read()
+    magic, found = b"__CLANG_OFFLOAD_BUNDLE__", []
+    bundle = blob.find(magic)
+    while bundle >= 0:
+        (entries,), entry = struct.unpack_from("<Q", blob, bundle + len(magic)), bundle + len(magic) + 8
+        for _ in range(entries):
+            offset, size, id_length = struct.unpack_from("<QQQ", blob, entry)
+            if b"gfx950" in blob[entry + 24:entry + 24 + id_length]:
+                readelf = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", "-"], input=blob[bundle + offset:bundle + offset + size],
+                                         stdout=subprocess.PIPE, check=True)
+                for kernel in readelf.stdout.decode().split(".agpr_count:")[1:]:
+                    field = lambda key: re.search(rf"^ *\.{key}: +(\S+)", kernel, re.M).group(1)
+                    found.append((field("name"), int(field("vgpr_spill_count")), int(field("private_segment_fixed_size"))))
+            entry += 24 + id_length
+        bundle = blob.find(magic, bundle + 1)
+    return found
+
+
+def test_no_tiling_of_the_fp6_gemm_spills():
+    """Its waits count the loads and stores in flight: a spilled register's are among them, and one that is fetched again behind a tile's
+    last step is a memory latency with nothing beside it."""
+    gemms = [k for k in kernel_resources() if "gemm_w4a4_fp6_kernel" in k[0]]
+    assert len(gemms) >= 12
+    assert [k for k in gemms if k[1] or k[2]] == []

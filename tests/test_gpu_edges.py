@@ -848,6 +848,21 @@ def test_fp6_tiles_of_every_number_of_steps_around_the_ring(tiling, steps):
         assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
 
 
+@pytest.mark.parametrize("K", [256, 384, 1024])
+@pytest.mark.parametrize("with_bias", [True, False])
+def test_fp6_three_of_the_largest_tiles_to_a_workgroup(K, with_bias):
+    """256 x 256 tiles keep their constants in one of two places in turn, written while the other is read: three tiles to most workgroups
+    and two to the others, ragged on either side, and a reader of every constant."""
+    M, N = 256 * 25 - 3, 256 * 23 - 40                          # 575 tiles on 256 workgroups
+    announce(f"three tiles M={M} N={N} K={K} bias={with_bias}")
+    A, A6, meta, W, W6, sw, zp, ws, c = random_product(M, N, K, seed=K)
+    c = c if with_bias else None
+    Y, want = (torch.full((M, N), -7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    B.basq_diag_w4a4_gemm_fp6(0, meta, K, sw, zp, ws, c, Y, None, A6, W6)
+    B.basq_w4a4_gemm(A, meta, W, sw, zp, ws, c, want)
+    assert torch.equal(Y.view(torch.int16), want.view(torch.int16))
+
+
 SPLIT_TILES = [(64, 64), (96, 64), (128, 64), (128, 128), (96, 96), (160, 96)]
 
 
