@@ -204,9 +204,10 @@ size_t basq_workspace_bytes(int64_t M, int32_t K, int32_t N);
  * so does M > 64 (from 33 on where the shape favours it) if the quantiser writes the fp6 form itself: rot_size == K in
  * {512, 1024, 2048, 4096, 8192, 14336}, or rot_size in {128, 256, 512} with K % 256 == 0 and K <= 16384.
  * group_size must be 0 or K here (BASQ_EUNSUPPORTED otherwise: groups go through basq_rotate_quant and
- * basq_w4a4_gemm_grouped).  With at most 4 tokens, rot_size == K in {4096, 8192}, N <= 4096 and
- * w_layout = BASQ_W_DECODE16 the whole layer is one kernel launch (same results bit for bit).  Nothing in this
- * call allocates or synchronises, so it may be recorded in a HIP graph.
+ * basq_w4a4_gemm_grouped).  With w_layout = BASQ_W_DECODE16 the whole layer is one kernel launch (same results bit for bit)
+ * for at most 4 tokens of rot_size == K in {4096, 8192} with N <= 4096, and for few tokens of rot_size == K in
+ * {512, 1024, 2048} (see basq_diag_one_launch).  Y may lie over X, bias or act_scale: the tokens are rotated and quantised
+ * before the first output is written.  Nothing in this call allocates or synchronises, so it may be recorded in a HIP graph.
  */
 int basq_linear_fused(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t rot_size,
                       const float* bias, const float* act_scale,
@@ -363,6 +364,13 @@ int basq_diag_grouped_tiling(int64_t M, int32_t K, int32_t N);
 int basq_diag_w4a4_gemm_grouped_fp6(int32_t tiling, const basq_tokmeta* meta, int64_t M, int32_t K, int32_t N,
                                     const void* w_scale, const void* w_zero, const int32_t* w_gsum, const float* out_bias,
                                     void* Y, int64_t ldy, const uint8_t* Aq6, const uint8_t* Wq6, void* stream);
+
+/*
+ * Whether basq_linear_fused takes a layer in one kernel launch: 1, or 0 where it takes several, as it does where Y lies over what the
+ * rotation reads.  Arguments as there; known on the host, nothing is read or launched.
+ */
+int basq_diag_one_launch(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t rot_size, const float* bias, const float* act_scale,
+                         int32_t N, int32_t w_layout, const void* Y, int64_t ldy);
 
 /*
  * The 256 x 192 tiling goes on requesting behind a workgroup's last tile, from lane offsets that the bounds check of the load drops.

@@ -25,7 +25,8 @@ EXPORTS = ["basq_version", "basq_last_error", "basq_rotate_quant", "basq_w4a4_ge
            "basq_w4a4_gemm_grouped", "basq_group_colsums", "basq_fp6_bytes", "basq_pack_fp6", "basq_decode_bytes", "basq_pack_decode", "basq_linear_fused", "basq_linear_fused_static", "basq_rotate_weights", "basq_quantize_weights", "basq_fused_bias", "basq_prepare_weights", "basq_calibrate_bias",
            "basq_hadamard28", "basq_diag_stream", "basq_diag_read", "basq_diag_mfma_i8", "basq_diag_mfma_f6",
            "basq_diag_fp6_tiling", "basq_diag_w4a4_gemm_fp6", "basq_diag_fp6_split_tiling", "basq_diag_w4a4_gemm_fp6_split",
-           "basq_diag_grouped_tiling", "basq_diag_w4a4_gemm_grouped_fp6", "basq_diag_grouped_wide_strays", "basq_diag_block_vector_channels"]
+           "basq_diag_grouped_tiling", "basq_diag_w4a4_gemm_grouped_fp6", "basq_diag_grouped_wide_strays", "basq_diag_block_vector_channels",
+           "basq_diag_one_launch"]
 
 
 class BasqError(RuntimeError):
@@ -106,6 +107,8 @@ def load() -> ctypes.CDLL:
     lib.basq_diag_w4a4_gemm_grouped_fp6.argtypes = [i32, vp, i64, i32, i32, vp, vp, vp, vp, vp, i64, vp, vp, vp]
     lib.basq_diag_grouped_wide_strays.restype = i64
     lib.basq_diag_grouped_wide_strays.argtypes = [i64, i32, i32]
+    lib.basq_diag_one_launch.restype = c.c_int
+    lib.basq_diag_one_launch.argtypes = [vp, i64, i32, i64, i32, vp, vp, i32, i32, vp, i64]
     lib.basq_diag_block_vector_channels.restype = c.c_int
     lib.basq_diag_block_vector_channels.argtypes = [i32]
     _lib = lib
@@ -407,6 +410,16 @@ def basq_diag_w4a4_gemm_grouped_fp6(tiling: int, meta: torch.Tensor, K: int, w_s
 def basq_diag_block_vector_channels(K: int) -> int:
     """One past the last channel of bias and act_scale that the blockwise rotation requests for tokens of K channels."""
     return int(load().basq_diag_block_vector_channels(K))
+
+
+def basq_diag_one_launch(X: torch.Tensor, rot_size: int, bias: Optional[torch.Tensor], act_scale: Optional[torch.Tensor],
+                         Y: torch.Tensor, w_layout: int) -> bool:
+    """Whether basq_linear_fused takes the layer X -> Y in one kernel launch; M, N = Y.shape."""
+    (M, K), N = X.shape, Y.shape[1]
+    rc = load().basq_diag_one_launch(_p(X), M, K, X.stride(0) if M > 0 else K, rot_size, _p(bias), _p(act_scale), N, w_layout,
+                                     _p(Y), Y.stride(0) if M > 0 else N)
+    _check(min(rc, 0))
+    return rc == 1
 
 
 # ---- allocation helpers (device memory only; no arithmetic) ----------------------------------

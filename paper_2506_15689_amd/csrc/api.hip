@@ -120,6 +120,35 @@ bool layer_fp6_only_applicable(const RotateQuantArgs& a) {
            (b.Aq6 != nullptr && b.group == b.K && (rotate_quant_small_applicable(b) || rotate_quant_block_applicable(b)));
 }
 
+// Whether the outputs lie over what every workgroup of a one-launch layer reads: the tokens, b^c and s^a.  Row by row: outputs
+// in the gaps between a wider matrix's tokens (and tokens in the gaps between outputs) are none.
+bool outputs_over_inputs(const RotateQuantArgs& q, const GemmArgs& g) {
+    const int64_t y0 = (int64_t)reinterpret_cast<uintptr_t>(g.Y), y_row = 2 * g.ldy, y_bytes = 2 * (int64_t)g.N;
+    auto over = [&](const void* p, int64_t rows, int64_t row, int64_t bytes) {
+        if (p == nullptr) return false;
+        const int64_t p0 = (int64_t)reinterpret_cast<uintptr_t>(p);
+        if (p0 >= y0 + (g.M - 1) * y_row + y_bytes || y0 >= p0 + (rows - 1) * row + bytes) return false;
+        for (int64_t m = 0; m < g.M; ++m) {
+            // the first row whose end lies behind the start of these outputs
+            const int64_t from = y0 + m * y_row - p0, first = from < bytes ? 0 : (from - bytes) / row + 1;
+            if (first < rows && first * row < from + y_bytes) return true;
+        }
+        return false;
+    };
+    const int64_t v_bytes = 4 * (int64_t)q.K;
+    return over(q.X, q.M, 2 * q.ldx, 2 * (int64_t)q.K) || over(q.bias, 1, v_bytes, v_bytes) || over(q.act_scale, 1, v_bytes, v_bytes);
+}
+
+// The kernel that takes the whole layer in one launch, if one does.  Not where the outputs lie over its inputs (a layer in
+// place): a workgroup may write what another has yet to read, which two launches keep apart.
+enum class OneLaunch { none, decode, small };
+OneLaunch one_launch_layer(const RotateQuantArgs& q, const GemmArgs& g) {
+    const OneLaunch kernel = linear_decode_applicable(q, g)  ? OneLaunch::decode
+                             : linear_small_applicable(q, g) ? OneLaunch::small
+                                                             : OneLaunch::none;
+    return kernel != OneLaunch::none && outputs_over_inputs(q, g) ? OneLaunch::none : kernel;
+}
+
 // the one-call layer on a workspace of the caller's or of the library's own (both entry points end here)
 int linear_fused_impl(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t rot_size, const float* bias,
                       const float* act_scale, float clip_lo, float clip_hi, int32_t bits, int32_t group_size,
@@ -167,8 +196,11 @@ int linear_fused_impl(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t 
     if (w_layout != BASQ_W_CANONICAL && M > GEMV_MAX_TOKENS && !gemm_fp6_applicable(g))      // before anything is launched
         return fail(BASQ_EUNSUPPORTED, "more than 128 tokens with the streaming weight layout need the fp6 operands "
                                         "(the int8 kernels read canonical weights)");
-    if (linear_decode_applicable(a, g)) return launch_linear_decode(a, g, s);      // a few tokens: one launch
-    if (linear_small_applicable(a, g)) return launch_linear_small(a, g, s);
+    switch (one_launch_layer(a, g)) {
+        case OneLaunch::decode: return launch_linear_decode(a, g, s);
+        case OneLaunch::small: return launch_linear_small(a, g, s);
+        case OneLaunch::none: break;
+    }
     rc = launch_rotate_quant(a, s);
     if (rc != BASQ_OK) return rc;
     return run_gemm(g, s);
@@ -277,6 +309,20 @@ int basq_w4a4_gemm_grouped(const uint8_t* Aq, const basq_tokmeta* meta, int64_t 
 int basq_diag_block_vector_channels(int32_t K) {
     if (K < 256 || K > 16384 || K % 256 != 0) return fail(BASQ_EINVAL, "K must be a multiple of 256 up to 16384 (got %d)", K);
     return rotate_quant_block_vector_channels(K);
+}
+
+int basq_diag_one_launch(const void* X, int64_t M, int32_t K, int64_t ldx, int32_t rot_size, const float* bias, const float* act_scale,
+                         int32_t N, int32_t w_layout, const void* Y, int64_t ldy) {
+    RotateQuantArgs q{};
+    const int rc = validate_rotate(X, M, K, ldx, rot_size, 4, 0, 1.0f, 1.0f, &q.pow2, &q.has28, bias, act_scale);
+    if (rc != BASQ_OK) return rc;
+    if (N < 1 || ldy < N || Y == nullptr) return fail(BASQ_EINVAL, "N must be >= 1, ldy >= N, Y not null (got %d, %lld)", N, (long long)ldy);
+    q.X = static_cast<const uint16_t*>(X);
+    q.M = M; q.K = K; q.ldx = ldx; q.rot_size = rot_size; q.bias = bias; q.act_scale = act_scale; q.group = K;
+    GemmArgs g{};
+    g.M = M; g.K = K; g.N = N; g.w_layout = w_layout; g.ldy = ldy;
+    g.Y = static_cast<uint16_t*>(const_cast<void*>(Y));
+    return one_launch_layer(q, g) != OneLaunch::none;
 }
 
 alignas(16) static const int32_t given[4] = {};                // stands for an operand or table: only that it is given, and aligned, counts

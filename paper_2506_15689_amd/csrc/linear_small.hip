@@ -140,13 +140,10 @@ int launch_ls(const RotateQuantArgs& q, const GemmArgs& g, hipStream_t s) {
 // (512) 8.1 and 6.0, 8 x 28672 (896) 9.3 and 9.9, 64 x 4096 (1024) 7.9 and 8.6, 64 x 8192 8.1 and 14.2; K = 512, 128 x 2048 (1024) 8.0
 // and 6.4 but 64 x 8192 (2048) 8.4 and 10.0; K = 2048, 16 x 2048 (128) 8.0 and 6.2, 64 x 1024 (256) 8.9 and 6.3, 1 x 28672 (448)
 // 11.0 and 11.2, 64 x 2048 (512) with both vectors 9.2 and 9.6.
-// Outputs that overlap the tokens (a layer in place) take two launches: here a workgroup may write what another has yet to read.
 bool linear_small_applicable(const RotateQuantArgs& q, const GemmArgs& g) {
     if (q.has28 || q.rot_size != q.K || q.group != q.K || !(q.K == 512 || q.K == 1024 || q.K == 2048) || q.rot_out != nullptr ||
         g.acc_out != nullptr || g.w_layout != BASQ_W_DECODE16 || g.M < 1 || g.M > 128)
         return false;
-    const auto x0 = reinterpret_cast<uintptr_t>(q.X), y0 = reinterpret_cast<uintptr_t>(g.Y);
-    if (x0 < y0 + 2 * ((g.M - 1) * g.ldy + g.N) && y0 < x0 + 2 * ((q.M - 1) * q.ldx + q.K)) return false;
     const int64_t groups = (g.M + LS_TOKENS - 1) / LS_TOKENS * (((int64_t)g.N + LS_ROWS - 1) / LS_ROWS);
     return groups <= (q.K == 2048 ? 256 : 512);
 }

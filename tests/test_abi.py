@@ -121,6 +121,43 @@ def test_blockwise_rotation_requests_no_channel_past_the_token(lib):
     assert [lib.basq_diag_block_vector_channels(K) for K in (0, 128, 384, 16640)] == [B.BASQ_EINVAL] * 4
 
 
+def one_launch(lib, M, K, N, rot=None, x=0x10000000, y=0x40000000, bias=None, scale=None, layout=B.BASQ_W_DECODE16, ldx=None, ldy=None):
+    return lib.basq_diag_one_launch(x, M, K, ldx or K, rot or K, bias, scale, N, layout, y, ldy or N)
+
+
+def test_layers_in_one_launch(lib):
+    """The rules by size, each on either side of its line."""
+    one = lambda *shape, **kw: one_launch(lib, *shape, **kw)
+    for K in (4096, 8192):
+        assert [one(1, K, 1), one(4, K, 4096), one(5, K, 4096), one(4, K, 4097), one(0, K, 64)] == [1, 1, 0, 0, 0]
+    for K in (512, 1024):
+        assert [one(128, K, 1024), one(128, K, 1025), one(129, K, 64), one(4, K, 32768), one(5, K, 32768), one(4, K, 32769)] == [1, 0, 0, 1, 0, 0]
+    assert [one(64, 2048, 1024), one(64, 2048, 1025), one(1, 2048, 16384), one(1, 2048, 16385)] == [1, 0, 1, 0]
+    assert [one(1, 256, 64), one(1, 14336, 64), one(1, 11008, 64, rot=256), one(1, 1024, 64, rot=512)] == [0] * 4
+    assert [one(1, K, 64, layout=B.BASQ_W_CANONICAL) for K in (1024, 4096)] == [0, 0]
+    assert one(1, 1024, 64, ldx=1020) == one(1, 1024, 64, ldy=63) == one(1, 1024, 64, y=None) == B.BASQ_EINVAL
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 4096, 4096), (4, 4096, 1000), (2, 8192, 4096), (1, 512, 512), (64, 1024, 1024), (16, 2048, 2048)])
+def test_outputs_over_a_layers_inputs_take_two_launches(lib, M, K, N):
+    """Workgroups of a one-launch layer read all of their tokens, b^c and s^a, in no order against the stores of the others: outputs over
+    any byte of these, by whole buffers and by the last or first byte that they share."""
+    x, ldx, ldy = 0x40000000, K + 16, N + 24
+    x_bytes, y_bytes, v_bytes = 2 * ((M - 1) * ldx + K), 2 * ((M - 1) * ldy + N), 4 * K
+    one = lambda y, **kw: one_launch(lib, M, K, N, x=x, y=y, ldx=ldx, ldy=ldy, **kw)
+    assert [one(x), one(x + x_bytes - 2), one(x - y_bytes + 2), one(x + 2 * K - 2)] == [0] * 4
+    assert [one(x + x_bytes), one(x - y_bytes)] == [1, 1]
+    # against the bytes themselves: tokens and outputs that share rows of one matrix, and rows of different lengths
+    for ldx, ldy, shift in [(K + N + 8, K + N + 8, 2 * d) for d in (0, 1, 8, K - 1, K, K + 1, K + 8, K + 9)] + [(K + N + 8, ldy, 2 * d) for d in (K, K + 8, K + N + 8 + K)]:
+        bytes_of = lambda start, ld, n: {start + 2 * (m * ld + i) for m in range(M) for i in range(n)}
+        shared = bytes_of(0, ldx, K) & bytes_of(shift, ldy, N)
+        assert one_launch(lib, M, K, N, x=x, y=x + shift, ldx=ldx, ldy=ldy) == (not shared), (ldx, ldy, shift)
+    for vector in ("bias", "scale"):
+        at = {vector: 0x70000000}
+        assert [one(0x70000000, **at), one(0x70000000 + v_bytes - 2, **at), one(0x70000000 - y_bytes + 2, **at)] == [0] * 3
+        assert [one(0x70000000 + v_bytes, **at), one(0x70000000 - y_bytes, **at), one(0x70000000)] == [1] * 3
+
+
 FAKE = ctypes.c_void_p(0x1000)      # aligned, never dereferenced: validation fails first
 
 

@@ -1095,6 +1095,7 @@ def test_small_tokens_in_one_launch(K):
         workspace = torch.empty(B.basq_workspace_bytes(M, K, N), dtype=torch.uint8, device=DEV)
         for six in (None, W6):
             buf, Y = output_view(M, N, ldy, offset)
+            assert B.basq_diag_one_launch(X, K, bias, scale, Y, B.BASQ_W_DECODE16) == (N <= most)
             B.basq_linear_fused(X, K, bias, scale, 0.9, 0.8, Wd, sw, zp, ws, out_bias, Y, workspace, Wq6=six, w_layout=B.BASQ_W_DECODE16, N=N)
             got = Y.contiguous()
             assert torch.equal(got.isnan(), want.isnan())
@@ -1103,7 +1104,7 @@ def test_small_tokens_in_one_launch(K):
             assert bool((buf == -7.0).all()), "wrote outside the output"
 
 
-@pytest.mark.parametrize("M,K,shift", [(64, 1024, 0), (128, 512, 0), (31, 1024, 8), (16, 2048, 0)])
+@pytest.mark.parametrize("M,K,shift", [(64, 1024, 0), (128, 512, 0), (31, 1024, 8), (16, 2048, 0), (1, 4096, 0), (4, 4096, 0), (3, 4096, 8)])
 def test_small_layers_in_place(M, K, shift):
     """Outputs over the layer's own tokens, or over the tokens shifted by some channels: as with outputs elsewhere."""
     gen = torch.Generator(device=DEV).manual_seed(M + K)
@@ -1114,10 +1115,34 @@ def test_small_layers_in_place(M, K, shift):
     workspace = torch.empty(B.basq_workspace_bytes(M, K, K), dtype=torch.uint8, device=DEV)
     layer = lambda x, y: B.basq_linear_fused(x, K, None, None, 0.9, 0.8, Wd, sw, zp, ws, c, y, workspace, w_layout=B.BASQ_W_DECODE16, N=K)
     want = torch.empty_like(X)
+    assert B.basq_diag_one_launch(X, K, None, None, want, B.BASQ_W_DECODE16)
     layer(X, want)
     for _ in range(20):
         buf = torch.zeros(M * K + shift, dtype=torch.bfloat16, device=DEV)
         x, y = buf[shift:].view(M, K), buf[:M * K].view(M, K)
         x.copy_(X)
+        assert not B.basq_diag_one_launch(x, K, None, None, y, B.BASQ_W_DECODE16)
         layer(x, y)
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("over", ["bias", "act_scale"])
+@pytest.mark.parametrize("K,N", [(512, 1024), (1024, 2048), (2048, 4096), (4096, 4096)])
+def test_small_layers_over_a_channel_vector(K, N, over):
+    """Outputs over b^c or s^a, which have been read when the first output is written: as with outputs elsewhere."""
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    _, _, _, W, _, sw, zp, ws, c = random_product(1, N, K, seed=K)
+    Wd = torch.empty(B.basq_decode_bytes(N, K), dtype=torch.uint8, device=DEV)
+    B.basq_pack_decode(W, Wd)
+    X = torch.randn((1, K), device=DEV, generator=gen).to(torch.bfloat16)
+    vectors = {"bias": torch.rand(K, device=DEV, generator=gen) - 0.5, "act_scale": torch.rand(K, device=DEV, generator=gen) + 0.5}
+    workspace = torch.empty(B.basq_workspace_bytes(1, K, N), dtype=torch.uint8, device=DEV)
+    layer = lambda v, y: B.basq_linear_fused(X, K, v["bias"], v["act_scale"], 0.9, 0.8, Wd, sw, zp, ws, c, y, workspace, w_layout=B.BASQ_W_DECODE16, N=N)
+    want = torch.empty((1, N), dtype=torch.bfloat16, device=DEV)
+    layer(vectors, want)
+    for _ in range(20):
+        mine = {k: v.clone() for k, v in vectors.items()}
+        y = mine[over].view(torch.bfloat16)[:N].view(1, N)
+        assert not B.basq_diag_one_launch(X, K, mine["bias"], mine["act_scale"], y, B.BASQ_W_DECODE16)
+        layer(mine, y)
         assert torch.equal(y.view(torch.int16), want.view(torch.int16))
