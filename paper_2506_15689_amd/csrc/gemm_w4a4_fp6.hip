@@ -84,7 +84,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     // share, SHARES times 256 bytes (4 a lane); where they do not divide so, or a round holds pieces of both operands as well,
     // the waves without a piece in the last round load nothing there (see issue_one).
     constexpr int WHOLE = PIECES / WAVES, LEFT = PIECES % WAVES;
-    constexpr bool BY_BLOCK = LEFT == 0 && WHOLE % 3 == 0 && A_PIECES % WHOLE == 0;      // whole 32-row blocks of one operand a wave
+    constexpr bool BY_BLOCK = LEFT == 0 && WHOLE % 3 == 0;    // whole 32-row blocks a wave
+    static_assert(!BY_BLOCK || WHOLE == 3 || A_PIECES % (3 * WAVES) == 0, "blocks of both operands in the first round at most");
     constexpr bool SHARED = LEFT != 0 && LEFT * 4 % WAVES == 0 && A_PIECES % WAVES == 0;
     constexpr bool PADDED = LEFT != 0 && !SHARED;
     constexpr int SHARES = SHARED ? LEFT * 4 / WAVES : 0;
@@ -147,15 +148,18 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     // pieces make one 32-row block.  Which block a piece comes from is uniform over the wave, so it goes
     // into the scalar offset of the load; the per-lane part is 16 * lane, except for the 1 KB of 8-byte tails: there the 128
     // bytes of rows 0 .. 15 and of rows 16 .. 31 trade places for the groups 2 and 3, see the fragment addressing.
-    // BY_BLOCK: a wave's pieces are whole blocks of one operand, so it needs one descriptor, and an address per block
-    // (256 x 4096 x 8192 on 128 x 128 tiles 12.0 -> 11.6 us, 700 x 384 x 3000 5.7 -> 5.4).
+    // BY_BLOCK: wave w copies whole blocks, number w, WAVES + w, .. of the stage, hence an address per block (256 x 4096 x 8192 on 128 x 128
+    // tiles 12.0 -> 11.6 us, 700 x 384 x 3000 5.7 -> 5.4).  All activations of a stage are requested before its weights: loads complete
+    // in order, and weights that come from memory hold up activations that the caches have (half of the waves with activations
+    // and the others with weights, whole layers with cold weights: 333 x 11008 x 8192 45.7 us, as built 43.1; 117 x 8192 x 23456
+    // 44.5 and 42.6; 237 x 14336 x 9408 59.1 and 56.8; 1021 x 11008 x 4096 with cached ones even).
     // Blocks past the matrix are clamped to its last block.
     int soff[LOADS];                                           // scalar: block and part of each of this wave's pieces
     auto set_tile = [&](int tile_m, int tile_n) {
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
             const int share = swave * SHARES + i - WHOLE;      // number of the 256 bytes among the last pieces
-            const int piece = BY_BLOCK ? swave * WHOLE + i : SHARED && i >= WHOLE ? WHOLE * WAVES + share / 4 : i * WAVES + swave;
+            const int piece = BY_BLOCK ? 3 * (i / 3 * WAVES + swave) + i % 3 : SHARED && i >= WHOLE ? WHOLE * WAVES + share / 4 : i * WAVES + swave;
             int blk = piece / 3;
             const int part = piece % 3;
             if (piece < A_PIECES) {
@@ -187,8 +191,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         share_off[i] = 4 * ((WHOLE * WAVES + share / 4) % 3 == 2 && share % 4 >= 2 ? lane ^ 32 : lane);
     }
     const int last_off = PADDED && WHOLE * WAVES + swave >= PIECES ? (int)0xFFFFFF00u : src_off[WHOLE % 3];
-    int wave_at = kgroup * (STAGES * STAGE_BYTES) + swave * (BY_BLOCK ? WHOLE * 1024 : 1024);
-    const bool loads_a = swave * WHOLE < A_PIECES;             // (BY_BLOCK)
+    int wave_at = kgroup * (STAGES * STAGE_BYTES) + swave * (BY_BLOCK ? BLOCK : 1024);
+    const bool loads_a = 3 * swave < A_PIECES;                 // (BY_BLOCK, first round)
     const __amdgpu_buffer_rsrc_t rsrc_own = loads_a ? rsrc_a : rsrc_w;
     auto issue_one = [&](int stage_off, unsigned koff_a, unsigned koff_w, int i) {
         if (SHARED && i >= WHOLE) {
@@ -198,11 +202,13 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         }
         if constexpr (BY_BLOCK) {
             // the parts of a block by the load's own offset, which counts in memory and in LDS
-            const unsigned at = (loads_a ? koff_a : koff_w) + (unsigned)soff[i / 3 * 3];
-            uint8_t* dst = lds_all + wave_at + stage_off + i / 3 * BLOCK;
-            if (i % 3 == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_own, LDS_PTR(dst), 16, src_off[0], (int)at, 0, 0);
-            else if (i % 3 == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_own, LDS_PTR(dst), 16, src_off[1], (int)at, 1024, 0);
-            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_own, LDS_PTR(dst), 16, src_off[2], (int)at, 2048, 0);
+            const bool mixed = i < 3 && 3 * WAVES > A_PIECES, is_a = mixed ? loads_a : i * WAVES < A_PIECES;
+            const __amdgpu_buffer_rsrc_t rsrc = mixed ? rsrc_own : is_a ? rsrc_a : rsrc_w;
+            const unsigned at = (is_a ? koff_a : koff_w) + (unsigned)soff[i / 3 * 3];
+            uint8_t* dst = lds_all + wave_at + stage_off + i / 3 * (WAVES * BLOCK);
+            if (i % 3 == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(dst), 16, src_off[0], (int)at, 0, 0);
+            else if (i % 3 == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(dst), 16, src_off[1], (int)at, 1024, 0);
+            else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(dst), 16, src_off[2], (int)at, 2048, 0);
             return;
         }
         const bool last = i >= WHOLE;
@@ -389,7 +395,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
                 if (decltype(do_loads)::value) {
 #pragma unroll
                     for (int u = 0; u < loads; ++u)
-                        if ((2 * u + 1) * MFMAS / (2 * loads) == t) issue_one(fill, koff_a, koff_w, first_load + u);
+                        if (u * MFMAS / loads == t) issue_one(fill, koff_a, koff_w, first_load + u);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -401,7 +407,9 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         // compiler then waits for every outstanding LDS read there -- including the ones just issued -- instead of only for the
         // operands the MFMAs use (a bubble of an LDS latency per step).
         // Reads and loads evenly between the MFMAs: all waves pass the barrier together, and with a read in front of each of the
-        // first MFMAs and a load behind it LDS and loads were what they all waited for (4096 x 8192 x 28672 402 and 390 us).
+        // first MFMAs and a load behind it LDS and loads were what they all waited for (4096 x 8192 x 28672 402 and 390 us).  A part's first
+        // load directly behind its first MFMA: half a space later costs where weights come from memory (whole layers, 385 x 14336 x
+        // 10976 76.2 and 74.7 us, 312 x 14336 x 12128 60.6 and 59.5, 135 x 14336 x 13488 57.7 and 56.7; in the caches even).
         unsigned koff_a = kbase_a + (STAGES - 1) * a_step, koff_w = kbase_w + (STAGES - 1) * w_step;   // the group's chunk ks + STAGES - 1
         auto k_step = [&](auto here, auto behind, auto fill0, auto fill1, auto loads0, auto loads1, auto has_next, auto&& wait) {
             constexpr int REST = TO - PART0;
