@@ -374,7 +374,7 @@ def run_workload(args, config, steps, warmup, *, with_ceilings, traffic_table, M
         ceilings["hbm_stream_GBps"] = ct * (2 * ck + ck // 2 + 16) / (ms * 1e-3) / 1e9
         del csrc, cdst, cmeta
         cout = torch.empty(512 * 256, dtype=torch.int32, device=dev)
-        iters = 2000
+        iters = 8000                                        # 2 ms a launch: the clock that the loop's power leaves has settled
 
         def mfma_once(i):
             B.basq_diag_mfma_i8(cout, 512, iters, stream=stream)
@@ -388,7 +388,7 @@ def run_workload(args, config, steps, warmup, *, with_ceilings, traffic_table, M
             B.basq_diag_mfma_f6(fout, 512, iters, stream=stream)
         mfma6_once(0)
         ms = timed(mfma6_once, 3)["mean"]
-        ceilings["fp6_mfma_TOPS"] = 512 * 4 * 8 * iters * 131072.0 / (ms * 1e-3) / 1e12
+        ceilings["fp6_mfma_TOPS"] = 512 * 4 * 16 * iters * 65536.0 / (ms * 1e-3) / 1e12
         del fout
     if decode and not rq_only:
         # read-only streaming over the same weight copies, launched the same way as the decode kernel: what a

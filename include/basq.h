@@ -328,9 +328,9 @@ int basq_diag_read(const void* src, int64_t bytes, uint32_t* out, int32_t blocks
 int basq_diag_mfma_i8(int32_t* out, int32_t blocks, int32_t iters, void* stream);
 
 /*
- * The same loop on the f8f6f4 matrix-core path the prefill GEMM uses by default: each wave issues
- * 8*iters v_mfma_f32_32x32x64_f8f6f4 with fp6 (e2m3) operands in the value range of the 4-bit codes;
- * out receives blocks*256 fp32 checksums.  Executes blocks*4*8*iters*131072 operations.
+ * Such a loop on the f8f6f4 matrix-core path the prefill GEMM uses by default: each wave issues
+ * 16*iters v_mfma_f32_16x16x128_f8f6f4, that GEMM's instruction, with fp6 (e2m3) operands that encode 4-bit codes;
+ * out receives blocks*256 fp32 checksums.  Executes blocks*4*16*iters*65536 operations.
  */
 int basq_diag_mfma_f6(float* out, int32_t blocks, int32_t iters, void* stream);
 

@@ -5,7 +5,7 @@
 //   basq_diag_read     a read-only streaming kernel with the decode kernel's access pattern (a workgroup
 //                      requests 32 KB, eight 16-byte non-temporal loads per lane, before it consumes any)
 //   basq_diag_mfma_i8  a register-resident v_mfma_i32_32x32x32_i8 loop, 4-bit valued operands
-//   basq_diag_mfma_f6  the same with v_mfma_f32_32x32x64_f8f6f4 on fp6 (e2m3) operands that encode 4-bit codes
+//   basq_diag_mfma_f6  a register-resident v_mfma_f32_16x16x128_f8f6f4 loop on fp6 (e2m3) operands that encode 4-bit codes
 // Neither computes anything of the method.
 #include "basq_internal.h"
 
@@ -75,39 +75,50 @@ __global__ __launch_bounds__(256) void diag_mfma_kernel(int* out, int iters) {
 }
 
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-// six-bit fields of a dword pattern forced into the range of the codes' encodings (0..15: the e2m3 values
-// q/8); field boundaries do not matter for a throughput loop, only realistic bits
-__device__ __forceinline__ int fp6_bits(int x) { return x & 0x3CF3CF3C; }
+// 32 codes, e2m3 numbers q/8 whose bit pattern is q, as a lane's operand: six dwords of 6-bit fields.  Binomial around 7.5, as
+// the codes of tokens are, since the power that the matrix cores draw, and with it their clock, depends on the bits.
+__device__ __forceinline__ v8i code_operand(uint32_t seed) {
+    v8i x = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        uint32_t h = (seed * 32 + i) * 0x9E3779B1u;
+        h = (h ^ (h >> 15)) * 0x85EBCA77u;
+        const uint32_t q = __builtin_popcount((h >> 12) & 0x7FFF);
+        x[6 * i / 32] |= (int)(q << (6 * i % 32));
+        if (6 * i % 32 > 26) x[6 * i / 32 + 1] |= (int)(q >> (32 - 6 * i % 32));
+    }
+    return x;
+}
 
-__global__ __launch_bounds__(256) void diag_mfma_f6_kernel(float* out, int iters) {
-    v16f acc[4];
+// Rows and columns of blocks back and forth, so that each MFMA shares an operand with the one before: the order of the fp6 GEMM.
+__global__ __launch_bounds__(256, 2) void diag_mfma_f6_kernel(float* out, int iters) {
+    v8i a[4], b[4];
+    v4f acc[4][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) {
+        a[i] = code_operand(threadIdx.x * 8 + i);
+        b[i] = code_operand(threadIdx.x * 8 + 4 + i);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
-    const int l = threadIdx.x;
-    v8i a[2], b[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int d = 0; d < 8; ++d) {
-            a[t][d] = d < 6 ? fp6_bits((l + 3 * t + 1) * (0x01030507 + 0x00020406 * d)) : 0;
-            b[t][d] = d < 6 ? fp6_bits((l + 5 * t + 2) * (0x0B0D1113 + 0x00040208 * d)) : 0;
-        }
+        for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    }
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[i & 1], b[(i >> 1) & 1], acc[i], 2, 2, 0, 0, 0, 0);
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[(i + 1) & 1], b[i & 1], acc[i], 2, 2, 0, 0, 0, 0);
-        }
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const int j = i & 1 ? 3 - jj : jj;
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b[j], a[i], acc[i][j], 2, 2, 0, 0, 0, 0);
+            }
     }
     float s = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s += acc[i][r];
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s += acc[i][j][r];
     out[blockIdx.x * 256 + threadIdx.x] = s;
 }
 

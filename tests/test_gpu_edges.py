@@ -1146,3 +1146,21 @@ def test_small_layers_over_a_channel_vector(K, N, over):
         assert not B.basq_diag_one_launch(X, K, mine["bias"], mine["act_scale"], y, B.BASQ_W_DECODE16)
         layer(mine, y)
         assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+
+
+def test_fp6_ceiling_loop_multiplies_codes():
+    """The loop that the benchmark's fp6 ceiling is measured with: sixteen 16 x 16 x 128 products a wave and round of operands that hold
+    codes q as the e2m3 numbers q/8.  The checksums of a wave add up to the products of the operands' column sums, exactly."""
+    seed = np.arange(64 * 8, dtype=np.uint64)[:, None] * 32 + np.arange(32, dtype=np.uint64)
+    h = seed * 0x9E3779B1 & 0xFFFFFFFF
+    h = (h ^ (h >> 15)) * 0x85EBCA77 & 0xFFFFFFFF
+    codes = np.zeros(h.shape, dtype=np.int64)
+    for bit in range(12, 27):
+        codes += (h >> bit & 1).astype(np.int64)
+    codes = codes.reshape(4, 16, 2, 4, 32).sum(axis=(1, 3))          # [lane / 16][a or b][channel]: over rows and operands
+    total = int((codes[:, 0] * codes[:, 1]).sum())
+    for iters in (1, 3):
+        out = torch.zeros(512, dtype=torch.float32, device=DEV)
+        B.basq_diag_mfma_f6(out, 2, iters)
+        waves = out.cpu().double().view(2, 4, 64).sum(-1) * 64
+        assert int(waves[0, 0]) == int(waves[1, 0]) == iters * total
