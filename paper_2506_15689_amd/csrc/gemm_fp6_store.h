@@ -7,8 +7,6 @@ namespace basq {
 
 namespace {
 
-typedef float fp6_acc_t __attribute__((ext_vector_type(16)));
-
 // A wave's outputs to memory.  With the weights as the first operand of the 32 x 32 MFMA, accumulator register r of lane l
 // belongs to token l % 32 of a row block and to output channel 8*(r/4) + 4*(l/32) + r%4 of a column block, so four adjacent
 // channels are two dwords of packed bf16: outv[i][j][q][p] = channels 8q + 4*(l/32) + 2p, +1 of row block i, column block j.
@@ -102,53 +100,6 @@ __device__ __forceinline__ void store_outputs(const GemmArgs& a, StoreForm form,
         store_outputs_as<StoreForm::any, TM, TN, BM>(a, m0, n0, row0, lane, outv, col_block);
 }
 
-// The optional dump of the integer accumulators (64 * acc) into a.acc_out, rows of N int32.  As above, with one channel a
-// dword: lane bits 4 and 3 trade places with the bits of q, so that a store covers 32 channels of eight rows (2048 x 4096,
-// K = 4096: 29 us with the dump, 23.7 without; dword stores into 32 rows an instruction: 128 us).
-template <int TM, int TN, int BM, class ColBlock>
-__device__ __forceinline__ void store_accumulators(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const fp6_acc_t (&acc)[TM][TN], ColBlock&& col_block) {
-    const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;
-    const int piece = 8 * (2 * ((lane >> 4) & 1) + ((lane >> 3) & 1)) + 4 * (lane >> 5);
-    auto store16 = [&](int row, int col, const int (&v)[4]) {
-        if (row >= row_end) return;
-        int32_t* dst = a.acc_out + (m0 + row) * a.N + n0 + col;
-        if (col + 4 <= col_end) {
-            __builtin_memcpy(dst, v, 16);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 3; ++e)
-                if (col + e < col_end) dst[e] = v[e];
-        }
-    };
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            int z[2][2][4];                                   // [token / 16][low bit of q][channel]
-#pragma unroll
-            for (int ql = 0; ql < 2; ++ql)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const auto u = __builtin_amdgcn_permlane16_swap((unsigned)__float2int_rn(64.0f * acc[i][j][4 * ql + e]),
-                                                                    (unsigned)__float2int_rn(64.0f * acc[i][j][4 * (2 + ql) + e]), false, false);
-                    z[0][ql][e] = (int)u[0]; z[1][ql][e] = (int)u[1];
-                }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                int lo[4], hi[4];                             // tokens 0..7 and 8..15 of the sixteen (row rotation by 8 lanes)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    lo[e] = __builtin_amdgcn_update_dpp(z[h][0][e], z[h][1][e], 0x128, 0xF, 0xC, false);
-                    hi[e] = __builtin_amdgcn_update_dpp(z[h][1][e], z[h][0][e], 0x128, 0xF, 0x3, false);
-                }
-                const int row = row0 + i * 32 + 16 * h + (lane & 7), col = col_block(j) * 32 + piece;
-                store16(row, col, lo);
-                store16(row + 8, col, hi);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-}
-
 // The same out of 16 x 16 blocks: accumulator register r of lane l belongs to token l % 16 and channel 4*(l/16) + r of a block,
 // outv[i][j][p] = channels 4*(l/16) + 2p, +1 of row block i, column block j of 16 (j / 2 of 32: col_block).  Lane bit 4 (channel)
 // trades places with the low bit of j, and in a pair of 32-column blocks lane bit 3 (token) with the block: as above a lane owns 16 bytes of
@@ -215,10 +166,13 @@ __device__ __forceinline__ void store_outputs16(const GemmArgs& a, StoreForm for
         store_outputs16_as<StoreForm::any, TM, TN, BM>(a, m0, n0, row0, lane, outv, col_block);
 }
 
-typedef float fp6_acc4_t __attribute__((ext_vector_type(4)));
+typedef float fp6_acc_t __attribute__((ext_vector_type(4)));
 
+// The optional dump of the integer accumulators (64 * acc) into a.acc_out, rows of N int32.  One channel a dword: lane bit 3 (token)
+// trades places with the column block, so that a store covers 32 channels of eight rows (2048 x 4096, K = 4096, the predecessor
+// on 32 x 32 blocks: 29 us with the dump, 23.7 without; dword stores into 32 rows an instruction: 128 us).
 template <int TM, int TN, int BM, class ColBlock>
-__device__ __forceinline__ void store_accumulators16(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const fp6_acc4_t (&acc)[TM][TN], ColBlock&& col_block) {
+__device__ __forceinline__ void store_accumulators16(const GemmArgs& a, int64_t m0, int n0, int row0, int lane, const fp6_acc_t (&acc)[TM][TN], ColBlock&& col_block) {
     const int row_end = (int)(a.M - m0 < BM ? a.M - m0 : BM), col_end = a.N - n0;
     auto store16 = [&](int row, int col, const int (&v)[4]) {
         if (row >= row_end) return;

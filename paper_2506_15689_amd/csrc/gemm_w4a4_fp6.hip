@@ -72,9 +72,9 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     constexpr bool ROWS_OUTER = TM >= TN;
     constexpr int TO = ROWS_OUTER ? TM : TN, TI = ROWS_OUTER ? TN : TM;
     // Outer blocks of a step's first part: half of them, one fewer where there are more outer than inner blocks (six at least),
-    // which leaves the barrier, at a part's end, farther from the reads of the next step's operands.  us, half and one fewer: 256 x 256
-    // 4096 x 8192 x 28672 381.4 and 376.7, 256 x 192 2048 x 8192 x 12288 88.2 and 86.9.  (96 x 96, as many of either: no
-    // difference, 320 x 4096 x 4096 9.1.)
+    // which leaves the barrier, at a part's end, farther from the reads of the next step's operands: 256 x 256, 256 x 192, 160 x 96 and
+    // 96 x 96 tiles.  us, half and one fewer: 256 x 256 4096 x 8192 x 28672 381.4 and 376.7, 256 x 192 2048 x 8192 x 12288 88.2
+    // and 86.9; 96 x 96 even (320 x 4096 x 4096 9.1).
     constexpr int PART0 = TO >= 6 && TO > TI ? TO / 2 - 1 : TO / 2;
     constexpr int ROWS = BM + BN;
     constexpr int STAGE_BYTES = ROWS * CHUNK;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     // wait.  Whole layers, us: 4096 x 8192 x 28672 447 -> 440, 4096 x 4096 x 28672 252.7 -> 246.7, 8000 x 512 x 14240 94.3 -> 86.7.)
     constexpr bool APART = TM * TN * 4 >= 128;
     static_assert(!APART || (KGROUPS == 1 && !PADDED), "nothing else stands behind the ring");
-    static_assert(KGROUPS == 1 || (BM * BN * 4 + ROWS * 16 <= STAGES * STAGE_BYTES && TM % OWN == 0), "K groups exchange their sums through their rings");
+    static_assert(KGROUPS == 1 || (BM * BN * 4 + ROWS * 16 <= STAGES * STAGE_BYTES && TM % KGROUPS == 0), "K groups exchange their sums through their rings, and each finishes row blocks");
 
     __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KGROUPS * STAGES * STAGE_BYTES + (PADDED ? 1024 : APART ? 2 * ROWS * 16 : 0)];
 
@@ -151,8 +151,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
     // BY_BLOCK: wave w copies whole blocks, number w, WAVES + w, .. of the stage, hence an address per block (256 x 4096 x 8192 on 128 x 128
     // tiles 12.0 -> 11.6 us, 700 x 384 x 3000 5.7 -> 5.4).  All activations of a stage are requested before its weights: loads complete
     // in order, and weights that come from memory hold up activations that the caches have (half of the waves with activations
-    // and the others with weights, whole layers with cold weights: 333 x 11008 x 8192 45.7 us, as built 43.1; 117 x 8192 x 23456
-    // 44.5 and 42.6; 237 x 14336 x 9408 59.1 and 56.8; 1021 x 11008 x 4096 with cached ones even).
+    // and the others with weights, whole layers with cold weights: 333 x 11008 x 8192 45.6 us, as built 43.3; 117 x 8192 x 23456
+    // 44.5 and 42.5; 237 x 14336 x 9408 59.3 and 56.8; 1021 x 11008 x 4096 with cached ones even).
     // Blocks past the matrix are clamped to its last block.
     int soff[LOADS];                                           // scalar: block and part of each of this wave's pieces
     auto set_tile = [&](int tile_m, int tile_n) {
@@ -408,8 +408,9 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         // operands the MFMAs use (a bubble of an LDS latency per step).
         // Reads and loads evenly between the MFMAs: all waves pass the barrier together, and with a read in front of each of the
         // first MFMAs and a load behind it LDS and loads were what they all waited for (4096 x 8192 x 28672 402 and 390 us).  A part's first
-        // load directly behind its first MFMA: half a space later costs where weights come from memory (whole layers, 385 x 14336 x
-        // 10976 76.2 and 74.7 us, 312 x 14336 x 12128 60.6 and 59.5, 135 x 14336 x 13488 57.7 and 56.7; in the caches even).
+        // load directly behind its first MFMA: half a space later costs where weights come from memory (us, later and so: whole layers on
+        // 160 x 96 tiles, 312 x 14336 x 12128 60.3 and 59.3, 135 x 14336 x 13488 57.7 and 56.6; product on 256 x 256, 453 x 11008 x 28576 79.3
+        // and 77.8; in the caches even).
         unsigned koff_a = kbase_a + (STAGES - 1) * a_step, koff_w = kbase_w + (STAGES - 1) * w_step;   // the group's chunk ks + STAGES - 1
         auto k_step = [&](auto here, auto behind, auto fill0, auto fill1, auto loads0, auto loads1, auto has_next, auto&& wait) {
             constexpr int REST = TO - PART0;
@@ -452,7 +453,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         };
         constexpr std::true_type yes{};
         constexpr std::false_type no{};
-        if (ROUNDS || STAGES - 1 < ksteps) {
+        if constexpr (ROUNDS) {
 #pragma unroll
             for (int i = 0; i < SPLIT; ++i) issue_one(prev, koff_a, koff_w, i);
         }
@@ -491,8 +492,6 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         } else {
             int ks = 0;
             auto wait = [&]() { wait_stages(ksteps - 2 - ks); };
-            for (; ks + STAGES < ksteps; ++ks) any_step(yes, yes, yes, [&]() { wait_stages(STAGES - 2); });
-            if (ks + STAGES - 1 < ksteps) { any_step(yes, no, yes, wait); ++ks; }
             for (; ks + 1 < ksteps; ++ks) any_step(no, no, yes, wait);
             if (!idle_last) any_step(no, no, no, wait);
             else wait_stages(0);
@@ -527,7 +526,6 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         // ---- epilogue (which output an accumulator register holds: gemm_fp6_store.h)
         if (!APART) lds_barrier();                                // LDS only: the next tile's loads stay in flight
         if constexpr (KGROUPS > 1) {
-            if (own0 >= TM) return;                               // fewer row blocks than groups
             // the first OWN blocks of `acc` become the sums of this wave's share
 #pragma unroll
             for (int i = OWN; i < TM; ++i)
@@ -641,6 +639,7 @@ int launch_fp6(const GemmArgs& a, hipStream_t s) {
                                           : BN > 128 && a.K >= 8192 && tm * tn <= 2 * resident;
     GemmArgs b = a;
     b.store_form = output_form(a, hides_stores);
+    // (split tilings are taken from K = 2048 on, eight steps a group: their kernels of few steps run only where a caller names the tiling)
     if ((a.K / 128 + KGROUPS - 1) / KGROUPS < STAGES)
         hipLaunchKernelGGL((gemm_w4a4_fp6_kernel<BM, BN, WAVES_M, WAVES_N, KGROUPS, STAGES, MINOCC, true>), dim3((unsigned)grid),
                            dim3(WAVES * 64), 0, s, b, (int)tm, (int)tn);
@@ -669,12 +668,12 @@ double tiling_cost(const Tiling& t, int64_t M, int64_t N, int K) {
     return us;
 }
 
-// Six tilings; the cheapest by the table is within 0.3 % of the fastest in the mean over those shapes (13 % at worst), whose
-// weights were in the caches.  With weights cold in memory it is as good from 334 tokens on, and 1.2 % off for 65 .. 333, where
-// a pass over the weights is what counts and 64 x 64 tiles make too many of them (192 x 8192, K = 14336: 45 us against 34 on 128 x 64,
-// with the weights in the caches 31 against 32).  Over 200 other shapes (129 .. 4096 tokens, same N and K) at the present kernels, whose
-// 256-row tiles finish in halves: 0.4 % off with weights in the caches (12 % at worst), 0.8 % with cold ones (24 %: 556 x 24368, K = 14336
-// on 128 x 128, where 256 x 192 is the faster one), so the fit stands.
+// Six tilings, fitted to this kernel's predecessor on 32 x 32 x 64 MFMAs: there the cheapest by the table was within 0.3 % of the fastest
+// in the mean over those shapes (13 % at worst), whose weights were in the caches.  The present kernel over 250 other shapes (65 .. 4096
+// tokens, same N and K): 0.8 % off with weights in the caches (23 % at worst: 295 x 4016, K = 8192 on 64 x 64, 18.8 us against 15.3
+// on 128 x 64), 1.6 % with cold ones, 2.0 % up to 333 tokens, where a pass over the weights is what counts and 64 x 64 tiles make too many of
+// them (142 x 7120, K = 11008 33.3 us against 24.3).  Where it is far off a split tiling is mostly taken instead: by both tables (below)
+// 0.3 % in the caches (9 % at worst) and 1.2 % cold (779 x 2272, K = 1024 9.0 us against 6.1 on 128 x 64; the next 20 %), so the fit stands.
 // Choosing among the first, second and fourth by how evenly their tiles fill the chip, as before, was 13 % off in the
 // mean and up to 2.6 times: it gave 129 .. 500 tokens tiles too large to occupy the chip (333 x 4096 x 4096: 96 tiles
 // of 128 x 128 take 14.1 us, 384 of 64 x 64 11.9 us), and where a round of 256 x 128 tiles fits exactly it takes
@@ -698,9 +697,9 @@ const Tiling tilings[NUM_TILINGS] = {
 // 128 0.88 and 1.03, with cold weights 0.90 and 1.0; K >= 8192 0.78 .. 0.99; K = 1024 even; 333 x 4096 x 4096 11.3 -> 9.5 us).  With a
 // second round of tiles they are slower, 1.05 .. 1.6: two one-group workgroups on a compute unit are two chains as well, and
 // overlap their ends.  Hence tiles <= 256 and K >= 2048.  Cost: base + (step + fill * share of the chip) * K / 128, least
-// squares over 330 shapes (33 .. 4096 tokens) with most weight where a tiling is near the fastest, 4-10 %.  The choice over
-// both tables is 0.9 % off the fastest in the mean with weights in the caches and 1.4 % with cold ones, 7.0 and 6.4 % faster than
-// without these; five shapes of the 330 became slower by more than 2 %, the worst by 6 % (warm only).
+// squares over 330 shapes (33 .. 4096 tokens) with most weight where a tiling is near the fastest, 4-10 %, on the predecessor.  The
+// present kernel, over 250 other shapes: 3.9 % faster with weights in the caches than without these, 5.4 % with cold ones; of the 117
+// that take one, four and four are slower by more than 2 %, the worst by 5 %.
 struct SplitTiling {
     int bm, bn;
     double base, step, fill;
@@ -750,12 +749,13 @@ int cheapest_split_tiling(int64_t M, int64_t N, int K) {
 // up to 80 tokens with long rows of 4096 .. 8192 channels (65 x 4096, K = 14336: 23.1 against 20.8 us); the line is drawn without
 // them.  Up to 32 it never is: its weights are half as large again.
 // Between, the line was fitted (5 %) to a streaming kernel that took four waves a workgroup beyond 8192 channels, against this
-// kernel's tilings without the split ones.  Both have become faster since, the streaming kernel the more with cold weights.
-// Where the line stands: 33, 40, 48, 56 and 64 tokens, N 8208 .. 28672, K 1024 .. 14336, the kernel taken is 2.3 % off the
-// faster one in the mean with cold weights and 7 % with weights in the caches.  Cold, calls that take this one lose up to 25 %
-// at 40 and 48 tokens (40 x 8208, K = 8192: 17.8 against 14.2 us) and little at 64 (x 12288, K = 4096 11.5 against 10.8, K = 8192
-// 18.6 against 17.9; K = 1024 4.9 against 6.5); in the caches this one is ahead at 64 tokens throughout (x 20480, K = 14336,
-// which streams: 39.5 against 59.8; cold 55.5 against 60.7).
+// kernel's predecessor without the split tilings.  Both have become faster since, this one the more.  Where the line stands: 60
+// shapes of 33, 40, 48, 56 and 64 tokens, N 8208 .. 28672, K 1024 .. 14336, products, this kernel's fastest tiling in its place where it
+// streams: the kernel taken is 9 % off the faster one in the mean with cold weights and 16 % with weights in the caches.  Cold, calls
+// that take this one lose up to 23 % at 40 tokens (x 9712, K = 14336: 28.4 against 23.0 us), 19 % at 48 and 12 % at 56; calls
+// that stream lose the more the longer their rows (64 x 21168, K = 11008 51.0 against 32.8; 48 x 20384 43.0 and 32.3; 40 x 19696
+// 39.8 and 31.8).  In the caches this one is the faster one wherever it is taken, and up to twice as fast where it is not (64 x 16560, K =
+// 14336 58.4 against 28.0).
 bool gemm_fp6_beats_streaming(int64_t M, int32_t N, int32_t K) {
     if (M > 64) return true;
     if (M <= 32 || N <= 8192) return false;
