@@ -219,6 +219,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         __builtin_amdgcn_raw_ptr_buffer_load_lds(is_a ? rsrc_a : rsrc_w, LDS_PTR(dst), 16, last ? last_off : src_off[i % 3],
                                                  (int)((is_a ? koff_a : koff_w) + (unsigned)soff[i]), 0, 0);
     };
+    constexpr int LATER = KGROUPS == 1 && BM == 256 && BN < 256 ? 1 : 0;       // by how many half spaces a part's loads stand behind its start (see k_step)
     constexpr int SPLIT = (LOADS + 1) / 2;                     // the first half of a stage's loads (see k_step)
     // Wait until the oldest stage in flight has landed, `ahead` stages having been requested behind it at most
     auto wait_stages = [&](int ahead) { wait_stages_and_barrier<LOADS, STAGES - 2>(ahead); };
@@ -395,7 +396,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
                 if (decltype(do_loads)::value) {
 #pragma unroll
                     for (int u = 0; u < loads; ++u)
-                        if (u * MFMAS / loads == t) issue_one(fill, koff_a, koff_w, first_load + u);
+                        if ((2 * u + LATER) * MFMAS / (2 * loads) == t) issue_one(fill, koff_a, koff_w, first_load + u);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -410,7 +411,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         // first MFMAs and a load behind it LDS and loads were what they all waited for (4096 x 8192 x 28672 402 and 390 us).  A part's first
         // load directly behind its first MFMA: half a space later costs where weights come from memory (us, later and so: whole layers on
         // 160 x 96 tiles, 312 x 14336 x 12128 60.3 and 59.3, 135 x 14336 x 13488 57.7 and 56.6; product on 256 x 256, 453 x 11008 x 28576 79.3
-        // and 77.8; in the caches even).
+        // and 77.8; in the caches even).  Not on 256 x 192 and 256 x 128 tiles, whose products with cached weights are up to 1 % shorter with that
+        // half space (2048 x 14336 x 4096 54.8 us and 55.4, 3332 x 8192 x 6704 89.6 and 90.4), with cold ones as long.
         unsigned koff_a = kbase_a + (STAGES - 1) * a_step, koff_w = kbase_w + (STAGES - 1) * w_step;   // the group's chunk ks + STAGES - 1
         auto k_step = [&](auto here, auto behind, auto fill0, auto fill1, auto loads0, auto loads1, auto has_next, auto&& wait) {
             constexpr int REST = TO - PART0;
