@@ -52,14 +52,12 @@ __global__ __launch_bounds__(LS_WAVES * 64, NP == 4 ? 2 : 4) void linear_small_k
     v4i w[CHUNKS];
 #pragma unroll
     for (int i = 0; i < CHUNKS; ++i) w[i] = *reinterpret_cast<const v4i*>(wblk + i * 1024);
-    // one constant a lane: of channel lane % 16 scale, zero point, sum or bias by lane / 16 (raw: a conversion would wait)
+    // Constants of channel lane % 16: scale and sum in lanes whose bit 4 is clear, zero point and bias in the others.  Addresses are selected
+    // and not the loads: behind a branch the compiler waits for the weights before it reuses a register (raw: a conversion would wait too).
     const int row = lane & 15, sub = lane >> 4;
     const int on = n0 + row < g.N ? n0 + row : g.N - 1;
-    int cst = 0;
-    if (sub == 0) cst = g.w_scale[on];
-    else if (sub == 1) cst = g.w_zero[on];
-    else if (sub == 2) cst = __float_as_int(g.w_sum[on]);
-    else if (g.out_bias) cst = __float_as_int(g.out_bias[on]);
+    const int cst2 = (sub & 1 ? g.w_zero : g.w_scale)[on];
+    const float cst4 = ((sub & 1) && g.out_bias ? g.out_bias : g.w_sum)[on];
     __builtin_amdgcn_sched_barrier(0);
 
     v8bf bop[2];
@@ -99,10 +97,10 @@ __global__ __launch_bounds__(LS_WAVES * 64, NP == 4 ? 2 : 4) void linear_small_k
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int from = 4 * (4 * sub + r);
-        const float sw = __int_as_float(__builtin_amdgcn_ds_bpermute(from, cst) << 16);
-        const float zp = __int_as_float(__builtin_amdgcn_ds_bpermute(from + 64, cst) << 16);
-        const float ws = __int_as_float(__builtin_amdgcn_ds_bpermute(from + 128, cst));
-        const float cb = __int_as_float(__builtin_amdgcn_ds_bpermute(from + 192, cst));
+        const float sw = __int_as_float(__builtin_amdgcn_ds_bpermute(from, cst2) << 16);
+        const float zp = __int_as_float(__builtin_amdgcn_ds_bpermute(from + 64, cst2) << 16);
+        const float ws = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(cst4)));
+        const float cb = g.out_bias ? __int_as_float(__builtin_amdgcn_ds_bpermute(from + 64, __float_as_int(cst4))) : 0.0f;
         const float t = (float)acc[r] - zp * (float)mt.rowsum;
         y[r] = f32_to_bf16(fmaf(mt.scale * sw, t, fmaf(mt.lo, ws, cb)));
     }
@@ -135,11 +133,13 @@ int launch_ls(const RotateQuantArgs& q, const GemmArgs& g, hipStream_t s) {
 }  // namespace
 
 // As many workgroups as rotate no longer than the launch and the wait between two kernels take: 512 with one or two pieces a token,
-// 256 with four (a workgroup's rotation is twice as long, and half as many are in flight).  Whole layers, us, two launches and one,
-// cold weights: K = 1024, 64 x 1024 (256 workgroups) 8.0 and 5.3, 1 x 28672 (448) 8.8 and 7.1, 16 x 8192 (512) 7.9 and 6.3, 128 x 1024
-// (512) 8.1 and 6.0, 8 x 28672 (896) 9.3 and 9.9, 64 x 4096 (1024) 7.9 and 8.6, 64 x 8192 8.1 and 14.2; K = 512, 128 x 2048 (1024) 8.0
-// and 6.4 but 64 x 8192 (2048) 8.4 and 10.0; K = 2048, 16 x 2048 (128) 8.0 and 6.2, 64 x 1024 (256) 8.9 and 6.3, 1 x 28672 (448)
-// 11.0 and 11.2, 64 x 2048 (512) with both vectors 9.2 and 9.6.
+// 256 with four (a workgroup's rotation is twice as long, and half as many are in flight).  Whole layers from a graph, cold weights,
+// us, two launches and one: K = 1024, 64 x 1024 (256 workgroups) 7.2 and 4.3, 1 x 28672 (448) 9.2 and 6.3, 16 x 8192 (512) 6.8 and 6.0,
+// 32 x 4096 with both vectors (512) 7.0 and 6.1, 64 x 4096 (1024) 7.7 and 8.2, 64 x 8192 8.3 and 13.1; K = 512, 128 x 1024 (512) 7.5 and
+// 4.4, 64 x 8192 (2048) 7.3 and 9.0; K = 2048, 1 x 2048 with both vectors (32) 6.4 and 6.4, 16 x 2048 (128) 7.1 and 6.0, 64 x 1024
+// (256) 9.1 and 6.0.  The lines were drawn when the constants' loads still waited for the weights; a little beyond them one
+// launch would be the faster one now (8 x 1024 x 28672, 896, 9.8 and 8.8; 128 x 512 x 2048, 1024, 7.7 and 5.9; 64 x 2048 x 2048,
+// 512, 9.5 and 8.5, with both vectors 9.8 and 9.2).
 bool linear_small_applicable(const RotateQuantArgs& q, const GemmArgs& g) {
     if (q.has28 || q.rot_size != q.K || q.group != q.K || !(q.K == 512 || q.K == 1024 || q.K == 2048) || q.rot_out != nullptr ||
         g.acc_out != nullptr || g.w_layout != BASQ_W_DECODE16 || g.M < 1 || g.M > 128)
