@@ -5,7 +5,7 @@
 // holds S = sum_k (qa/8)(qb/8) exactly (multiples of 1/64, S < 2^17 for K <= 32768).  The integer
 // accumulator of the INT4 product is ACC = 64*S; the epilogue de-quantises exactly as the int8 kernels do.
 // (16 x 16 x 128 and not 32 x 32 x 64: the chip's power sets the clock under such a loop, and a register-resident one on
-// code-valued operands runs at 8.7 POP/s in this shape, 7.6 in the other.  Products with the weights in the caches, this kernel
+// code-valued operands runs at 8.7 POP/s in this shape, 7.6 in the other (in longer launches, basq_diag_mfma_f6, 7.9 .. 8.5).  Products with the weights in the caches, this kernel
 // against its predecessor on 32 x 32 x 64, us: 4096 x 8192 x 28672 408 -> 377, 2048 x 4096 x 12288 54.7 -> 50.6, 2048 x 14336 x 4096
 // 59.5 -> 54.2, 256 x 4096 x 8192 on 128 x 64 tiles 11.0 -> 9.4.)
 //
@@ -412,7 +412,8 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * KGROUPS * 64, MINOCC) void gemm
         // load directly behind its first MFMA: half a space later costs where weights come from memory (us, later and so: whole layers on
         // 160 x 96 tiles, 312 x 14336 x 12128 60.3 and 59.3, 135 x 14336 x 13488 57.7 and 56.6; product on 256 x 256, 453 x 11008 x 28576 79.3
         // and 77.8; in the caches even).  Not on 256 x 192 and 256 x 128 tiles, whose products with cached weights are up to 1 % shorter with that
-        // half space (2048 x 14336 x 4096 54.8 us and 55.4, 3332 x 8192 x 6704 89.6 and 90.4), with cold ones as long.
+        // half space (2048 x 14336 x 4096 54.8 us and 55.4, 3332 x 8192 x 6704 89.6 and 90.4), with cold ones as long (a layer that is not:
+        // 410 x 11008 x 13584 62.3 and 60.6).
         unsigned koff_a = kbase_a + (STAGES - 1) * a_step, koff_w = kbase_w + (STAGES - 1) * w_step;   // the group's chunk ks + STAGES - 1
         auto k_step = [&](auto here, auto behind, auto fill0, auto fill1, auto loads0, auto loads1, auto has_next, auto&& wait) {
             constexpr int REST = TO - PART0;
